@@ -179,7 +179,7 @@ struct pulda_plan {
     // (32, 8), (16, 16), (16, 8); 8-bit counts serve documents under 256 tokens
     static constexpr int NCLS = 7;
     static_assert(NCLS <= Z_QUEUES, "one work queue per class");
-    int32_t cls_first[NCLS] = {}, cls_count[NCLS] = {};
+    int32_t cls_first[NCLS] = {}, cls_count[NCLS] = {}, cls_longest[NCLS] = {};
     int32_t n_cu = 0;                 // compute units of the device
     // internal streams: the three group-size kernels of a z-step run
     // concurrently, forked from and joined back to the caller's stream
@@ -505,21 +505,7 @@ static hipError_t phase_event(pulda_plan *p, hipStream_t s, size_t *idx)
     return hipEventRecord(p->ev_pool[*idx], s);
 }
 
-// a z-step class fits when one wave's count tables, topic lists and staged
-// tokens take at most 32 KB of LDS (groups of 8 only for documents shorter
-// than 256 tokens); one document per lane (group 1) takes documents shorter
-// than 128 tokens (longest is the work item's longest document)
-static bool class_fits(int32_t g, bool narrow, int32_t K, int32_t longest)
-{
-    // one document per lane: a list of at most 127 topics with 8-bit
-    // counts (every list fits when K <= 127; a count stays below 256)
-    if (g == 1) return longest < 128 || (K <= 127 && longest < 256);
-    if (g == 8 && !narrow) return false;
-    return z_layout(g, narrow, K).wave_bytes + 64 * 32 <= 32 * 1024;
-}
-
 static const int32_t kClassGroup[pulda_plan::NCLS] = {64, 32, 32, 16, 16, 8, 1};
-static const bool kClassNarrow[pulda_plan::NCLS] = {false, false, true, false, true, true, true};
 
 static int item_class(int32_t g, bool narrow)
 {
@@ -550,8 +536,8 @@ static pulda_status build_items(pulda_plan *p)
             const bool narrow = p->len_sorted[s] < 256;
             // the bucket's group size, or the next larger one that fits
             int32_t g = p->group[b];
-            if (g == 1 && !class_fits(1, narrow, p->K, p->len_sorted[s])) g = 16;
-            while (g < 64 && !class_fits(g, narrow, p->K, p->len_sorted[s])) g *= 2;
+            if (g == 1 && !z_group_fits(1, p->K, p->len_sorted[s])) g = 16;
+            while (g < 64 && !z_group_fits(g, p->K, p->len_sorted[s])) g *= 2;
             w.group = g;
             cls[item_class(w.group, narrow)].push_back(w);
         }
@@ -560,6 +546,8 @@ static pulda_status build_items(pulda_plan *p)
     for (int c = 0; c < pulda_plan::NCLS; ++c) {
         p->cls_first[c] = (int32_t)items.size();
         p->cls_count[c] = (int32_t)cls[c].size();
+        // (items in decreasing document length)
+        p->cls_longest[c] = cls[c].empty() ? 0 : p->len_sorted[cls[c][0].first];
         items.insert(items.end(), cls[c].begin(), cls[c].end());
     }
     if ((int64_t)items.size() > p->items_cap) return fail(PULDA_ERR_INVALID_ARG, "schedule yields too many work items");
@@ -722,7 +710,7 @@ static pulda_status enqueue_z_classes(pulda_plan *p, hipStream_t s, double *ll_d
     if (used <= 1) {
         for (int c = 0; c < pulda_plan::NCLS; ++c)
             if (p->cls_count[c])
-                HIP_TRY(launch_z_class(p->c, p->m, kClassGroup[c], kClassNarrow[c], p->items + p->cls_first[c],
+                HIP_TRY(launch_z_class(p->c, p->m, kClassGroup[c], p->cls_longest[c], p->items + p->cls_first[c],
                                        p->cls_count[c], p->n_cu, p->queue + c, stats, ll_doc, s));
     } else {
         // classes run concurrently: long documents (large groups) next to
@@ -731,7 +719,7 @@ static pulda_status enqueue_z_classes(pulda_plan *p, hipStream_t s, double *ll_d
         for (int c = 0; c < pulda_plan::NCLS; ++c) {
             if (!p->cls_count[c]) continue;
             HIP_TRY(hipStreamWaitEvent(p->aux[c], p->fork_ev, 0));
-            HIP_TRY(launch_z_class(p->c, p->m, kClassGroup[c], kClassNarrow[c], p->items + p->cls_first[c],
+            HIP_TRY(launch_z_class(p->c, p->m, kClassGroup[c], p->cls_longest[c], p->items + p->cls_first[c],
                                    p->cls_count[c], p->n_cu, p->queue + c, stats, ll_doc, p->aux[c]));
             HIP_TRY(hipEventRecord(p->join_ev[c], p->aux[c]));
             HIP_TRY(hipStreamWaitEvent(s, p->join_ev[c], 0));
@@ -1092,9 +1080,8 @@ pulda_status pulda_autotune(pulda_plan *p, uint32_t t, int32_t reps, void *strea
         mean_len /= (double)(hi - lo);
         bucket_mean[b] = mean_len;
         float best_ms = 1e30f;
-        const bool narrow = p->len_sorted[lo] < 256;
         for (int gsz : {64, 32, 16, 8, 1}) {
-            if (!class_fits(gsz, narrow, p->K, p->len_sorted[lo])) continue;
+            if (!z_group_fits(gsz, p->K, p->len_sorted[lo])) continue;
             for (int ratio : {1, 4, 16}) {
                 const int ng = 64 / gsz;
                 int per = (int)std::max(1.0, std::round(4096.0 / std::max(1.0, mean_len) / ng)) * ng;
@@ -1108,7 +1095,7 @@ pulda_status pulda_autotune(pulda_plan *p, uint32_t t, int32_t reps, void *strea
                     if (p->N) HIP_TRY(hipMemcpyAsync(p->c.z, p->zsave, p->N * 2, hipMemcpyDeviceToDevice, s));
                     HIP_TRY(hipEventRecord(e0, s));
                     HIP_TRY(launch_z_prepare(p->m, p->queue, nullptr, s));
-                    HIP_TRY(launch_z_class(p->c, p->m, gsz, gsz < 64 && narrow, p->items,
+                    HIP_TRY(launch_z_class(p->c, p->m, gsz, p->len_sorted[lo], p->items,
                                            (int32_t)items.size(), p->n_cu, p->queue, nullptr, nullptr, s));
                     HIP_TRY(hipEventRecord(e1, s));
                     HIP_TRY(hipEventSynchronize(e1));
@@ -1328,6 +1315,7 @@ pulda_status pulda_foldin_bind(pulda_foldin *f, void *ws, int64_t bytes)
     F.sweeps = f->desc.sweeps;
     F.burn_in = f->desc.burn_in;
     F.group = f->desc.group;
+    F.max_len = f->desc.max_len;
     F.key0 = (uint32_t)f->desc.seed;
     F.key1 = (uint32_t)(f->desc.seed >> 32);
     F.A = f->model->A;
@@ -1635,6 +1623,7 @@ static pulda_status heldout_run(const pulda_plan *model, int64_t D, const int64_
     h.D = D;
     h.R = particles;
     h.group = group;
+    h.longest = (int32_t)(off[order[0] + 1] - off[order[0]]);
     h.key0 = (uint32_t)seed;
     h.key1 = (uint32_t)(seed >> 32);
     h.A = model->A;

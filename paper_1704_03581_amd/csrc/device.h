@@ -167,10 +167,24 @@ __device__ __forceinline__ int group_bcast(int x, int src)
     }
 }
 
+// value of the group's last lane to every lane of it, without LDS: lane reads
+// across rows, DPP row_newbcast (0x150 + lane) within a row
 template <int G>
-__device__ __forceinline__ float group_bcast_f32(float x, int src)
+__device__ __forceinline__ float group_last_f32(float x)
 {
-    return __int_as_float(group_bcast<G>(__float_as_int(x), src));
+    const int v = __float_as_int(x);
+    if constexpr (G == 64) {
+        return __int_as_float(__builtin_amdgcn_readlane(v, 63));
+    } else if constexpr (G == 32) {
+        const int lo = __builtin_amdgcn_readlane(v, 31), hi = __builtin_amdgcn_readlane(v, 63);
+        return __int_as_float(__lane_id() < 32 ? lo : hi);
+    } else if constexpr (G == 16) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, v, 0x15F, 0xF, 0xF, true));
+    } else {
+        // lanes 0-7 of the row from lane 7, lanes 8-15 (banks 2 and 3) from 15
+        const int lo = __builtin_amdgcn_update_dpp(0, v, 0x157, 0xF, 0xF, true);
+        return __int_as_float(__builtin_amdgcn_update_dpp(lo, v, 0x15F, 0xF, 0xC, false));
+    }
 }
 
 template <int G>

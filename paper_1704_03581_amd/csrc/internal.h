@@ -46,7 +46,8 @@ struct DevModel {
     double *sigma_a;              // [V]
     float *phimax;                // [V] the largest phi of each word's column
     // per word, what a z-step token needs of its word in one 16-byte load:
-    // {first CSC entry, column length, fp32(sigma_a), phimax} (as bits)
+    // {first CSC entry, column length | WREC_F32, fp32(sigma_a), phimax} (as
+    // bits); phimax[v] itself is negative when the word has WREC_F32
     uint4 *wrec;                  // [V]
     // the corpus's most frequent words, whose count increments the z-step
     // gathers per block in LDS when K is small (hot[v]: the word's index
@@ -89,31 +90,70 @@ struct WorkItem {
     int32_t first, count, group, side_ratio;
 };
 
-// slots per lane of the z-step's windowed topic list (groups of 16: 8,
-// else 4)
-inline int32_t z_window(int32_t group) { return group == 16 ? 8 : 4; }
+// The z-step's slots per lane: a draw handles up to SLOTS_MAX a lane with
+// the kernel's fixed counts of them; longer topic lists turn dense
+constexpr int32_t SLOTS_MAX = 16;
+constexpr int32_t SLOTS_FEW = 6;           // the most of the kernels for short lists
+constexpr size_t LDS_BYTES = 160 * 1024;   // per CU, and the most a block takes
+// wrec: the word has a cell whose 16-bit draw is the escape; its terms are
+// gathered as fp32 phi
+constexpr uint32_t WREC_F32 = 0x80000000u;
 
-// LDS layout of one z-step class (group size, count width): per group a
-// count table (K counters of 1 or 2 bytes, rounded to 16 bytes) and the
-// document's topic list (u16; min(K, 255) entries for documents shorter
-// than 256 tokens, else K, and at least W slots per lane and W more, for
-// the list's windows of W = z_window(group) slots, 16-byte aligned), 64/G
-// groups per wave, and the block's copy of R_k (K floats) first
-struct ZLayout {
-    int32_t m_bytes, group_bytes, wave_bytes, r_bytes;
+// LDS of one group of lanes with a document of at most `longest` tokens:
+// slot counts (fp32), the block's draw records, a bit per topic, the slots'
+// topics, the list entries before each chunk of topics, the drawn slots
+struct SlotLds {
+    int32_t ms_n;                              // slot counts
+    int32_t o_tok, o_p, o_lst, o_pre, o_out;   // byte offsets (ms at 0)
+    int32_t group_bytes;
+    int32_t p_words;                           // 32-bit words of topic bits
+    int32_t log_b, chunks, ch_lane;            // topics per chunk (log2), chunks, chunks per lane
 };
 
-inline ZLayout z_layout(int32_t group, bool narrow, int32_t K)
+inline SlotLds slot_lds(int32_t G, int32_t K, int32_t longest)
 {
-    ZLayout L;
-    const int32_t W = z_window(group);
-    L.m_bytes = (K * (narrow ? 1 : 2) + 15) / 16 * 16;
-    int32_t lcap = narrow ? (K < 255 ? K : 255) : K;
-    if (lcap < W * group + W) lcap = W * group + W;
-    L.group_bytes = L.m_bytes + (lcap * 2 + 15) / 16 * 16;
-    L.wave_bytes = ((64 / group) * L.group_bytes + 15) / 16 * 16;
-    L.r_bytes = (K * 4 + 15) / 16 * 16;
-    return L;
+    SlotLds A{};
+    // a block's slots: topics of the document and of G staged a-parts
+    const int32_t most = K < longest + G ? K : longest + G;
+    const int32_t need = (most + G - 1) / G;
+    static const int32_t sizes[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
+    int32_t sl = SLOTS_MAX;
+    for (int32_t x : sizes)
+        if (x >= need) {
+            sl = x;
+            break;
+        }
+    A.ms_n = need <= SLOTS_MAX ? sl * G : (K + G - 1) / G * G;
+    const int32_t cap = sl * G;
+    A.p_words = (K + 31) / 32;
+    A.log_b = 0;
+    while (A.log_b < 5 && ((int64_t)G << A.log_b) < K) ++A.log_b;
+    A.chunks = (K + (1 << A.log_b) - 1) >> A.log_b;
+    A.ch_lane = (A.chunks + G - 1) / G;
+    auto up = [](int32_t x) { return (x + 15) / 16 * 16; };
+    A.o_tok = up(A.ms_n * 4);
+    A.o_p = A.o_tok + (G + 2) * 16;
+    A.o_lst = A.o_p + up(A.p_words * 4);
+    A.o_pre = A.o_lst + up(cap * 2);
+    A.o_out = A.o_pre + up(A.chunks * 2);
+    A.group_bytes = A.o_out + up(G * 2);
+    return A;
+}
+
+// a z-step group size fits documents of at most `longest` tokens when their
+// slots do (groups of 8 take documents shorter than 256 tokens; 64 lanes
+// take every document); one document per lane (group 1) keeps a list of at
+// most 127 topics with 8-bit counts (every list fits when K <= 127; a count
+// stays below 256)
+inline bool z_group_fits(int32_t group, int32_t K, int32_t longest)
+{
+    if (group == 1) return longest < 128 || (K <= 127 && longest < 256);
+    if (group == 64) return true;
+    if (group == 8 && longest >= 256) return false;
+    const int32_t most = K < longest + group ? K : longest + group;
+    return most <= SLOTS_MAX * group &&
+           (size_t)(K * 4 + 15) / 16 * 16 + 4 * (64 / group) * (size_t)slot_lds(group, K, longest).group_bytes <=
+               LDS_BYTES;
 }
 
 // LDS for the per-block counts of the frequent words (hot words) and the
@@ -149,11 +189,10 @@ constexpr int32_t ROWSUM_COLS = 256;      // words per block of the row-sum kern
 // With ll_doc non-null (symmetric alpha) the z-step also writes each
 // document's term of the log joint for the state it leaves.
 hipError_t launch_z_prepare(const DevModel &m, int32_t *queues, unsigned long long *stats, hipStream_t s);
-// narrow: 8-bit document-topic counts (every document of the items is
-// shorter than 256 tokens; group 8, 16 or 32).  The grid is as many blocks
-// as n_cu compute units hold at once.
-hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, bool narrow, const WorkItem *items,
-                          int32_t n_items, int32_t n_cu, int32_t *queue, unsigned long long *stats,
+// longest: no document of the items has more tokens.  The grid is as many
+// blocks as n_cu compute units hold at once.
+hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, int32_t longest,
+                          const WorkItem *items, int32_t n_items, int32_t n_cu, int32_t *queue, unsigned long long *stats,
                           double *ll_doc, hipStream_t s);
 // log joint of the current state; with ll_doc non-null the document terms
 // are taken from it (written by the z-step) instead of recounted from z
@@ -190,6 +229,7 @@ struct FoldSlot {
 
 struct DevFoldin {
     int32_t sweeps, burn_in, group;
+    int32_t max_len;        // longest request
     uint32_t key0, key1;
     double A;
     const FoldSlot *slots;  // [max_slots] control, written by the host
@@ -215,6 +255,7 @@ hipError_t launch_foldin_step(const DevModel &m, const DevFoldin &f, const int32
 struct DevHeldout {
     int64_t D;
     int32_t R, group;
+    int32_t longest;           // tokens of the longest document
     uint32_t key0, key1;
     double A;                  // sum_k alpha_k
     const int64_t *doc_off;    // [D+1]

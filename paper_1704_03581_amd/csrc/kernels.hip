@@ -421,6 +421,7 @@ __global__ void __launch_bounds__(256) phi_dense_kernel(DevModel m)
     uint16_t *g16col = m.g16 + (int64_t)v * m.ks16;
     int32_t run = 0;
     float fmax = 0.0f;
+    bool esc = false;
     // the column's draws are read PB rounds of 64 cells at a time, so that
     // many loads are in flight before the rounds are processed in order
     constexpr int PB = 8;
@@ -458,6 +459,7 @@ __global__ void __launch_bounds__(256) phi_dense_kernel(DevModel m)
         if (k < K) pcol[k] = f;
         fmax = f > fmax ? f : fmax;
         g16col[k] = (uint16_t)x16;
+        esc |= x16 == 0xFFFFu;
         const uint64_t bal = __builtin_amdgcn_ballot_w64(nz);
         if (nz) {
             const int32_t e = run + __builtin_popcountll(bal & ((1ull << lane) - 1ull));
@@ -472,7 +474,8 @@ __global__ void __launch_bounds__(256) phi_dense_kernel(DevModel m)
         const float y = __shfl_xor(fmax, o, 64);
         fmax = y > fmax ? y : fmax;
     }
-    if (lane == 0) m.phimax[v] = fmax;
+    const bool f32 = __builtin_amdgcn_ballot_w64(esc) != 0;
+    if (lane == 0) m.phimax[v] = f32 ? -fmax : fmax;
 }
 
 // Columns with at most ALIAS_SMALL nonzeros: one wave per column, four per
@@ -651,8 +654,9 @@ __global__ void word_records_kernel(DevModel m)
     const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= m.V) return;
     const int32_t cb = m.colptr[v];
-    m.wrec[v] = make_uint4((uint32_t)cb, (uint32_t)(m.colptr[v + 1] - cb), __float_as_uint((float)m.sigma_a[v]),
-                           __float_as_uint(m.phimax[v]));
+    const uint32_t pm = __float_as_uint(m.phimax[v]);   // sign: WREC_F32
+    m.wrec[v] = make_uint4((uint32_t)cb, (uint32_t)(m.colptr[v + 1] - cb) | (pm & WREC_F32),
+                           __float_as_uint((float)m.sigma_a[v]), pm & ~WREC_F32);
 }
 
 hipError_t launch_word_records(const DevModel &m, hipStream_t s)
@@ -860,29 +864,61 @@ hipError_t launch_phi_step_dirichlet(const DevModel &m, unsigned long long *stat
 // ---------------------------------------------------------------------------
 // z-step (Section 3.5).  A group of G lanes (G = 8, 16, 32, 64) owns one
 // document at a time and walks its tokens in stored order (sequential Gibbs
-// within the document).  The document-topic counts m_d live in LDS, indexed
-// by topic, beside lst, the document's topics with a nonzero count in
-// ascending order.  For each token:
-//   sigma_b = sum_k phi_kv m_k is taken over the document's topics (lst,
-//   phi from the word's dense column of draws) or the word's Phi column
-//   (its CSC entries, m from LDS); either way lane g takes a contiguous
-//   block of entries in ascending topic order and a group prefix sum orders
-//   the lanes, so the running sums are ascending in k as the definition
-//   requires;
-//   u_sigma = u (sigma_a + sigma_b) < sigma_a takes the word's alias draw,
-//   otherwise the crossing lane (first with prefix > u_sigma - sigma_a)
-//   walks its entries to find the topic;
-//   the counts and lst are updated: a topic that leaves or enters the
-//   document moves the entries above it by one place.
+// within the document), a block of up to G tokens at a time (one per lane).
+//
+// Slots.  Before a block's draws its tokens are staged: a token's word record
+// and alias entry are loaded and its a-part topic drawn, which depends on the
+// word and the token's random numbers only.  The block's topics are then
+// known: a draw either takes the staged a-part topic or one with a nonzero
+// count.  So the document's topics with a nonzero count and the block's
+// a-part topics, in ascending order, are laid out once per block: topic e of
+// them is slot e, and lane g holds the SL slots [g SL, g SL + SL).  The
+// layout stays fixed for the whole block (a topic whose count falls to zero
+// keeps its slot with a zero b-term), which is what makes a draw short:
+//   - a slot's gather offset and R_k stay in registers, and the draws
+//     phi_kv ~ x_kv of a later token are gathered DEPTH draws ahead;
+//   - m_d is the slots' counts in LDS (fp32, exact), changed by one LDS add
+//     each way per token, and read once per draw, SL per lane;
+//   - no topic list is kept sorted between draws, and no lane's result is
+//     broadcast: the lane whose slots hold the crossing adds the token to its
+//     slot itself.
+// A set bit per topic in the list (P) and the number of list entries before
+// each chunk of 2^log_b topics (pre) give a topic's slot by a popcount.
+//
+// A draw of token i, with m^{-i} (Section 3.5):
+//   sigma_b = sum_k phi_kv m_k over the slots, a group prefix sum ordering
+//   the lanes, so running sums ascend in k; u (sigma_a + sigma_b) < sigma_a
+//   takes the a-part, else the first slot whose running sum passes
+//   y = u (sigma_a + sigma_b) - sigma_a.
+//
+// The b-part in fp32, with a proof of exactness.  Every quantity is within a
+// known relative error of its exact value: a term b~ = fp32(fp32(x R~_k) m)
+// (R~_k = fp32(R_k)) or fp32(phi m) is within 4.01 u of phi_kv m_k
+// (u = 2^-24), a lane's running sum of SL terms adds (SL - 1) u, the group
+// scan log2(G) u, the exclusive prefix and y minus it u each (relative to
+// Z = sigma_a + sigma_b).  x = u0 Z and y = x - sigma_a are within
+// (SL + 8 + log2 G) u Z, so every comparison of y with 0 or with a running sum
+// errs by less than (3 SL + 2 log2 G + 14) u Z.  The decision is taken only
+// when y lies farther than tol = (64 + 8 SL) u Z from the boundary it is
+// compared with (more than twice that error); it is then the decision of
+// exact arithmetic, which is also the fp64 path's.  Otherwise (a few draws in
+// ten thousand) draw_f64 decides in fp64.  So the result is the fp64 one bit
+// for bit, whatever the split of the topics over lanes.
+//
+// When the list would exceed 16 G slots (possible only when K > 16 G) the
+// wave's groups turn dense: slot = topic, and every draw sums the word's Phi
+// column in fp64 with the counts read by topic.
+//
+// What bounds it: the draws of a document are a serial chain (LDS add, LDS
+// read, the scan, the decision), so a long document is bound by the chain's
+// latency and a full chip by VALU issue: see the figures at z_step_kernel.
 // ---------------------------------------------------------------------------
 struct ZArgs {
     DevModel m;
     DevCorpus c;
     const WorkItem *items;
     int32_t n_items;
-    int32_t m_bytes;           // count table of one group
-    int32_t group_bytes;       // count table and topic list of one group
-    int32_t wave_bytes;        // the groups of one wave
+    SlotLds lds;               // one group's layout
     int32_t r_bytes;           // the block's copy of R_k, at the start of LDS
     int32_t n_hot;             // frequent words counted per block in LDS (0: none)
     int32_t hot_off;           // their counters' byte offset in LDS
@@ -891,73 +927,24 @@ struct ZArgs {
     double *ll_doc;         // per-document log-joint terms (or null)
 };
 
-// inputs of one token draw, staged in LDS so every lane of the group reads
-// them with one broadcast load
-struct alignas(16) TokenIn {
-    uint32_t vk;     // v * K: the word's row of n and of the dense phi
-    int32_t cb;      // first CSC entry of the word's Phi column
-    uint16_t kold;   // topic before the draw
-    uint16_t kv;     // nonzeros in the column (K_v^Phi <= K <= 4096)
-    float u0;        // the 24-bit uniform of the a/b decision and the b-walk
-                     // (r >> 8) 2^-24, exact in fp32
-    uint16_t ka;     // the a-part's topic: the alias draw depends only on the
-                     // word and the token's random numbers, so it is taken at
-                     // staging time, off the draw's critical path
-    uint16_t sure;   // 1: the a-part is certain whatever the document's counts
-    uint32_t vs;     // v * ks16: the word's row of the 16-bit draws (the
-                     // products are taken once, at staging)
-    double sa;       // sigma_a(v)
+// one draw's inputs, staged in LDS in draw order; every lane of the group
+// reads them with one broadcast load
+struct alignas(16) DrawRec {
+    uint32_t row;    // byte offset of the word's row: 16-bit draws, or fp32 phi (flag)
+    uint32_t uc;     // 24-bit uniform << 8 | flag << 7 | lane of the token (127: no draw)
+    float saf;       // fp32(sigma_a(v)); NaN when it is too small for fp32's normal
+                     // range (no comparison holds: the fp64 path decides)
+    uint32_t pad;
 };
 
-static_assert(sizeof(TokenIn) == 32, "TokenIn is staged as 32-byte records");
+constexpr uint32_t REC_F32 = 128;      // the word's terms are gathered as fp32 phi
+constexpr uint32_t REC_NONE = 127;
 
-// the z-step's staged token: as TokenIn, with sigma_a in fp32 (its fp32
-// b-part) and the word id (the fp64 b-part reads sigma_a(v) itself)
-struct alignas(16) TokenZ {
-    uint32_t vk;     // v * K
-    int32_t cb;      // first CSC entry of the word's Phi column
-    uint16_t kold;   // topic before the draw
-    uint16_t kv;     // nonzeros in the column
-    float u0;        // (r0 >> 8) 2^-24
-    uint16_t ka;     // the a-part's alias draw
-    uint16_t sure;   // 1: the a-part is certain whatever the document's counts
-    uint32_t vs;     // v * ks16
-    float saf;       // fp32(sigma_a(v))
-    uint32_t v;      // the word
+// draw statistics of a lane's tokens
+struct ZStat {
+    unsigned long long j = 0, jb = 0;    // sum of J; over the tokens not decided at staging
+    uint32_t a = 0, deg = 0, fb = 0;     // a-part draws, degenerate tokens, fp64 draws
 };
-
-static_assert(sizeof(TokenZ) == 32, "TokenZ is staged as 32-byte records");
-
-// draw statistics of a lane's group: totals, and the current document's J
-// and a-part counts in 32 bits (cheaper to add per draw), moved into the
-// totals when the document is done
-struct ZCount {
-    unsigned long long J, A, degenerate;
-    uint32_t j, a;
-    __device__ void flush()
-    {
-        J += j;
-        A += a;
-        j = 0;
-        a = 0;
-    }
-};
-
-// the z-step's draw statistics of the current document (group-uniform,
-// 32-bit), added to the wave's 64-bit totals in LDS when the document is
-// done: sum of J, the same over the tokens whose b-terms were computed (not
-// decided at staging), a-part draws, degenerate tokens
-struct ZCount32 {
-    uint32_t j, jb, a, deg, fb;   // fb: draws the fp32 b-part left to the fp64 one
-};
-
-// b-terms per lane kept in registers for the walk: one gather round covers
-// G * keep entries
-template <int G>
-constexpr int keep_of()
-{
-    return G <= 8 ? 8 : 4;
-}
 
 template <int G>
 constexpr int log2g()
@@ -965,212 +952,6 @@ constexpr int log2g()
     return G == 64 ? 6 : (G == 32 ? 5 : (G == 16 ? 4 : 3));
 }
 
-// list slots per lane in the windowed topic list: W G slots hold the list
-// while it is no longer than that (128 for groups of 16 and 32)
-template <int G>
-constexpr int win_of()
-{
-    return G == 16 ? 8 : 4;
-}
-
-// value of the windowed list's slots past its end: above every topic
-// (K <= 4096) and below 2^15, so that packed signed 16-bit differences of
-// slot values never overflow
-constexpr int32_t LIST_PAD = 0x7FFF;
-
-// The state of the document a group is working on: m_d by topic (mt) and
-// lst, its topics with a nonzero count in ascending order (during a draw it
-// also holds the token's old topic, whose count may be zero: that b-term is
-// zero).  lst[0] always holds a valid topic, so padding slots can read it.
-// WIN: lst is 16-byte aligned and has room for W G + W slots (W =
-// win_of<G>()), and every slot in [L, W G + W) holds LIST_PAD (see
-// list_window_update).
-template <typename CT, bool WIN = false>
-struct DocState {
-    CT *mt;
-    uint16_t *lst;
-    int32_t L;       // entries of lst (group-uniform)
-};
-
-// lst <- the topics with a nonzero count; lane g scans topics [g*R, g*R + R)
-template <int G, typename CT, bool WIN>
-__device__ __forceinline__ void build_list(DocState<CT, WIN> &S, int g, int32_t K)
-{
-    if constexpr (WIN) {
-        // the windows read LIST_PAD past the list
-        constexpr int W = win_of<G>();
-        const uint32_t pad2 = (uint32_t)LIST_PAD * 0x10001u;
-#pragma unroll
-        for (int j = 0; j < W; j += 2) *(uint32_t *)(S.lst + W * g + j) = pad2;
-        if (g == 0) {
-#pragma unroll
-            for (int j = 0; j < W; j += 2) *(uint32_t *)(S.lst + W * G + j) = pad2;
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
-    const int32_t R = (K + G - 1) / G;
-    const int32_t t0 = g * R;
-    const int32_t t1 = t0 + R < K ? t0 + R : K;
-    int32_t c = 0;
-    for (int32_t t = t0; t < t1; ++t) c += S.mt[t] != 0;
-    const int32_t incl = group_scan_incl_i32<G>(c);
-    int32_t o = incl - c;
-    S.L = group_bcast<G>(incl, G - 1);
-    for (int32_t t = t0; t < t1; ++t)
-        if (S.mt[t]) S.lst[o++] = (uint16_t)t;
-    __builtin_amdgcn_wave_barrier();
-}
-
-// lane g's block of lst: entries [base, base + n), q = ceil(L / G) per lane
-template <int G>
-__device__ __forceinline__ int32_t list_block(int32_t L, int g, int32_t &base)
-{
-    const int32_t q = (L + G - 1) / G;
-    base = (int32_t)__umul24((uint32_t)g, (uint32_t)q);
-    const int32_t n = L - base < q ? L - base : q;
-    return n > 0 ? n : 0;
-}
-
-// insert topic k (not in lst): the entries above it move up one place
-template <int G, typename CT, bool WIN>
-__device__ __forceinline__ void list_insert(DocState<CT, WIN> &S, int32_t k, int g)
-{
-    int32_t base;
-    const int32_t n = list_block<G>(S.L, g, base);
-    // the block's first entry is overwritten by the lane below: read it first
-    const int32_t first = n > 0 ? S.lst[base] : 0;
-    __builtin_amdgcn_wave_barrier();
-    int32_t below = 0;
-    for (int32_t j = n - 1; j >= 1; --j) {
-        const int32_t v = S.lst[base + j];
-        if (v > k) S.lst[base + j + 1] = (uint16_t)v;
-        else ++below;
-    }
-    if (n > 0) {
-        if (first > k) S.lst[base + 1] = (uint16_t)first;
-        else ++below;
-    }
-    const int32_t pos = group_bcast<G>(group_scan_incl_i32<G>(below), G - 1);
-    __builtin_amdgcn_wave_barrier();
-    if (g == 0) S.lst[pos] = (uint16_t)k;
-    S.L += 1;
-    __builtin_amdgcn_wave_barrier();
-}
-
-// remove topic k (in lst): the entries above it move down one place
-template <int G, typename CT, bool WIN>
-__device__ __forceinline__ void list_remove(DocState<CT, WIN> &S, int32_t k, int g)
-{
-    int32_t base;
-    const int32_t n = list_block<G>(S.L, g, base);
-    // the block's last entry is overwritten by the lane above: read it first
-    const int32_t last = n > 0 ? S.lst[base + n - 1] : 0;
-    __builtin_amdgcn_wave_barrier();
-    for (int32_t j = 0; j < n; ++j) {
-        const int32_t v = j == n - 1 ? last : S.lst[base + j];
-        if (v > k) S.lst[base + j - 1] = (uint16_t)v;
-    }
-    S.L -= 1;
-    // the slot freed at the end reads LIST_PAD again
-    if constexpr (WIN)
-        if (g == 0) S.lst[S.L] = (uint16_t)LIST_PAD;
-    __builtin_amdgcn_wave_barrier();
-}
-
-// The list as windows of W slots: lane g of the group holds slots
-// [W g, W g + W), W/2 32-bit LDS words of two slots each.  While every entry
-// lies inside the windows (L <= W G before and after), removing kout and
-// inserting kin (LIST_PAD: nothing) take one pass: each lane reads its window
-// and the slot on either side, forms its new window in registers and writes
-// it back.  Slots past the list hold LIST_PAD, so the same rules cover the
-// list's end.  With o the old slots (ascending) the two steps are
-//   removal:   o'[j] = o[j] < kout ? o[j] : o[j+1]
-//              = min(max(o[j], M_j), o[j+1]),  M_j = (o[j] >= kout) ? 0xFFFF : 0
-//   insertion: o''[j] = min(o'[j], max(o'[j-1], kin))
-// (for a sorted list the first entry not below kin takes kin and the ones
-// above it take their left neighbour), evaluated two slots at a time with
-// packed 16-bit min, max, subtract and shift.
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-typedef short i16x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ u16x2 as_u16x2(uint32_t x) { return __builtin_bit_cast(u16x2, x); }
-__device__ __forceinline__ uint32_t as_u32(u16x2 x) { return __builtin_bit_cast(uint32_t, x); }
-
-template <int W>
-struct alignas(2 * W) WinWords {
-    uint32_t w[W / 2];
-};
-
-template <int G, typename CT, bool WIN>
-__device__ __forceinline__ void list_window_update(DocState<CT, WIN> &S, int32_t kout, int32_t kin, int g)
-{
-    static_assert(WIN, "the windows need the padded list");
-    constexpr int W = win_of<G>();
-    constexpr int NW = W / 2;
-    uint16_t *w = S.lst + W * g;
-    WinWords<W> cur = *(const WinWords<W> *)w;
-    // (lane 0 reads the slot before the list, inside the count table, and
-    // drops it: an unconditional read needs no lane mask)
-    const uint32_t lraw = w[-1];
-    const uint32_t left = g > 0 ? lraw : 0u;
-    const uint32_t right = w[W];
-    __builtin_amdgcn_wave_barrier();
-    // removal (kout - 1 wraps to 0xFFFF for kout = 0: every slot moves)
-    const u16x2 km1 = (u16x2)(unsigned short)(kout - 1);
-    uint32_t r[NW];
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        const uint32_t nxt = __builtin_amdgcn_alignbit(i + 1 < NW ? cur.w[i + 1] : right, cur.w[i], 16);
-        const u16x2 a = as_u16x2(cur.w[i]);
-        const u16x2 m = __builtin_bit_cast(u16x2, __builtin_bit_cast(i16x2, km1 - a) >> (i16x2)15);
-        r[i] = as_u32(__builtin_elementwise_min(__builtin_elementwise_max(a, m), as_u16x2(nxt)));
-    }
-    // the new value of the slot left of the window
-    const uint32_t o0 = cur.w[0] & 0xFFFFu;
-    const uint32_t p = (int32_t)left < kout ? left : o0;
-    // insertion
-    const u16x2 kin2 = (u16x2)(unsigned short)kin;
-    WinWords<W> out;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        const uint32_t prv = __builtin_amdgcn_alignbit(r[i], i > 0 ? r[i - 1] : p << 16, 16);
-        out.w[i] = as_u32(__builtin_elementwise_min(as_u16x2(r[i]), __builtin_elementwise_max(as_u16x2(prv), kin2)));
-    }
-    *(WinWords<W> *)w = out;
-    __builtin_amdgcn_wave_barrier();
-}
-
-// after a draw: the old topic leaves the list when its count fell to zero,
-// the new one enters when it was absent
-template <int G, typename CT, bool WIN>
-__device__ __forceinline__ void list_update(DocState<CT, WIN> &S, int32_t kold, int32_t knew, int32_t mo,
-                                            int32_t mn, int g)
-{
-    const bool out = knew != kold && mo == 1;
-    const bool in = knew != kold && mn == 0;
-    if constexpr (WIN) {
-        if (__builtin_amdgcn_ballot_w64(out || in) == 0) return;
-        constexpr int32_t CAP = win_of<G>() * G;
-        const int32_t L2 = S.L + (in ? 1 : 0) - (out ? 1 : 0);
-        const bool wide = (out || in) && (S.L > CAP || L2 > CAP);
-        if (__builtin_amdgcn_ballot_w64(wide) == 0) {
-            list_window_update<G>(S, out ? kold : LIST_PAD, in ? knew : LIST_PAD, g);
-            S.L = L2;
-            return;
-        }
-    }
-    if (out) list_remove<G>(S, kold, g);
-    if (in) list_insert<G>(S, knew, g);
-}
-
-// up to KP b-terms of this lane: entries first + base + u (u < KP) of its
-// block, which has nl entries: topic, phi and m_d of each (count zeroed
-// past the end).  DOC: the block is in the document's topic list (LDS) and
-// the draw is gathered from the word's dense 16-bit column; otherwise the
-// block is of the word's packed CSC entries (topic | draw << 16), read
-// contiguously.  R (LDS) holds R_k.  Every slot loads from a valid address
-// (padding slots read entry `pad`), so all loads of a round are in flight
-// together.
 // Global reads take a 32-bit byte offset from the table's base (the plan
 // keeps every table under 4 GiB), so each address is one 32-bit add.
 template <typename T>
@@ -1179,610 +960,604 @@ __device__ __forceinline__ T load_at(const T *base, uint32_t byte_off)
     return *(const T *)((const char *)base + byte_off);
 }
 
-template <int KP, bool DOC, typename CT>
-__device__ __forceinline__ void lane_terms(const DevModel &M, const uint16_t *lst, const uint32_t g16o,
-                                           const uint32_t vk, const double *R, const CT *mt, const int32_t pad,
-                                           const int32_t first, const int32_t base, const int32_t nl,
-                                           int32_t (&kk)[KP], float (&fk)[KP], int32_t (&mk)[KP])
+// LDS accesses of the wave before and after are kept in this order (LDS
+// executes a wave's instructions in order; only the compiler is held)
+__device__ __forceinline__ void lds_order()
 {
-    bool ok[KP];
-    uint32_t x[KP];
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+__device__ __forceinline__ float lds_add(float *p, float x)
+{
+    return __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// the document a group is working on (all pointers in LDS)
+struct SlotDoc {
+    float *ms;        // counts by slot
+    DrawRec *tok;     // [G + 2] the block's draws, in order
+    uint32_t *P;      // a bit per topic: in the list
+    uint16_t *lst;    // topic of each slot
+    uint16_t *pre;    // list entries before each chunk of topics
+    uint16_t *out;    // [G] the new slot of each of the block's tokens
+    int32_t L;        // slots in use (group-uniform)
+    int32_t nz;       // topics with a nonzero count (group-uniform)
+    bool dense;       // slot = topic
+};
+
+__device__ __forceinline__ SlotDoc slot_doc(uint8_t *base, const SlotLds &A)
+{
+    SlotDoc S;
+    S.ms = (float *)base;
+    S.tok = (DrawRec *)(base + A.o_tok);
+    S.P = (uint32_t *)(base + A.o_p);
+    S.lst = (uint16_t *)(base + A.o_lst);
+    S.pre = (uint16_t *)(base + A.o_pre);
+    S.out = (uint16_t *)(base + A.o_out);
+    S.L = 0;
+    S.nz = 0;
+    S.dense = false;
+    return S;
+}
+
+// the list bits of chunk ch (topics [ch 2^log_b, (ch + 1) 2^log_b))
+__device__ __forceinline__ uint32_t chunk_bits(const uint32_t *P, int32_t ch, int32_t log_b)
+{
+    const int32_t k0 = ch << log_b;
+    const uint32_t w = P[k0 >> 5] >> (k0 & 31);
+    return log_b == 5 ? w : w & ((1u << (1 << log_b)) - 1u);
+}
+
+// the slot of topic k (in the list)
+__device__ __forceinline__ int32_t slot_of(const SlotDoc &S, const SlotLds &A, int32_t k)
+{
+    if (S.dense) return k;
+    const uint32_t bits = chunk_bits(S.P, k >> A.log_b, A.log_b);
+    return (int32_t)S.pre[k >> A.log_b] + __builtin_popcount(bits & ((1u << (k & ((1 << A.log_b) - 1))) - 1u));
+}
+
+__device__ __forceinline__ int32_t topic_of(const SlotDoc &S, int32_t slot) { return S.dense ? slot : S.lst[slot]; }
+
+// the count of any topic
+__device__ __forceinline__ int32_t count_of(const SlotDoc &S, const SlotLds &A, int32_t k)
+{
+    if (!S.dense && !((S.P[k >> 5] >> (k & 31)) & 1u)) return 0;
+    return (int32_t)S.ms[slot_of(S, A, k)];
+}
+
+// an empty document: no topic in the list
+template <int G>
+__device__ __forceinline__ void slots_clear(SlotDoc &S, const SlotLds &A, int g)
+{
+    for (int32_t w = g; w < A.p_words; w += G) S.P[w] = 0u;
+    S.L = 0;
+    S.nz = 0;
+    S.dense = false;
+    lds_order();
+}
+
+// after the list's bits were set from a document's tokens: its topics with a
+// nonzero count
+template <int G>
+__device__ __forceinline__ void slots_count_topics(SlotDoc &S, const SlotLds &A, int g)
+{
+    lds_order();
+    int32_t c = 0;
+    for (int32_t w = g; w < A.p_words; w += G) c += __builtin_popcount(S.P[w]);
+    S.nz = group_bcast<G>(group_scan_incl_i32<G>(c), G - 1);
+}
+
+// lay the slots out for a block: the topics with a nonzero count (first: the
+// bits already set in P, counts added afterwards by the caller; else the
+// previous layout's nonzero slots) and each marked lane's topic ka
+template <int G, bool BIG>
+__device__ __forceinline__ void slots_layout(SlotDoc &S, const SlotLds &A, int32_t K, bool first, bool mark,
+                                             int32_t ka, int g)
+{
+    // the previous layout's slots, topic | count << 16, in registers
+    constexpr int MAXU = BIG ? SLOTS_MAX : SLOTS_FEW;
+    uint32_t pk[MAXU];
 #pragma unroll
-    for (int u = 0; u < KP; ++u) {
-        ok[u] = base + u < nl;
-        const uint32_t e = (uint32_t)(ok[u] ? first + base + u : pad);
-        if constexpr (DOC) {
-            kk[u] = lst[e];
-        } else {
-            const uint32_t kg = load_at(M.ckg, e << 2);
-            kk[u] = (int32_t)(kg & 0xFFFFu);
-            x[u] = kg >> 16;
+    for (int u = 0; u < MAXU; ++u) {
+        pk[u] = 0;
+        if (__builtin_amdgcn_ballot_w64(!first && !S.dense && u * G < S.L) == 0) continue;
+        const int32_t e = u * G + g;
+        if (!first && !S.dense && e < S.L) {
+            const uint32_t k = S.lst[e];
+            const uint32_t m = (uint32_t)S.ms[e];
+            pk[u] = k | (m << 16);
+            if (m == 0) atomicAnd(&S.P[k >> 5], ~(1u << (k & 31)));
         }
     }
-    if constexpr (DOC) {
-        if (M.phi_method == 1) {
-            // Algorithm 1's Phi has no integer draws: phi itself is gathered
+    lds_order();
+    if (mark) atomicOr(&S.P[ka >> 5], 1u << (ka & 31));
+    lds_order();
+    // list entries of this lane's chunks, and before them
+    const int32_t c0 = g * A.ch_lane;
+    int32_t n = 0;
+    for (int32_t j = 0; j < A.ch_lane; ++j)
+        if (c0 + j < A.chunks) n += __builtin_popcount(chunk_bits(S.P, c0 + j, A.log_b));
+    const int32_t incl = group_scan_incl_i32<G>(n);
+    const int32_t L = group_bcast<G>(incl, G - 1);
+    const bool was_dense = S.dense;
+    if (BIG && __builtin_amdgcn_ballot_w64(was_dense || L > SLOTS_MAX * G) != 0) {
+        S.dense = true;
+        S.L = K;
+        if (!was_dense)
+            for (int32_t e = g; e < K; e += G) S.ms[e] = 0.0f;
+        lds_order();
 #pragma unroll
-            for (int u = 0; u < KP; ++u) {
-                fk[u] = load_at(M.phid, (vk + (uint32_t)kk[u]) << 2);
-                const int32_t m = mt[kk[u]];
-                mk[u] = ok[u] ? m : 0;
-            }
-            return;
+        for (int u = 0; u < MAXU; ++u)
+            if (pk[u] >> 16) S.ms[pk[u] & 0xFFFFu] = (float)(pk[u] >> 16);
+        lds_order();
+        return;
+    }
+    S.L = L;
+    int32_t o = incl - n;
+    for (int32_t j = 0; j < A.ch_lane; ++j) {
+        if (c0 + j >= A.chunks) break;
+        S.pre[c0 + j] = (uint16_t)o;
+        uint32_t bits = chunk_bits(S.P, c0 + j, A.log_b);
+        const int32_t k0 = (c0 + j) << A.log_b;
+        while (bits) {
+            S.lst[o++] = (uint16_t)(k0 + __builtin_ctz(bits));
+            bits &= bits - 1;
         }
-#pragma unroll
-        for (int u = 0; u < KP; ++u) x[u] = load_at(M.g16, g16o + ((uint32_t)kk[u] << 1));
     }
-    // phi_kv = fp32(x * R_k) == fp32(RN64(x / S_k)) for x < 2^16 and
-    // S_k < 2^27; every other nonzero cell carries 0xFFFF and its phi is
-    // read from the dense table (rare: one wave-uniform test per round)
-    bool esc = false;
-#pragma unroll
-    for (int u = 0; u < KP; ++u) {
-        const double r = R[kk[u]];
-        const int32_t m = mt[kk[u]];
-        fk[u] = (float)((double)x[u] * r);
-        esc |= x[u] == 0xFFFFu;
-        mk[u] = ok[u] ? m : 0;
+    // (the slots up to the next multiple of any SL are zero too)
+    for (int32_t e = g; e < A.ms_n; e += G) {
+        if (__builtin_amdgcn_ballot_w64(e - g < L + 4 * G) == 0) break;
+        S.ms[e] = 0.0f;
     }
-    if (__builtin_amdgcn_ballot_w64(esc)) {
+    lds_order();
 #pragma unroll
-        for (int u = 0; u < KP; ++u)
-            if (x[u] == 0xFFFFu) fk[u] = load_at(M.phid, (vk + (uint32_t)kk[u]) << 2);
+    for (int u = 0; u < MAXU; ++u) {
+        if (__builtin_amdgcn_ballot_w64((pk[u] >> 16) != 0) == 0) continue;
+        if (pk[u] >> 16) S.ms[slot_of(S, A, (int32_t)(pk[u] & 0xFFFFu))] = (float)(pk[u] >> 16);
+    }
+    lds_order();
+}
+
+// set the list's bits from tokens' topics, then (after the first layout) add
+// up their counts
+template <int G>
+__device__ __forceinline__ void slots_mark_tokens(SlotDoc &S, const uint16_t *z, int64_t s, int64_t e, int g)
+{
+#pragma unroll 4
+    for (int64_t i = s + g; i < e; i += G) {
+        const uint32_t k = z[i];
+        atomicOr(&S.P[k >> 5], 1u << (k & 31));
     }
 }
 
-// sigma_b = sum of the b-terms phi_kv m_k over one side, the a/b decision,
-// and for the b-part the topic whose running sum first exceeds
-// y = u_sigma - sigma_a (Section 3.5).  Returns the topic, or -1 for the
-// a-part (the caller takes the word's alias draw).  KP terms per lane and
-// round; the first round's terms stay in registers for the walk.
-template <int G, bool DOC, typename CT, int KP, bool WIN>
-__device__ __forceinline__ int32_t b_part(const DevModel &M, const TokenIn &tk, DocState<CT, WIN> &S, const double *R,
-                                          const int g, double &Zo)
+template <int G>
+__device__ __forceinline__ void slots_add_tokens(SlotDoc &S, const SlotLds &A, const uint16_t *z, int64_t s,
+                                                 int64_t e, int g)
 {
-    constexpr int LG = log2g<G>();
-    const int32_t J = DOC ? S.L : (int32_t)tk.kv;
-    const int32_t q = (J + G - 1) >> LG;
-    int32_t nl = J - g * q < q ? J - g * q : q;
-    nl = nl > 0 ? nl : 0;
-    const uint32_t g16o = tk.vs << 1;
-    const int32_t pad = DOC ? 0 : tk.cb;
-    const int32_t first = pad + (int32_t)__umul24((uint32_t)g, (uint32_t)q);
-    int32_t kk[KP], mk[KP];
-    float fk[KP];
-    lane_terms<KP, DOC, CT>(M, S.lst, g16o, tk.vk, R, S.mt, pad, first, 0, nl, kk, fk, mk);
-    // the products phi * m are exact in fp64, so adding them (or an fma)
-    // rounds exactly like the sum of the products
-    double bk[KP];
+#pragma unroll 4
+    for (int64_t i = s + g; i < e; i += G) lds_add(&S.ms[slot_of(S, A, z[i])], 1.0f);
+    lds_order();
+}
+
+// a token of the block as its lane holds it
+struct LaneTok {
+    int32_t v;          // word
+    int32_t ka;         // the a-part's alias draw (the old topic for an empty column)
+    int32_t kv;         // nonzeros in the word's column
+    uint32_t row, uc;   // as DrawRec (uc without the lane)
+    float saf;
+    bool sure;          // the a-part is certain whatever the document's counts, or
+                        // the column is empty: no draw
+};
+
+__device__ __forceinline__ LaneTok no_token() { return {0, 0, 0, 0u, 0u, 1.0f, true}; }
+
+// stage the token at this lane from its word's record.  nd: tokens in the
+// document's counts.  The a-part's draw from the word's alias table over
+// alpha_k phi_kv: slot j = floor(r1 K_v / 2^32), kept when r2 < its
+// threshold, else its alias (Section 3.5).  The b-terms sum to
+// sigma_b = sum_k phi_kv m_k <= phimax(v) (nd - 1), so when
+// u (sigma_a + phimax(v) (nd - 1)) < sigma_a the token takes the a-part
+// whatever the counts: tested in fp32 with a margin of 2^-20 (each side
+// rounds by less than 6 2^-24), so a token so decided has
+// x < sigma_a (1 - 10 2^-24) exactly, far outside any rounding of the sums.
+__device__ __forceinline__ LaneTok stage_token(const DevModel &M, int32_t v, int32_t kold, const r4 &r,
+                                               const int32_t nd)
+{
+    const uint4 rec = M.wrec[v];
+    LaneTok x;
+    x.v = v;
+    const uint32_t kv = rec.y & ~WREC_F32;
+    x.kv = (int32_t)kv;
+    const bool f32 = (rec.y & WREC_F32) != 0;
+    x.row = f32 ? (uint32_t)v * (uint32_t)M.K * 4u : (uint32_t)v * (uint32_t)M.ks16 * 2u;
+    x.uc = (r.x & 0xFFFFFF00u) | (f32 ? REC_F32 : 0u);
+    const float sa = __uint_as_float(rec.z);
+    x.saf = sa > 0x1p-100f ? sa : __uint_as_float(0x7FC00000u);
+    x.ka = kold;
+    x.sure = true;
+    if (kv > 0) {
+        const uint32_t j = scale32(r.y, kv);
+        const uint64_t a = M.calias[rec.x + j];
+        x.ka = (int32_t)((r.z < (uint32_t)a) ? ((a >> 32) & 0xFFFFu) : (a >> 48));
+        const float u0 = (float)(r.x >> 8) * 0x1p-24f;
+        const float B = __uint_as_float(rec.w) * (float)(nd - 1);
+        x.sure = nd > 0 && u0 * (sa + B) < sa * (1.0f - 0x1p-20f);
+    }
+    return x;
+}
+
+// The draw in fp64: every lane sums its terms in ascending order, the group
+// scan orders the lanes.  COL: the terms are the word's Phi column, the
+// counts read by topic (dense layout); else the slots.  Returns the slot of
+// the new topic, or -1 for the a-part; Z: sigma_a + sigma_b.
+template <int G, bool COL>
+__device__ __forceinline__ int32_t draw_f64(const uint4 *wrec, const double *sigma_a, const double *Rd,
+                                         const uint32_t *ckg, const uint16_t *g16, const float *phid, int32_t K,
+                                         int32_t ks16, int32_t v, float u0, const float *ms, const uint16_t *lst,
+                                         int32_t L, int32_t per, double &Zo)
+{
+    const int g = __lane_id() & (G - 1);
+    const uint4 rec = wrec[v];
+    const int32_t n = COL ? (int32_t)(rec.y & ~WREC_F32) : L;
+    const int32_t q = COL ? (n + G - 1) / G : per;
+    const int32_t e0 = g * q;
+    const int32_t e1 = e0 + q < n ? e0 + q : n;
+    const uint32_t row16 = (uint32_t)v * (uint32_t)ks16, row32 = (uint32_t)v * (uint32_t)K;
+    // term of entry e (exact in fp64: a 24-bit phi times a count below 2^16)
+    auto term = [&](int32_t e) -> double {
+        int32_t k;
+        uint32_t x;
+        float m;
+        if (COL) {
+            const uint32_t kg = ckg[rec.x + (uint32_t)e];
+            k = (int32_t)(kg & 0xFFFFu);
+            x = kg >> 16;
+            m = ms[k];
+        } else {
+            k = lst[e];
+            m = ms[e];
+            x = g16[row16 + (uint32_t)k];
+        }
+        // phi_kv = fp32(x R_k) == fp32(RN64(x / S_k)) for x < 2^16 and
+        // S_k < 2^27; every other nonzero cell holds 0xFFFF
+        const float f = x == 0xFFFFu ? phid[row32 + (uint32_t)k] : (float)((double)x * Rd[k]);
+        return (double)f * (double)m;
+    };
     double p = 0.0;
-#pragma unroll
-    for (int u = 0; u < KP; ++u) {
-        bk[u] = (double)fk[u] * (double)mk[u];
-        p += bk[u];
-    }
-    for (int32_t base = KP; base < nl; base += KP) {
-        int32_t k2[KP], m2[KP];
-        float f2[KP];
-        lane_terms<KP, DOC, CT>(M, S.lst, g16o, tk.vk, R, S.mt, pad, first, base, nl, k2, f2, m2);
-#pragma unroll
-        for (int u = 0; u < KP; ++u) p = __builtin_fma((double)f2[u], (double)m2[u], p);
-    }
+#pragma unroll 1
+    for (int32_t e = e0; e < e1; ++e) p += term(e);
     const double incl = group_scan_incl<G>(p);
     const double T = group_bcast_f64<G>(incl, G - 1);
-    const double Z = tk.sa + T;
+    const double sa = sigma_a[v];
+    const double Z = sa + T;
     Zo = Z;
-    const double x = (double)tk.u0 * Z;
-    if (x < tk.sa) return -1;
-    // b-part: the first lane whose running sum passes y walks its terms
-    const double y = x - tk.sa;
+    const double x = (double)u0 * Z;
+    if (x < sa) return -1;
+    const double y = x - sa;
+    // the first lane whose running sum passes y; none (rounding): the last
+    // positive term; no positive term: the a-part is the whole law
     const uint64_t bal = group_ballot<G>(incl > y);
     int f = -1;
     if (bal) {
-        f = G <= 32 ? __builtin_ctz((uint32_t)bal) : __builtin_ctzll(bal);
+        f = __builtin_ctzll(bal);
     } else {
         const uint64_t pos = group_ballot<G>(p > 0.0);
         if (pos) f = 63 - __builtin_clzll(pos);
     }
-    if (f < 0) return -1;  // no positive b-term survived rounding: the a-part is the whole law
-    // every lane walks its kept terms (registers only, no branch around the
-    // crossing lane); the crossing lane's result is the draw, unless its
-    // block holds more terms than were kept: then that lane walks them all
-    int32_t kf = -1;
-    {
+    if (f < 0) return -1;
+    int32_t at = -1;
+    if (g == f) {
         double c = incl - p;
-        int32_t last = -1;
-#pragma unroll
-        for (int u = 0; u < KP; ++u) {
-            if (bk[u] > 0.0) {
-                c += bk[u];
-                last = kk[u];
-                if (kf < 0 && c > y) kf = kk[u];
+#pragma unroll 1
+        for (int32_t e = e0; e < e1; ++e) {
+            const double b = term(e);
+            if (b > 0.0) {
+                c += b;
+                at = e;
+                if (c > y) break;
             }
         }
-        if (kf < 0) kf = last;
+        if (COL && at >= 0) at = (int32_t)(ckg[rec.x + (uint32_t)at] & 0xFFFFu);
     }
-    if (nl > KP && g == f) {
-        double c = incl - p;
-        int32_t last = -1;
-        kf = -1;
-        {
-            for (int32_t base = 0; base < nl && kf < 0; base += KP) {
-                int32_t k2[KP], m2[KP];
-                float f2[KP];
-                lane_terms<KP, DOC, CT>(M, S.lst, g16o, tk.vk, R, S.mt, pad, first, base, nl, k2, f2, m2);
-#pragma unroll
-                for (int u = 0; u < KP; ++u) {
-                    const double bv = (double)f2[u] * (double)m2[u];
-                    if (bv > 0.0) {
-                        c += bv;
-                        last = k2[u];
-                        if (kf < 0 && c > y) kf = k2[u];
-                    }
-                }
-            }
-        }
-        if (kf < 0) kf = last;
-    }
-    return group_bcast<G>(kf, f);
+    return __shfl(at, f, G);
 }
 
-// ---------------------------------------------------------------------------
-// The same b-part in fp32 with a proven error bound, the z-step's common
-// path.  Every quantity is within a known relative error of its exact value:
-// a term b~ = fp32(fp32(x R~_k) m) (R~_k = fp32(R_k)) or fp32(phi m) is
-// within 4.01 u of phi_kv m_k (u = 2^-24), a lane's partial sum of q terms
-// adds (q - 1) u, the group scan log2(G) u and the exclusive prefix u
-// (relative to sigma_b), and the walk over the crossing lane's terms q u
-// more.  x = u0 (sigma_a + sigma_b) and y = x - sigma_a are within
-// (q + 8 + log2 G) u Z of their exact values, so every comparison of y with
-// 0 or with a running sum errs by less than (3q + 2 log2 G + 13) u Z.  The
-// decision is taken here only when y lies farther than
-// tol = (64 + 8q) u Z from the boundary it is compared with (at least 2.4
-// times that error); it is then the exact-arithmetic decision, which is also
-// the fp64 path's (b_part).  Otherwise (returned as -2; the z-step counts
-// these draws: about 5e-4 per token on a 1000-topic corpus) the caller runs
-// b_part.  So the result is b_part's bit for bit.
-// Returns the topic, -1 for the a-part or -2 for undecided.
-// ---------------------------------------------------------------------------
-template <int KP, bool DOC, typename CT, bool EARLY>
-__device__ __forceinline__ void lane_terms_f32(const DevModel &M, const uint16_t *lst, const uint32_t g16o,
-                                               const uint32_t vk, const float *Rf, const CT *mt, const int32_t pad,
-                                               const int32_t first, const int32_t base, const int32_t nl,
-                                               int32_t (&kk)[KP], float (&bf)[KP])
+template <int G, bool COL>
+__device__ __forceinline__ int32_t slots_draw_f64(const DevModel &M, const SlotDoc &S, int32_t v, float u0,
+                                                  int32_t per, double &Z)
 {
-    bool ok[KP];
-    uint32_t x[KP];
+    return draw_f64<G, COL>(M.wrec, M.sigma_a, M.Rd, M.ckg, M.g16, M.phid, M.K, M.ks16, v, u0, S.ms, S.lst, S.L, per,
+                            Z);
+}
+
+// a lane's token during a block: old slot, a-part slot, the counts its old
+// and new slot held when it left and entered (for the statistics), and what
+// was drawn
+struct LaneDraw {
+    int32_t po, pa;
+    uint32_t key;       // segment << 7 | rank within it for a token decided at
+                        // staging (segment: draws before it); ~0: none
+    float ro, rn;       // (2 and 1: no topic left or entered)
+    uint32_t a, fb;
+};
+
+// tokens decided at staging that lie before draw i: old slot to a-part slot,
+// one after the other
+template <bool STATS>
+__device__ __forceinline__ void move_segment(const SlotDoc &S, LaneDraw &d, uint32_t i)
+{
+    for (uint32_t t = i << 7; __builtin_amdgcn_ballot_w64(d.key == t) != 0; ++t)
+        if (d.key == t) {
+            if (STATS) {
+                d.ro = lds_add(&S.ms[d.po], -1.0f);
+                d.rn = lds_add(&S.ms[d.pa], 1.0f);
+            } else {
+                (void)lds_add(&S.ms[d.po], -1.0f);
+                (void)lds_add(&S.ms[d.pa], 1.0f);
+            }
+        }
+}
+
+// the block's draws, n_max of them (the largest group's), with SL slots per
+// lane; DEPTH draws' gathers in flight
+template <int G, int SL, bool STATS>
+__device__ __forceinline__ void draw_slots(const DevModel &M, const SlotDoc &S, const float *Rf, const int32_t v,
+                                           LaneDraw &d, const uint32_t n_max, const int lane_g)
+{
+    constexpr int DEPTH = SL <= 6 ? 2 : 1;
+    // (opaque to the compiler, which would otherwise compute every SL's slot
+    // addresses ahead of the token loop and spill them)
+    int g = lane_g;
+    asm volatile("" : "+v"(g));
+    uint32_t kk[SL];       // topic of each slot (slots past the list: the first's)
+    float R[SL];
 #pragma unroll
-    for (int u = 0; u < KP; ++u) {
-        ok[u] = base + u < nl;
-        const uint32_t e = (uint32_t)(ok[u] ? first + base + u : pad);
-        if constexpr (DOC) {
-            kk[u] = lst[e];
+    for (int u = 0; u < SL; ++u) {
+        const int32_t e = g * SL + u;
+        kk[u] = S.lst[e < S.L ? e : 0];
+        R[u] = Rf[kk[u]];
+    }
+    DrawRec rec[DEPTH];
+    uint32_t x[DEPTH][SL];
+    auto gather = [&](int b) {
+        const uint32_t row = rec[b].row;
+        const bool f32 = (rec[b].uc & REC_F32) != 0;
+        if (__builtin_amdgcn_ballot_w64(f32) == 0) {
+#pragma unroll
+            for (int u = 0; u < SL; ++u) x[b][u] = load_at(M.g16, (kk[u] << 1) + row);
+        } else if (f32) {
+#pragma unroll
+            for (int u = 0; u < SL; ++u) x[b][u] = __float_as_uint(load_at(M.phid, (kk[u] << 2) + row));
         } else {
-            const uint32_t kg = load_at(M.ckg, e << 2);
-            kk[u] = (int32_t)(kg & 0xFFFFu);
-            x[u] = kg >> 16;
-        }
-    }
-    if constexpr (DOC) {
-        if (M.phi_method == 1) {
 #pragma unroll
-            for (int u = 0; u < KP; ++u) {
-                const float f = load_at(M.phid, (vk + (uint32_t)kk[u]) << 2);
-                const int32_t m = mt[kk[u]];
-                bf[u] = f * (float)(ok[u] ? m : 0);
+            for (int u = 0; u < SL; ++u) x[b][u] = load_at(M.g16, (kk[u] << 1) + row);
+        }
+    };
+#pragma unroll
+    for (int b = 0; b < DEPTH; ++b) {
+        rec[b] = S.tok[b];
+        gather(b);
+    }
+    const uint64_t here = __builtin_amdgcn_ballot_w64(true);
+    for (uint32_t i0 = 0; i0 < n_max; i0 += DEPTH) {
+#pragma unroll
+        for (int b = 0; b < DEPTH; ++b) {
+            const uint32_t i = i0 + b;
+            if (b > 0 && i >= n_max) break;
+            move_segment<STATS>(S, d, i);
+            const uint32_t uc = rec[b].uc;
+            const float sa = rec[b].saf;
+            const int c = (int)(uc & 127u);
+            // phi of the slots (to rounding), from the gathered draws
+            float f[SL];
+            const bool f32 = (uc & REC_F32) != 0;
+#pragma unroll
+            for (int u = 0; u < SL; ++u) f[u] = (float)x[b][u] * R[u];
+            if (__builtin_amdgcn_ballot_w64(f32) != 0) {
+#pragma unroll
+                for (int u = 0; u < SL; ++u) f[u] = f32 ? __uint_as_float(x[b][u]) : f[u];
             }
-            return;
-        }
+            rec[b] = S.tok[i + DEPTH < G ? i + DEPTH : G];
+            // m^{-i}
+            if (g == c) {
+                if (STATS) d.ro = lds_add(&S.ms[d.po], -1.0f);
+                else (void)lds_add(&S.ms[d.po], -1.0f);
+            }
+            float m[SL];
 #pragma unroll
-        for (int u = 0; u < KP; ++u) x[u] = load_at(M.g16, g16o + ((uint32_t)kk[u] << 1));
-    }
-    // each term's R_k and count (LDS).  EARLY: all issued before any
-    // gathered draw is used; left to itself the scheduler waits for the
-    // first gather before the later terms' LDS reads, adding their latency
-    // to the gathers' (the z-step's long documents draw 4% faster so; the
-    // fold-in kernel, which passes false, 2% slower)
-    float rr[KP];
-    int32_t mm[KP];
+            for (int u = 0; u < SL; ++u) m[u] = S.ms[g * SL + u];
+            gather(b);
+            // running sums of the lane's terms
+            float cs[SL];
+            cs[0] = f[0] * m[0];
 #pragma unroll
-    for (int u = 0; u < KP; ++u) {
-        rr[u] = Rf[kk[u]];
-        mm[u] = mt[kk[u]];
-    }
-    if constexpr (EARLY) __builtin_amdgcn_sched_barrier(0);
-    bool esc = false;
-    float mf[KP];
+            for (int u = 1; u < SL; ++u) cs[u] = cs[u - 1] + f[u] * m[u];
+            const float incl = group_scan_incl_f32<G>(cs[SL - 1]);
+            const float T = group_last_f32<G>(incl);
+            const float Z = sa + T;
+            const float y = ((float)(uc >> 8) * 0x1p-24f) * Z - sa;
+            const float tol = Z * ((float)(64 + 8 * SL) * 0x1p-24f);
+            const bool is_a = y < -tol;
+            // y relative to the lane's slots; how far it is from every
+            // boundary of them, negative outside
+            const float yl = y - (incl - cs[SL - 1]);
+            float near = fminf(yl, cs[SL - 1] - yl);
 #pragma unroll
-    for (int u = 0; u < KP; ++u) {
-        mf[u] = (float)(ok[u] ? mm[u] : 0);
-        bf[u] = ((float)x[u] * rr[u]) * mf[u];
-        esc |= x[u] == 0xFFFFu;
-    }
-    if (__builtin_amdgcn_ballot_w64(esc)) {
+            for (int u = 0; u + 1 < SL; ++u) near = fminf(near, fabsf(cs[u] - yl));
+            const bool mine = near > tol;
+            const uint64_t in_a = __builtin_amdgcn_ballot_w64(is_a), in_b = __builtin_amdgcn_ballot_w64(mine);
+            if (mine) {
+                // this lane's slots hold the crossing
+                int32_t at = 0;
 #pragma unroll
-        for (int u = 0; u < KP; ++u)
-            if (x[u] == 0xFFFFu) bf[u] = load_at(M.phid, (vk + (uint32_t)kk[u]) << 2) * mf[u];
-    }
-}
-
-template <int G, bool DOC, typename CT, int KP, bool WIN, bool EARLY>
-__device__ __forceinline__ int32_t b_part_f32(const DevModel &M, const TokenZ &tk, DocState<CT, WIN> &S,
-                                              const float *Rf, const int g)
-{
-    constexpr int LG = log2g<G>();
-    const int32_t J = DOC ? S.L : (int32_t)tk.kv;
-    const int32_t q = (J + G - 1) >> LG;
-    int32_t nl = J - g * q < q ? J - g * q : q;
-    nl = nl > 0 ? nl : 0;
-    const uint32_t g16o = tk.vs << 1;
-    const int32_t pad = DOC ? 0 : tk.cb;
-    const int32_t first = pad + (int32_t)__umul24((uint32_t)g, (uint32_t)q);
-    int32_t kk[KP];
-    float bf[KP];
-    lane_terms_f32<KP, DOC, CT, EARLY>(M, S.lst, g16o, tk.vk, Rf, S.mt, pad, first, 0, nl, kk, bf);
-    float p = 0.0f;
-#pragma unroll
-    for (int u = 0; u < KP; ++u) p += bf[u];
-    for (int32_t base = KP; base < nl; base += KP) {
-        int32_t k2[KP];
-        float f2[KP];
-        lane_terms_f32<KP, DOC, CT, EARLY>(M, S.lst, g16o, tk.vk, Rf, S.mt, pad, first, base, nl, k2, f2);
-#pragma unroll
-        for (int u = 0; u < KP; ++u) p += f2[u];
-    }
-    const float incl = group_scan_incl_f32<G>(p);
-    const float T = group_bcast_f32<G>(incl, G - 1);
-    const float sa = tk.saf;
-    const float Z = sa + T;
-    const float y = tk.u0 * Z - sa;
-    const float tol = Z * ((float)(64 + 8 * q) * 0x1p-24f);
-    // (a sigma_a too small for fp32's normal range goes to the fp64 path)
-    if (y < -tol && sa > 0x1p-100f) return -1;
-    if (!(y > tol) || !(sa > 0x1p-100f)) return -2;
-    const uint64_t bal = group_ballot<G>(incl > y);
-    if (!bal) return -2;
-    const int f = G <= 32 ? __builtin_ctz((uint32_t)bal) : __builtin_ctzll(bal);
-    // every lane walks its kept terms; the crossing lane's result is the
-    // draw when its interval [lo, hi) keeps tol from y on both sides
-    float c = incl - p;
-    int32_t kf = -1;
-    float lo = 0.0f, hi = 0.0f;
-#pragma unroll
-    for (int u = 0; u < KP; ++u) {
-        const float c2 = c + bf[u];
-        if (kf < 0 && bf[u] > 0.0f && c2 > y) {
-            kf = kk[u];
-            lo = c;
-            hi = c2;
-        }
-        c = c2;
-    }
-    if (nl > KP && g == f && kf < 0) {
-        for (int32_t base = KP; base < nl && kf < 0; base += KP) {
-            int32_t k2[KP];
-            float f2[KP];
-            lane_terms_f32<KP, DOC, CT, EARLY>(M, S.lst, g16o, tk.vk, Rf, S.mt, pad, first, base, nl, k2, f2);
-#pragma unroll
-            for (int u = 0; u < KP; ++u) {
-                const float c2 = c + f2[u];
-                if (kf < 0 && f2[u] > 0.0f && c2 > y) {
-                    kf = k2[u];
-                    lo = c;
-                    hi = c2;
+                for (int u = 0; u + 1 < SL; ++u) at += cs[u] <= yl ? 1 : 0;
+                at += g * SL;
+                (void)lds_add(&S.ms[at], 1.0f);
+                S.out[c] = (uint16_t)at;
+            }
+            if (is_a && g == c) {
+                if (STATS) d.rn = lds_add(&S.ms[d.pa], 1.0f);
+                else (void)lds_add(&S.ms[d.pa], 1.0f);
+                d.a = 1;
+            }
+            // a decided group has all its lanes in in_a or one in in_b
+            if (__builtin_popcountll(in_a) + G * __builtin_popcountll(in_b) != __builtin_popcountll(here)) {
+                const bool open = !is_a && group_ballot<G>(mine) == 0;
+                double Zd;
+                const int32_t vc = __shfl(v, c & (G - 1), G);
+                const int32_t at = slots_draw_f64<G, false>(M, S, vc, (float)(uc >> 8) * 0x1p-24f, SL, Zd);
+                if (open) {
+                    if (at >= 0) {
+                        if (g == 0) {
+                            (void)lds_add(&S.ms[at], 1.0f);
+                            S.out[c] = (uint16_t)at;
+                        }
+                    } else if (g == c) {
+                        const float was = lds_add(&S.ms[d.pa], 1.0f);
+                        if (STATS) d.rn = was;
+                        d.a = 1;
+                    }
+                    if (g == c) d.fb = 1;
                 }
-                c = c2;
             }
         }
     }
-    const int32_t res = (kf >= 0 && y - lo > tol && hi - y > tol) ? kf : -2;
-    return group_bcast<G>(res, f);
+    move_segment<STATS>(S, d, n_max);
 }
 
-// draw one token (group-uniform control flow); returns the new topic, or
-// -1 - kold for a token whose word has an empty Phi column (it keeps kold)
-template <int G, typename CT, bool WIN>
-// (Zo: the conditional's normaliser sigma_a + sigma_b, when it is computed)
-__device__ __forceinline__ int32_t draw_token(const DevModel &M, const TokenIn &tk, DocState<CT, WIN> &S, const double *R,
-                                              const int g, const int32_t side_ratio, ZCount &cnt, double &Zo)
+// the block's draws in the dense layout (fp64 over the word's column)
+template <int G, bool STATS>
+__device__ __forceinline__ void draw_dense(const DevModel &M, const SlotDoc &S, const int32_t v, LaneDraw &d,
+                                           const uint32_t n_max, const int g)
 {
-    CT *mt = S.mt;
-    // m^{-i}: remove the token from its document's counts.  (Every lane of
-    // the group stores the same count to the same address: one store without
-    // a lane mask, cheaper than the branch around a single lane's store.)
-    const int32_t kold = tk.kold;
-    const int32_t mo = mt[kold];
-    __builtin_amdgcn_wave_barrier();
-    mt[kold] = (CT)(mo - 1);
-    __builtin_amdgcn_wave_barrier();
-    const int32_t Kv = tk.kv;
-    // (tested for the wave first: a wave without such a token skips the
-    // lane-masked branch)
-    if (__builtin_amdgcn_ballot_w64(Kv == 0) != 0 && Kv == 0) {
-        // 0/0 conditional: the token keeps its topic
-        mt[kold] = (CT)mo;
-        __builtin_amdgcn_wave_barrier();
-        cnt.degenerate++;
-        return -1 - kold;
-    }
-    // the document's topics with a nonzero count besides the token
-    const int32_t Kd = S.L - (mo == 1 ? 1 : 0);
-    cnt.j += (uint32_t)(Kd < Kv ? Kd : Kv);
-    // b-terms over one side: the document's topics (lst) or the word's Phi
-    // column, ascending topic order either way.  The column is read
-    // contiguously while the document side gathers single draws from the
-    // dense column, so a group prefers the column side up to side_ratio
-    // times the document's topic count.  The side is taken for the whole
-    // wave (the document side if any of its groups prefers it: a frequent
-    // word's column is long, a document's topic list is not), so the
-    // wave's groups do not diverge; the side changes cost, not the law.
-    int32_t knew = -1;
-    // when every group's token in the wave takes the a-part whatever its
-    // b-terms (decided at staging), the b-terms are not needed
-    if (__builtin_amdgcn_ballot_w64(tk.sure == 0) != 0) {
-        const bool prefer_doc = Kd == 0 || (uint32_t)Kv > __umul24((uint32_t)side_ratio, (uint32_t)Kd);
-        const bool doc = __builtin_amdgcn_ballot_w64(prefer_doc) != 0;
-        // terms per lane and round: a half or three quarters of the
-        // registers' worth when no group of the wave has more than that many
-        // per lane (one round either way)
-        constexpr int KP = keep_of<G>();
-        const int32_t J = doc ? S.L : Kv;
-        const bool over2 = __builtin_amdgcn_ballot_w64(J > (KP / 2) * G) != 0;
-        const bool over3 = __builtin_amdgcn_ballot_w64(J > (3 * KP / 4) * G) != 0;
-        if (doc)
-            knew = !over2 ? b_part<G, true, CT, KP / 2>(M, tk, S, R, g, Zo)
-                          : (!over3 ? b_part<G, true, CT, 3 * KP / 4>(M, tk, S, R, g, Zo)
-                                    : b_part<G, true, CT, KP>(M, tk, S, R, g, Zo));
-        else
-            knew = !over2 ? b_part<G, false, CT, KP / 2>(M, tk, S, R, g, Zo)
-                          : (!over3 ? b_part<G, false, CT, 3 * KP / 4>(M, tk, S, R, g, Zo)
-                                    : b_part<G, false, CT, KP>(M, tk, S, R, g, Zo));
-    }
-    if (knew < 0) {
-        // a-part: the word's alias table over alpha_k phi_kv (drawn when the
-        // token was staged)
-        knew = tk.ka;
-        cnt.a++;
-    }
-    // add the token back with its new topic
-    const int32_t mn = mt[knew];
-    __builtin_amdgcn_wave_barrier();
-    mt[knew] = (CT)(mn + 1);
-    __builtin_amdgcn_wave_barrier();
-    list_update<G>(S, kold, knew, mo, mn, g);
-    return knew;
-}
-
-// the fp64 b-part for the draws the fp32 one leaves undecided (a few per
-// ten thousand tokens), with the fields it reads in registers
-template <int G, bool DOC, typename CT, int KP>
-__device__ __forceinline__ int32_t b_part_fp64(uint32_t *ckg, uint16_t *g16, float *phid, const double *Rd,
-                                               const double *sigma_a, const int32_t phi_method, const TokenZ tz,
-                                               CT *mt, uint16_t *lst, const int32_t L, const int g)
-{
-    // the fields b_part reads, in registers
-    DevModel M;
-    M.ckg = ckg;
-    M.g16 = g16;
-    M.phid = phid;
-    M.phi_method = phi_method;
-    TokenIn tk;
-    tk.vk = tz.vk;
-    tk.cb = tz.cb;
-    tk.kv = tz.kv;
-    tk.u0 = tz.u0;
-    tk.vs = tz.vs;
-    tk.sa = sigma_a[tz.v];
-    DocState<CT, true> S;
-    S.mt = mt;
-    S.lst = lst;
-    S.L = L;
-    double Zo;
-    return b_part<G, DOC, CT, KP>(M, tk, S, Rd, g, Zo);
-}
-
-// draw_token with the b-part in fp32 (b_part_f32), the fp64 b_part for the
-// draws it leaves undecided: the same results.  Rf (LDS) holds fp32(R_k);
-// the fp64 path reads R_k from global memory.
-// EARLY: each b-term round's LDS reads issued before its gathered draws are
-// used (the z-step's choice; the fold-in kernel draws faster without)
-template <int G, typename CT, bool WIN, bool EARLY = WIN>
-__device__ __forceinline__ int32_t draw_token_f32(const DevModel &M, const TokenZ &tk, DocState<CT, WIN> &S,
-                                                  const float *Rf, const int g, const int32_t side_ratio,
-                                                  ZCount32 &cnt)
-{
-    CT *mt = S.mt;
-    const int32_t kold = tk.kold;
-    const int32_t mo = mt[kold];
-    __builtin_amdgcn_wave_barrier();
-    mt[kold] = (CT)(mo - 1);
-    __builtin_amdgcn_wave_barrier();
-    const int32_t Kv = tk.kv;
-    if (__builtin_amdgcn_ballot_w64(Kv == 0) != 0 && Kv == 0) {
-        mt[kold] = (CT)mo;
-        __builtin_amdgcn_wave_barrier();
-        cnt.deg++;
-        return -1 - kold;
-    }
-    const int32_t Kd = S.L - (mo == 1 ? 1 : 0);
-    const uint32_t jt = (uint32_t)(Kd < Kv ? Kd : Kv);
-    cnt.j += jt;
-    cnt.jb += tk.sure ? 0u : jt;
-    int32_t knew = -1;
-    if (__builtin_amdgcn_ballot_w64(tk.sure == 0) != 0) {
-        const bool prefer_doc = Kd == 0 || (uint32_t)Kv > __umul24((uint32_t)side_ratio, (uint32_t)Kd);
-        const bool doc = __builtin_amdgcn_ballot_w64(prefer_doc) != 0;
-        constexpr int KP = keep_of<G>();
-        const int32_t J = doc ? S.L : Kv;
-        const bool over2 = __builtin_amdgcn_ballot_w64(J > (KP / 2) * G) != 0;
-        const bool over3 = __builtin_amdgcn_ballot_w64(J > (3 * KP / 4) * G) != 0;
-        if (doc)
-            knew = !over2 ? b_part_f32<G, true, CT, KP / 2, WIN, EARLY>(M, tk, S, Rf, g)
-                          : (!over3 ? b_part_f32<G, true, CT, 3 * KP / 4, WIN, EARLY>(M, tk, S, Rf, g)
-                                    : b_part_f32<G, true, CT, KP, WIN, EARLY>(M, tk, S, Rf, g));
-        else
-            knew = !over2 ? b_part_f32<G, false, CT, KP / 2, WIN, EARLY>(M, tk, S, Rf, g)
-                          : (!over3 ? b_part_f32<G, false, CT, 3 * KP / 4, WIN, EARLY>(M, tk, S, Rf, g)
-                                    : b_part_f32<G, false, CT, KP, WIN, EARLY>(M, tk, S, Rf, g));
-        if (__builtin_amdgcn_ballot_w64(knew == -2) != 0) {
-            // a draw too close to a boundary for fp32: the fp64 b-part
-            const int32_t k64 = doc ? b_part_fp64<G, true, CT, KP>(M.ckg, M.g16, M.phid, M.Rd, M.sigma_a,
-                                                                   M.phi_method, tk, S.mt, S.lst, S.L, g)
-                                    : b_part_fp64<G, false, CT, KP>(M.ckg, M.g16, M.phid, M.Rd, M.sigma_a,
-                                                                    M.phi_method, tk, S.mt, S.lst, S.L, g);
-            if (knew == -2) {
-                knew = k64;
-                cnt.fb++;
+    for (uint32_t i = 0; i < n_max; ++i) {
+        move_segment<STATS>(S, d, i);
+        const DrawRec rec = S.tok[i];
+        const int c = (int)(rec.uc & 127u);
+        if (g == c) {
+            const float was = lds_add(&S.ms[d.po], -1.0f);
+            if (STATS) d.ro = was;
+        }
+        lds_order();
+        double Z;
+        const int32_t vc = __shfl(v, c & (G - 1), G);
+        const int32_t at = slots_draw_f64<G, true>(M, S, vc, (float)(rec.uc >> 8) * 0x1p-24f, 0, Z);
+        if (c < G) {
+            if (at >= 0) {
+                if (g == 0) {
+                    (void)lds_add(&S.ms[at], 1.0f);
+                    S.out[c] = (uint16_t)at;
+                }
+            } else if (g == c) {
+                const float was = lds_add(&S.ms[d.pa], 1.0f);
+                if (STATS) d.rn = was;
+                d.a = 1;
             }
         }
+        lds_order();
     }
-    if (knew < 0) {
-        knew = tk.ka;
-        cnt.a++;
-    }
-    const int32_t mn = mt[knew];
-    __builtin_amdgcn_wave_barrier();
-    mt[knew] = (CT)(mn + 1);
-    __builtin_amdgcn_wave_barrier();
-    list_update<G>(S, kold, knew, mo, mn, g);
-    return knew;
+    move_segment<STATS>(S, d, n_max);
 }
 
-// a token whose a-part was decided at staging (tk.sure): the same count and
-// list updates as draw_token, with the new topic the word's alias draw
-template <int G, typename CT, bool WIN>
-__device__ __forceinline__ int32_t move_token(const TokenZ &tk, DocState<CT, WIN> &S, const int g, ZCount32 &cnt)
+// Draw a block of tokens, lane g's token x of old topic kold (valid: the
+// lane has one), after slots_layout; returns the lane's new topic.  The
+// group's lanes are converged.
+template <int G, bool STATS, bool BIG>
+__device__ __forceinline__ int32_t draw_block(const DevModel &M, SlotDoc &S, const SlotLds &A, const float *Rf,
+                                              const LaneTok &x, int32_t kold, bool valid, ZStat &st, const int g)
 {
-    CT *mt = S.mt;
-    const int32_t kold = tk.kold;
-    const int32_t mo = mt[kold];
-    __builtin_amdgcn_wave_barrier();
-    mt[kold] = (CT)(mo - 1);
-    __builtin_amdgcn_wave_barrier();
-    const int32_t Kv = tk.kv;
-    const int32_t Kd = S.L - (mo == 1 ? 1 : 0);
-    cnt.j += (uint32_t)(Kd < Kv ? Kd : Kv);
-    const int32_t knew = tk.ka;
-    cnt.a++;
-    const int32_t mn = mt[knew];
-    __builtin_amdgcn_wave_barrier();
-    mt[knew] = (CT)(mn + 1);
-    __builtin_amdgcn_wave_barrier();
-    list_update<G>(S, kold, knew, mo, mn, g);
-    return knew;
-}
-
-// load a document's topic counts into the group's LDS table (CT: 8-bit
-// counts for documents shorter than 256 tokens, else 16-bit) and list them
-template <int G, typename CT, bool WIN>
-__device__ __forceinline__ void load_doc_counts(DocState<CT, WIN> &S, const uint16_t *z, int64_t s, int64_t e, int g,
-                                                int32_t K, int32_t m_words)
-{
-    constexpr int PER_WORD = 4 / sizeof(CT);   // counters per 32-bit word
-    constexpr int SHIFT = 8 * sizeof(CT);
-    uint32_t *w32 = (uint32_t *)S.mt;
-    for (int32_t i = g; i < m_words; i += G) w32[i] = 0;
-    __builtin_amdgcn_wave_barrier();
-    for (int64_t i = s + g; i < e; i += G) {
-        const int32_t k = z[i];
-        atomicAdd(w32 + k / PER_WORD, 1u << (SHIFT * (k % PER_WORD)));
+    const bool draws = valid && !x.sure;
+    const uint64_t db = group_ballot<G>(draws);
+    const uint64_t below = (1ull << g) - 1ull;
+    const uint32_t before = (uint32_t)__builtin_popcountll(db & below);
+    const uint32_t nd = (uint32_t)__builtin_popcountll(db);
+    // records in draw order, the lanes without a draw behind them
+    DrawRec rec;
+    rec.row = draws ? x.row : 0u;
+    rec.uc = draws ? (x.uc | (uint32_t)g) : REC_NONE;
+    rec.saf = draws ? x.saf : 1.0f;
+    rec.pad = 0;
+    S.tok[draws ? before : nd + (uint32_t)g - before] = rec;
+    if (g < 2) {
+        DrawRec none = {0u, REC_NONE, 1.0f, 0u};
+        S.tok[G + g] = none;
     }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    build_list<G, CT>(S, g, K);
-}
-
-// stage the inputs of tokens i0 + g (one per lane) for a block of draws.
-// nd: tokens of the document (0: never decide the a-part here).  The b-terms
-// of a token sum to sigma_b = sum_k phi_kv m_k <= phimax(v) (nd - 1), so when
-// u (sigma_a + phimax(v) (nd - 1)) < sigma_a the token takes the a-part
-// whatever the counts; the test keeps a margin of 2^-36 relative, far above
-// the rounding of either side's sums, so it never decides a token that the
-// full computation (or the definition's order of sums) would send to the
-// b-part.
-__device__ __forceinline__ void stage_token(const DevModel &M, TokenIn *tok, int g, int32_t v, int32_t kold,
-                                            const r4 &r, const int32_t nd)
-{
-    TokenIn x;
-    x.vk = (uint32_t)v * (uint32_t)M.K;
-    x.vs = (uint32_t)v * (uint32_t)M.ks16;
-    x.cb = M.colptr[v];
-    x.kold = (uint16_t)kold;
-    const int32_t kv = M.colptr[v + 1] - x.cb;
-    x.kv = (uint16_t)kv;
-    x.u0 = (float)(r.x >> 8) * 0x1p-24f;
-    x.sa = M.sigma_a[v];
-    // the a-part's draw from the word's alias table over alpha_k phi_kv:
-    // slot j = floor(r1 * K_v / 2^32), kept when r2 < its threshold, else
-    // its alias (Section 3.5)
-    uint32_t ka = 0;
-    if (kv > 0) {
-        const uint32_t j = scale32(r.y, (uint32_t)kv);
-        const uint64_t a = M.calias[x.cb + j];
-        ka = (r.z < (uint32_t)a) ? (uint32_t)((a >> 32) & 0xFFFFu) : (uint32_t)(a >> 48);
+    LaneDraw d;
+    d.po = valid ? slot_of(S, A, kold) : 0;
+    d.pa = valid ? slot_of(S, A, x.ka) : 0;
+    d.key = 0xFFFFFFFFu;
+    const bool moves = valid && x.sure && x.kv > 0;
+    {
+        // rank among the segment's tokens decided at staging (tokens of an
+        // empty column keep their topic: no move)
+        const uint64_t mb = group_ballot<G>(moves);
+        const uint64_t prev = db & below;
+        const uint64_t seg = prev ? below & ~((2ull << (63 - __builtin_clzll(prev))) - 1ull) : below;
+        if (moves) d.key = (before << 7) | (uint32_t)__builtin_popcountll(mb & seg);
     }
-    x.ka = (uint16_t)ka;
-    bool sure = false;
-    if (kv > 0 && nd > 0) {
-        const double B = (double)M.phimax[v] * (double)(nd - 1);
-        sure = unit24(r.x) * (x.sa + B) < x.sa * (1.0 - 0x1p-36);
+    d.ro = 2.0f;
+    d.rn = 1.0f;
+    d.a = moves ? 1u : 0u;
+    d.fb = 0;
+    if (valid) S.out[g] = (uint16_t)d.pa;
+    lds_order();
+    // the wave's largest number of draws (scalar: the ballot's fields)
+    const uint64_t all = __builtin_amdgcn_ballot_w64(draws);
+    uint32_t n_max = 0;
+#pragma unroll
+    for (int o = 0; o < 64; o += G) {
+        const uint32_t n = (uint32_t)__builtin_popcountll(G == 64 ? all : (all >> o) & ((1ull << (G & 63)) - 1ull));
+        n_max = n > n_max ? n : n_max;
     }
-    x.sure = sure ? 1 : 0;
-    tok[g] = x;
-}
-
-// stage the inputs of the z-step's token at lane g from its word's record:
-// as stage_token, with the a-part decided at staging by the same bound in
-// fp32: u (sigma_a + phimax(v) (nd - 1)) < sigma_a (1 - 2^-20), both sides
-// rounded to fp32 (a relative error below 6 2^-24 each), so a token so
-// decided has x < sigma_a (1 - 10 2^-24) exactly, far outside any rounding
-// of the sums (the fp64 and exact decisions agree)
-// (returns the token's sure flag)
-__device__ __forceinline__ bool stage_token_z(const DevModel &M, TokenZ *tok, int g, int32_t v, int32_t kold,
-                                              const r4 &r, const int32_t nd)
-{
-    const uint4 rec = M.wrec[v];
-    TokenZ x;
-    x.vk = (uint32_t)v * (uint32_t)M.K;
-    x.vs = (uint32_t)v * (uint32_t)M.ks16;
-    x.cb = (int32_t)rec.x;
-    x.kold = (uint16_t)kold;
-    const uint32_t kv = rec.y;
-    x.kv = (uint16_t)kv;
-    x.u0 = (float)(r.x >> 8) * 0x1p-24f;
-    x.saf = __uint_as_float(rec.z);
-    x.v = (uint32_t)v;
-    uint32_t ka = 0;
-    if (kv > 0) {
-        const uint32_t j = scale32(r.y, kv);
-        const uint64_t a = M.calias[rec.x + j];
-        ka = (r.z < (uint32_t)a) ? (uint32_t)((a >> 32) & 0xFFFFu) : (uint32_t)(a >> 48);
+    auto over = [&](int sl) { return __builtin_amdgcn_ballot_w64(S.L > sl * G) != 0; };
+    if (!over(1)) draw_slots<G, 1, STATS>(M, S, Rf, x.v, d, n_max, g);
+    else if (!over(2)) draw_slots<G, 2, STATS>(M, S, Rf, x.v, d, n_max, g);
+    else if (!over(3)) draw_slots<G, 3, STATS>(M, S, Rf, x.v, d, n_max, g);
+    else if (!over(4)) draw_slots<G, 4, STATS>(M, S, Rf, x.v, d, n_max, g);
+    else if (!over(5)) draw_slots<G, 5, STATS>(M, S, Rf, x.v, d, n_max, g);
+    else if (!BIG || !over(6)) draw_slots<G, 6, STATS>(M, S, Rf, x.v, d, n_max, g);
+    else if constexpr (BIG) {
+        if (S.dense) draw_dense<G, STATS>(M, S, x.v, d, n_max, g);
+        else if (!over(8)) draw_slots<G, 8, STATS>(M, S, Rf, x.v, d, n_max, g);
+        else if (!over(10)) draw_slots<G, 10, STATS>(M, S, Rf, x.v, d, n_max, g);
+        else if (!over(12)) draw_slots<G, 12, STATS>(M, S, Rf, x.v, d, n_max, g);
+        else draw_slots<G, 16, STATS>(M, S, Rf, x.v, d, n_max, g);
     }
-    x.ka = (uint16_t)ka;
-    bool sure = false;
-    if (kv > 0 && nd > 0) {
-        const float B = __uint_as_float(rec.w) * (float)(nd - 1);
-        sure = x.u0 * (x.saf + B) < x.saf * (1.0f - 0x1p-20f);
+    lds_order();
+    if constexpr (STATS) {
+        // J = min(K_d^{-i}, K_v): the topics with a nonzero count when token
+        // g was drawn, from the topics that left and entered before it
+        const int32_t left = d.ro == 1.0f ? 1 : 0;
+        const int32_t delta = (d.rn == 0.0f ? 1 : 0) - left;
+        const int32_t incl = group_scan_incl_i32<G>(delta);
+        const int32_t Kd = S.nz + incl - delta - left;
+        if (valid && x.kv > 0) {
+            const uint32_t j = (uint32_t)(Kd < x.kv ? Kd : x.kv);
+            st.j += j;
+            if (draws) st.jb += j;
+        }
+        S.nz += group_bcast<G>(incl, G - 1);
+        st.a += d.a;
+        st.fb += d.fb;
+        st.deg += valid && x.kv == 0 ? 1u : 0u;
     }
-    x.sure = sure ? 1 : 0;
-    tok[g] = x;
-    return sure;
+    return valid ? topic_of(S, S.out[g]) : 0;
 }
 
 // HOT: the frequent words' count increments go to the block's counters in
 // LDS (hist), the others' to n
-template <int G, typename CT, bool HOT>
-__device__ void z_step_item(const ZArgs &a, const WorkItem &w, const float *R, uint8_t *wave_base,
-                            TokenZ *wave_tok, unsigned long long *wave_cnt, uint32_t *hist)
+template <int G, bool BIG, bool HOT>
+__device__ __forceinline__ void z_step_item(const ZArgs &a, const WorkItem &w, const float *R, uint8_t *base,
+                                            ZStat &st, uint32_t *hist)
 {
     constexpr int NG = 64 / G;
     const int lane = __lane_id();
     const int g = lane & (G - 1);
     const int grp = lane / G;
-    DocState<CT, true> S;
-    S.mt = (CT *)(wave_base + grp * a.group_bytes);
-    S.lst = (uint16_t *)(wave_base + grp * a.group_bytes + a.m_bytes);
-    TokenZ *tok = wave_tok + grp * G;
+    const SlotLds &A = a.lds;
+    SlotDoc S = slot_doc(base + grp * A.group_bytes, A);
     const DevModel &M = a.m;
     const uint32_t t = *M.tptr;
     for (int32_t di = grp; di < w.count; di += NG) {
@@ -1792,61 +1567,25 @@ __device__ void z_step_item(const ZArgs &a, const WorkItem &w, const float *R, u
             if (a.ll_doc && g == 0) a.ll_doc[d] = 0.0;
             continue;
         }
-        load_doc_counts<G, CT>(S, a.c.z, s, e, g, M.K, a.m_bytes / 4);
-        ZCount32 cnt = {0, 0, 0, 0, 0};
+        slots_clear<G>(S, A, g);
+        slots_mark_tokens<G>(S, a.c.z, s, e, g);
+        slots_count_topics<G>(S, A, g);
         for (int64_t i0 = s; i0 < e; i0 += G) {
             const int64_t i = i0 + g;
             const bool valid = i < e;
             int32_t zo = 0, wv = 0;
-            bool sure = false;
+            LaneTok x = no_token();
             if (valid) {
                 // the token stream is read once per sweep: non-temporal, so
-                // it does not displace the tables the draws reuse
+                // it does not displace the tables that the draws reuse
                 wv = __builtin_nontemporal_load(a.c.words + i);
                 zo = __builtin_nontemporal_load(a.c.z + i);
                 const r4 r = philox((uint32_t)i, (uint32_t)((uint64_t)i >> 32), t, TAG_Z, M.key0, M.key1);
-                sure = stage_token_z(M, tok, g, wv, zo, r, (int32_t)(e - s));
+                x = stage_token(M, wv, zo, r, (int32_t)(e - s));
             }
-            // bit j: the group's token j was decided at staging (the cursor
-            // tests it in a register instead of reading LDS)
-            const auto sure_bits = (typename std::conditional<(G > 32), uint64_t, uint32_t>::type)group_ballot<G>(sure);
-            __builtin_amdgcn_wave_barrier();
-            int32_t znew = zo;
-            const int nb = (int)((e - i0) < G ? (e - i0) : G);
-            // each group walks its tokens with its own cursor: the tokens
-            // whose a-part was decided at staging move at once, then every
-            // group with a token left draws it, all groups together, so a
-            // wave runs the b-terms as often as its busiest group needs.
-            // (With 8 groups a wave the runs of decided tokens no longer line
-            // up: those groups draw in step, and skip the b-terms only when
-            // all eight tokens are decided.)
-            if constexpr (G < 16) {
-                for (int jj = 0; jj < nb; ++jj) {
-                    const TokenZ tk = tok[jj];
-                    int32_t k = draw_token_f32<G, CT>(M, tk, S, R, g, w.side_ratio, cnt);
-                    if (k < 0) k = -1 - k;
-                    if (g == jj) znew = k;
-                }
-            } else {
-            int cur = 0;
-            while (true) {
-                while (cur < nb && ((sure_bits >> cur) & 1u)) {
-                    const TokenZ tk = tok[cur];
-                    const int32_t k = move_token<G, CT>(tk, S, g, cnt);
-                    if (g == cur) znew = k;
-                    ++cur;
-                }
-                if (cur < nb) {
-                    const TokenZ tk = tok[cur];
-                    int32_t k = draw_token_f32<G, CT>(M, tk, S, R, g, w.side_ratio, cnt);
-                    if (k < 0) k = -1 - k;
-                    if (g == cur) znew = k;
-                    ++cur;
-                }
-                if (__builtin_amdgcn_ballot_w64(cur < nb) == 0) break;
-            }
-            }
-            __builtin_amdgcn_wave_barrier();
+            slots_layout<G, BIG>(S, A, M.K, i0 == s, valid, x.ka, g);
+            if (i0 == s) slots_add_tokens<G>(S, A, a.c.z, s, e, g);
+            const int32_t znew = draw_block<G, true, BIG>(M, S, A, R, x, zo, valid, st, g);
             // the count rebuild: each lane adds its own token, once the
             // block's draws are done (a frequent word's into the block's
             // counters in LDS, added to n when the kernel ends)
@@ -1857,34 +1596,28 @@ __device__ void z_step_item(const ZArgs &a, const WorkItem &w, const float *R, u
                 else atomicAdd(&M.n[(uint32_t)wv * (uint32_t)M.K + (uint32_t)znew], 1);
             }
         }
-        if (g == 0) {
-            atomicAdd(&wave_cnt[0], (unsigned long long)cnt.j);
-            atomicAdd(&wave_cnt[1], (unsigned long long)cnt.a);
-            atomicAdd(&wave_cnt[2], (unsigned long long)cnt.deg);
-            atomicAdd(&wave_cnt[3], (unsigned long long)cnt.jb);
-            atomicAdd(&wave_cnt[4], (unsigned long long)cnt.fb);
-        }
         if (a.ll_doc) {
             // the document's term of log p(z | alpha) for its final counts:
             // lgamma(A) - lgamma(N_d + A) + sum_k [lgamma(m_k + alpha) - lgamma(alpha)]
-            int32_t base;
-            const int32_t n = list_block<G>(S.L, g, base);
             double part = 0.0;
-            for (int32_t j = 0; j < n; ++j) part += M.lg_alpha[S.mt[S.lst[base + j]]];
+            for (int32_t j = g; j < S.L; j += G) part += M.lg_alpha[(int32_t)S.ms[j]];
             const double tot = group_bcast_f64<G>(group_scan_incl<G>(part), G - 1);
             if (g == 0) a.ll_doc[d] = tot + M.lg_A[e - s];
         }
+        lds_order();
     }
 }
 
-// one persistent kernel per group size and count width: waves take work
-// items from this class's queue until it is empty
-// 5 waves per SIMD (96 VGPRs): more resident groups hide the chains'
-// latency, more than 96 registers would spill in the draw loop.  Groups of
-// 8 keep 8 b-terms per lane and their LDS allows 2 waves per SIMD, so they
-// take the registers instead.
-template <int G, typename CT, bool HOT>
-__global__ void __launch_bounds__(256, (G == 8 ? 2 : 5)) z_step_kernel(ZArgs a)
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
+{
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
+
+// one persistent kernel per group size and layout: waves take work items
+// from this class's queue until it is empty
+template <int G, bool BIG, bool HOT>
+__global__ void __launch_bounds__(256, BIG ? 4 : 5) z_step_kernel(ZArgs a)
 {
     extern __shared__ __align__(16) uint8_t z_lds[];
     // fp32(R_k) for the fp32 b-terms (the fp64 path reads R_k from global
@@ -1897,31 +1630,28 @@ __global__ void __launch_bounds__(256, (G == 8 ? 2 : 5)) z_step_kernel(ZArgs a)
     for (int32_t i = threadIdx.x; i < n_hist; i += blockDim.x) hist[i] = 0u;
     __syncthreads();
     const int wave = threadIdx.x >> 6;
-    uint8_t *blk = z_lds + a.r_bytes;
-    uint8_t *wave_base = blk + wave * a.wave_bytes;
-    TokenZ *wave_tok = (TokenZ *)(blk + 4 * a.wave_bytes) + wave * 64;
-    // the wave's statistics: sum of J, a-part draws, degenerate tokens, sum
-    // of J over the tokens whose b-terms were computed, fp64 fallbacks
-    unsigned long long *wave_cnt = (unsigned long long *)(blk + 4 * a.wave_bytes + 4 * 64 * sizeof(TokenZ)) + 5 * wave;
-    if (__lane_id() < 5) wave_cnt[__lane_id()] = 0ull;
-    __builtin_amdgcn_wave_barrier();
+    uint8_t *base = z_lds + a.r_bytes + wave * (64 / G) * a.lds.group_bytes;
+    ZStat st;
     while (true) {
         int item = 0;
         if (__lane_id() == 0) item = atomicAdd(a.queue, 1);
-        item = __builtin_amdgcn_readlane(item, 0);
+        item = __builtin_amdgcn_readfirstlane(item);
         if (item >= a.n_items) break;
         // a private copy: a reference into global memory would be reloaded
         // after every store of the item (stores may alias it)
         const WorkItem w = a.items[item];
-        z_step_item<G, CT, HOT>(a, w, R, wave_base, wave_tok, wave_cnt, hist);
+        z_step_item<G, BIG, HOT>(a, w, R, base, st, hist);
     }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (a.stats && __lane_id() < 5) {
-        const unsigned long long v = wave_cnt[__lane_id()];
-        const int l = __lane_id();
-        const int idx = l == 0 ? ST_SUM_J : (l == 1 ? ST_SUM_A : (l == 2 ? ST_DEGENERATE : (l == 3 ? ST_SUM_JB : ST_FALLBACK)));
-        if (v) atomicAdd(&a.stats[idx], v);
+    if (a.stats) {
+        const unsigned long long j = wave_sum_u64(st.j), jb = wave_sum_u64(st.jb), na = wave_sum_u64(st.a),
+                                 deg = wave_sum_u64(st.deg), fb = wave_sum_u64(st.fb);
+        if (__lane_id() == 0) {
+            if (j) atomicAdd(&a.stats[ST_SUM_J], j);
+            if (na) atomicAdd(&a.stats[ST_SUM_A], na);
+            if (deg) atomicAdd(&a.stats[ST_DEGENERATE], deg);
+            if (jb) atomicAdd(&a.stats[ST_SUM_JB], jb);
+            if (fb) atomicAdd(&a.stats[ST_FALLBACK], fb);
+        }
     }
     if (HOT) {
         // every wave of the block is done: add the block's counters to n
@@ -2002,13 +1732,16 @@ __device__ __forceinline__ void lane_block_terms(const uint16_t *kl, const uint8
 
 __global__ void __launch_bounds__(64) z_lane_kernel(ZArgs a)
 {
+    struct ZCount {
+        unsigned long long J, A, degenerate;
+    };
     extern __shared__ __align__(16) uint8_t l_lds[];
     const int lane = __lane_id();
     uint16_t *kl = (uint16_t *)l_lds + lane;                            // entry j at kl[j * 64]
     uint8_t *ml = l_lds + LANE_CAP * 64 * sizeof(uint16_t) + lane;      // entry j at ml[j * 64]
     const DevModel &M = a.m;
     const uint32_t t = *M.tptr;
-    ZCount cnt = {0, 0, 0, 0, 0};
+    ZCount cnt = {0, 0, 0};
     while (true) {
         int item = 0;
         if (lane == 0) item = atomicAdd(a.queue, 1);
@@ -2185,12 +1918,12 @@ hipError_t launch_z_prepare(const DevModel &m, int32_t *queues, unsigned long lo
     return launch_fill_u32((uint32_t *)queues, 0u, Z_QUEUES, s);
 }
 
-hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, bool narrow, const WorkItem *items,
-                          int32_t n_items, int32_t n_cu, int32_t *queue, unsigned long long *stats,
+hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, int32_t longest,
+                          const WorkItem *items, int32_t n_items, int32_t n_cu, int32_t *queue, unsigned long long *stats,
                           double *ll_doc, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    if ((group == 8 || group == 1) && !narrow) return hipErrorInvalidValue;
+    if (!z_group_fits(group, m.K, longest)) return hipErrorInvalidValue;
     ZArgs a;
     a.m = m;
     a.c = c;
@@ -2199,12 +1932,9 @@ hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, 
     a.queue = queue;
     a.stats = stats;
     a.ll_doc = m.lg_alpha ? ll_doc : nullptr;
-    const ZLayout L = z_layout(group, narrow, m.K);
-    a.m_bytes = L.m_bytes;
-    a.group_bytes = L.group_bytes;
-    a.wave_bytes = L.wave_bytes;
-    a.r_bytes = L.r_bytes;
-    size_t lds = ((size_t)a.r_bytes + 4 * ((size_t)a.wave_bytes + 64 * sizeof(TokenIn) + 40) + 15) / 16 * 16;
+    a.lds = slot_lds(group, m.K, longest);
+    a.r_bytes = (m.K * 4 + 15) / 16 * 16;
+    size_t lds = (size_t)a.r_bytes + 4 * (size_t)(group == 1 ? 0 : 64 / group) * a.lds.group_bytes;
     a.n_hot = 0;
     a.hot_off = (int32_t)lds;
     auto launch = [&](auto kernel, auto kernel_hot) -> hipError_t {
@@ -2246,14 +1976,14 @@ hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, 
         z_lane_kernel<<<(unsigned)blocks, 64, llds, s>>>(a);
         return hipGetLastError();
     }
-    if (narrow) {
-        if (group == 32) return launch(z_step_kernel<32, uint8_t, false>, z_step_kernel<32, uint8_t, true>);
-        if (group == 16) return launch(z_step_kernel<16, uint8_t, false>, z_step_kernel<16, uint8_t, true>);
-        return launch(z_step_kernel<8, uint8_t, false>, z_step_kernel<8, uint8_t, true>);
-    }
-    if (group == 64) return launch(z_step_kernel<64, uint16_t, false>, z_step_kernel<64, uint16_t, true>);
-    if (group == 32) return launch(z_step_kernel<32, uint16_t, false>, z_step_kernel<32, uint16_t, true>);
-    return launch(z_step_kernel<16, uint16_t, false>, z_step_kernel<16, uint16_t, true>);
+#define PULDA_Z(G_)                                                                                    \
+    (a.lds.ms_n > SLOTS_FEW * G_ ? launch(z_step_kernel<G_, true, false>, z_step_kernel<G_, true, true>) \
+                                 : launch(z_step_kernel<G_, false, false>, z_step_kernel<G_, false, true>))
+    if (group == 64) return PULDA_Z(64);
+    if (group == 32) return PULDA_Z(32);
+    if (group == 16) return PULDA_Z(16);
+    return PULDA_Z(8);
+#undef PULDA_Z
 }
 
 // ---------------------------------------------------------------------------
@@ -2498,7 +2228,7 @@ __global__ void import_phi_kernel(DevModel m, const int64_t *colptr64, const uin
         const float y = __shfl_xor(fmax, o, 64);
         fmax = y > fmax ? y : fmax;
     }
-    if (lane == 0) m.phimax[v] = fmax;
+    if (lane == 0) m.phimax[v] = b > a ? -fmax : fmax;
 }
 
 hipError_t launch_import_phi(const DevModel &m, const int64_t *colptr64, const uint16_t *topic, const float *phi_e,
@@ -2623,15 +2353,10 @@ hipError_t launch_scan_i64(const int64_t *in, int64_t *out_excl, int64_t n, long
 // final state.
 // ---------------------------------------------------------------------------
 template <int G, bool SYM>
-__device__ void foldin_slot(const DevModel &M, const DevFoldin &F, int32_t sid, const float *Rf, uint16_t *mt,
-                            TokenZ *tok)
+__device__ __forceinline__ void foldin_slot(const DevModel &M, const DevFoldin &F, int32_t sid, const float *Rf,
+                                            uint8_t *base, const SlotLds &A)
 {
-    // the count table (K u16, rounded to 16 bytes), then the topic list with
-    // room for its windows (launch_foldin_step sizes the same layout)
-    const int32_t Kp = (M.K + 7) & ~7;
-    DocState<uint16_t, true> S;
-    S.mt = mt;
-    S.lst = mt + Kp;
+    SlotDoc S = slot_doc(base, A);
     const int lane = __lane_id();
     const int g = lane & (G - 1);
     const int32_t K = M.K;
@@ -2676,8 +2401,10 @@ __device__ void foldin_slot(const DevModel &M, const DevFoldin &F, int32_t sid, 
         // collected it): its results stay as they are
         if (done >= F.sweeps) return;
     }
-    load_doc_counts<G, uint16_t>(S, zz, 0, kept, g, K, Kp / 2);
-    ZCount32 st = {0, 0, 0, 0, 0};
+    slots_clear<G>(S, A, g);
+    slots_mark_tokens<G>(S, zz, 0, kept, g);
+    bool first = true;
+    ZStat st;
     int32_t budget = sl.budget;
     while (budget > 0 && done < F.sweeps) {
         const int32_t s = done + 1;
@@ -2686,24 +2413,17 @@ __device__ void foldin_slot(const DevModel &M, const DevFoldin &F, int32_t sid, 
             const int32_t q = q0 + g;
             const bool valid = q < t1;
             int32_t zo = 0;
+            LaneTok x = no_token();
             if (valid) {
                 const int32_t p = pos[q];
                 zo = zz[q];
                 const r4 r = philox((uint32_t)p, sl.req, (uint32_t)s, TAG_FOLDIN_Z, F.key0, F.key1);
-                stage_token_z(M, tok, g, wds[p], zo, r, kept);
+                x = stage_token(M, wds[p], zo, r, kept);
             }
-            __builtin_amdgcn_wave_barrier();
-            int32_t znew = zo;
-            const int nb = (t1 - q0) < G ? (t1 - q0) : G;
-            // the z-step's draw: b-terms in fp32 where a rounding bound proves
-            // the decision, the fp64 b-part elsewhere (the same results)
-            for (int jj = 0; jj < nb; ++jj) {
-                const TokenZ tk = tok[jj];
-                int32_t k = draw_token_f32<G, uint16_t, true, false>(M, tk, S, Rf, g, 1, st);
-                if (k < 0) k = -1 - k;
-                if (g == jj) znew = k;
-            }
-            __builtin_amdgcn_wave_barrier();
+            slots_layout<G, true>(S, A, K, first, valid, x.ka, g);
+            if (first) slots_add_tokens<G>(S, A, zz, 0, kept, g);
+            first = false;
+            const int32_t znew = draw_block<G, false, true>(M, S, A, Rf, x, zo, valid, st, g);
             if (valid) zz[q] = (uint16_t)znew;
         }
         budget -= t1 - next;
@@ -2711,7 +2431,10 @@ __device__ void foldin_slot(const DevModel &M, const DevFoldin &F, int32_t sid, 
         if (next == kept) {
             // the sweep is complete
             if (s > F.burn_in) {
-                for (int32_t k = g; k < K; k += G) acc[k] += mt[k];
+                for (int32_t j = g; j < S.L; j += G) {
+                    const uint32_t c = (uint32_t)S.ms[j];
+                    if (c) atomicAdd(&acc[topic_of(S, j)], c);
+                }
             }
             done = s;
             next = 0;
@@ -2729,8 +2452,9 @@ __device__ void foldin_slot(const DevModel &M, const DevFoldin &F, int32_t sid, 
             F.theta[(int64_t)sid * K + k] = (float)(((double)acc[k] / ns + M.alpha[k]) / denom);
         double part = 0.0;
         for (int32_t q = g; q < kept; q += G) part += log((double)M.phid[(int64_t)wds[pos[q]] * K + zz[q]]);
+        // (topics in a fixed order, whatever the slots)
         for (int32_t k = g; k < K; k += G) {
-            const int32_t c = mt[k];
+            const int32_t c = count_of(S, A, k);
             if (c > 0) {
                 if constexpr (SYM) part += M.lg_alpha[c];
                 else part += lgamma((double)c + M.alpha[k]) - lgamma(M.alpha[k]);
@@ -2746,63 +2470,56 @@ __device__ void foldin_slot(const DevModel &M, const DevFoldin &F, int32_t sid, 
 }
 
 template <int G, bool SYM>
-__global__ void __launch_bounds__(256) foldin_step_kernel(DevModel M, DevFoldin F, const int32_t *active,
-                                                          int32_t n_active, int32_t per_group)
+__global__ void __launch_bounds__(256, 4) foldin_step_kernel(DevModel M, DevFoldin F, const int32_t *active,
+                                                          int32_t n_active, SlotLds A)
 {
-    extern __shared__ __align__(16) uint16_t f_lds[];
-    // the block's copy of fp32(R_k), then the groups' tables, then staged
-    // tokens
+    extern __shared__ __align__(16) uint8_t f_lds[];
+    // the block's copy of fp32(R_k), then the groups' regions
     float *R = (float *)f_lds;
     for (int32_t k = threadIdx.x; k < M.K; k += blockDim.x) R[k] = (float)M.Rd[k];
     __syncthreads();
-    uint16_t *blk = f_lds + (M.K * 4 + 15) / 16 * 8;
-    const int lane = __lane_id();
-    const int wave = threadIdx.x >> 6;
-    constexpr int gsz = G;
-    const int grp = lane / gsz;
-    const int ngw = 64 / gsz;
-    const int64_t gid = ((int64_t)blockIdx.x * 4 + wave) * ngw + grp;
-    uint16_t *mt = blk + (wave * ngw + grp) * per_group;
-    TokenZ *tok = (TokenZ *)(blk + 4 * ngw * per_group) + wave * 64 + grp * gsz;
+    constexpr int NG = 64 / G;
+    const int slot = (int)(threadIdx.x >> 6) * NG + (int)(__lane_id() / G);   // group in the block
+    const int64_t gid = (int64_t)blockIdx.x * (blockDim.x / G) + slot;
     if (gid >= n_active) return;
-    const int32_t sid = active[gid];
-    foldin_slot<G, SYM>(M, F, sid, R, mt, tok);
+    foldin_slot<G, SYM>(M, F, active[gid], R, f_lds + (M.K * 4 + 15) / 16 * 16 + slot * A.group_bytes, A);
+}
+
+// Launch of a kernel with one group of G lanes per unit of work, its slots
+// in LDS behind the block's copy of R_k: four waves a block, or as many as
+// LDS holds
+template <typename Launch>
+static hipError_t launch_groups(int32_t K, int32_t G, int64_t groups, const SlotLds &A, Launch go)
+{
+    for (int waves = 4; waves >= 1; waves >>= 1) {
+        const int per_block = waves * (64 / G);
+        const size_t lds = (size_t)(K * 4 + 15) / 16 * 16 + (size_t)per_block * A.group_bytes;
+        if (lds > LDS_BYTES) continue;
+        go((unsigned)((groups + per_block - 1) / per_block), (unsigned)(waves * 64), lds);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidConfiguration;  // a wave's LDS exceeds the CU's
 }
 
 hipError_t launch_foldin_step(const DevModel &m, const DevFoldin &f, const int32_t *active, int32_t n_active,
                               hipStream_t s)
 {
     if (n_active == 0) return hipSuccess;
-    // per group (u16 units): the count table (K entries), then the topic
-    // list (K entries, at least W slots a lane and W more for its windows),
-    // each rounded to 16 bytes
-    const int32_t W = f.group == 16 ? 8 : 4;   // the list's window (slots per lane)
-    const int32_t lcap = m.K > W * f.group + W ? m.K : W * f.group + W;
-    const int per_group = ((m.K + 7) & ~7) + ((lcap + 7) & ~7);
-    const int ngw = 64 / f.group;
-    const int64_t waves = (n_active + ngw - 1) / ngw;
-    const unsigned blocks = (unsigned)((waves + 3) / 4);
-    const size_t lds = (size_t)(m.K * 4 + 15) / 16 * 16 + 4 * ngw * per_group * sizeof(uint16_t) +
-                       4 * 64 * sizeof(TokenZ);
-    int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, foldin_step_kernel<64, true>, 256, lds);
-    if (e != hipSuccess) return e;
-    if (per_cu <= 0) return hipErrorInvalidConfiguration;  // the block's LDS exceeds the CU's
-#define PULDA_FOLDIN(G_, S_) foldin_step_kernel<G_, S_><<<blocks, 256, lds, s>>>(m, f, active, n_active, per_group)
-    if (m.lg_alpha) {
-        if (f.group == 64) PULDA_FOLDIN(64, true);
-        else if (f.group == 32) PULDA_FOLDIN(32, true);
-        else PULDA_FOLDIN(16, true);
-    } else {
-        if (f.group == 64) PULDA_FOLDIN(64, false);
-        else if (f.group == 32) PULDA_FOLDIN(32, false);
-        else PULDA_FOLDIN(16, false);
-    }
+    const SlotLds A = slot_lds(f.group, m.K, f.max_len);
+    return launch_groups(m.K, f.group, n_active, A, [&](unsigned blocks, unsigned threads, size_t lds) {
+#define PULDA_FOLDIN(G_, S_) foldin_step_kernel<G_, S_><<<blocks, threads, lds, s>>>(m, f, active, n_active, A)
+        if (m.lg_alpha) {
+            if (f.group == 64) PULDA_FOLDIN(64, true);
+            else if (f.group == 32) PULDA_FOLDIN(32, true);
+            else PULDA_FOLDIN(16, true);
+        } else {
+            if (f.group == 64) PULDA_FOLDIN(64, false);
+            else if (f.group == 32) PULDA_FOLDIN(32, false);
+            else PULDA_FOLDIN(16, false);
+        }
 #undef PULDA_FOLDIN
-    return hipGetLastError();
+    });
 }
-
-
 
 // ---------------------------------------------------------------------------
 // Held-out log-likelihood of new documents, log p(w_d | Phi, alpha), by the
@@ -2819,16 +2536,10 @@ hipError_t launch_foldin_step(const DevModel &m, const DevFoldin &f, const int32
 // token).
 // ---------------------------------------------------------------------------
 template <int G>
-__device__ void ltr_particle(const DevModel &M, const DevHeldout &H, int64_t d, int32_t r, const float *Rf,
-                             uint16_t *mt, TokenZ *tok)
+__device__ __forceinline__ void ltr_particle(const DevModel &M, const DevHeldout &H, int64_t d, int32_t r,
+                                             const float *Rf, uint8_t *lds, const SlotLds &A)
 {
-    // the count table (K u16, rounded to 16 bytes), then the topic list with
-    // room for its windows (launch_heldout sizes the same layout)
-    const int32_t Kp = (M.K + 7) & ~7;
-    DocState<uint16_t, true> S;
-    S.mt = mt;
-    S.lst = mt + Kp;
-    S.L = 0;
+    SlotDoc S = slot_doc(lds, A);
     const int lane = __lane_id();
     const int g = lane & (G - 1);
     const int64_t s = H.doc_off[d];
@@ -2854,85 +2565,61 @@ __device__ void ltr_particle(const DevModel &M, const DevHeldout &H, int64_t d, 
         nk += __builtin_popcountll(bal);
     }
     if (r == 0 && g == 0) H.kept[d] = nk;
-    for (int32_t k = g; k < Kp; k += G) mt[k] = 0;
-    // the empty list: every window slot holds the padding value
-    for (int32_t j = g; j < win_of<G>() * G + win_of<G>(); j += G) S.lst[j] = (uint16_t)LIST_PAD;
     __threadfence();
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    ZCount st = {0, 0, 0, 0, 0};
-    ZCount32 st32 = {0, 0, 0, 0, 0};
+    slots_clear<G>(S, A, g);
+    ZStat st;
     for (int32_t n = 0; n < nk; ++n) {
-        // redraw z_0 .. z_{n-1} in order (lane q mod G stages token q), with
-        // the z-step's draw (fp32 b-terms where the rounding bound proves the
-        // decision, fp64 elsewhere: the fp64 draws' results)
-        for (int32_t q0 = 0; q0 < n; q0 += G) {
+        // redraw z_0 .. z_{n-1} in order, then draw z_n: blocks of G tokens,
+        // lane q mod G holding token q.  (n tokens counted: the redraws may
+        // settle the a-part at staging; only the new token's draw needs its Z)
+        for (int32_t q0 = 0; q0 <= n; q0 += G) {
             const int32_t q = q0 + g;
-            const bool valid = q < n;
+            const bool redraw = q < n;
             int32_t zo = 0;
-            if (valid) {
-                zo = zz[q];
+            LaneTok x = no_token();
+            if (q <= n) {
+                zo = redraw ? zz[q] : 0;
                 const r4 rr = philox((uint32_t)q, (uint32_t)n, req, tag, H.key0, H.key1);
-                // (n tokens counted: the redraws may settle the a-part at
-                // staging; only the new token's draw needs its Z)
-                stage_token_z(M, tok, g, kw[q], zo, rr, n);
+                x = stage_token(M, kw[q], zo, rr, redraw ? n : 0);
             }
-            __builtin_amdgcn_wave_barrier();
-            int32_t znew = zo;
-            const int nb = n - q0 < G ? n - q0 : G;
-            for (int jj = 0; jj < nb; ++jj) {
-                const TokenZ tk = tok[jj];
-                int32_t k = draw_token_f32<G, uint16_t, true, false>(M, tk, S, Rf, g, 1, st32);
-                if (k < 0) k = -1 - k;
-                if (g == jj) znew = k;
+            // (the first block: no counts yet)
+            slots_layout<G, true>(S, A, M.K, n == 0, q <= n, x.ka, g);
+            int32_t znew = draw_block<G, false, true>(M, S, A, Rf, x, zo, redraw, st, g);
+            if (n - q0 < G) {
+                // the new token, from the counts of z_<n in fp64 (its Z)
+                const int c = n - q0;
+                const int32_t v = group_bcast<G>(x.v, c);
+                const float u0 = (float)((uint32_t)group_bcast<G>((int)x.uc, c) >> 8) * 0x1p-24f;
+                const int32_t ka = group_bcast<G>(x.ka, c);
+                double Z;
+                int32_t at = S.dense ? slots_draw_f64<G, true>(M, S, v, u0, 0, Z)
+                                     : slots_draw_f64<G, false>(M, S, v, u0, (S.L + G - 1) / G, Z);
+                if (at < 0) at = slot_of(S, A, ka);
+                if (g == 0) {
+                    (void)lds_add(&S.ms[at], 1.0f);
+                    Zs[n] = Z;
+                }
+                if (g == c) znew = topic_of(S, at);
+                lds_order();
             }
-            __builtin_amdgcn_wave_barrier();
-            if (valid) zz[q] = (uint16_t)znew;
+            if (q <= n) zz[q] = (uint16_t)znew;
         }
-        // the new token: counted under a topic the particle already holds
-        // (topic 0 at the first step), which the draw removes again, so the
-        // draw sees the counts of z_<n
-        const int32_t k0 = S.L > 0 ? S.lst[0] : 0;
-        const int32_t c0 = mt[k0];
-        __builtin_amdgcn_wave_barrier();
-        if (g == 0) mt[k0] = (uint16_t)(c0 + 1);
-        __builtin_amdgcn_wave_barrier();
-        if (c0 == 0) list_insert<G, uint16_t>(S, k0, g);
-        // (the fp64 draw, which hands back Z; its R_k from global memory:
-        // one such draw per step)
-        TokenIn *tin = (TokenIn *)tok;
-        if (g == 0) {
-            const r4 rr = philox((uint32_t)n, (uint32_t)n, req, tag, H.key0, H.key1);
-            stage_token(M, tin, 0, kw[n], k0, rr, 0);
-        }
-        __builtin_amdgcn_wave_barrier();
-        const TokenIn tk = tin[0];
-        double Z = 0.0;
-        int32_t k = draw_token<G, uint16_t>(M, tk, S, M.Rd, g, 1, st, Z);
-        if (k < 0) k = -1 - k;
-        __builtin_amdgcn_wave_barrier();
-        if (g == (n & (G - 1))) zz[n] = (uint16_t)k;
-        if (g == 0) Zs[n] = Z;
     }
 }
 
 template <int G>
-__global__ void __launch_bounds__(256) ltr_kernel(DevModel M, DevHeldout H, int32_t per_group)
+__global__ void __launch_bounds__(256, 4) ltr_kernel(DevModel M, DevHeldout H, SlotLds A)
 {
-    extern __shared__ __align__(16) uint16_t h_lds[];
+    extern __shared__ __align__(16) uint8_t h_lds[];
     float *R = (float *)h_lds;
     for (int32_t k = threadIdx.x; k < M.K; k += blockDim.x) R[k] = (float)M.Rd[k];
     __syncthreads();
-    uint16_t *blk = h_lds + (M.K * 4 + 15) / 16 * 8;
-    const int lane = __lane_id();
-    const int wave = threadIdx.x >> 6;
     constexpr int NG = 64 / G;
-    const int grp = lane / G;
-    const int64_t gid = ((int64_t)blockIdx.x * 4 + wave) * NG + grp;
-    uint16_t *mt = blk + (wave * NG + grp) * per_group;
-    TokenZ *tok = (TokenZ *)(blk + 4 * NG * per_group) + wave * 64 + grp * G;
+    const int slot = (int)(threadIdx.x >> 6) * NG + (int)(__lane_id() / G);   // group in the block
+    const int64_t gid = (int64_t)blockIdx.x * (blockDim.x / G) + slot;
     if (gid >= H.D * H.R) return;
-    ltr_particle<G>(M, H, H.order[gid / H.R], (int32_t)(gid % H.R), R, mt, tok);
+    ltr_particle<G>(M, H, H.order[gid / H.R], (int32_t)(gid % H.R), R,
+                    h_lds + (M.K * 4 + 15) / 16 * 16 + slot * A.group_bytes, A);
 }
 
 // one wave per document: sum over steps of log((1/R) sum_r Z_n^(r) / (n + A)),
@@ -2958,26 +2645,12 @@ __global__ void __launch_bounds__(256) ltr_finish_kernel(DevHeldout H)
 hipError_t launch_heldout(const DevModel &m, const DevHeldout &h, hipStream_t s)
 {
     if (h.D == 0) return hipSuccess;
-    // per particle (u16 units): the count table (K entries), then the topic
-    // list (K entries, at least W slots a lane and W more for its windows),
-    // each rounded to 16 bytes
-    const int32_t W = h.group == 16 ? 8 : 4;
-    const int32_t lcap = m.K > W * h.group + W ? m.K : W * h.group + W;
-    const int per_group = ((m.K + 7) & ~7) + ((lcap + 7) & ~7);
-    const int ngw = 64 / h.group;
-    const int64_t groups = h.D * h.R;
-    const int64_t waves = (groups + ngw - 1) / ngw;
-    const unsigned blocks = (unsigned)((waves + 3) / 4);
-    const size_t lds = (size_t)(m.K * 4 + 15) / 16 * 16 + 4 * ngw * per_group * sizeof(uint16_t) +
-                       4 * 64 * sizeof(TokenZ);
-    int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ltr_kernel<64>, 256, lds);
-    if (e != hipSuccess) return e;
-    if (per_cu <= 0) return hipErrorInvalidConfiguration;  // the block's LDS exceeds the CU's
-    if (h.group == 64) ltr_kernel<64><<<blocks, 256, lds, s>>>(m, h, per_group);
-    else if (h.group == 32) ltr_kernel<32><<<blocks, 256, lds, s>>>(m, h, per_group);
-    else ltr_kernel<16><<<blocks, 256, lds, s>>>(m, h, per_group);
-    e = hipGetLastError();
+    const SlotLds A = slot_lds(h.group, m.K, h.longest);
+    hipError_t e = launch_groups(m.K, h.group, h.D * h.R, A, [&](unsigned blocks, unsigned threads, size_t lds) {
+        if (h.group == 64) ltr_kernel<64><<<blocks, threads, lds, s>>>(m, h, A);
+        else if (h.group == 32) ltr_kernel<32><<<blocks, threads, lds, s>>>(m, h, A);
+        else ltr_kernel<16><<<blocks, threads, lds, s>>>(m, h, A);
+    });
     if (e != hipSuccess) return e;
     ltr_finish_kernel<<<(unsigned)((h.D + 3) / 4), 256, 0, s>>>(h);
     return hipGetLastError();
