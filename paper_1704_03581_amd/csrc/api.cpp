@@ -144,7 +144,7 @@ struct pulda_plan {
     uint8_t *ws = nullptr;
     int64_t ws_need = 0;
     struct {
-        int64_t z, n, gam, phid, g16, Rd, gamd, Sd, dpart, phimax, wrec, hot, hot_word, beta_v, ztp, ztp_off, ckg, colcnt, colptr, ctopic, cphi, calias, sigma_a, S, nk, alpha, pois, pois_off,
+        int64_t z, n, gam, phid, g16, g8, Rd, gamd, Sd, dpart, phimax, wrec, hot, hot_word, beta_v, ztp, ztp_off, ckg, colcnt, colptr, ctopic, cphi, calias, sigma_a, S, nk, alpha, pois, pois_off,
             doc_order, items, queue, stats, ll_part, ll_out, ll_hist, tptr, err, scratch, cnt_a, ptr_a, cnt_b,
             ptr_b, zsave, lg_beta, lg_alpha, lg_A, ll_doc;
     } off;
@@ -322,9 +322,10 @@ pulda_status pulda_plan_create(const pulda_model_desc *desc, int64_t D, int64_t 
     p->off.z = L.take(N * 2);
     p->off.n = L.take(VK * 4);
     p->off.gam = L.take(VK * 4);
-    p->off.phid = L.take(VK * 4);
     p->ks16 = (p->K + 63) / 64 * 64;
     p->off.g16 = L.take((int64_t)p->V * p->ks16 * 2);
+    p->off.g8 = L.take((int64_t)p->V * p->ks16 + 4);   // (a row's last topics are read 4 bytes at a time)
+    p->off.phid = L.take(VK * 4);
     p->off.Rd = L.take((int64_t)p->K * 8);
     p->off.gamd = L.take(VK * 8);
     p->off.Sd = L.take((int64_t)p->K * 8);
@@ -402,6 +403,11 @@ pulda_status pulda_plan_bind(pulda_plan *p, void *workspace_dev, int64_t bytes)
     m.phid = (float *)(w + p->off.phid);
     m.g16 = (uint16_t *)(w + p->off.g16);
     m.ks16 = p->ks16;
+    m.g8 = w + p->off.g8;
+    const bool near = p->off.g8 + (int64_t)p->V * p->ks16 - p->off.gam < (1ll << 32);
+    m.row16 = near ? (uint32_t)(p->off.g16 - p->off.gam) : 0u;
+    m.row8 = near ? (uint32_t)(p->off.g8 - p->off.gam) : 0u;
+    m.values = 0;
     m.Rd = (double *)(w + p->off.Rd);
     m.gamd = (double *)(w + p->off.gamd);
     m.Sd = (double *)(w + p->off.Sd);
@@ -414,7 +420,7 @@ pulda_status pulda_plan_bind(pulda_plan *p, void *workspace_dev, int64_t bytes)
     m.cphi = (float *)(w + p->off.cphi);
     m.calias = (uint64_t *)(w + p->off.calias);
     m.sigma_a = (double *)(w + p->off.sigma_a);
-    m.phimax = (float *)(w + p->off.phimax);
+    m.phimax = (uint32_t *)(w + p->off.phimax);
     m.hot = (int32_t *)(w + p->off.hot);
     m.hot_word = (int32_t *)(w + p->off.hot_word);
     m.n_hot = 0;
@@ -526,11 +532,9 @@ static pulda_status build_items(pulda_plan *p)
     for (int32_t b = 0; b < nb; ++b) {
         const int64_t start = pos;
         while (pos < p->D && p->len_sorted[pos] >= p->min_len[b]) ++pos;
-        const int32_t per = p->dpi[b];
-        for (int64_t s = start; s < pos; s += per) {
+        for (int64_t s = start; s < pos;) {
             WorkItem w;
             w.first = (int32_t)s;
-            w.count = (int32_t)std::min<int64_t>(per, pos - s);
             w.side_ratio = p->side[b];
             // documents are in decreasing length: the first is the longest
             const bool narrow = p->len_sorted[s] < 256;
@@ -539,6 +543,8 @@ static pulda_status build_items(pulda_plan *p)
             if (g == 1 && !z_group_fits(1, p->K, p->len_sorted[s])) g = 16;
             while (g < 64 && !z_group_fits(g, p->K, p->len_sorted[s])) g *= 2;
             w.group = g;
+            w.count = (int32_t)std::min<int64_t>(p->dpi[b], pos - s);
+            s += w.count;
             cls[item_class(w.group, narrow)].push_back(w);
         }
     }
@@ -692,6 +698,7 @@ static pulda_status enqueue_phi(pulda_plan *p, hipStream_t s)
     size_t a = 0, b = 0;
     if (p->timing) HIP_TRY(phase_event(p, s, &a));
     p->m.phi_method = p->phi_method;
+    p->m.values = p->phi_method == PULDA_PHI_DIRICHLET;
     if (p->phi_method == PULDA_PHI_DIRICHLET) HIP_TRY(launch_phi_step_dirichlet(p->m, p->stats, s));
     else HIP_TRY(launch_phi_step(p->m, p->stats, s));
     if (p->timing) {
@@ -966,6 +973,7 @@ pulda_status pulda_set_phi(pulda_plan *p, const pulda_phi_view *in, void *stream
     // zero cells (every nonzero cell is read from phid)
     HIP_TRY(launch_fill_u64((unsigned long long *)p->m.Rd, 0ull, p->K, s));
     p->m.phi_method = PULDA_PHI_POLYA_URN;
+    p->m.values = 1;
     p->have_phi = true;
     return PULDA_OK;
 }

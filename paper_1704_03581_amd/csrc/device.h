@@ -129,8 +129,15 @@ __device__ __forceinline__ float group_scan_incl_f32(float x)
     x += dpp_f32<0x112, 0xF>(x);
     x += dpp_f32<0x114, 0xF>(x);
     x += dpp_f32<0x118, 0xF>(x);
-    if constexpr (G >= 32) x += dpp_f32<0x142, 0xA>(x);
-    if constexpr (G >= 64) x += dpp_f32<0x143, 0xC>(x);
+    // rows outside the row mask keep x: one instruction a level (the compiler
+    // makes three of it), each behind the two wait states that DPP needs
+    // after a VALU write of its source
+    if constexpr (G == 32)
+        asm volatile("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\ts_nop 1" : "+v"(x));
+    if constexpr (G == 64)
+        asm volatile("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+                     "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\ts_nop 1"
+                     : "+v"(x));
     return x;
 }
 

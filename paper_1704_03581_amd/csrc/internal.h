@@ -30,6 +30,13 @@ struct DevModel {
     // a Phi loaded from values) holds 0xFFFF and is read from phid.
     uint16_t *g16;
     int32_t ks16;
+    // the low bytes of the draws, row stride ks16 (meaningful for words of
+    // format ROW_8), and the byte offsets of g16 and g8 from gam (32-bit; 0:
+    // the tables span more than 4 GiB and every word is ROW_32)
+    uint8_t *g8;
+    uint32_t row16, row8;
+    // Phi has no integer draws: the rows are phid's fp32 values
+    int32_t values;
     double *Rd;                   // [K] RN64(1 / S_k) (0 for an empty row)
     // Algorithm 1's Phi-step (phi_k ~ Dir(n_k + beta)): Gamma draws
     // (word-major dense, fp64), their row sums, and per-block partial sums
@@ -44,10 +51,12 @@ struct DevModel {
     uint32_t *ckg;                // [cap] topic | 16-bit draw << 16 (as g16)
     uint64_t *calias;             // [cap] thr | topic << 32 | alias_topic << 48
     double *sigma_a;              // [V]
-    float *phimax;                // [V] the largest phi of each word's column
+    // largest phi of each word's column (bits of a float below 2) | row
+    // format << 30
+    uint32_t *phimax;             // [V]
     // per word, what a z-step token needs of its word in one 16-byte load:
-    // {first CSC entry, column length | WREC_F32, fp32(sigma_a), phimax} (as
-    // bits); phimax[v] itself is negative when the word has WREC_F32
+    // {first CSC entry, column length | row format << 30, fp32(sigma_a),
+    // largest phi} (as bits)
     uint4 *wrec;                  // [V]
     // the corpus's most frequent words, whose count increments the z-step
     // gathers per block in LDS when K is small (hot[v]: the word's index
@@ -95,19 +104,25 @@ struct WorkItem {
 constexpr int32_t SLOTS_MAX = 16;
 constexpr int32_t SLOTS_FEW = 6;           // the most of the kernels for short lists
 constexpr size_t LDS_BYTES = 160 * 1024;   // per CU, and the most a block takes
-// wrec: the word has a cell whose 16-bit draw is the escape; its terms are
-// gathered as fp32 phi
-constexpr uint32_t WREC_F32 = 0x80000000u;
+// the row that a word's b-terms are gathered from, by the word's largest
+// draw: 8-bit draws (g8), 16-bit draws (g16) or the dense 32-bit table (the
+// urn's draws gam; phi itself where Phi has no draws: Algorithm 1's, or one
+// loaded as values).  log2 of the bytes per topic, held in the top two bits
+// of phimax[v] and of wrec[v].y.
+constexpr uint32_t ROW_8 = 0, ROW_16 = 1, ROW_32 = 2;
+constexpr uint32_t WREC_LOW = 0x3FFFFFFFu;
 
 // LDS of one group of lanes with a document of at most `longest` tokens:
-// slot counts (fp32), the block's draw records, a bit per topic, the slots'
-// topics, the list entries before each chunk of topics, the drawn slots
+// counts by topic, counts by slot (groups under 64 lanes), the block's draw
+// records, a bit per topic, the slots' topics, the list entries before each
+// chunk of topics, the drawn slots
 struct SlotLds {
-    int32_t ms_n;                              // slot counts
-    int32_t o_tok, o_p, o_lst, o_pre, o_out;   // byte offsets (ms at 0)
+    int32_t slots;                                   // the most per lane
+    int32_t wide;                                    // counts by topic of 2 bytes, not 1
+    int32_t o_ms, o_tok, o_p, o_lst, o_pre, o_out;   // byte offsets (counts by topic at 0)
     int32_t group_bytes;
-    int32_t p_words;                           // 32-bit words of topic bits
-    int32_t log_b, chunks, ch_lane;            // topics per chunk (log2), chunks, chunks per lane
+    int32_t p_words;                                 // 32-bit words of topic bits
+    int32_t log_b, chunks, ch_lane;                  // topics per chunk (log2), chunks, chunks per lane
 };
 
 inline SlotLds slot_lds(int32_t G, int32_t K, int32_t longest)
@@ -117,26 +132,26 @@ inline SlotLds slot_lds(int32_t G, int32_t K, int32_t longest)
     const int32_t most = K < longest + G ? K : longest + G;
     const int32_t need = (most + G - 1) / G;
     static const int32_t sizes[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-    int32_t sl = SLOTS_MAX;
+    A.slots = SLOTS_MAX;
     for (int32_t x : sizes)
         if (x >= need) {
-            sl = x;
+            A.slots = x;
             break;
         }
-    A.ms_n = need <= SLOTS_MAX ? sl * G : (K + G - 1) / G * G;
-    const int32_t cap = sl * G;
+    A.wide = longest > 255;
     A.p_words = (K + 31) / 32;
     A.log_b = 0;
     while (A.log_b < 5 && ((int64_t)G << A.log_b) < K) ++A.log_b;
     A.chunks = (K + (1 << A.log_b) - 1) >> A.log_b;
     A.ch_lane = (A.chunks + G - 1) / G;
     auto up = [](int32_t x) { return (x + 15) / 16 * 16; };
-    A.o_tok = up(A.ms_n * 4);
-    A.o_p = A.o_tok + (G + 2) * 16;
+    A.o_ms = up((K + 1) << A.wide);   // (and a place for slots past the list)
+    A.o_tok = A.o_ms + (G == 64 ? 0 : A.slots * G * 4);
+    A.o_p = A.o_tok + (G == 64 ? (64 + 8) * 32 : (G + 2) * 16);
     A.o_lst = A.o_p + up(A.p_words * 4);
-    A.o_pre = A.o_lst + up(cap * 2);
+    A.o_pre = A.o_lst + up(A.slots * G * 2);
     A.o_out = A.o_pre + up(A.chunks * 2);
-    A.group_bytes = A.o_out + up(G * 2);
+    A.group_bytes = A.o_out + up((G == 64 ? 128 : G) * 2);   // (64 lanes: a place each for no result)
     return A;
 }
 

@@ -419,9 +419,10 @@ __global__ void __launch_bounds__(256) phi_dense_kernel(DevModel m)
     const double *gdcol = m.gamd + (int64_t)v * K;
     float *pcol = m.phid + (int64_t)v * K;
     uint16_t *g16col = m.g16 + (int64_t)v * m.ks16;
+    uint8_t *g8col = m.g8 + (int64_t)v * m.ks16;
     int32_t run = 0;
     float fmax = 0.0f;
-    bool esc = false;
+    uint32_t xmax = 0;
     // the column's draws are read PB rounds of 64 cells at a time, so that
     // many loads are in flight before the rounds are processed in order
     constexpr int PB = 8;
@@ -459,7 +460,8 @@ __global__ void __launch_bounds__(256) phi_dense_kernel(DevModel m)
         if (k < K) pcol[k] = f;
         fmax = f > fmax ? f : fmax;
         g16col[k] = (uint16_t)x16;
-        esc |= x16 == 0xFFFFu;
+        g8col[k] = (uint8_t)x16;
+        xmax = x16 > xmax ? x16 : xmax;
         const uint64_t bal = __builtin_amdgcn_ballot_w64(nz);
         if (nz) {
             const int32_t e = run + __builtin_popcountll(bal & ((1ull << lane) - 1ull));
@@ -474,8 +476,11 @@ __global__ void __launch_bounds__(256) phi_dense_kernel(DevModel m)
         const float y = __shfl_xor(fmax, o, 64);
         fmax = y > fmax ? y : fmax;
     }
-    const bool f32 = __builtin_amdgcn_ballot_w64(esc) != 0;
-    if (lane == 0) m.phimax[v] = f32 ? -fmax : fmax;
+    // the narrowest row that holds every draw of the word
+    const uint32_t fmt = __builtin_amdgcn_ballot_w64(xmax == 0xFFFFu) != 0 || m.row8 == 0
+                             ? ROW_32
+                             : (__builtin_amdgcn_ballot_w64(xmax > 0xFFu) != 0 ? ROW_16 : ROW_8);
+    if (lane == 0) m.phimax[v] = __float_as_uint(fmax) | (fmt << 30);
 }
 
 // Columns with at most ALIAS_SMALL nonzeros: one wave per column, four per
@@ -654,9 +659,9 @@ __global__ void word_records_kernel(DevModel m)
     const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= m.V) return;
     const int32_t cb = m.colptr[v];
-    const uint32_t pm = __float_as_uint(m.phimax[v]);   // sign: WREC_F32
-    m.wrec[v] = make_uint4((uint32_t)cb, (uint32_t)(m.colptr[v + 1] - cb) | (pm & WREC_F32),
-                           __float_as_uint((float)m.sigma_a[v]), pm & ~WREC_F32);
+    const uint32_t pm = m.phimax[v];   // row format in the top bits
+    m.wrec[v] = make_uint4((uint32_t)cb, (uint32_t)(m.colptr[v + 1] - cb) | (pm & ~WREC_LOW),
+                           __float_as_uint((float)m.sigma_a[v]), pm & WREC_LOW);
 }
 
 hipError_t launch_word_records(const DevModel &m, hipStream_t s)
@@ -892,13 +897,13 @@ hipError_t launch_phi_step_dirichlet(const DevModel &m, unsigned long long *stat
 //   y = u (sigma_a + sigma_b) - sigma_a.
 //
 // The b-part in fp32, with a proof of exactness.  Every quantity is within a
-// known relative error of its exact value: a term b~ = fp32(fp32(x R~_k) m)
-// (R~_k = fp32(R_k)) or fp32(phi m) is within 4.01 u of phi_kv m_k
-// (u = 2^-24), a lane's running sum of SL terms adds (SL - 1) u, the group
+// known relative error of its exact value: a term
+// b~ = fp32(fp32(fp32(x) R~_k) m) (R~_k = fp32(R_k)) or fp32(phi m) is within
+// 5.01 u of phi_kv m_k (u = 2^-24; phi_kv itself is rounded to fp32), a lane's running sum of SL terms adds (SL - 1) u, the group
 // scan log2(G) u, the exclusive prefix and y minus it u each (relative to
 // Z = sigma_a + sigma_b).  x = u0 Z and y = x - sigma_a are within
 // (SL + 8 + log2 G) u Z, so every comparison of y with 0 or with a running sum
-// errs by less than (3 SL + 2 log2 G + 14) u Z.  The decision is taken only
+// errs by less than (3 SL + 2 log2 G + 16) u Z.  The decision is taken only
 // when y lies farther than tol = (64 + 8 SL) u Z from the boundary it is
 // compared with (more than twice that error); it is then the decision of
 // exact arithmetic, which is also the fp64 path's.  Otherwise (a few draws in
@@ -930,15 +935,19 @@ struct ZArgs {
 // one draw's inputs, staged in LDS in draw order; every lane of the group
 // reads them with one broadcast load
 struct alignas(16) DrawRec {
-    uint32_t row;    // byte offset of the word's row: 16-bit draws, or fp32 phi (flag)
-    uint32_t uc;     // 24-bit uniform << 8 | flag << 7 | lane of the token (127: no draw)
+    uint32_t row;    // byte offset of the word's row from gam (phid for values)
+    float u0;        // (r >> 8) 2^-24, exact
     float saf;       // fp32(sigma_a(v)); NaN when it is too small for fp32's normal
                      // range (no comparison holds: the fp64 path decides)
-    uint32_t pad;
+    uint32_t w;      // row format | lane of the token << 2 (127: no draw)
+    __device__ uint32_t fmt() const { return w & 3u; }
+    __device__ int lane() const { return (int)__builtin_amdgcn_ubfe(w, 2, 7); }
 };
 
-constexpr uint32_t REC_F32 = 128;      // the word's terms are gathered as fp32 phi
-constexpr uint32_t REC_NONE = 127;
+// a record without a draw: it reads the first word's row, and its sigma_a
+// (far above any sigma_b) makes it an a-part of no lane
+constexpr uint32_t REC_NONE = ROW_32 | 127u << 2;
+constexpr float REC_NONE_SA = 1e30f;
 
 // draw statistics of a lane's tokens
 struct ZStat {
@@ -960,6 +969,25 @@ __device__ __forceinline__ T load_at(const T *base, uint32_t byte_off)
     return *(const T *)((const char *)base + byte_off);
 }
 
+struct __attribute__((packed, aligned(1))) Unaligned32 {
+    uint32_t x;
+};
+
+__device__ __forceinline__ uint32_t load_u32_at(const void *base, uint32_t byte_off)
+{
+    return ((const Unaligned32 *)((const char *)base + byte_off))->x;
+}
+
+// the bits of a gathered word that are the draw
+__device__ __forceinline__ uint32_t row_mask(uint32_t fmt) { return 0xFFFFFFFFu >> (32u - (8u << fmt)); }
+
+// phi of a slot (to rounding) from the gathered word
+template <bool VALUES>
+__device__ __forceinline__ float slot_phi(uint32_t x, uint32_t mask, float R)
+{
+    return VALUES ? __uint_as_float(x) : (float)(x & mask) * R;
+}
+
 // LDS accesses of the wave before and after are kept in this order (LDS
 // executes a wave's instructions in order; only the compiler is held)
 __device__ __forceinline__ void lds_order()
@@ -975,21 +1003,24 @@ __device__ __forceinline__ float lds_add(float *p, float x)
 
 // the document a group is working on (all pointers in LDS)
 struct SlotDoc {
-    float *ms;        // counts by slot
-    DrawRec *tok;     // [G + 2] the block's draws, in order
+    uint8_t *mt;      // counts by topic, 1 or 2 bytes each (wide); up to date between blocks
+    float *ms;        // counts by slot during a block (groups under 64 lanes)
+    DrawRec *tok;     // the block's draws, in order
     uint32_t *P;      // a bit per topic: in the list
     uint16_t *lst;    // topic of each slot
     uint16_t *pre;    // list entries before each chunk of topics
-    uint16_t *out;    // [G] the new slot of each of the block's tokens
+    uint16_t *out;    // [G] the new slots of the block's draws, in order
     int32_t L;        // slots in use (group-uniform)
     int32_t nz;       // topics with a nonzero count (group-uniform)
+    bool wide;        // (uniform)
     bool dense;       // slot = topic
 };
 
 __device__ __forceinline__ SlotDoc slot_doc(uint8_t *base, const SlotLds &A)
 {
     SlotDoc S;
-    S.ms = (float *)base;
+    S.mt = base;
+    S.ms = (float *)(base + A.o_ms);
     S.tok = (DrawRec *)(base + A.o_tok);
     S.P = (uint32_t *)(base + A.o_p);
     S.lst = (uint16_t *)(base + A.o_lst);
@@ -997,8 +1028,21 @@ __device__ __forceinline__ SlotDoc slot_doc(uint8_t *base, const SlotLds &A)
     S.out = (uint16_t *)(base + A.o_out);
     S.L = 0;
     S.nz = 0;
+    S.wide = A.wide != 0;
     S.dense = false;
     return S;
+}
+
+// the count of topic k
+__device__ __forceinline__ uint32_t count_of(const SlotDoc &S, int32_t k)
+{
+    return S.wide ? (uint32_t)((const uint16_t *)S.mt)[k] : (uint32_t)S.mt[k];
+}
+
+__device__ __forceinline__ void set_count(const SlotDoc &S, int32_t k, uint32_t c)
+{
+    if (S.wide) ((uint16_t *)S.mt)[k] = (uint16_t)c;
+    else S.mt[k] = (uint8_t)c;
 }
 
 // the list bits of chunk ch (topics [ch 2^log_b, (ch + 1) 2^log_b))
@@ -1019,78 +1063,56 @@ __device__ __forceinline__ int32_t slot_of(const SlotDoc &S, const SlotLds &A, i
 
 __device__ __forceinline__ int32_t topic_of(const SlotDoc &S, int32_t slot) { return S.dense ? slot : S.lst[slot]; }
 
-// the count of any topic
-__device__ __forceinline__ int32_t count_of(const SlotDoc &S, const SlotLds &A, int32_t k)
+// a document's counts from its tokens' topics z[s, e): by topic, and the
+// list's bits
+template <int G, bool STATS>
+__device__ __forceinline__ void slots_load(SlotDoc &S, const SlotLds &A, const uint16_t *z, int64_t s, int64_t e,
+                                           int g)
 {
-    if (!S.dense && !((S.P[k >> 5] >> (k & 31)) & 1u)) return 0;
-    return (int32_t)S.ms[slot_of(S, A, k)];
-}
-
-// an empty document: no topic in the list
-template <int G>
-__device__ __forceinline__ void slots_clear(SlotDoc &S, const SlotLds &A, int g)
-{
+    for (int32_t i = g; i < A.o_ms / 16; i += G) ((uint4 *)S.mt)[i] = make_uint4(0u, 0u, 0u, 0u);
     for (int32_t w = g; w < A.p_words; w += G) S.P[w] = 0u;
     S.L = 0;
     S.nz = 0;
     S.dense = false;
     lds_order();
-}
-
-// after the list's bits were set from a document's tokens: its topics with a
-// nonzero count
-template <int G>
-__device__ __forceinline__ void slots_count_topics(SlotDoc &S, const SlotLds &A, int g)
-{
-    lds_order();
-    int32_t c = 0;
-    for (int32_t w = g; w < A.p_words; w += G) c += __builtin_popcount(S.P[w]);
-    S.nz = group_bcast<G>(group_scan_incl_i32<G>(c), G - 1);
-}
-
-// lay the slots out for a block: the topics with a nonzero count (first: the
-// bits already set in P, counts added afterwards by the caller; else the
-// previous layout's nonzero slots) and each marked lane's topic ka
-template <int G, bool BIG>
-__device__ __forceinline__ void slots_layout(SlotDoc &S, const SlotLds &A, int32_t K, bool first, bool mark,
-                                             int32_t ka, int g)
-{
-    // the previous layout's slots, topic | count << 16, in registers
-    constexpr int MAXU = BIG ? SLOTS_MAX : SLOTS_FEW;
-    uint32_t pk[MAXU];
-#pragma unroll
-    for (int u = 0; u < MAXU; ++u) {
-        pk[u] = 0;
-        if (__builtin_amdgcn_ballot_w64(!first && !S.dense && u * G < S.L) == 0) continue;
-        const int32_t e = u * G + g;
-        if (!first && !S.dense && e < S.L) {
-            const uint32_t k = S.lst[e];
-            const uint32_t m = (uint32_t)S.ms[e];
-            pk[u] = k | (m << 16);
-            if (m == 0) atomicAnd(&S.P[k >> 5], ~(1u << (k & 31)));
-        }
+    uint32_t *m32 = (uint32_t *)S.mt;
+#pragma unroll 4
+    for (int64_t i = s + g; i < e; i += G) {
+        const uint32_t k = z[i];
+        if (S.wide) atomicAdd(&m32[k >> 1], 1u << 16 * (k & 1));
+        else atomicAdd(&m32[k >> 2], 1u << 8 * (k & 3));
+        atomicOr(&S.P[k >> 5], 1u << (k & 31));
     }
     lds_order();
+    if constexpr (STATS) {
+        int32_t c = 0;
+        for (int32_t w = g; w < A.p_words; w += G) c += __builtin_popcount(S.P[w]);
+        S.nz = group_bcast<G>(group_scan_incl_i32<G>(c), G - 1);
+    }
+}
+
+// lay the slots out for a block: the topics with a nonzero count (their bits
+// are set) and each marked lane's topic ka
+template <int G, bool BIG>
+__device__ __forceinline__ void slots_layout(SlotDoc &S, const SlotLds &A, int32_t K, bool mark, int32_t ka, int g)
+{
     if (mark) atomicOr(&S.P[ka >> 5], 1u << (ka & 31));
     lds_order();
     // list entries of this lane's chunks, and before them
     const int32_t c0 = g * A.ch_lane;
     int32_t n = 0;
+    uint32_t bits0 = 0;
     for (int32_t j = 0; j < A.ch_lane; ++j)
-        if (c0 + j < A.chunks) n += __builtin_popcount(chunk_bits(S.P, c0 + j, A.log_b));
+        if (c0 + j < A.chunks) {
+            const uint32_t bits = chunk_bits(S.P, c0 + j, A.log_b);
+            bits0 = j == 0 ? bits : bits0;
+            n += __builtin_popcount(bits);
+        }
     const int32_t incl = group_scan_incl_i32<G>(n);
     const int32_t L = group_bcast<G>(incl, G - 1);
-    const bool was_dense = S.dense;
-    if (BIG && __builtin_amdgcn_ballot_w64(was_dense || L > SLOTS_MAX * G) != 0) {
+    if (BIG && __builtin_amdgcn_ballot_w64(S.dense || L > SLOTS_MAX * G) != 0) {
         S.dense = true;
         S.L = K;
-        if (!was_dense)
-            for (int32_t e = g; e < K; e += G) S.ms[e] = 0.0f;
-        lds_order();
-#pragma unroll
-        for (int u = 0; u < MAXU; ++u)
-            if (pk[u] >> 16) S.ms[pk[u] & 0xFFFFu] = (float)(pk[u] >> 16);
-        lds_order();
         return;
     }
     S.L = L;
@@ -1098,45 +1120,52 @@ __device__ __forceinline__ void slots_layout(SlotDoc &S, const SlotLds &A, int32
     for (int32_t j = 0; j < A.ch_lane; ++j) {
         if (c0 + j >= A.chunks) break;
         S.pre[c0 + j] = (uint16_t)o;
-        uint32_t bits = chunk_bits(S.P, c0 + j, A.log_b);
+        uint32_t bits = j == 0 ? bits0 : chunk_bits(S.P, c0 + j, A.log_b);
         const int32_t k0 = (c0 + j) << A.log_b;
         while (bits) {
             S.lst[o++] = (uint16_t)(k0 + __builtin_ctz(bits));
             bits &= bits - 1;
         }
     }
-    // (the slots up to the next multiple of any SL are zero too)
-    for (int32_t e = g; e < A.ms_n; e += G) {
-        if (__builtin_amdgcn_ballot_w64(e - g < L + 4 * G) == 0) break;
-        S.ms[e] = 0.0f;
-    }
     lds_order();
+}
+
+// counts of this lane's slots, at the start of a block, and back: a topic
+// whose count is zero leaves the list.  Slots past the list stand for topic
+// K, whose count is zero and whose place the table has.  (No branch: one on
+// a lane's slot costs more than an access that changes nothing.)
+template <int SL>
+__device__ __forceinline__ void slots_counts(const SlotDoc &S, const uint32_t (&kk)[SL], int32_t e0, int32_t K,
+                                             uint32_t (&c)[SL])
+{
+    uint32_t k[SL];
 #pragma unroll
-    for (int u = 0; u < MAXU; ++u) {
-        if (__builtin_amdgcn_ballot_w64((pk[u] >> 16) != 0) == 0) continue;
-        if (pk[u] >> 16) S.ms[slot_of(S, A, (int32_t)(pk[u] & 0xFFFFu))] = (float)(pk[u] >> 16);
-    }
-    lds_order();
-}
-
-// set the list's bits from tokens' topics, then (after the first layout) add
-// up their counts
-template <int G>
-__device__ __forceinline__ void slots_mark_tokens(SlotDoc &S, const uint16_t *z, int64_t s, int64_t e, int g)
-{
-#pragma unroll 4
-    for (int64_t i = s + g; i < e; i += G) {
-        const uint32_t k = z[i];
-        atomicOr(&S.P[k >> 5], 1u << (k & 31));
+    for (int u = 0; u < SL; ++u) k[u] = e0 + u < S.L ? kk[u] : (uint32_t)K;
+    if (S.wide) {
+#pragma unroll
+        for (int u = 0; u < SL; ++u) c[u] = ((const uint16_t *)S.mt)[k[u]];
+    } else {
+#pragma unroll
+        for (int u = 0; u < SL; ++u) c[u] = S.mt[k[u]];
     }
 }
 
-template <int G>
-__device__ __forceinline__ void slots_add_tokens(SlotDoc &S, const SlotLds &A, const uint16_t *z, int64_t s,
-                                                 int64_t e, int g)
+template <int SL>
+__device__ __forceinline__ void slots_store(const SlotDoc &S, const uint32_t (&kk)[SL], int32_t e0, int32_t K,
+                                            const uint32_t (&c)[SL], bool drop)
 {
-#pragma unroll 4
-    for (int64_t i = s + g; i < e; i += G) lds_add(&S.ms[slot_of(S, A, z[i])], 1.0f);
+    if (S.wide) {
+#pragma unroll
+        for (int u = 0; u < SL; ++u) ((uint16_t *)S.mt)[e0 + u < S.L ? kk[u] : (uint32_t)K] = (uint16_t)c[u];
+    } else {
+#pragma unroll
+        for (int u = 0; u < SL; ++u) S.mt[e0 + u < S.L ? kk[u] : (uint32_t)K] = (uint8_t)c[u];
+    }
+    if (drop) {
+#pragma unroll
+        for (int u = 0; u < SL; ++u)
+            atomicAnd(&S.P[kk[u] >> 5], e0 + u < S.L && c[u] == 0 ? ~(1u << (kk[u] & 31)) : 0xFFFFFFFFu);
+    }
     lds_order();
 }
 
@@ -1145,13 +1174,13 @@ struct LaneTok {
     int32_t v;          // word
     int32_t ka;         // the a-part's alias draw (the old topic for an empty column)
     int32_t kv;         // nonzeros in the word's column
-    uint32_t row, uc;   // as DrawRec (uc without the lane)
-    float saf;
+    uint32_t row, fmt;  // as DrawRec
+    float u0, saf;
     bool sure;          // the a-part is certain whatever the document's counts, or
                         // the column is empty: no draw
 };
 
-__device__ __forceinline__ LaneTok no_token() { return {0, 0, 0, 0u, 0u, 1.0f, true}; }
+__device__ __forceinline__ LaneTok no_token() { return {0, 0, 0, 0u, 0u, 0.0f, 1.0f, true}; }
 
 // stage the token at this lane from its word's record.  nd: tokens in the
 // document's counts.  The a-part's draw from the word's alias table over
@@ -1168,11 +1197,12 @@ __device__ __forceinline__ LaneTok stage_token(const DevModel &M, int32_t v, int
     const uint4 rec = M.wrec[v];
     LaneTok x;
     x.v = v;
-    const uint32_t kv = rec.y & ~WREC_F32;
+    const uint32_t kv = rec.y & WREC_LOW;
     x.kv = (int32_t)kv;
-    const bool f32 = (rec.y & WREC_F32) != 0;
-    x.row = f32 ? (uint32_t)v * (uint32_t)M.K * 4u : (uint32_t)v * (uint32_t)M.ks16 * 2u;
-    x.uc = (r.x & 0xFFFFFF00u) | (f32 ? REC_F32 : 0u);
+    x.fmt = rec.y >> 30;
+    const uint32_t vs = (uint32_t)v * (uint32_t)M.ks16;
+    x.row = x.fmt == ROW_8 ? M.row8 + vs : (x.fmt == ROW_16 ? M.row16 + 2u * vs : (uint32_t)v * (uint32_t)M.K * 4u);
+    x.u0 = (float)(r.x >> 8) * 0x1p-24f;
     const float sa = __uint_as_float(rec.z);
     x.saf = sa > 0x1p-100f ? sa : __uint_as_float(0x7FC00000u);
     x.ka = kold;
@@ -1181,9 +1211,8 @@ __device__ __forceinline__ LaneTok stage_token(const DevModel &M, int32_t v, int
         const uint32_t j = scale32(r.y, kv);
         const uint64_t a = M.calias[rec.x + j];
         x.ka = (int32_t)((r.z < (uint32_t)a) ? ((a >> 32) & 0xFFFFu) : (a >> 48));
-        const float u0 = (float)(r.x >> 8) * 0x1p-24f;
         const float B = __uint_as_float(rec.w) * (float)(nd - 1);
-        x.sure = nd > 0 && u0 * (sa + B) < sa * (1.0f - 0x1p-20f);
+        x.sure = nd > 0 && x.u0 * (sa + B) < sa * (1.0f - 0x1p-20f);
     }
     return x;
 }
@@ -1192,15 +1221,15 @@ __device__ __forceinline__ LaneTok stage_token(const DevModel &M, int32_t v, int
 // scan orders the lanes.  COL: the terms are the word's Phi column, the
 // counts read by topic (dense layout); else the slots.  Returns the slot of
 // the new topic, or -1 for the a-part; Z: sigma_a + sigma_b.
-template <int G, bool COL>
+template <int G, bool COL, typename Count>
 __device__ __forceinline__ int32_t draw_f64(const uint4 *wrec, const double *sigma_a, const double *Rd,
                                          const uint32_t *ckg, const uint16_t *g16, const float *phid, int32_t K,
-                                         int32_t ks16, int32_t v, float u0, const float *ms, const uint16_t *lst,
+                                         int32_t ks16, int32_t v, float u0, Count count, const uint16_t *lst,
                                          int32_t L, int32_t per, double &Zo)
 {
     const int g = __lane_id() & (G - 1);
     const uint4 rec = wrec[v];
-    const int32_t n = COL ? (int32_t)(rec.y & ~WREC_F32) : L;
+    const int32_t n = COL ? (int32_t)(rec.y & WREC_LOW) : L;
     const int32_t q = COL ? (n + G - 1) / G : per;
     const int32_t e0 = g * q;
     const int32_t e1 = e0 + q < n ? e0 + q : n;
@@ -1209,15 +1238,15 @@ __device__ __forceinline__ int32_t draw_f64(const uint4 *wrec, const double *sig
     auto term = [&](int32_t e) -> double {
         int32_t k;
         uint32_t x;
-        float m;
+        uint32_t m;
         if (COL) {
             const uint32_t kg = ckg[rec.x + (uint32_t)e];
             k = (int32_t)(kg & 0xFFFFu);
             x = kg >> 16;
-            m = ms[k];
+            m = count(e, k);
         } else {
             k = lst[e];
-            m = ms[e];
+            m = count(e, k);
             x = g16[row16 + (uint32_t)k];
         }
         // phi_kv = fp32(x R_k) == fp32(RN64(x / S_k)) for x < 2^16 and
@@ -1264,12 +1293,13 @@ __device__ __forceinline__ int32_t draw_f64(const uint4 *wrec, const double *sig
     return __shfl(at, f, G);
 }
 
-template <int G, bool COL>
+// (count(e, k): the count of slot e, of topic k)
+template <int G, bool COL, typename Count>
 __device__ __forceinline__ int32_t slots_draw_f64(const DevModel &M, const SlotDoc &S, int32_t v, float u0,
-                                                  int32_t per, double &Z)
+                                                  int32_t per, Count count, double &Z)
 {
-    return draw_f64<G, COL>(M.wrec, M.sigma_a, M.Rd, M.ckg, M.g16, M.phid, M.K, M.ks16, v, u0, S.ms, S.lst, S.L, per,
-                            Z);
+    return draw_f64<G, COL>(M.wrec, M.sigma_a, M.Rd, M.ckg, M.g16, M.phid, M.K, M.ks16, v, u0, count, S.lst, S.L,
+                            per, Z);
 }
 
 // a lane's token during a block: old slot, a-part slot, the counts its old
@@ -1280,6 +1310,11 @@ struct LaneDraw {
     uint32_t key;       // segment << 7 | rank within it for a token decided at
                         // staging (segment: draws before it); ~0: none
     float ro, rn;       // (2 and 1: no topic left or entered)
+    // counts in registers: topics with a nonzero count when the token was
+    // moved, when the block's draw number g was drawn, and the draws that
+    // took the a-part
+    int32_t kd, kd_draw;
+    uint64_t a_draws;
     uint32_t a, fb;
 };
 
@@ -1288,21 +1323,23 @@ struct LaneDraw {
 template <bool STATS>
 __device__ __forceinline__ void move_segment(const SlotDoc &S, LaneDraw &d, uint32_t i)
 {
-    for (uint32_t t = i << 7; __builtin_amdgcn_ballot_w64(d.key == t) != 0; ++t)
+    uint32_t t = i << 7;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(d.key == t) == 0, 1)) return;
+    do {
         if (d.key == t) {
+            const float ro = lds_add(&S.ms[d.po], -1.0f), rn = lds_add(&S.ms[d.pa], 1.0f);
             if (STATS) {
-                d.ro = lds_add(&S.ms[d.po], -1.0f);
-                d.rn = lds_add(&S.ms[d.pa], 1.0f);
-            } else {
-                (void)lds_add(&S.ms[d.po], -1.0f);
-                (void)lds_add(&S.ms[d.pa], 1.0f);
+                d.ro = ro;
+                d.rn = rn;
             }
         }
+        ++t;
+    } while (__builtin_amdgcn_ballot_w64(d.key == t) != 0);
 }
 
 // the block's draws, n_max of them (the largest group's), with SL slots per
 // lane; DEPTH draws' gathers in flight
-template <int G, int SL, bool STATS>
+template <int G, int SL, bool STATS, bool VALUES>
 __device__ __forceinline__ void draw_slots(const DevModel &M, const SlotDoc &S, const float *Rf, const int32_t v,
                                            LaneDraw &d, const uint32_t n_max, const int lane_g)
 {
@@ -1319,46 +1356,44 @@ __device__ __forceinline__ void draw_slots(const DevModel &M, const SlotDoc &S, 
         kk[u] = S.lst[e < S.L ? e : 0];
         R[u] = Rf[kk[u]];
     }
+    {
+        uint32_t c[SL];
+        slots_counts(S, kk, g * SL, M.K, c);
+#pragma unroll
+        for (int u = 0; u < SL; ++u) S.ms[g * SL + u] = (float)c[u];
+        lds_order();
+    }
     DrawRec rec[DEPTH];
     uint32_t x[DEPTH][SL];
+    // one unaligned 4-byte load a slot, whatever the row's format (no branch
+    // that would make the loads wait where its sides meet)
     auto gather = [&](int b) {
-        const uint32_t row = rec[b].row;
-        const bool f32 = (rec[b].uc & REC_F32) != 0;
-        if (__builtin_amdgcn_ballot_w64(f32) == 0) {
 #pragma unroll
-            for (int u = 0; u < SL; ++u) x[b][u] = load_at(M.g16, (kk[u] << 1) + row);
-        } else if (f32) {
-#pragma unroll
-            for (int u = 0; u < SL; ++u) x[b][u] = __float_as_uint(load_at(M.phid, (kk[u] << 2) + row));
-        } else {
-#pragma unroll
-            for (int u = 0; u < SL; ++u) x[b][u] = load_at(M.g16, (kk[u] << 1) + row);
-        }
+        for (int u = 0; u < SL; ++u) x[b][u] = load_u32_at(VALUES ? (const void *)M.phid : (const void *)M.gam, (kk[u] << rec[b].fmt()) + rec[b].row);
     };
 #pragma unroll
     for (int b = 0; b < DEPTH; ++b) {
         rec[b] = S.tok[b];
         gather(b);
+        // (in this order: the first draw then waits for its own loads only)
+        __builtin_amdgcn_sched_barrier(0);
     }
     const uint64_t here = __builtin_amdgcn_ballot_w64(true);
     for (uint32_t i0 = 0; i0 < n_max; i0 += DEPTH) {
 #pragma unroll
         for (int b = 0; b < DEPTH; ++b) {
+            // (past n_max: records without a draw.  No early exit: the paths
+            // would meet at the loop's end and make its first draw wait for
+            // every load)
             const uint32_t i = i0 + b;
-            if (b > 0 && i >= n_max) break;
             move_segment<STATS>(S, d, i);
-            const uint32_t uc = rec[b].uc;
-            const float sa = rec[b].saf;
-            const int c = (int)(uc & 127u);
+            const float u0 = rec[b].u0, sa = rec[b].saf;
+            const int c = rec[b].lane();
             // phi of the slots (to rounding), from the gathered draws
             float f[SL];
-            const bool f32 = (uc & REC_F32) != 0;
+            const uint32_t low = row_mask(rec[b].fmt());
 #pragma unroll
-            for (int u = 0; u < SL; ++u) f[u] = (float)x[b][u] * R[u];
-            if (__builtin_amdgcn_ballot_w64(f32) != 0) {
-#pragma unroll
-                for (int u = 0; u < SL; ++u) f[u] = f32 ? __uint_as_float(x[b][u]) : f[u];
-            }
+            for (int u = 0; u < SL; ++u) f[u] = slot_phi<VALUES>(x[b][u], low, R[u]);
             rec[b] = S.tok[i + DEPTH < G ? i + DEPTH : G];
             // m^{-i}
             if (g == c) {
@@ -1368,6 +1403,9 @@ __device__ __forceinline__ void draw_slots(const DevModel &M, const SlotDoc &S, 
             float m[SL];
 #pragma unroll
             for (int u = 0; u < SL; ++u) m[u] = S.ms[g * SL + u];
+            // (issued before the gather's record is waited for: one LDS round
+            // trip, not two)
+            __builtin_amdgcn_sched_barrier(0);
             gather(b);
             // running sums of the lane's terms
             float cs[SL];
@@ -1377,7 +1415,7 @@ __device__ __forceinline__ void draw_slots(const DevModel &M, const SlotDoc &S, 
             const float incl = group_scan_incl_f32<G>(cs[SL - 1]);
             const float T = group_last_f32<G>(incl);
             const float Z = sa + T;
-            const float y = ((float)(uc >> 8) * 0x1p-24f) * Z - sa;
+            const float y = u0 * Z - sa;
             const float tol = Z * ((float)(64 + 8 * SL) * 0x1p-24f);
             const bool is_a = y < -tol;
             // y relative to the lane's slots; how far it is from every
@@ -1395,7 +1433,7 @@ __device__ __forceinline__ void draw_slots(const DevModel &M, const SlotDoc &S, 
                 for (int u = 0; u + 1 < SL; ++u) at += cs[u] <= yl ? 1 : 0;
                 at += g * SL;
                 (void)lds_add(&S.ms[at], 1.0f);
-                S.out[c] = (uint16_t)at;
+                S.out[i] = (uint16_t)at;
             }
             if (is_a && g == c) {
                 if (STATS) d.rn = lds_add(&S.ms[d.pa], 1.0f);
@@ -1403,16 +1441,18 @@ __device__ __forceinline__ void draw_slots(const DevModel &M, const SlotDoc &S, 
                 d.a = 1;
             }
             // a decided group has all its lanes in in_a or one in in_b
-            if (__builtin_popcountll(in_a) + G * __builtin_popcountll(in_b) != __builtin_popcountll(here)) {
+            if (__builtin_expect(
+                    __builtin_popcountll(in_a) + G * __builtin_popcountll(in_b) != __builtin_popcountll(here), 0)) {
                 const bool open = !is_a && group_ballot<G>(mine) == 0;
                 double Zd;
                 const int32_t vc = __shfl(v, c & (G - 1), G);
-                const int32_t at = slots_draw_f64<G, false>(M, S, vc, (float)(uc >> 8) * 0x1p-24f, SL, Zd);
+                const int32_t at = slots_draw_f64<G, false>(
+                    M, S, vc, u0, SL, [&](int32_t e, int32_t) { return (uint32_t)S.ms[e]; }, Zd);
                 if (open) {
                     if (at >= 0) {
                         if (g == 0) {
                             (void)lds_add(&S.ms[at], 1.0f);
-                            S.out[c] = (uint16_t)at;
+                            S.out[i] = (uint16_t)at;
                         }
                     } else if (g == c) {
                         const float was = lds_add(&S.ms[d.pa], 1.0f);
@@ -1424,84 +1464,376 @@ __device__ __forceinline__ void draw_slots(const DevModel &M, const SlotDoc &S, 
             }
         }
     }
-    move_segment<STATS>(S, d, n_max);
+    // the tokens behind the last draw (a step past n_max has moved them)
+    if (n_max % DEPTH == 0) move_segment<STATS>(S, d, n_max);
+    lds_order();
+    uint32_t c[SL];
+#pragma unroll
+    for (int u = 0; u < SL; ++u) c[u] = (uint32_t)S.ms[g * SL + u];
+    slots_store(S, kk, g * SL, M.K, c, true);
+}
+
+// The block's draws of one document per wave (64 lanes), the counts in
+// registers too: lane g holds the counts of its SL slots for the whole block
+// (written back to LDS at the end), one per register, or with BYTES (SL <= 4,
+// no count above 255) one per byte of one register, where an addition needs
+// no compare per slot.  A draw touches LDS for its record only, read DEPTH
+// draws ahead, so its chain is the scan and the decision.  Control is
+// uniform: draws and moves are bit masks over the block's tokens.
+//
+// A wave alone on its SIMD issues an instruction every 4 to 5 cycles, a
+// taken branch costs 20 to 90 and a branch on a vector compare 33: so a draw
+// is straight-line code (about 80 instructions at SL = 3), whichever part it
+// takes, and what is seldom needed stands outside the loop: a round of DEPTH
+// draws in which one is undecided in fp32 is taken back and drawn again up to
+// that one in fp64.
+struct alignas(16) RegRec {
+    uint32_t row;       // as DrawRec
+    float u0, saf;
+    uint32_t w;         // bits of a draw in the row (8, 16; 31 stands for 32) | row format << 30
+    uint32_t o, a;      // old and a-part slot; BYTES: the lane that holds it
+    uint32_t io, ia;    // BYTES: 1 in its byte
+};
+
+constexpr int REG_PAD = 8;      // records past the block's draws that may be read
+constexpr uint32_t REG_NONE = 0xFFFFu;   // no slot, no lane
+
+template <int SL, bool STATS, bool VALUES, bool BYTES>
+__device__ __forceinline__ void draw_regs(const DevModel &M, SlotDoc &S, const float *Rf, const LaneTok &t,
+                                          const bool draw, const uint32_t place, uint64_t moves,
+                                          const uint64_t move_draws, const uint32_t n_draws, LaneDraw &d,
+                                          const int lane_g)
+{
+    static_assert(!BYTES || SL <= 4, "four counts a register");
+    constexpr int DEPTH = SL <= 2 ? 4 : (SL <= 4 ? 3 : (SL <= 10 ? 2 : 1));
+    constexpr int NM = BYTES ? 1 : SL;
+    int g = lane_g;
+    asm volatile("" : "+v"(g));
+    const int32_t e0 = g * SL;
+    RegRec *const recs = (RegRec *)S.tok;
+    {
+        RegRec r = {0u, 0.0f, REC_NONE_SA, 31u | ROW_32 << 30, REG_NONE, REG_NONE, 0u, 0u};
+        if (g < REG_PAD) recs[64 + g] = r;
+        if (draw) {
+            r.row = t.row;
+            r.u0 = t.u0;
+            r.saf = t.saf;
+            r.w = (t.fmt == ROW_32 ? 31u : 8u << t.fmt) | t.fmt << 30;
+            if (BYTES) {
+                r.o = (uint32_t)d.po / SL;
+                r.a = (uint32_t)d.pa / SL;
+                r.io = 1u << 8 * (d.po - (int32_t)r.o * SL);
+                r.ia = 1u << 8 * (d.pa - (int32_t)r.a * SL);
+            } else {
+                r.o = (uint32_t)d.po;
+                r.a = (uint32_t)d.pa;
+            }
+        }
+        recs[place] = r;
+    }
+    uint32_t kk[SL];
+    float R[SL];
+    uint32_t m[NM];
+    if (BYTES) m[0] = 0;
+#pragma unroll
+    for (int u = 0; u < SL; ++u) {
+        const int32_t e = e0 + u;
+        kk[u] = S.lst[e < S.L ? e : 0];
+        R[u] = VALUES ? 0.0f : Rf[kk[u]];
+    }
+    {
+        uint32_t c[SL];
+        slots_counts(S, kk, e0, M.K, c);
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            if (BYTES) m[0] |= c[u] << 8 * u;
+            else m[BYTES ? 0 : u] = c[u];
+        }
+    }
+    lds_order();
+    // count of slot u, and in fp32
+    auto at = [&](int u) { return BYTES ? (m[0] >> 8 * u) & 255u : m[BYTES ? 0 : u]; };
+    // add (sign: 1 or -1) the token at slot e (a uniform slot number)
+    auto add = [&](int32_t e, bool up) {
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            const uint32_t one = e - e0 == u ? 1u : 0u;
+            if (BYTES) m[0] = up ? m[0] + (one << 8 * u) : m[0] - (one << 8 * u);
+            else m[BYTES ? 0 : u] = up ? m[BYTES ? 0 : u] + one : m[BYTES ? 0 : u] - one;
+        }
+    };
+    RegRec rec[DEPTH];
+    uint32_t x[DEPTH][SL];
+    auto gather = [&](int b) {
+        const uint32_t fmt = rec[b].w >> 30;
+#pragma unroll
+        for (int u = 0; u < SL; ++u)
+            x[b][u] = load_u32_at(VALUES ? (const void *)M.phid : (const void *)M.gam, (kk[u] << fmt) + rec[b].row);
+    };
+    // topics with a nonzero count
+    auto count = [&]() {
+        int32_t n = 0;
+#pragma unroll
+        for (int u = 0; u < SL; ++u) n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(at(u) != 0));
+        return n;
+    };
+    auto store = [&](bool drop) {
+        uint32_t c[SL];
+#pragma unroll
+        for (int u = 0; u < SL; ++u) c[u] = at(u);
+        slots_store(S, kk, e0, M.K, c, drop);
+    };
+    const uint32_t po_pa = (uint32_t)d.po | ((uint32_t)d.pa << 16);
+    // (lane i: the token of draw i)
+    const int32_t token = __builtin_amdgcn_ds_permute((int)place << 2, g);
+    auto move_before = [&](uint64_t below) {
+        uint64_t todo = moves & below;
+        moves &= ~below;
+        while (todo) {
+            const int c = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)po_pa, c);
+            add((int32_t)(w & 0xFFFFu), false);
+            if constexpr (STATS) {
+                const int32_t n = count();
+                if (g == c) d.kd = n;
+            }
+            add((int32_t)(w >> 16), true);
+        }
+    };
+    auto moves_of_draw = [&](uint32_t i) {
+        move_before((1ull << __builtin_amdgcn_readlane(token, (int)i)) - 1ull);
+    };
+    uint64_t a_draws = 0;      // draws that took the a-part
+    uint32_t start = 0;
+    while (start < n_draws) {
+        // Rounds of DEPTH draws, every step of them run also past the last
+        // draw (those records change nothing): an exit inside a round would
+        // meet the loop's end and make its first step wait for every load.
+#pragma unroll
+        for (int b = 0; b < DEPTH; ++b) {
+            rec[b] = recs[start + b];
+            gather(b);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        uint32_t i0 = start, open = 0;
+        uint64_t moves0 = moves;
+        uint32_t m0[NM];
+#pragma unroll
+        for (int u = 0; u < NM; ++u) m0[u] = m[u];
+        // places of the round's results, and this lane's for no result
+        const uint32_t nowhere = 64u + (uint32_t)g;
+        for (; i0 < n_draws; i0 += DEPTH) {
+            const uint64_t mv = move_draws >> i0;
+            open = 0;
+            moves0 = moves;
+#pragma unroll
+            for (int u = 0; u < NM; ++u) m0[u] = m[u];
+#pragma unroll
+            for (int b = 0; b < DEPTH; ++b) {
+                const uint32_t i = i0 + b;
+                if (mv & (1ull << b)) moves_of_draw(i);
+                const RegRec r = rec[b];
+                float f[SL];
+#pragma unroll
+                for (int u = 0; u < SL; ++u)
+                    f[u] = VALUES ? __uint_as_float(x[b][u]) : (float)__builtin_amdgcn_ubfe(x[b][u], 0u, r.w) * R[u];
+                rec[b] = recs[i + DEPTH];
+                // m^{-i}
+                if (BYTES) {
+                    m[0] -= (uint32_t)g == r.o ? r.io : 0u;
+                } else {
+                    const uint32_t ro = r.o - (uint32_t)e0;
+#pragma unroll
+                    for (int u = 0; u < NM; ++u) m[u] -= ro == (uint32_t)u ? 1u : 0u;
+                }
+                if constexpr (STATS) {
+                    const int32_t n = count();
+                    if ((uint32_t)g == i) d.kd_draw = n;
+                }
+                float cs[SL];
+                cs[0] = f[0] * (float)at(0);
+#pragma unroll
+                for (int u = 1; u < SL; ++u) cs[u] = cs[u - 1] + f[u] * (float)at(u);
+                const float incl = group_scan_incl_f32<64>(cs[SL - 1]);
+                const float T = group_last_f32<64>(incl);
+                gather(b);
+                const float Z = r.saf + T;
+                const float y = r.u0 * Z - r.saf;
+                const float tol = Z * ((float)(64 + 8 * SL) * 0x1p-24f);
+                const bool is_a = y < -tol;
+                // y relative to the lane's slots; how far it is from every
+                // boundary of them, negative outside; the first slot whose
+                // running sum passes it
+                const float yl = y - (incl - cs[SL - 1]);
+                float near = fminf(yl, cs[SL - 1] - yl);
+                uint32_t n = 0;
+#pragma unroll
+                for (int u = 0; u + 1 < SL; ++u) {
+                    near = fminf(near, fabsf(cs[u] - yl));
+                    n += cs[u] <= yl ? 1u : 0u;
+                }
+                const bool mine = near > tol;
+                // the a-part's slot gains the token, or this lane's slot n
+                if (BYTES) {
+                    const uint32_t ga = (uint32_t)g == r.a ? r.ia : 0u;
+                    const uint32_t gb = mine ? 1u << (8u * n) : 0u;
+                    m[0] += is_a ? ga : gb;
+                } else {
+                    const uint32_t gain = is_a ? r.a - (uint32_t)e0 : (mine ? n : REG_NONE);
+#pragma unroll
+                    for (int u = 0; u < NM; ++u) m[u] += gain == (uint32_t)u ? 1u : 0u;
+                }
+                S.out[mine ? i : nowhere] = (uint16_t)((uint32_t)e0 + n);
+                const uint64_t in_a = __builtin_amdgcn_ballot_w64(is_a), in_b = __builtin_amdgcn_ballot_w64(mine);
+                open |= (in_a | in_b) == 0 ? 1u << b : 0u;
+                if constexpr (STATS) a_draws |= in_a & (i < n_draws ? 1ull << i : 0ull);
+            }
+            if (__builtin_expect(open != 0, 0)) break;
+        }
+        if (__builtin_expect(open == 0, 1)) break;
+        // a draw of this round is too close to a boundary for fp32: the round
+        // again up to it, in fp64 from the counts in LDS (the draws before it
+        // give what they gave)
+        moves = moves0;
+#pragma unroll
+        for (int u = 0; u < NM; ++u) m[u] = m0[u];
+        const uint32_t end = i0 + (uint32_t)__builtin_ctz(open) + 1;
+        for (uint32_t i = i0; i < end; ++i) {
+            if ((move_draws >> i) & 1ull) moves_of_draw(i);
+            const int c = __builtin_amdgcn_readlane(token, (int)i);
+            const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)po_pa, c);
+            add((int32_t)(w & 0xFFFFu), false);
+            if constexpr (STATS) {
+                const int32_t n = count();
+                if ((uint32_t)g == i) d.kd_draw = n;
+            }
+            store(false);
+            double Zd;
+            int32_t to = slots_draw_f64<64, false>(
+                M, S, __builtin_amdgcn_readlane(t.v, c), recs[i].u0, SL,
+                [&](int32_t, int32_t k) { return count_of(S, k); }, Zd);
+            lds_order();
+            a_draws &= ~(1ull << i);
+            if (to < 0) {
+                to = (int32_t)(w >> 16);
+                a_draws |= 1ull << i;
+            }
+            if (g == 0) S.out[i] = (uint16_t)to;
+            if (g == c && i + 1 == end) d.fb = 1;
+            add(to, true);
+            lds_order();
+        }
+        start = end;
+    }
+    move_before(~0ull);
+    store(true);
+    if constexpr (STATS) {
+        S.nz = count();
+        d.a_draws = a_draws;
+    }
 }
 
 // the block's draws in the dense layout (fp64 over the word's column)
-template <int G, bool STATS>
+template <int G>
 __device__ __forceinline__ void draw_dense(const DevModel &M, const SlotDoc &S, const int32_t v, LaneDraw &d,
                                            const uint32_t n_max, const int g)
 {
-    for (uint32_t i = 0; i < n_max; ++i) {
-        move_segment<STATS>(S, d, i);
-        const DrawRec rec = S.tok[i];
-        const int c = (int)(rec.uc & 127u);
-        if (g == c) {
-            const float was = lds_add(&S.ms[d.po], -1.0f);
-            if (STATS) d.ro = was;
+    // one token leaves or enters topic k (one lane of the group); the count before
+    auto change = [&](int32_t k, int by) {
+        const uint32_t was = count_of(S, k);
+        set_count(S, k, was + (uint32_t)by);
+        return (float)was;
+    };
+    auto moves = [&](uint32_t i) {
+        for (uint32_t t = i << 7; __builtin_amdgcn_ballot_w64(d.key == t) != 0; ++t) {
+            if (d.key == t) {
+                d.ro = change(d.po, -1);
+                d.rn = change(d.pa, 1);
+            }
+            lds_order();
         }
+    };
+    for (uint32_t i = 0; i < n_max; ++i) {
+        moves(i);
+        const DrawRec rec = S.tok[i];
+        const int c = rec.lane();
+        if (g == c) d.ro = change(d.po, -1);
         lds_order();
         double Z;
         const int32_t vc = __shfl(v, c & (G - 1), G);
-        const int32_t at = slots_draw_f64<G, true>(M, S, vc, (float)(rec.uc >> 8) * 0x1p-24f, 0, Z);
+        const int32_t at =
+            slots_draw_f64<G, true>(M, S, vc, rec.u0, 0, [&](int32_t, int32_t k) { return count_of(S, k); }, Z);
         if (c < G) {
             if (at >= 0) {
                 if (g == 0) {
-                    (void)lds_add(&S.ms[at], 1.0f);
-                    S.out[c] = (uint16_t)at;
+                    (void)change(at, 1);
+                    S.out[i] = (uint16_t)at;
                 }
             } else if (g == c) {
-                const float was = lds_add(&S.ms[d.pa], 1.0f);
-                if (STATS) d.rn = was;
+                d.rn = change(d.pa, 1);
                 d.a = 1;
             }
         }
         lds_order();
     }
-    move_segment<STATS>(S, d, n_max);
+    moves(n_max);
+}
+
+// the block's records, in draw order, the lanes without a draw behind them
+template <int G>
+__device__ __forceinline__ void stage_draws(const SlotDoc &S, const LaneTok &x, const LaneDraw &d, bool draw,
+                                            uint32_t place, int g)
+{
+    DrawRec rec;
+    rec.row = draw ? x.row : 0u;
+    rec.u0 = draw ? x.u0 : 0.0f;
+    rec.saf = draw ? x.saf : REC_NONE_SA;
+    rec.w = draw ? (x.fmt | ((uint32_t)g << 2)) : REC_NONE;
+    S.tok[place] = rec;
+    if (g < 2) {
+        DrawRec none = {0u, 0.0f, REC_NONE_SA, REC_NONE};
+        S.tok[G + g] = none;
+    }
+    lds_order();
 }
 
 // Draw a block of tokens, lane g's token x of old topic kold (valid: the
-// lane has one), after slots_layout; returns the lane's new topic.  The
+// lane has one), after slots_layout (bytes: no count can pass
+// 255); returns the lane's new topic.  The
 // group's lanes are converged.
 template <int G, bool STATS, bool BIG>
 __device__ __forceinline__ int32_t draw_block(const DevModel &M, SlotDoc &S, const SlotLds &A, const float *Rf,
-                                              const LaneTok &x, int32_t kold, bool valid, ZStat &st, const int g)
+                                              const LaneTok &x, int32_t kold, bool valid, bool bytes, ZStat &st,
+                                              const int g)
 {
     const bool draws = valid && !x.sure;
     const uint64_t db = group_ballot<G>(draws);
     const uint64_t below = (1ull << g) - 1ull;
     const uint32_t before = (uint32_t)__builtin_popcountll(db & below);
     const uint32_t nd = (uint32_t)__builtin_popcountll(db);
-    // records in draw order, the lanes without a draw behind them
-    DrawRec rec;
-    rec.row = draws ? x.row : 0u;
-    rec.uc = draws ? (x.uc | (uint32_t)g) : REC_NONE;
-    rec.saf = draws ? x.saf : 1.0f;
-    rec.pad = 0;
-    S.tok[draws ? before : nd + (uint32_t)g - before] = rec;
-    if (g < 2) {
-        DrawRec none = {0u, REC_NONE, 1.0f, 0u};
-        S.tok[G + g] = none;
-    }
     LaneDraw d;
     d.po = valid ? slot_of(S, A, kold) : 0;
     d.pa = valid ? slot_of(S, A, x.ka) : 0;
     d.key = 0xFFFFFFFFu;
     const bool moves = valid && x.sure && x.kv > 0;
-    {
-        // rank among the segment's tokens decided at staging (tokens of an
-        // empty column keep their topic: no move)
-        const uint64_t mb = group_ballot<G>(moves);
-        const uint64_t prev = db & below;
-        const uint64_t seg = prev ? below & ~((2ull << (63 - __builtin_clzll(prev))) - 1ull) : below;
-        if (moves) d.key = (before << 7) | (uint32_t)__builtin_popcountll(mb & seg);
-    }
+    // rank among the segment's tokens decided at staging (tokens of an empty
+    // column keep their topic: no move)
+    const uint64_t mb = group_ballot<G>(moves);
+    const uint64_t prev = db & below;
+    const uint64_t seg = prev ? below & ~((2ull << (63 - __builtin_clzll(prev))) - 1ull) : below;
+    if (moves) d.key = (before << 7) | (uint32_t)__builtin_popcountll(mb & seg);
     d.ro = 2.0f;
     d.rn = 1.0f;
+    d.kd = 0;
+    d.kd_draw = 0;
+    d.a_draws = 0;
     d.a = moves ? 1u : 0u;
     d.fb = 0;
-    if (valid) S.out[g] = (uint16_t)d.pa;
+    // draws in order, the lanes without one behind them; the drawn slots'
+    // places start as the a-part's
+    const uint32_t place = draws ? before : nd + (uint32_t)g - before;
+    S.out[place] = (uint16_t)d.pa;
     lds_order();
     // the wave's largest number of draws (scalar: the ballot's fields)
     const uint64_t all = __builtin_amdgcn_ballot_w64(draws);
@@ -1512,38 +1844,75 @@ __device__ __forceinline__ int32_t draw_block(const DevModel &M, SlotDoc &S, con
         n_max = n > n_max ? n : n_max;
     }
     auto over = [&](int sl) { return __builtin_amdgcn_ballot_w64(S.L > sl * G) != 0; };
-    if (!over(1)) draw_slots<G, 1, STATS>(M, S, Rf, x.v, d, n_max, g);
-    else if (!over(2)) draw_slots<G, 2, STATS>(M, S, Rf, x.v, d, n_max, g);
-    else if (!over(3)) draw_slots<G, 3, STATS>(M, S, Rf, x.v, d, n_max, g);
-    else if (!over(4)) draw_slots<G, 4, STATS>(M, S, Rf, x.v, d, n_max, g);
-    else if (!over(5)) draw_slots<G, 5, STATS>(M, S, Rf, x.v, d, n_max, g);
-    else if (!BIG || !over(6)) draw_slots<G, 6, STATS>(M, S, Rf, x.v, d, n_max, g);
-    else if constexpr (BIG) {
-        if (S.dense) draw_dense<G, STATS>(M, S, x.v, d, n_max, g);
-        else if (!over(8)) draw_slots<G, 8, STATS>(M, S, Rf, x.v, d, n_max, g);
-        else if (!over(10)) draw_slots<G, 10, STATS>(M, S, Rf, x.v, d, n_max, g);
-        else if (!over(12)) draw_slots<G, 12, STATS>(M, S, Rf, x.v, d, n_max, g);
-        else draw_slots<G, 16, STATS>(M, S, Rf, x.v, d, n_max, g);
+    // (64 lanes: the draws that have moves before them, in draw order)
+    uint64_t mv_draws = 0;
+    if constexpr (G == 64) {
+        const int first = draws && (mb & seg) != 0 ? 1 : 0;
+        mv_draws = __builtin_amdgcn_ballot_w64(__builtin_amdgcn_ds_permute((int)place << 2, first) != 0);
     }
+    bool regs = false;
+#define PULDA_REGS(SL_, V_, B_) draw_regs<SL_, STATS, V_, B_>(M, S, Rf, x, draws, place, mb, mv_draws, nd, d, g)
+#define PULDA_DRAW(SL_)                                                                            \
+    do {                                                                                           \
+        if constexpr (G == 64) {                                                \
+            if (SL_ <= 4 && bytes) {                                                               \
+                if (M.values) PULDA_REGS(SL_, true, SL_ <= 4);                                     \
+                else PULDA_REGS(SL_, false, SL_ <= 4);                                             \
+            } else {                                                                               \
+                if (M.values) PULDA_REGS(SL_, true, false);                                        \
+                else PULDA_REGS(SL_, false, false);                                                \
+            }                                                                                      \
+            regs = true;                                                                           \
+        } else {                                                                                   \
+            stage_draws<G>(S, x, d, draws, place, g);                                              \
+            if (M.values) draw_slots<G, SL_, STATS, true>(M, S, Rf, x.v, d, n_max, g);             \
+            else draw_slots<G, SL_, STATS, false>(M, S, Rf, x.v, d, n_max, g);                     \
+        }                                                                                          \
+    } while (0)
+    if (!over(1)) PULDA_DRAW(1);
+    else if (!over(2)) PULDA_DRAW(2);
+    else if (!over(3)) PULDA_DRAW(3);
+    else if (!over(4)) PULDA_DRAW(4);
+    else if (!over(5)) PULDA_DRAW(5);
+    else if (!BIG || !over(6)) PULDA_DRAW(6);
+    else if constexpr (BIG) {
+        if (S.dense) {
+            stage_draws<G>(S, x, d, draws, place, g);
+            draw_dense<G>(M, S, x.v, d, n_max, g);
+        }
+        else if (!over(8)) PULDA_DRAW(8);
+        else if (!over(10)) PULDA_DRAW(10);
+        else if (!over(12)) PULDA_DRAW(12);
+        else PULDA_DRAW(16);
+    }
+#undef PULDA_DRAW
+#undef PULDA_REGS
     lds_order();
     if constexpr (STATS) {
         // J = min(K_d^{-i}, K_v): the topics with a nonzero count when token
         // g was drawn, from the topics that left and entered before it
-        const int32_t left = d.ro == 1.0f ? 1 : 0;
-        const int32_t delta = (d.rn == 0.0f ? 1 : 0) - left;
-        const int32_t incl = group_scan_incl_i32<G>(delta);
-        const int32_t Kd = S.nz + incl - delta - left;
+        int32_t Kd;
+        if (regs) {
+            const int32_t drawn = __shfl(d.kd_draw, (int)before, 64);
+            Kd = draws ? drawn : d.kd;
+            if (draws) d.a = (uint32_t)((d.a_draws >> before) & 1ull);
+        } else {
+            const int32_t left = d.ro == 1.0f ? 1 : 0;
+            const int32_t delta = (d.rn == 0.0f ? 1 : 0) - left;
+            const int32_t incl = group_scan_incl_i32<G>(delta);
+            Kd = S.nz + incl - delta - left;
+            S.nz += group_bcast<G>(incl, G - 1);
+        }
         if (valid && x.kv > 0) {
             const uint32_t j = (uint32_t)(Kd < x.kv ? Kd : x.kv);
             st.j += j;
             if (draws) st.jb += j;
         }
-        S.nz += group_bcast<G>(incl, G - 1);
         st.a += d.a;
         st.fb += d.fb;
         st.deg += valid && x.kv == 0 ? 1u : 0u;
     }
-    return valid ? topic_of(S, S.out[g]) : 0;
+    return valid ? topic_of(S, draws ? S.out[place] : d.pa) : 0;
 }
 
 // HOT: the frequent words' count increments go to the block's counters in
@@ -1567,9 +1936,7 @@ __device__ __forceinline__ void z_step_item(const ZArgs &a, const WorkItem &w, c
             if (a.ll_doc && g == 0) a.ll_doc[d] = 0.0;
             continue;
         }
-        slots_clear<G>(S, A, g);
-        slots_mark_tokens<G>(S, a.c.z, s, e, g);
-        slots_count_topics<G>(S, A, g);
+        slots_load<G, true>(S, A, a.c.z, s, e, g);
         for (int64_t i0 = s; i0 < e; i0 += G) {
             const int64_t i = i0 + g;
             const bool valid = i < e;
@@ -1583,9 +1950,8 @@ __device__ __forceinline__ void z_step_item(const ZArgs &a, const WorkItem &w, c
                 const r4 r = philox((uint32_t)i, (uint32_t)((uint64_t)i >> 32), t, TAG_Z, M.key0, M.key1);
                 x = stage_token(M, wv, zo, r, (int32_t)(e - s));
             }
-            slots_layout<G, BIG>(S, A, M.K, i0 == s, valid, x.ka, g);
-            if (i0 == s) slots_add_tokens<G>(S, A, a.c.z, s, e, g);
-            const int32_t znew = draw_block<G, true, BIG>(M, S, A, R, x, zo, valid, st, g);
+            slots_layout<G, BIG>(S, A, M.K, valid, x.ka, g);
+            const int32_t znew = draw_block<G, true, BIG>(M, S, A, R, x, zo, valid, e - s < 256, st, g);
             // the count rebuild: each lane adds its own token, once the
             // block's draws are done (a frequent word's into the block's
             // counters in LDS, added to n when the kernel ends)
@@ -1600,7 +1966,7 @@ __device__ __forceinline__ void z_step_item(const ZArgs &a, const WorkItem &w, c
             // the document's term of log p(z | alpha) for its final counts:
             // lgamma(A) - lgamma(N_d + A) + sum_k [lgamma(m_k + alpha) - lgamma(alpha)]
             double part = 0.0;
-            for (int32_t j = g; j < S.L; j += G) part += M.lg_alpha[(int32_t)S.ms[j]];
+            for (int32_t j = g; j < S.L; j += G) part += M.lg_alpha[count_of(S, topic_of(S, j))];
             const double tot = group_bcast_f64<G>(group_scan_incl<G>(part), G - 1);
             if (g == 0) a.ll_doc[d] = tot + M.lg_A[e - s];
         }
@@ -1977,7 +2343,7 @@ hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, 
         return hipGetLastError();
     }
 #define PULDA_Z(G_)                                                                                    \
-    (a.lds.ms_n > SLOTS_FEW * G_ ? launch(z_step_kernel<G_, true, false>, z_step_kernel<G_, true, true>) \
+    (a.lds.slots > SLOTS_FEW ? launch(z_step_kernel<G_, true, false>, z_step_kernel<G_, true, true>) \
                                  : launch(z_step_kernel<G_, false, false>, z_step_kernel<G_, false, true>))
     if (group == 64) return PULDA_Z(64);
     if (group == 32) return PULDA_Z(32);
@@ -2228,7 +2594,7 @@ __global__ void import_phi_kernel(DevModel m, const int64_t *colptr64, const uin
         const float y = __shfl_xor(fmax, o, 64);
         fmax = y > fmax ? y : fmax;
     }
-    if (lane == 0) m.phimax[v] = b > a ? -fmax : fmax;
+    if (lane == 0) m.phimax[v] = __float_as_uint(fmax) | (ROW_32 << 30);
 }
 
 hipError_t launch_import_phi(const DevModel &m, const int64_t *colptr64, const uint16_t *topic, const float *phi_e,
@@ -2371,15 +2737,19 @@ __device__ __forceinline__ void foldin_slot(const DevModel &M, const DevFoldin &
         int32_t run = 0;
         for (int32_t p0 = 0; p0 < sl.len; p0 += G) {
             const int32_t p = p0 + g;
+            int32_t v = -1;
             bool keep = false;
             if (p < sl.len) {
-                const int32_t v = wds[p];
+                v = wds[p];
                 keep = v >= 0 && v < M.V && M.colptr[v + 1] > M.colptr[v];
             }
             const uint64_t bal = group_ballot<G>(keep);
             if (keep) {
+                // (the kept words move up in place: q <= p, and this block's
+                // words have been read)
                 const int32_t q = run + __builtin_popcountll(bal & ((1ull << g) - 1ull));
                 pos[q] = p;
+                wds[q] = v;
                 const r4 r = philox((uint32_t)p, sl.req, 0u, TAG_FOLDIN_INIT, F.key0, F.key1);
                 zz[q] = (uint16_t)scale32(r.x, (uint32_t)K);
             }
@@ -2401,9 +2771,7 @@ __device__ __forceinline__ void foldin_slot(const DevModel &M, const DevFoldin &
         // collected it): its results stay as they are
         if (done >= F.sweeps) return;
     }
-    slots_clear<G>(S, A, g);
-    slots_mark_tokens<G>(S, zz, 0, kept, g);
-    bool first = true;
+    slots_load<G, false>(S, A, zz, 0, kept, g);
     ZStat st;
     int32_t budget = sl.budget;
     while (budget > 0 && done < F.sweeps) {
@@ -2418,12 +2786,10 @@ __device__ __forceinline__ void foldin_slot(const DevModel &M, const DevFoldin &
                 const int32_t p = pos[q];
                 zo = zz[q];
                 const r4 r = philox((uint32_t)p, sl.req, (uint32_t)s, TAG_FOLDIN_Z, F.key0, F.key1);
-                x = stage_token(M, wds[p], zo, r, kept);
+                x = stage_token(M, wds[q], zo, r, kept);
             }
-            slots_layout<G, true>(S, A, K, first, valid, x.ka, g);
-            if (first) slots_add_tokens<G>(S, A, zz, 0, kept, g);
-            first = false;
-            const int32_t znew = draw_block<G, false, true>(M, S, A, Rf, x, zo, valid, st, g);
+            slots_layout<G, true>(S, A, K, valid, x.ka, g);
+            const int32_t znew = draw_block<G, false, true>(M, S, A, Rf, x, zo, valid, kept < 256, st, g);
             if (valid) zz[q] = (uint16_t)znew;
         }
         budget -= t1 - next;
@@ -2432,8 +2798,9 @@ __device__ __forceinline__ void foldin_slot(const DevModel &M, const DevFoldin &
             // the sweep is complete
             if (s > F.burn_in) {
                 for (int32_t j = g; j < S.L; j += G) {
-                    const uint32_t c = (uint32_t)S.ms[j];
-                    if (c) atomicAdd(&acc[topic_of(S, j)], c);
+                    const int32_t k = topic_of(S, j);
+                    const uint32_t c = count_of(S, k);
+                    if (c) atomicAdd(&acc[k], c);
                 }
             }
             done = s;
@@ -2451,10 +2818,10 @@ __device__ __forceinline__ void foldin_slot(const DevModel &M, const DevFoldin &
         for (int32_t k = g; k < K; k += G)
             F.theta[(int64_t)sid * K + k] = (float)(((double)acc[k] / ns + M.alpha[k]) / denom);
         double part = 0.0;
-        for (int32_t q = g; q < kept; q += G) part += log((double)M.phid[(int64_t)wds[pos[q]] * K + zz[q]]);
+        for (int32_t q = g; q < kept; q += G) part += log((double)M.phid[(int64_t)wds[q] * K + zz[q]]);
         // (topics in a fixed order, whatever the slots)
         for (int32_t k = g; k < K; k += G) {
-            const int32_t c = count_of(S, A, k);
+            const int32_t c = (int32_t)count_of(S, k);
             if (c > 0) {
                 if constexpr (SYM) part += M.lg_alpha[c];
                 else part += lgamma((double)c + M.alpha[k]) - lgamma(M.alpha[k]);
@@ -2566,7 +2933,7 @@ __device__ __forceinline__ void ltr_particle(const DevModel &M, const DevHeldout
     }
     if (r == 0 && g == 0) H.kept[d] = nk;
     __threadfence();
-    slots_clear<G>(S, A, g);
+    slots_load<G, false>(S, A, zz, 0, 0, g);
     ZStat st;
     for (int32_t n = 0; n < nk; ++n) {
         // redraw z_0 .. z_{n-1} in order, then draw z_n: blocks of G tokens,
@@ -2582,24 +2949,26 @@ __device__ __forceinline__ void ltr_particle(const DevModel &M, const DevHeldout
                 const r4 rr = philox((uint32_t)q, (uint32_t)n, req, tag, H.key0, H.key1);
                 x = stage_token(M, kw[q], zo, rr, redraw ? n : 0);
             }
-            // (the first block: no counts yet)
-            slots_layout<G, true>(S, A, M.K, n == 0, q <= n, x.ka, g);
-            int32_t znew = draw_block<G, false, true>(M, S, A, Rf, x, zo, redraw, st, g);
+            slots_layout<G, true>(S, A, M.K, q <= n, x.ka, g);
+            int32_t znew = draw_block<G, false, true>(M, S, A, Rf, x, zo, redraw, nk < 256, st, g);
             if (n - q0 < G) {
                 // the new token, from the counts of z_<n in fp64 (its Z)
                 const int c = n - q0;
                 const int32_t v = group_bcast<G>(x.v, c);
-                const float u0 = (float)((uint32_t)group_bcast<G>((int)x.uc, c) >> 8) * 0x1p-24f;
+                const float u0 = __int_as_float(group_bcast<G>(__float_as_int(x.u0), c));
                 const int32_t ka = group_bcast<G>(x.ka, c);
                 double Z;
-                int32_t at = S.dense ? slots_draw_f64<G, true>(M, S, v, u0, 0, Z)
-                                     : slots_draw_f64<G, false>(M, S, v, u0, (S.L + G - 1) / G, Z);
-                if (at < 0) at = slot_of(S, A, ka);
+                auto count = [&](int32_t, int32_t k) { return count_of(S, k); };
+                const int32_t at = S.dense ? slots_draw_f64<G, true>(M, S, v, u0, 0, count, Z)
+                                           : slots_draw_f64<G, false>(M, S, v, u0, (S.L + G - 1) / G, count, Z);
+                const int32_t k = at < 0 ? ka : topic_of(S, at);
                 if (g == 0) {
-                    (void)lds_add(&S.ms[at], 1.0f);
+                    // (its bit may have been dropped with the block's counts)
+                    set_count(S, k, count_of(S, k) + 1);
+                    S.P[k >> 5] |= 1u << (k & 31);
                     Zs[n] = Z;
                 }
-                if (g == c) znew = topic_of(S, at);
+                if (g == c) znew = k;
                 lds_order();
             }
             if (q <= n) zz[q] = (uint16_t)znew;
