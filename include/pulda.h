@@ -280,8 +280,9 @@ pulda_status pulda_set_timing(pulda_plan *plan, int32_t enable);
 /* z-step schedule: documents are ordered by decreasing length and split
  * into n_buckets length buckets; bucket b holds documents with length >=
  * min_len[b] (min_len decreasing, last 0) and is processed by groups of
- * group[b] lanes (1, 8, 16, 32 or 64) with docs_per_item[b] documents per
- * work item (a multiple of 64 / group).  Group 1 runs one document per lane
+ * group[b] lanes (1, 8, 16, 32 or 64) with at most docs_per_item[b] documents
+ * per work item (a multiple of 64 / group; fewer where the bucket would
+ * otherwise leave part of the chip idle).  Group 1 runs one document per lane
  * (its b-sum is the sequential ascending sum) and takes documents shorter
  * than 128 tokens (256 when K <= 127); groups of 8 take documents shorter than 256
  * tokens; a
