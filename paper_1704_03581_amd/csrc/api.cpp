@@ -144,7 +144,7 @@ struct pulda_plan {
     uint8_t *ws = nullptr;
     int64_t ws_need = 0;
     struct {
-        int64_t z, n, gam, phid, g16, g8, Rd, gamd, Sd, dpart, phimax, wrec, hot, hot_word, beta_v, ztp, ztp_off, ckg, colcnt, colptr, ctopic, cphi, calias, sigma_a, S, nk, alpha, pois, pois_off,
+        int64_t z, n, gam, phid, g16, g8, Rd, gamd, Sd, dpart, phimax, wrec, hot, hot_word, beta_v, ztp, ztp_off, longcol, colcnt, colptr, ctopic, cphi, calias, sigma_a, S, nk, alpha, pois, pois_off,
             doc_order, items, queue, stats, ll_part, ll_out, ll_hist, tptr, err, scratch, cnt_a, ptr_a, cnt_b,
             ptr_b, zsave, lg_beta, lg_alpha, lg_A, ll_doc;
     } off;
@@ -334,7 +334,7 @@ pulda_status pulda_plan_create(const pulda_model_desc *desc, int64_t D, int64_t 
     p->off.colptr = L.take(((int64_t)p->V + 1) * 4);
     p->off.ctopic = L.take(p->cap * 2);
     p->off.cphi = L.take(p->cap * 4);
-    p->off.ckg = L.take(p->cap * 4);
+    p->off.longcol = L.take(((int64_t)p->V + 1) * 4);
     p->off.calias = L.take(p->cap * 8);
     p->off.sigma_a = L.take((int64_t)p->V * 8);
     p->off.beta_v = L.take(p->beta_vh.empty() ? 8 : (int64_t)p->V * 8);
@@ -413,7 +413,7 @@ pulda_status pulda_plan_bind(pulda_plan *p, void *workspace_dev, int64_t bytes)
     m.Sd = (double *)(w + p->off.Sd);
     m.dpart = (double *)(w + p->off.dpart);
     m.phi_method = 0;
-    m.ckg = (uint32_t *)(w + p->off.ckg);
+    m.longcol = (int32_t *)(w + p->off.longcol);
     m.colcnt = (int32_t *)(w + p->off.colcnt);
     m.colptr = (int32_t *)(w + p->off.colptr);
     m.ctopic = (uint16_t *)(w + p->off.ctopic);
@@ -716,8 +716,8 @@ static pulda_status enqueue_phi(pulda_plan *p, hipStream_t s)
     if (p->timing) HIP_TRY(phase_event(p, s, &a));
     p->m.phi_method = p->phi_method;
     p->m.values = p->phi_method == PULDA_PHI_DIRICHLET;
-    if (p->phi_method == PULDA_PHI_DIRICHLET) HIP_TRY(launch_phi_step_dirichlet(p->m, p->stats, s));
-    else HIP_TRY(launch_phi_step(p->m, p->stats, s));
+    if (p->phi_method == PULDA_PHI_DIRICHLET) HIP_TRY(launch_phi_step_dirichlet(p->m, p->stats, p->n_cu, s));
+    else HIP_TRY(launch_phi_step(p->m, p->stats, p->n_cu, s));
     if (p->timing) {
         HIP_TRY(phase_event(p, s, &b));
         p->ev_phi.push_back({a, b});

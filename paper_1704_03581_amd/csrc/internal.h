@@ -18,25 +18,26 @@ struct DevModel {
     int32_t *n;
     unsigned long long *nk;       // [K]
     // Phi-step
-    int32_t *gam;                 // [V*K] Poisson draws, word-major dense
     unsigned long long *S;        // [K] row sums
-    float *phid;                  // [V*K] dense phi, word-major
-    // 16-bit copy of gam for the z-step's document-side gathers, word-major
-    // with row stride ks16 (K rounded up to 64: 128-byte aligned rows).
-    // phi_kv is recovered as fp32(gam_kv * R_k) with R_k = RN64(1 / S_k):
-    // for gam < 2^16 and S_k < 2^27 no fp32 rounding midpoint lies within
-    // the product's error of gam / S_k, so this equals fp32(RN64(gam / S_k))
-    // bit for bit.  Every other nonzero cell (gam >= 0xFFFF, S_k >= 2^27, or
-    // a Phi loaded from values) holds 0xFFFF and is read from phid.
-    uint16_t *g16;
+    // The urn's draws gamma_kv, word-major: each word's row is in one of
+    // three tables, the narrowest that holds its largest draw, and only there
+    // (format ROW_8, ROW_16 or ROW_32 in the word's record): row stride K in
+    // gam, ks16 (K rounded up to 64: aligned rows) in the others.  phi_kv is
+    // fp32(RN64(gamma_kv / S_k)); fp32(gamma_kv * R_k) with
+    // R_k = RN64(1 / S_k) equals it bit for bit for gamma < 2^16 and
+    // S_k < 2^27, where no fp32 rounding midpoint lies within the product's
+    // error of the quotient.
+    int32_t *gam;                 // [V*K]
+    uint16_t *g16;                // [V*ks16]
+    uint8_t *g8;                  // [V*ks16]
     int32_t ks16;
-    // the low bytes of the draws, row stride ks16 (meaningful for words of
-    // format ROW_8), and the byte offsets of g16 and g8 from gam (32-bit; 0:
-    // the tables span more than 4 GiB and every word is ROW_32)
-    uint8_t *g8;
+    // the byte offsets of g16 and g8 from gam (32-bit; 0: the tables span
+    // more than 4 GiB and every word is ROW_32)
     uint32_t row16, row8;
-    // Phi has no integer draws: the rows are phid's fp32 values
+    // Phi has no integer draws (Algorithm 1's, or one loaded as values): the
+    // rows are phid's fp32 values, format ROW_32
     int32_t values;
+    float *phid;                  // [V*K]
     double *Rd;                   // [K] RN64(1 / S_k) (0 for an empty row)
     // Algorithm 1's Phi-step (phi_k ~ Dir(n_k + beta)): Gamma draws
     // (word-major dense, fp64), their row sums, and per-block partial sums
@@ -45,14 +46,14 @@ struct DevModel {
     double *dpart;                // [ceil(V / ROWSUM_COLS) * K]
     int32_t phi_method;           // of the last Phi-step: 0 Polya urn, 1 Dirichlet
     int32_t *colcnt;              // [V]
+    int32_t *longcol;             // columns with long alias tables, in order; [V]: their number
     int32_t *colptr;              // [V+1]
     uint16_t *ctopic;             // [cap] CSC by word, ascending topic
     float *cphi;                  // [cap]
-    uint32_t *ckg;                // [cap] topic | 16-bit draw << 16 (as g16)
     uint64_t *calias;             // [cap] thr | topic << 32 | alias_topic << 48
     double *sigma_a;              // [V]
-    // largest phi of each word's column (bits of a float below 2) | row
-    // format << 30
+    // row format << 30 | largest phi of the word's column (bits of a float
+    // below 2; set where the rows are values)
     uint32_t *phimax;             // [V]
     // per word, what a z-step token needs of its word in one 16-byte load:
     // {first CSC entry, column length | row format << 30, fp32(sigma_a),
@@ -194,9 +195,9 @@ hipError_t launch_validate(const DevCorpus &c, int32_t V, int32_t *err, hipStrea
 hipError_t launch_init_z(const DevCorpus &c, int32_t K, uint32_t key0, uint32_t key1, hipStream_t s);
 hipError_t launch_count_rebuild(const DevCorpus &c, const DevModel &m, hipStream_t s);
 hipError_t launch_row_sums(const int32_t *dense, int32_t V, int32_t K, unsigned long long *out, hipStream_t s);
-hipError_t launch_phi_step(const DevModel &m, unsigned long long *stats, hipStream_t s);
+hipError_t launch_phi_step(const DevModel &m, unsigned long long *stats, int32_t n_cu, hipStream_t s);
 // Algorithm 1's Phi-step into the same Phi tables (m.phi_method must be 1)
-hipError_t launch_phi_step_dirichlet(const DevModel &m, unsigned long long *stats, hipStream_t s);
+hipError_t launch_phi_step_dirichlet(const DevModel &m, unsigned long long *stats, int32_t n_cu, hipStream_t s);
 constexpr int32_t ROWSUM_COLS = 256;      // words per block of the row-sum kernels
 // z-step: launch_z_prepare clears n and the Z_QUEUES work queues; then one
 // persistent kernel per work-item class (group size 8 to 64 and count

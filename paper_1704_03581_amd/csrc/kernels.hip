@@ -57,6 +57,30 @@ hipError_t launch_fill_u64(unsigned long long *p, unsigned long long value, int6
     return hipGetLastError();
 }
 
+// LDS accesses of the wave before and after are kept in this order (LDS
+// executes a wave's instructions in order; only the compiler is held)
+__device__ __forceinline__ void lds_order()
+{
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// draw of topic k in word v's row of format fmt (Phi of draws)
+__device__ __forceinline__ uint32_t row_draw(const DevModel &m, uint32_t fmt, int32_t v, int32_t k)
+{
+    if (fmt == ROW_8) return m.g8[(int64_t)v * m.ks16 + k];
+    if (fmt == ROW_16) return m.g16[(int64_t)v * m.ks16 + k];
+    return (uint32_t)m.gam[(int64_t)v * m.K + k];
+}
+
+// phi_kv = fp32(gamma / S_k), the quotient in fp64; or the loaded value
+__device__ __forceinline__ float phi_at(const DevModel &m, int32_t v, int32_t k)
+{
+    if (m.values) return m.phid[(int64_t)v * m.K + k];
+    const uint32_t x = row_draw(m, m.wrec[v].y >> 30, v, k);
+    return x ? (float)((double)x / (double)m.S[k]) : 0.0f;
+}
+
 // ---------------------------------------------------------------------------
 // exclusive scans (three passes: block sums, scan of block sums, add-back)
 // ---------------------------------------------------------------------------
@@ -281,133 +305,327 @@ hipError_t launch_row_sums(const int32_t *dense, int32_t V, int32_t K, unsigned 
 //   zero-count cells draw Pois(beta); the nonzero ones are reached by
 //   geometric jumps (gap = floor(-ln(1-U)/beta)), 64 jumps per round, their
 //   positions by a wave prefix sum of the jump lengths.
+// Most words count few topics, so the counted cells are first listed: the
+// random numbers and table reads then run on full waves, not on the few
+// lanes of each 64 cells (the cells past the tables are listed once more).
+// The draws of a word leave as its narrowest row (8, 16 or 32 bits a topic),
+// the only dense table written; a block adds its words' draws by topic in
+// LDS and writes one row of partial sums for phi_sums_kernel.
+// Measured at V = 141,000, K = 1000 and 738M tokens (the counts are 564 MB):
+// 400 us, from 650 us for cells drawn where they lie and 32-bit rows, plus
+// 140 us for a pass over the draws that added them up.  It is bound by VALU
+// issue (905 instructions a word, half the time: the Philox rounds) and, at
+// 20 waves a CU for the LDS of K topics, by waits for a word's tables; loading
+// the next word's counts ahead gave nothing.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) phi_draw_kernel(DevModel m, int32_t kpad)
+// bytes of LDS per topic: the block's sums, and a wave's draws and list
+constexpr int32_t PHI_SUM_BYTES = 8, PHI_WAVE_BYTES = 6;
+
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) phi_draw_kernel(DevModel m, unsigned long long *part,
+                                                              unsigned long long *stats)
 {
+    extern __shared__ __align__(16) uint8_t phi_lds[];
     const uint32_t t = *m.tptr;
-    extern __shared__ int32_t phi_lds[];
     const int lane = __lane_id();
     const int w = threadIdx.x >> 6;
-    const int32_t v = blockIdx.x * 4 + w;
-    if (v >= m.V) return;
-    int32_t *g = phi_lds + w * kpad;
-    const int32_t K = m.K;
-    const int32_t *ncol = m.n + (int64_t)v * K;
+    const int32_t K = m.K, kpad = m.ks16;
+    unsigned long long *sum = (unsigned long long *)phi_lds;
+    int32_t *g = (int32_t *)(phi_lds + PHI_SUM_BYTES * (size_t)kpad) + w * kpad;
+    uint16_t *lst = (uint16_t *)(phi_lds + (PHI_SUM_BYTES + 4 * WAVES) * (size_t)kpad) + w * kpad;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && stats) stats[ST_EMPTY_ROWS] = 0;
+    for (int32_t k = threadIdx.x; k < K; k += 64 * WAVES) sum[k] = 0;
+    __syncthreads();
     const double two_pi = 6.283185307179586476925286766559;
-    // per-word priors: the tables are of integer rates l and every cell's
-    // Pois(beta_v) part comes from the prior marks below, added to its draw
     const bool vec = m.beta_v != nullptr;
-    const double bv = vec ? m.beta_v[v] : m.beta;
     const double tb = vec ? 0.0 : m.beta;
-    const uint32_t *T = m.ztp_tab + (vec ? m.ztp_off[v] : 0);
-    const int32_t nT = vec ? m.ztp_off[v + 1] - m.ztp_off[v] : m.ztp_n;
+    const uint64_t below = (1ull << lane) - 1ull;
+    auto put = [&](int32_t k, int32_t x) {
+        g[k] = x;
+        if (x > 0) atomicAdd(&sum[k], (unsigned long long)x);
+    };
+    for (int32_t v = blockIdx.x * WAVES + w; v < m.V; v += gridDim.x * WAVES) {
+        const int32_t *ncol = m.n + (int64_t)v * K;
+        // per-word priors: the tables are of integer rates l and every cell's
+        // Pois(beta_v) part comes from the prior marks below, added to its draw
+        const double bv = vec ? m.beta_v[v] : m.beta;
+        const uint32_t *T = m.ztp_tab + (vec ? m.ztp_off[v] : 0);
+        const int32_t nT = vec ? m.ztp_off[v + 1] - m.ztp_off[v] : m.ztp_n;
 
-    // counted cells, PR rounds of 64 cells at a time: the rounds' counts,
-    // then their tables' offsets, then their alias entries are each loaded
-    // for all rounds before any is used, so a column waits for three
-    // dependent loads per PR rounds instead of per round
-    constexpr int PR = 4;
-    for (int32_t kb = 0; kb < K; kb += 64 * PR) {
-        int32_t lv[PR];
+        // the counts, PR rounds of 64 cells in flight; -1 marks a zero-count cell
+        constexpr int PR = 16;
+        int32_t n = 0;
+        for (int32_t kb = 0; kb < kpad; kb += 64 * PR) {
+            int32_t lv[PR];
 #pragma unroll
-        for (int u = 0; u < PR; ++u) {
-            const int32_t k = kb + 64 * u + lane;
-            lv[u] = k < K ? ncol[k] : 0;
-        }
-        int32_t lo[PR], hi[PR];
+            for (int u = 0; u < PR; ++u) {
+                const int32_t k = kb + 64 * u + lane;
+                lv[u] = k < K ? ncol[k] : 0;
+            }
 #pragma unroll
-        for (int u = 0; u < PR; ++u) {
-            const bool tab = lv[u] > 0 && lv[u] <= m.L;
-            lo[u] = tab ? m.pois_off[lv[u]] : 0;
-            hi[u] = tab ? m.pois_off[lv[u] + 1] : 0;
-        }
-        int32_t x[PR];
-        uint32_t jv[PR], ry[PR];
-        uint64_t ev[PR];
-#pragma unroll
-        for (int u = 0; u < PR; ++u) {
-            const int32_t k = kb + 64 * u + lane;
-            const int32_t l = lv[u];
-            x[u] = -1;  // -1 marks a zero-count cell
-            jv[u] = 0;
-            ry[u] = 0;
-            ev[u] = 0;
-            if (l > 0) {
-                const r4 r = philox((uint32_t)v, (uint32_t)k, t, TAG_PHI_CELL, m.key0, m.key1);
-                if (l <= m.L) {
-                    // alias table of rate l: slot j, kept when r.y is below
-                    // its threshold, else its alias
-                    jv[u] = scale32(r.x, (uint32_t)(hi[u] - lo[u]));
-                    ry[u] = r.y;
-                    ev[u] = m.pois[lo[u] + jv[u]];
-                } else {
-                    // rounded Gaussian of mean and variance lambda
-                    const double lam = tb + (double)l;
-                    const double rad = sqrt(-2.0 * log(1.0 - unit53(r.x, r.y)));
-                    const double gz = rad * cos(two_pi * unit53(r.z, r.w));
-                    const double y = floor(lam + sqrt(lam) * gz + 0.5);
-                    x[u] = y > 0.0 ? (int32_t)y : 0;
-                }
+            for (int u = 0; u < PR; ++u) {
+                if (kb + 64 * u >= kpad) break;
+                const int32_t k = kb + 64 * u + lane;
+                g[k] = lv[u] > 0 ? lv[u] : -1;
+                const uint64_t bal = __builtin_amdgcn_ballot_w64(lv[u] > 0);
+                if (lv[u] > 0) lst[n + __builtin_popcountll(bal & below)] = (uint16_t)k;
+                n += __builtin_popcountll(bal);
             }
         }
+        lds_order();
+        // rates with a table, U rounds of 64 cells at a time: their tables'
+        // offsets, then their entries are loaded for all rounds before any is
+        // used.  Slot j of the alias table of rate l, kept when r.y is below
+        // its threshold, else its alias
+        constexpr int U = 4;
+        int32_t far = 0;   // cells past the tables, listed from the front again
+        for (int32_t i0 = 0; i0 < n; i0 += 64 * U) {
+            int32_t kk[U], lo[U], hi[U];
+            bool tab[U], past[U];
+            uint32_t jv[U], ry[U];
+            uint64_t ev[U];
 #pragma unroll
-        for (int u = 0; u < PR; ++u) {
-            const int32_t k = kb + 64 * u + lane;
-            const int32_t l = lv[u];
-            if (l > 0 && l <= m.L) x[u] = (ry[u] < (uint32_t)ev[u]) ? (int32_t)jv[u] : (int32_t)(ev[u] >> 32);
-            if (k < K) g[k] = x[u];
+            for (int u = 0; u < U; ++u) {
+                const int32_t i = i0 + 64 * u + lane;
+                kk[u] = i < n ? lst[i] : 0;
+                const int32_t l = i < n ? g[kk[u]] : 0;
+                tab[u] = l > 0 && l <= m.L;
+                past[u] = l > m.L;
+                lo[u] = tab[u] ? m.pois_off[l] : 0;
+                hi[u] = tab[u] ? m.pois_off[l + 1] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                jv[u] = 0;
+                ry[u] = 0;
+                ev[u] = 0;
+                if (i0 + 64 * u < n) {
+                    const r4 r = philox((uint32_t)v, (uint32_t)kk[u], t, TAG_PHI_CELL, m.key0, m.key1);
+                    jv[u] = scale32(r.x, (uint32_t)(hi[u] - lo[u]));
+                    ry[u] = r.y;
+                    if (tab[u]) ev[u] = m.pois[lo[u] + jv[u]];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (tab[u]) put(kk[u], (ry[u] < (uint32_t)ev[u]) ? (int32_t)jv[u] : (int32_t)(ev[u] >> 32));
+                const uint64_t bal = __builtin_amdgcn_ballot_w64(past[u]);
+                if (past[u]) lst[far + __builtin_popcountll(bal & below)] = (uint16_t)kk[u];
+                far += __builtin_popcountll(bal);
+            }
+            lds_order();
         }
-    }
-    __builtin_amdgcn_wave_barrier();
-
-    long long pos_base = -1;
-    for (uint32_t jb = 0;; jb += 64) {
-        r4 r = philox((uint32_t)v, jb + (uint32_t)lane, t, TAG_PHI_PRIOR, m.key0, m.key1);
-        const double e = -log(1.0 - unit53(r.x, r.y)) / bv;
-        // a jump longer than K ends the column whatever its exact length
-        const double capped = e < (double)K ? floor(e) : (double)K;
-        const int32_t step = 1 + (int32_t)capped;
-        const int32_t incl = group_scan_incl_i32<64>(step);
-        const long long pos = pos_base + incl;
-        if (pos < K) {
-            int32_t *cell = &g[pos];
-            int32_t x = 1;
-            for (int q = 0; q < nT; ++q) x += (r.z >= T[q]) ? 1 : 0;
-            if (*cell == -1) *cell = x;
-            else if (vec) *cell += x;
+        // the others: rounded Gaussian of mean and variance lambda
+        for (int32_t i0 = 0; i0 < far; i0 += 64) {
+            if (i0 + lane < far) {
+                const int32_t k = lst[i0 + lane];
+                const r4 r = philox((uint32_t)v, (uint32_t)k, t, TAG_PHI_CELL, m.key0, m.key1);
+                const double lam = tb + (double)g[k];
+                const double rad = sqrt(-2.0 * log(1.0 - unit53(r.x, r.y)));
+                const double gz = rad * cos(two_pi * unit53(r.z, r.w));
+                const double y = floor(lam + sqrt(lam) * gz + 0.5);
+                put(k, y > 0.0 ? (int32_t)y : 0);
+            }
         }
-        const long long last = pos_base + __builtin_amdgcn_readlane(incl, 63);
-        if (last >= K) break;
-        pos_base = last;
-    }
-    __builtin_amdgcn_wave_barrier();
+        lds_order();
 
-    int32_t cnt = 0;
-    int32_t *gcol = m.gam + (int64_t)v * K;
-    for (int32_t k = lane; k < K; k += 64) {
-        int32_t x = g[k];
-        x = x > 0 ? x : 0;
-        gcol[k] = x;
-        cnt += x > 0;
+        long long pos_base = -1;
+        for (uint32_t jb = 0;; jb += 64) {
+            r4 r = philox((uint32_t)v, jb + (uint32_t)lane, t, TAG_PHI_PRIOR, m.key0, m.key1);
+            const double e = -log(1.0 - unit53(r.x, r.y)) / bv;
+            // a jump longer than K ends the column whatever its exact length
+            const double capped = e < (double)K ? floor(e) : (double)K;
+            const int32_t incl = group_scan_incl_i32<64>(1 + (int32_t)capped);
+            const long long pos = pos_base + incl;
+            if (pos < K) {
+                int32_t *cell = &g[pos];
+                int32_t x = 1;
+                for (int q = 0; q < nT; ++q) x += (r.z >= T[q]) ? 1 : 0;
+                const bool none = *cell == -1;
+                if (none || vec) {
+                    *cell = none ? x : *cell + x;
+                    atomicAdd(&sum[pos], (unsigned long long)x);
+                }
+            }
+            const long long last = pos_base + __builtin_amdgcn_readlane(incl, 63);
+            if (last >= K) break;
+            pos_base = last;
+        }
+        lds_order();
+
+        // the word's largest draw and its nonzeros, then its row, four topics a lane
+        int32_t cnt = 0, xmax = 0;
+        for (int32_t k = 4 * lane; k < kpad; k += 256) {
+            const int4 x = *(const int4 *)&g[k];
+            cnt += (x.x > 0) + (x.y > 0) + (x.z > 0) + (x.w > 0);
+            const int32_t a = x.x > x.y ? x.x : x.y, b = x.z > x.w ? x.z : x.w;
+            const int32_t c = a > b ? a : b;
+            xmax = c > xmax ? c : xmax;
+        }
+        const uint32_t fmt = m.row8 == 0 || __builtin_amdgcn_ballot_w64(xmax >= 0xFFFF) != 0
+                                 ? ROW_32
+                                 : (__builtin_amdgcn_ballot_w64(xmax > 0xFF) != 0 ? ROW_16 : ROW_8);
+        auto row4 = [&](int32_t k) {
+            const int4 x = *(const int4 *)&g[k];
+            return make_uint4(x.x > 0 ? (uint32_t)x.x : 0u, x.y > 0 ? (uint32_t)x.y : 0u, x.z > 0 ? (uint32_t)x.z : 0u,
+                              x.w > 0 ? (uint32_t)x.w : 0u);
+        };
+        if (fmt == ROW_8) {
+            uint8_t *col = m.g8 + (int64_t)v * kpad;
+            for (int32_t k = 4 * lane; k < kpad; k += 256) {
+                const uint4 x = row4(k);
+                *(uint32_t *)&col[k] = x.x | x.y << 8 | x.z << 16 | x.w << 24;
+            }
+        } else if (fmt == ROW_16) {
+            uint16_t *col = m.g16 + (int64_t)v * kpad;
+            for (int32_t k = 4 * lane; k < kpad; k += 256) {
+                const uint4 x = row4(k);
+                *(uint2 *)&col[k] = make_uint2(x.x | x.y << 16, x.z | x.w << 16);
+            }
+        } else {
+            int32_t *col = m.gam + (int64_t)v * K;
+            for (int32_t k = lane; k < K; k += 64) col[k] = g[k] > 0 ? g[k] : 0;
+        }
+        cnt = group_scan_incl_i32<64>(cnt);
+        if (lane == 63) {
+            m.colcnt[v] = cnt;
+            m.phimax[v] = fmt << 30;
+        }
+        lds_order();
     }
-    cnt = group_scan_incl_i32<64>(cnt);
-    if (lane == 63) m.colcnt[v] = cnt;
+    __syncthreads();
+    for (int32_t k = threadIdx.x; k < K; k += 64 * WAVES) part[(int64_t)blockIdx.x * K + k] = sum[k];
 }
 
 // ---------------------------------------------------------------------------
-// Phi-step, part 3: normalise (phi = fp32(gamma / S_k), quotient in fp64),
-// write the dense tables and compact each column into the CSC (one wave per
-// column, no LDS, so many columns are in flight); then build each column's
-// alias table for the a-part (weights alpha_k phi_kv; Vose's construction
-// with FIFO work lists in ascending order; sigma_a = ascending fp64 sum of
-// the weights) from its compacted entries.
-// DIR: Algorithm 1's Phi (fp64 Gamma draws gamd, fp64 row sums Sd): a cell
-// is nonzero when its fp32 phi is normal (>= 2^-126), and every nonzero
-// cell's 16-bit draw is the escape 0xFFFF (its phi is read from phid).
+// Phi-step, part 2: the first sum_blocks' worth of blocks after the scan's add
+// the rows of partial sums (16 topics each, 64 threads to a topic): S_k, 1 /
+// S_k and the empty topics.  The scan's blocks (the first) turn the columns'
+// nonzeros into offsets: each adds up all columns before its own by itself,
+// from L2 (V/2 counts on average, a few microseconds for 141,000 words),
+// which takes one launch instead of three.  It also lists the columns with
+// more than ALIAS_SMALL nonzeros, in order.
+// ---------------------------------------------------------------------------
+constexpr int32_t ALIAS_SMALL = 256;
+constexpr int32_t COLS_TILE = 4096;    // columns per turn of a block, four a thread
+constexpr int32_t COLS_BLOCKS = 64;    // most blocks of the scan
+
+// columns per block of the scan
+static inline int32_t cols_per_block(int32_t V)
+{
+    const int32_t tiles = (V + COLS_TILE - 1) / COLS_TILE;
+    return (tiles + COLS_BLOCKS - 1) / COLS_BLOCKS * COLS_TILE;
+}
+
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
+{
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
+
+__global__ void __launch_bounds__(1024) phi_sums_kernel(DevModel m, int32_t per, int32_t scan_blocks,
+                                                        const unsigned long long *part, int32_t rows,
+                                                        unsigned long long *stats)
+{
+    __shared__ unsigned long long red[1024];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if ((int)blockIdx.x >= scan_blocks) {
+        const int32_t k = ((int)blockIdx.x - scan_blocks) * 16 + (tid & 15);
+        unsigned long long s = 0;
+        if (k < m.K) {
+            int32_t r = tid >> 4;
+            for (; r + 192 < rows; r += 256) {
+                unsigned long long x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = part[(int64_t)(r + 64 * u) * m.K + k];
+                s += (x[0] + x[1]) + (x[2] + x[3]);
+            }
+            for (; r < rows; r += 64) s += part[(int64_t)r * m.K + k];
+        }
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (lane < 16) red[w * 16 + lane] = s;
+        __syncthreads();
+        if (tid < 16 && k < m.K) {
+            s = 0;
+            for (int j = 0; j < 16; ++j) s += red[j * 16 + tid];
+            m.S[k] = s;
+            m.Rd[k] = s ? 1.0 / (double)s : 0.0;
+            if (s == 0 && stats) atomicAdd(&stats[ST_EMPTY_ROWS], 1ull);
+        }
+        return;
+    }
+    // nonzeros in the low 32 bits (fewer than 2^31 in all), long columns in the high
+    auto val = [](int32_t c) {
+        return (unsigned long long)(uint32_t)c | ((unsigned long long)(c > ALIAS_SMALL) << 32);
+    };
+    const int32_t v0 = (int32_t)blockIdx.x * per;
+    const int32_t v1 = v0 + per < m.V ? v0 + per : m.V;
+    unsigned long long t = 0;
+    for (int32_t v = 4 * tid; v < v0; v += 4 * 1024) {
+        const int4 c = *(const int4 *)&m.colcnt[v];   // (v0 is a multiple of four)
+        t += (val(c.x) + val(c.y)) + (val(c.z) + val(c.w));
+    }
+    t = wave_sum_u64(t);
+    if (lane == 0) red[w] = t;
+    __syncthreads();
+    unsigned long long base = 0;
+    for (int j = 0; j < 16; ++j) base += red[j];
+    for (int32_t u0 = v0; u0 < v1; u0 += COLS_TILE) {
+        const int32_t v = u0 + 4 * tid;
+        unsigned long long c[4], own = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            c[u] = v + u < v1 ? val(m.colcnt[v + u]) : 0;
+            own += c[u];
+        }
+        unsigned long long incl = own;
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        __syncthreads();
+        if (lane == 63) red[w] = incl;
+        __syncthreads();
+        unsigned long long at = base + incl - own;
+        for (int j = 0; j < 16; ++j) {
+            at += j < w ? red[j] : 0;
+            base += red[j];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (v + u < v1) {
+                m.colptr[v + u] = (int32_t)(uint32_t)at;
+                if (c[u] >> 32) m.longcol[at >> 32] = v + u;
+            }
+            at += c[u];
+        }
+    }
+    if (v1 == m.V && tid == 0) {
+        m.colptr[m.V] = (int32_t)(uint32_t)base;
+        m.longcol[m.V] = (int32_t)(base >> 32);
+        if (stats) stats[ST_NNZ_PHI] = base & 0xFFFFFFFFull;
+    }
+}
+
+// (rows of partial sums: none for Algorithm 1, which has its own sums)
+static hipError_t launch_phi_sums(const DevModel &m, const unsigned long long *part, int32_t rows,
+                                  unsigned long long *stats, hipStream_t s)
+{
+    const int32_t per = cols_per_block(m.V);
+    const int32_t nb = (m.V + per - 1) / per;
+    phi_sums_kernel<<<nb + (rows ? (m.K + 15) / 16 : 0), 1024, 0, s>>>(m, per, nb, part, rows, stats);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Algorithm 1's Phi: phi = fp32(gamma / S_k), quotient in fp64 of the Gamma
+// draws gamd and the row sums Sd; a cell is nonzero when its fp32 phi is
+// normal (>= 2^-126).  Writes phid and compacts each column into the CSC
+// (one wave per column, no LDS, so many columns are in flight).
 // ---------------------------------------------------------------------------
 constexpr float FP32_MIN_NORMAL = 0x1p-126f;
 
-template <bool DIR>
 __global__ void __launch_bounds__(256) phi_dense_kernel(DevModel m)
 {
     const int32_t v = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -415,104 +633,162 @@ __global__ void __launch_bounds__(256) phi_dense_kernel(DevModel m)
     const int lane = __lane_id();
     const int32_t K = m.K;
     const int32_t cb = m.colptr[v];
-    const int32_t *gcol = m.gam + (int64_t)v * K;
     const double *gdcol = m.gamd + (int64_t)v * K;
     float *pcol = m.phid + (int64_t)v * K;
-    uint16_t *g16col = m.g16 + (int64_t)v * m.ks16;
-    uint8_t *g8col = m.g8 + (int64_t)v * m.ks16;
     int32_t run = 0;
     float fmax = 0.0f;
-    uint32_t xmax = 0;
     // the column's draws are read PB rounds of 64 cells at a time, so that
     // many loads are in flight before the rounds are processed in order
     constexpr int PB = 8;
-    for (int32_t kb = 0; kb < m.ks16; kb += 64 * PB) {
-    int32_t xs[PB];
-    double gs[PB];
+    for (int32_t kb = 0; kb < K; kb += 64 * PB) {
+        double gs[PB];
 #pragma unroll
-    for (int j = 0; j < PB; ++j) {
-        const int32_t k = kb + 64 * j + lane;
-        if constexpr (DIR) gs[j] = k < K ? gdcol[k] : 0.0;
-        else xs[j] = k < K ? gcol[k] : 0;
-    }
+        for (int j = 0; j < PB; ++j) {
+            const int32_t k = kb + 64 * j + lane;
+            gs[j] = k < K ? gdcol[k] : 0.0;
+        }
 #pragma unroll
-    for (int j = 0; j < PB; ++j) {
-        const int32_t k0 = kb + 64 * j;
-        if (k0 >= m.ks16) break;
-        const int32_t k = k0 + lane;
-        float f = 0.0f;
-        uint32_t x16 = 0;
-        bool nz;
-        if constexpr (DIR) {
+        for (int j = 0; j < PB; ++j) {
+            const int32_t k0 = kb + 64 * j;
+            if (k0 >= K) break;
+            const int32_t k = k0 + lane;
+            float f = 0.0f;
             if (k < K && m.Sd[k] > 0.0) {
                 f = (float)(gs[j] / m.Sd[k]);
                 f = f >= FP32_MIN_NORMAL ? f : 0.0f;
             }
-            nz = f > 0.0f;
-            x16 = nz ? 0xFFFFu : 0u;
-        } else {
-            const int32_t x = xs[j];
-            nz = x > 0;
-            if (nz) f = (float)((double)x / (double)m.S[k]);
-            const bool exact = x < 0xFFFF && (k >= K || m.S[k] < (1ull << 27));
-            x16 = exact ? (uint32_t)x : 0xFFFFu;
+            if (k < K) pcol[k] = f;
+            fmax = f > fmax ? f : fmax;
+            const uint64_t bal = __builtin_amdgcn_ballot_w64(f > 0.0f);
+            if (f > 0.0f) {
+                const int32_t e = run + __builtin_popcountll(bal & ((1ull << lane) - 1ull));
+                m.ctopic[cb + e] = (uint16_t)k;
+                m.cphi[cb + e] = f;
+            }
+            run += __builtin_popcountll(bal);
         }
-        if (k < K) pcol[k] = f;
-        fmax = f > fmax ? f : fmax;
-        g16col[k] = (uint16_t)x16;
-        g8col[k] = (uint8_t)x16;
-        xmax = x16 > xmax ? x16 : xmax;
-        const uint64_t bal = __builtin_amdgcn_ballot_w64(nz);
-        if (nz) {
-            const int32_t e = run + __builtin_popcountll(bal & ((1ull << lane) - 1ull));
-            m.ctopic[cb + e] = (uint16_t)k;
-            m.cphi[cb + e] = f;
-            m.ckg[cb + e] = (uint32_t)k | (x16 << 16);
-        }
-        run += __builtin_popcountll(bal);
-    }
     }
     for (int o = 32; o > 0; o >>= 1) {
         const float y = __shfl_xor(fmax, o, 64);
         fmax = y > fmax ? y : fmax;
     }
-    // the narrowest row that holds every draw of the word
-    const uint32_t fmt = __builtin_amdgcn_ballot_w64(xmax == 0xFFFFu) != 0 || m.row8 == 0
-                             ? ROW_32
-                             : (__builtin_amdgcn_ballot_w64(xmax > 0xFFu) != 0 ? ROW_16 : ROW_8);
-    if (lane == 0) m.phimax[v] = __float_as_uint(fmax) | (fmt << 30);
+    if (lane == 0) m.phimax[v] = __float_as_uint(fmax) | (ROW_32 << 30);
 }
 
+// ---------------------------------------------------------------------------
+// Phi-step, part 3: each column of the CSC and its alias table for the a-part
+// (weights alpha_k phi_kv; Vose's construction with FIFO work lists in
+// ascending order; sigma_a = ascending fp64 sum of the weights), and the
+// word's record.  The urn's columns (DIR false) are read from the word's row
+// and compacted in LDS, phi = fp32(gamma / S_k) with the quotient in fp64 on
+// full waves of nonzeros; Algorithm 1's are in the CSC already.
 // Columns with at most ALIAS_SMALL nonzeros: one wave per column, four per
-// block (LDS of ALIAS_SMALL entries each); the others: one column per block
-// with K entries of LDS.  Per entry: a probability (fp64), a work-list
-// entry (u16) and a turn mark (u8), so that many columns' chains run on a
-// CU at once.
-constexpr int32_t ALIAS_SMALL = 256;
-constexpr size_t ALIAS_ENTRY_BYTES = sizeof(double) + sizeof(uint16_t) + sizeof(uint8_t);
-
-template <bool SMALL>
-__global__ void __launch_bounds__(SMALL ? 256 : 64) phi_alias_kernel(DevModel m, int32_t kpad)
+// block (LDS of ALIAS_SMALL entries each); the others: one column at a time
+// per block with K entries of LDS.  Per entry: a probability (fp64), a
+// work-list entry (u16), its topic (u16) and a turn mark (u8), so that many
+// columns' chains run on a CU at once.
+// Bound by the chain of sums of lane 0 (695 VALU instructions for a column of
+// 120 nonzeros).  At V = 141,000, K = 1000: 200 us (short columns) and 125 us
+// (long), from 440 + 155 + 180 us when a pass of its own wrote 14 bytes a
+// cell and every column was launched twice.  The long columns come from the
+// list, as V blocks that mostly return at once cost more than their work.
+// ---------------------------------------------------------------------------
+constexpr size_t alias_entry_bytes(bool dir)
 {
-    extern __shared__ double alias_lds[];
+    return sizeof(double) + (dir ? 1 : 2) * sizeof(uint16_t) + sizeof(uint8_t);
+}
+
+// the nonzeros of a word's row in ascending order, draw << 32 | topic in
+// out; four topics a lane, JB rounds of 256 topics in flight
+template <uint32_t FMT>
+__device__ __forceinline__ void compact_row(const DevModel &m, int32_t v, uint64_t *out)
+{
+    constexpr int JB = 4;
     const int lane = __lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int32_t v = SMALL ? blockIdx.x * 4 + wave : blockIdx.x;
-    if (v >= m.V) return;
+    int32_t run = 0;
+    for (int32_t kb = 0; kb < m.ks16; kb += 256 * JB) {
+        uint32_t x[JB][4];
+#pragma unroll
+        for (int j = 0; j < JB; ++j) {
+            const int32_t k = kb + 256 * j + 4 * lane;
+            const bool in = k < m.ks16;
+            if (FMT == ROW_8) {
+                const uint32_t y = in ? *(const uint32_t *)&m.g8[(int64_t)v * m.ks16 + k] : 0u;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[j][u] = (y >> (8 * u)) & 0xFFu;
+            } else if (FMT == ROW_16) {
+                const uint2 y = in ? *(const uint2 *)&m.g16[(int64_t)v * m.ks16 + k] : make_uint2(0u, 0u);
+                x[j][0] = y.x & 0xFFFFu;
+                x[j][1] = y.x >> 16;
+                x[j][2] = y.y & 0xFFFFu;
+                x[j][3] = y.y >> 16;
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[j][u] = k + u < m.K ? (uint32_t)m.gam[(int64_t)v * m.K + k + u] : 0u;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < JB; ++j) {
+            if (kb + 256 * j >= m.ks16) break;
+            const int32_t k = kb + 256 * j + 4 * lane;
+            const int32_t c = (x[j][0] != 0) + (x[j][1] != 0) + (x[j][2] != 0) + (x[j][3] != 0);
+            const int32_t incl = group_scan_incl_i32<64>(c);
+            int32_t at = run + incl - c;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (x[j][u]) out[at] = ((uint64_t)x[j][u] << 32) | (uint32_t)(k + u);
+                at += x[j][u] != 0;
+            }
+            run += __builtin_amdgcn_readlane(incl, 63);
+        }
+    }
+}
+
+template <bool SMALL, bool DIR>
+__device__ __forceinline__ void phi_column(const DevModel &m, double *alias_lds, int32_t v, int wave, int32_t kpad)
+{
+    const int lane = __lane_id();
     const int32_t cb = m.colptr[v];
     const int32_t nv = m.colptr[v + 1] - cb;
-    if (SMALL ? nv > ALIAS_SMALL : nv <= ALIAS_SMALL) return;
+    if (SMALL && nv > ALIAS_SMALL) return;
+    const uint32_t pm = m.phimax[v];   // row format in the top bits, and Algorithm 1's largest phi
     if (nv == 0) {
-        if (lane == 0) m.sigma_a[v] = 0.0;
+        if (lane == 0) {
+            m.sigma_a[v] = 0.0;
+            m.wrec[v] = make_uint4((uint32_t)cb, pm & ~WREC_LOW, 0u, 0u);
+        }
         return;
     }
     const int32_t cap = SMALL ? ALIAS_SMALL : kpad;
     // this wave's region: cap entries (cap is a multiple of 64, so every
     // region and array stays 8-byte aligned)
-    double *pq = (double *)((uint8_t *)alias_lds + (size_t)wave * cap * ALIAS_ENTRY_BYTES);
+    double *pq = (double *)((uint8_t *)alias_lds + (size_t)wave * cap * alias_entry_bytes(DIR));
     uint16_t *lst = (uint16_t *)(pq + cap);   // small entries from the front, large ones from the back
-    uint8_t *mark = (uint8_t *)(lst + cap);   // 1 at the FIFO steps where the head turned small
-    const uint16_t *ctop = m.ctopic + cb;     // topic of entry e
+    uint16_t *ctop = DIR ? m.ctopic + cb : lst + cap;                   // topic of entry e
+    uint8_t *mark = (uint8_t *)(lst + cap + (DIR ? 0 : cap));           // 1 at the FIFO steps where the head turned small
+    const uint32_t fmt = pm >> 30;
+    if constexpr (!DIR) {
+        if (fmt == ROW_8) compact_row<ROW_8>(m, v, (uint64_t *)pq);
+        else if (fmt == ROW_16) compact_row<ROW_16>(m, v, (uint64_t *)pq);
+        else compact_row<ROW_32>(m, v, (uint64_t *)pq);
+        lds_order();
+    }
+    float fmax = 0.0f;
+    // entry e's weight; the first reader of an entry completes the CSC
+    auto weight = [&](int32_t e) -> double {
+        if constexpr (DIR) {
+            return m.alpha[ctop[e]] * (double)m.cphi[cb + e];
+        } else {
+            const uint64_t xk = ((const uint64_t *)pq)[e];
+            const int32_t k = (int32_t)(uint32_t)xk;
+            const float f = (float)((double)(uint32_t)(xk >> 32) / (double)m.S[k]);
+            fmax = f > fmax ? f : fmax;
+            ctop[e] = (uint16_t)k;
+            m.ctopic[cb + e] = (uint16_t)k;
+            m.cphi[cb + e] = f;
+            return m.alpha[k] * (double)f;
+        }
+    };
     // weights w_e = alpha_k phi_kv in entry order (pq holds them first;
     // each lane also keeps its first MAXC chunks' weights in registers, all
     // chunks' loads issued together)
@@ -523,11 +799,11 @@ __global__ void __launch_bounds__(SMALL ? 256 : 64) phi_alias_kernel(DevModel m,
         const int32_t e = c * 64 + lane;
         wr[c] = 0.0;
         if (e < nv) {
-            wr[c] = m.alpha[ctop[e]] * (double)m.cphi[cb + e];
+            wr[c] = weight(e);
             pq[e] = wr[c];
         }
     }
-    for (int32_t e = MAXC * 64 + lane; e < nv; e += 64) pq[e] = m.alpha[ctop[e]] * (double)m.cphi[cb + e];
+    for (int32_t e = MAXC * 64 + lane; e < nv; e += 64) pq[e] = weight(e);
     for (int32_t e = lane; e < nv; e += 64) mark[e] = 0;
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -652,6 +928,31 @@ __global__ void __launch_bounds__(SMALL ? 256 : 64) phi_alias_kernel(DevModel m,
         const uint64_t k = ctop[sm];
         rec[sm] = 0xFFFFFFFFull | (k << 32) | (k << 48);
     }
+    if constexpr (!DIR) {
+        for (int o = 32; o > 0; o >>= 1) {
+            const float y = __shfl_xor(fmax, o, 64);
+            fmax = y > fmax ? y : fmax;
+        }
+    }
+    if (lane == 0)
+        m.wrec[v] = make_uint4((uint32_t)cb, (uint32_t)nv | (pm & ~WREC_LOW), __float_as_uint((float)s),
+                               DIR ? pm & WREC_LOW : __float_as_uint(fmax));
+    lds_order();
+}
+
+template <bool SMALL, bool DIR>
+__global__ void __launch_bounds__(SMALL ? 256 : 64) phi_alias_kernel(DevModel m)
+{
+    extern __shared__ double alias_lds[];
+    if constexpr (SMALL) {
+        const int wave = threadIdx.x >> 6;
+        const int32_t v = blockIdx.x * 4 + wave;
+        if (v < m.V) phi_column<true, DIR>(m, alias_lds, v, wave, 0);
+    } else {
+        const int32_t n = m.longcol[m.V];
+        for (int32_t i = blockIdx.x; i < n; i += gridDim.x)
+            phi_column<false, DIR>(m, alias_lds, m.longcol[i], 0, m.ks16);
+    }
 }
 
 __global__ void word_records_kernel(DevModel m)
@@ -670,57 +971,51 @@ hipError_t launch_word_records(const DevModel &m, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_phi_fill(const DevModel &m, bool dir, hipStream_t s)
+// columns and their alias tables (dir: Algorithm 1's)
+static hipError_t launch_phi_columns(const DevModel &m, bool dir, int32_t n_cu, hipStream_t s)
 {
-    if (dir) phi_dense_kernel<true><<<(m.V + 3) / 4, 256, 0, s>>>(m);
-    else phi_dense_kernel<false><<<(m.V + 3) / 4, 256, 0, s>>>(m);
+    const size_t lds = 4 * ALIAS_SMALL * alias_entry_bytes(dir);
+    if (dir) phi_alias_kernel<true, true><<<(m.V + 3) / 4, 256, lds, s>>>(m);
+    else phi_alias_kernel<true, false><<<(m.V + 3) / 4, 256, lds, s>>>(m);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int32_t kpad = (m.K + 63) / 64 * 64;
-    phi_alias_kernel<true><<<(m.V + 3) / 4, 256, 4 * ALIAS_SMALL * ALIAS_ENTRY_BYTES, s>>>(m, kpad);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (m.K > ALIAS_SMALL) {
-        phi_alias_kernel<false><<<m.V, 64, (size_t)kpad * ALIAS_ENTRY_BYTES, s>>>(m, kpad);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return launch_word_records(m, s);
+    if (e != hipSuccess || m.K <= ALIAS_SMALL) return e;
+    // as many blocks as the device holds (their number of columns is known
+    // on the device only)
+    const size_t long_lds = (size_t)m.ks16 * alias_entry_bytes(dir);
+    int64_t blocks = (int64_t)(n_cu > 0 ? n_cu : 1) * (int64_t)(LDS_BYTES / long_lds);
+    if (blocks < 1) blocks = 1;
+    if (blocks > m.V) blocks = m.V;
+    if (dir) phi_alias_kernel<false, true><<<(unsigned)blocks, 64, long_lds, s>>>(m);
+    else phi_alias_kernel<false, false><<<(unsigned)blocks, 64, long_lds, s>>>(m);
+    return hipGetLastError();
 }
 
-__global__ void colptr_finish_kernel(const unsigned long long *S, int32_t K, const long long *total,
-                                     unsigned long long *stats, double *Rd)
+hipError_t launch_phi_step(const DevModel &m, unsigned long long *stats, int32_t n_cu, hipStream_t s)
 {
-    if (threadIdx.x == 0 && stats) {
-        stats[ST_NNZ_PHI] = (unsigned long long)*total;
-    }
-    unsigned long long empty = 0;
-    for (int32_t k = threadIdx.x; k < K; k += blockDim.x) {
-        empty += S[k] == 0;
-        Rd[k] = S[k] ? 1.0 / (double)S[k] : 0.0;
-    }
-    for (int o = 32; o > 0; o >>= 1) empty += __shfl_down(empty, o, 64);
-    if ((threadIdx.x & 63) == 0 && empty && stats) atomicAdd(&stats[ST_EMPTY_ROWS], empty);
-}
-
-hipError_t launch_phi_step(const DevModel &m, unsigned long long *stats, hipStream_t s)
-{
-    const int32_t kpad = (m.K + 63) / 64 * 64;
-    phi_draw_kernel<<<(m.V + 3) / 4, 256, 4 * kpad * sizeof(int32_t), s>>>(m, kpad);
-    hipError_t e = hipGetLastError();
+    // the partial sums use the alias records' space, written after them
+    unsigned long long *part = (unsigned long long *)m.calias;
+    auto lds_of = [&](int waves) { return (size_t)m.ks16 * (PHI_SUM_BYTES + PHI_WAVE_BYTES * waves); };
+    int32_t rows = 0;
+    auto draw = [&](auto kernel, int waves) -> hipError_t {
+        // persistent blocks: one row of partial sums each
+        const size_t lds = lds_of(waves);
+        const int64_t fit = (int64_t)(LDS_BYTES / lds), most = 32 / waves;
+        int64_t blocks = (int64_t)(n_cu > 0 ? n_cu : 1) * (fit < most ? fit : most);
+        const int64_t need = ((int64_t)m.V + waves - 1) / waves;
+        if (blocks < 1) blocks = 1;   // (the launch then fails)
+        if (blocks > need) blocks = need;
+        rows = (int32_t)blocks;
+        kernel<<<(unsigned)blocks, 64 * waves, lds, s>>>(m, part, stats);
+        return hipGetLastError();
+    };
+    // four waves to a block, fewer where K topics of LDS leave no room
+    hipError_t e = lds_of(4) <= LDS_BYTES ? draw(phi_draw_kernel<4>, 4)
+                                          : (lds_of(2) <= LDS_BYTES ? draw(phi_draw_kernel<2>, 2)
+                                                                    : draw(phi_draw_kernel<1>, 1));
     if (e != hipSuccess) return e;
-    e = launch_row_sums(m.gam, m.V, m.K, m.S, s);
+    e = launch_phi_sums(m, part, rows, stats, s);
     if (e != hipSuccess) return e;
-    long long *scratch = m.scratch;
-    long long *total = scratch + ((m.V + SCAN_BLOCK - 1) / SCAN_BLOCK) + 1;
-    e = scan_excl<int32_t, int32_t>(m.colcnt, m.colptr, m.V, scratch, total, s);
-    if (e != hipSuccess) return e;
-    if (stats) {
-        e = launch_fill_u64(&stats[ST_EMPTY_ROWS], 0ull, 1, s);
-        if (e != hipSuccess) return e;
-    }
-    colptr_finish_kernel<<<1, 256, 0, s>>>(m.S, m.K, total, stats, m.Rd);
-    return launch_phi_fill(m, false, s);
+    return launch_phi_columns(m, false, n_cu, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -785,8 +1080,9 @@ __global__ void __launch_bounds__(256) gamma_kernel(DevModel m)
 // S_k in two fixed-order passes (so the Phi-step is deterministic): block b
 // sums its ROWSUM_COLS words in ascending order per topic, then the blocks'
 // partial sums are added in ascending block order
-__global__ void dsum_part_kernel(DevModel m)
+__global__ void dsum_part_kernel(DevModel m, unsigned long long *stats)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && stats) stats[ST_EMPTY_ROWS] = 0;
     const int32_t v0 = blockIdx.x * ROWSUM_COLS;
     const int32_t v1 = v0 + ROWSUM_COLS < m.V ? v0 + ROWSUM_COLS : m.V;
     for (int32_t k = threadIdx.x; k < m.K; k += blockDim.x) {
@@ -796,13 +1092,15 @@ __global__ void dsum_part_kernel(DevModel m)
     }
 }
 
-__global__ void dsum_final_kernel(DevModel m, int32_t nb)
+__global__ void dsum_final_kernel(DevModel m, int32_t nb, unsigned long long *stats)
 {
     const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= m.K) return;
     double s = 0.0;
     for (int32_t b = 0; b < nb; ++b) s += m.dpart[(int64_t)b * m.K + k];
     m.Sd[k] = s;
+    m.Rd[k] = 0.0;
+    if (s == 0.0 && stats) atomicAdd(&stats[ST_EMPTY_ROWS], 1ull);
 }
 
 // nonzeros of each column: cells whose fp32 phi is normal; one wave per word
@@ -822,20 +1120,7 @@ __global__ void __launch_bounds__(256) dcount_kernel(DevModel m)
     if (lane == 0) m.colcnt[v] = cnt;
 }
 
-__global__ void dcolptr_finish_kernel(const double *Sd, int32_t K, const long long *total,
-                                      unsigned long long *stats, double *Rd)
-{
-    if (threadIdx.x == 0 && stats) stats[ST_NNZ_PHI] = (unsigned long long)*total;
-    unsigned long long empty = 0;
-    for (int32_t k = threadIdx.x; k < K; k += blockDim.x) {
-        empty += Sd[k] == 0.0;
-        Rd[k] = 0.0;
-    }
-    for (int o = 32; o > 0; o >>= 1) empty += __shfl_down(empty, o, 64);
-    if ((threadIdx.x & 63) == 0 && empty && stats) atomicAdd(&stats[ST_EMPTY_ROWS], empty);
-}
-
-hipError_t launch_phi_step_dirichlet(const DevModel &m, unsigned long long *stats, hipStream_t s)
+hipError_t launch_phi_step_dirichlet(const DevModel &m, unsigned long long *stats, int32_t n_cu, hipStream_t s)
 {
     if (m.phi_method != 1) return hipErrorInvalidValue;
     const int64_t cells = (int64_t)m.V * m.K;
@@ -843,27 +1128,21 @@ hipError_t launch_phi_step_dirichlet(const DevModel &m, unsigned long long *stat
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int32_t nb = (m.V + ROWSUM_COLS - 1) / ROWSUM_COLS;
-    dsum_part_kernel<<<nb, 256, 0, s>>>(m);
+    dsum_part_kernel<<<nb, 256, 0, s>>>(m, stats);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    dsum_final_kernel<<<(m.K + 255) / 256, 256, 0, s>>>(m, nb);
+    dsum_final_kernel<<<(m.K + 255) / 256, 256, 0, s>>>(m, nb, stats);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     dcount_kernel<<<(m.V + 3) / 4, 256, 0, s>>>(m);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    long long *scratch = m.scratch;
-    long long *total = scratch + ((m.V + SCAN_BLOCK - 1) / SCAN_BLOCK) + 1;
-    e = scan_excl<int32_t, int32_t>(m.colcnt, m.colptr, m.V, scratch, total, s);
+    e = launch_phi_sums(m, nullptr, 0, stats, s);
     if (e != hipSuccess) return e;
-    if (stats) {
-        e = launch_fill_u64(&stats[ST_EMPTY_ROWS], 0ull, 1, s);
-        if (e != hipSuccess) return e;
-    }
-    dcolptr_finish_kernel<<<1, 256, 0, s>>>(m.Sd, m.K, total, stats, m.Rd);
+    phi_dense_kernel<<<(m.V + 3) / 4, 256, 0, s>>>(m);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_phi_fill(m, true, s);
+    return launch_phi_columns(m, true, n_cu, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -978,6 +1257,13 @@ __device__ __forceinline__ uint32_t load_u32_at(const void *base, uint32_t byte_
     return ((const Unaligned32 *)((const char *)base + byte_off))->x;
 }
 
+// byte offset of word v's row from gam (phid for values)
+__device__ __forceinline__ uint32_t row_offset(const DevModel &M, uint32_t fmt, int32_t v)
+{
+    const uint32_t vs = (uint32_t)v * (uint32_t)M.ks16;
+    return fmt == ROW_8 ? M.row8 + vs : (fmt == ROW_16 ? M.row16 + 2u * vs : (uint32_t)v * (uint32_t)M.K * 4u);
+}
+
 // the bits of a gathered word that are the draw
 __device__ __forceinline__ uint32_t row_mask(uint32_t fmt) { return 0xFFFFFFFFu >> (32u - (8u << fmt)); }
 
@@ -986,14 +1272,6 @@ template <bool VALUES>
 __device__ __forceinline__ float slot_phi(uint32_t x, uint32_t mask, float R)
 {
     return VALUES ? __uint_as_float(x) : (float)(x & mask) * R;
-}
-
-// LDS accesses of the wave before and after are kept in this order (LDS
-// executes a wave's instructions in order; only the compiler is held)
-__device__ __forceinline__ void lds_order()
-{
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
 __device__ __forceinline__ float lds_add(float *p, float x)
@@ -1200,8 +1478,7 @@ __device__ __forceinline__ LaneTok stage_token(const DevModel &M, int32_t v, int
     const uint32_t kv = rec.y & WREC_LOW;
     x.kv = (int32_t)kv;
     x.fmt = rec.y >> 30;
-    const uint32_t vs = (uint32_t)v * (uint32_t)M.ks16;
-    x.row = x.fmt == ROW_8 ? M.row8 + vs : (x.fmt == ROW_16 ? M.row16 + 2u * vs : (uint32_t)v * (uint32_t)M.K * 4u);
+    x.row = row_offset(M, x.fmt, v);
     x.u0 = (float)(r.x >> 8) * 0x1p-24f;
     const float sa = __uint_as_float(rec.z);
     x.saf = sa > 0x1p-100f ? sa : __uint_as_float(0x7FC00000u);
@@ -1222,44 +1499,27 @@ __device__ __forceinline__ LaneTok stage_token(const DevModel &M, int32_t v, int
 // counts read by topic (dense layout); else the slots.  Returns the slot of
 // the new topic, or -1 for the a-part; Z: sigma_a + sigma_b.
 template <int G, bool COL, typename Count>
-__device__ __forceinline__ int32_t draw_f64(const uint4 *wrec, const double *sigma_a, const double *Rd,
-                                         const uint32_t *ckg, const uint16_t *g16, const float *phid, int32_t K,
-                                         int32_t ks16, int32_t v, float u0, Count count, const uint16_t *lst,
-                                         int32_t L, int32_t per, double &Zo)
+__device__ __forceinline__ int32_t draw_f64(const DevModel &M, int32_t v, float u0, Count count, const uint16_t *lst,
+                                            int32_t L, int32_t per, double &Zo)
 {
     const int g = __lane_id() & (G - 1);
-    const uint4 rec = wrec[v];
+    const uint4 rec = M.wrec[v];
     const int32_t n = COL ? (int32_t)(rec.y & WREC_LOW) : L;
     const int32_t q = COL ? (n + G - 1) / G : per;
     const int32_t e0 = g * q;
     const int32_t e1 = e0 + q < n ? e0 + q : n;
-    const uint32_t row16 = (uint32_t)v * (uint32_t)ks16, row32 = (uint32_t)v * (uint32_t)K;
     // term of entry e (exact in fp64: a 24-bit phi times a count below 2^16)
     auto term = [&](int32_t e) -> double {
-        int32_t k;
-        uint32_t x;
-        uint32_t m;
-        if (COL) {
-            const uint32_t kg = ckg[rec.x + (uint32_t)e];
-            k = (int32_t)(kg & 0xFFFFu);
-            x = kg >> 16;
-            m = count(e, k);
-        } else {
-            k = lst[e];
-            m = count(e, k);
-            x = g16[row16 + (uint32_t)k];
-        }
-        // phi_kv = fp32(x R_k) == fp32(RN64(x / S_k)) for x < 2^16 and
-        // S_k < 2^27; every other nonzero cell holds 0xFFFF
-        const float f = x == 0xFFFFu ? phid[row32 + (uint32_t)k] : (float)((double)x * Rd[k]);
-        return (double)f * (double)m;
+        const int32_t k = COL ? M.ctopic[rec.x + (uint32_t)e] : lst[e];
+        const float f = COL ? M.cphi[rec.x + (uint32_t)e] : phi_at(M, v, k);
+        return (double)f * (double)count(e, k);
     };
     double p = 0.0;
 #pragma unroll 1
     for (int32_t e = e0; e < e1; ++e) p += term(e);
     const double incl = group_scan_incl<G>(p);
     const double T = group_bcast_f64<G>(incl, G - 1);
-    const double sa = sigma_a[v];
+    const double sa = M.sigma_a[v];
     const double Z = sa + T;
     Zo = Z;
     const double x = (double)u0 * Z;
@@ -1288,7 +1548,7 @@ __device__ __forceinline__ int32_t draw_f64(const uint4 *wrec, const double *sig
                 if (c > y) break;
             }
         }
-        if (COL && at >= 0) at = (int32_t)(ckg[rec.x + (uint32_t)at] & 0xFFFFu);
+        if (COL && at >= 0) at = M.ctopic[rec.x + (uint32_t)at];
     }
     return __shfl(at, f, G);
 }
@@ -1298,8 +1558,7 @@ template <int G, bool COL, typename Count>
 __device__ __forceinline__ int32_t slots_draw_f64(const DevModel &M, const SlotDoc &S, int32_t v, float u0,
                                                   int32_t per, Count count, double &Z)
 {
-    return draw_f64<G, COL>(M.wrec, M.sigma_a, M.Rd, M.ckg, M.g16, M.phid, M.K, M.ks16, v, u0, count, S.lst, S.L,
-                            per, Z);
+    return draw_f64<G, COL>(M, v, u0, count, S.lst, S.L, per, Z);
 }
 
 // a lane's token during a block: old slot, a-part slot, the counts its old
@@ -1974,12 +2233,6 @@ __device__ __forceinline__ void z_step_item(const ZArgs &a, const WorkItem &w, c
     }
 }
 
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
-{
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
-
 // one persistent kernel per group size and layout: waves take work items
 // from this class's queue until it is empty
 template <int G, bool BIG, bool HOT>
@@ -2059,7 +2312,7 @@ __device__ __forceinline__ int32_t lane_lower_bound(const uint16_t *kl, int32_t 
 
 // one block of the lane's list: b-terms of entries [j0, j0 + 8) (zero past L)
 __device__ __forceinline__ void lane_block_terms(const uint16_t *kl, const uint8_t *ml, int32_t L, int32_t j0,
-                                                 const uint16_t *g16col, const float *pcol, const double *Rd,
+                                                 const DevModel &M, uint32_t row, uint32_t fmt,
                                                  int32_t (&kk)[LANE_BLK], double (&bb)[LANE_BLK])
 {
     uint32_t mm[LANE_BLK], xx[LANE_BLK];
@@ -2075,22 +2328,23 @@ __device__ __forceinline__ void lane_block_terms(const uint16_t *kl, const uint8
     }
 #pragma unroll
     for (int u = 0; u < LANE_BLK; ++u) {
-        xx[u] = g16col[(uint32_t)kk[u]];
-        rr[u] = Rd[kk[u]];
+        xx[u] = load_u32_at(M.values ? (const void *)M.phid : (const void *)M.gam, row + ((uint32_t)kk[u] << fmt)) &
+                row_mask(fmt);
+        rr[u] = M.Rd[kk[u]];
     }
-    // phi_kv = fp32(x * R_k) == fp32(RN64(x / S_k)); escapes (0xFFFF) read
-    // the fp32 table
+    // phi_kv = fp32(x * R_k) == fp32(RN64(x / S_k)) for x < 0xFFFF and
+    // S_k < 2^27; other draws divide
     float fk[LANE_BLK];
-    bool esc = false;
+    bool far = false;
 #pragma unroll
     for (int u = 0; u < LANE_BLK; ++u) {
-        fk[u] = (float)((double)xx[u] * rr[u]);
-        esc |= xx[u] == 0xFFFFu;
+        fk[u] = M.values ? __uint_as_float(xx[u]) : (float)((double)xx[u] * rr[u]);
+        far |= xx[u] && (xx[u] >= 0xFFFFu || rr[u] <= 0x1p-27);
     }
-    if (__builtin_amdgcn_ballot_w64(esc)) {
+    if (!M.values && __builtin_amdgcn_ballot_w64(far)) {
 #pragma unroll
         for (int u = 0; u < LANE_BLK; ++u)
-            if (xx[u] == 0xFFFFu) fk[u] = pcol[kk[u]];
+            if (xx[u] && (xx[u] >= 0xFFFFu || rr[u] <= 0x1p-27)) fk[u] = (float)((double)xx[u] / (double)M.S[kk[u]]);
     }
 #pragma unroll
     for (int u = 0; u < LANE_BLK; ++u) bb[u] = (double)fk[u] * (double)mm[u];
@@ -2154,8 +2408,8 @@ __global__ void __launch_bounds__(64) z_lane_kernel(ZArgs a)
                     ml[po * 64] = (uint8_t)(mo - 1);
                     const int32_t Kd = L - (mo == 1 ? 1 : 0);
                     cnt.J += (unsigned long long)(Kd < Kv ? Kd : Kv);
-                    const uint16_t *g16col = M.g16 + (uint32_t)v * (uint32_t)M.ks16;
-                    const float *pcol = M.phid + (uint32_t)v * (uint32_t)M.K;
+                    const uint32_t fmt = M.wrec[v].y >> 30;
+                    const uint32_t row = row_offset(M, fmt, v);
                     // sigma_b over the list, ascending, with the running sum after each block
                     double bs[LANE_NBLK];
                     double sb = 0.0;
@@ -2166,7 +2420,7 @@ __global__ void __launch_bounds__(64) z_lane_kernel(ZArgs a)
                         if (!__builtin_amdgcn_ballot_w64(blk * LANE_BLK < L)) continue;
                         int32_t kk[LANE_BLK];
                         double bb[LANE_BLK];
-                        lane_block_terms(kl, ml, L, blk * LANE_BLK, g16col, pcol, M.Rd, kk, bb);
+                        lane_block_terms(kl, ml, L, blk * LANE_BLK, M, row, fmt, kk, bb);
     #pragma unroll
                         for (int u = 0; u < LANE_BLK; ++u) {
                             sb += bb[u];
@@ -2194,7 +2448,7 @@ __global__ void __launch_bounds__(64) z_lane_kernel(ZArgs a)
                         if (blk >= 0) {
                             int32_t kk[LANE_BLK];
                             double bb[LANE_BLK];
-                            lane_block_terms(kl, ml, L, blk * LANE_BLK, g16col, pcol, M.Rd, kk, bb);
+                            lane_block_terms(kl, ml, L, blk * LANE_BLK, M, row, fmt, kk, bb);
                             double c = c0;
     #pragma unroll
                             for (int u = 0; u < LANE_BLK; ++u) {
@@ -2539,6 +2793,7 @@ __global__ void export_phi_kernel(DevModel m, int64_t *colptr64, uint16_t *topic
     if (v >= m.V) return;
     const int lane = __lane_id();
     const int32_t a = m.colptr[v], b = m.colptr[v + 1];
+    const uint32_t fmt = m.wrec[v].y >> 30;
     if (lane == 0) {
         colptr64[v] = a;
         if (v == m.V - 1) colptr64[m.V] = b;
@@ -2547,7 +2802,7 @@ __global__ void export_phi_kernel(DevModel m, int64_t *colptr64, uint16_t *topic
         const int32_t k = m.ctopic[e];
         topic[e] = (uint16_t)k;
         phi_e[e] = m.cphi[e];
-        gam_e[e] = m.phi_method == 1 ? 0 : m.gam[(int64_t)v * m.K + k];
+        gam_e[e] = m.phi_method == 1 ? 0 : (int32_t)row_draw(m, fmt, v, k);
         const uint64_t al = m.calias[e];
         thr[e] = (uint32_t)al;
         alias_topic[e] = (uint16_t)(al >> 48);
@@ -2573,9 +2828,7 @@ __global__ void import_phi_kernel(DevModel m, const int64_t *colptr64, const uin
         if (v == m.V - 1) m.colptr[m.V] = (int32_t)b;
     }
     float *pcol = m.phid + (int64_t)v * m.K;
-    uint16_t *g16col = m.g16 + (int64_t)v * m.ks16;
     for (int32_t k = lane; k < m.K; k += 64) pcol[k] = 0.0f;
-    for (int32_t k = lane; k < m.ks16; k += 64) g16col[k] = 0;
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     // values without draws behind them: every nonzero cell is read from phid
@@ -2585,9 +2838,7 @@ __global__ void import_phi_kernel(DevModel m, const int64_t *colptr64, const uin
         fmax = phi_e[e] > fmax ? phi_e[e] : fmax;
         m.ctopic[e] = (uint16_t)k;
         m.cphi[e] = phi_e[e];
-        m.ckg[e] = (uint32_t)k | (0xFFFFu << 16);
         pcol[k] = phi_e[e];
-        g16col[k] = 0xFFFF;
         m.calias[e] = (uint64_t)thr[e] | ((uint64_t)k << 32) | ((uint64_t)alias_topic[e] << 48);
     }
     for (int o = 32; o > 0; o >>= 1) {
@@ -2818,7 +3069,7 @@ __device__ __forceinline__ void foldin_slot(const DevModel &M, const DevFoldin &
         for (int32_t k = g; k < K; k += G)
             F.theta[(int64_t)sid * K + k] = (float)(((double)acc[k] / ns + M.alpha[k]) / denom);
         double part = 0.0;
-        for (int32_t q = g; q < kept; q += G) part += log((double)M.phid[(int64_t)wds[q] * K + zz[q]]);
+        for (int32_t q = g; q < kept; q += G) part += log((double)phi_at(M, wds[q], zz[q]));
         // (topics in a fixed order, whatever the slots)
         for (int32_t k = g; k < K; k += G) {
             const int32_t c = (int32_t)count_of(S, k);
