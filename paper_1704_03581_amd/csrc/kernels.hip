@@ -1958,6 +1958,10 @@ __device__ __forceinline__ void draw_regs(const DevModel &M, SlotDoc &S, const f
 #pragma unroll
         for (int u = 0; u < NM; ++u) m[u] = m0[u];
         const uint32_t end = i0 + (uint32_t)__builtin_ctz(open) + 1;
+        // (the draws behind it start over, as if not drawn: their places are
+        // the a-part's again)
+        a_draws &= (1ull << i0) - 1ull;
+        if (place >= end && place < i0 + DEPTH) S.out[place] = (uint16_t)d.pa;
         for (uint32_t i = i0; i < end; ++i) {
             if ((move_draws >> i) & 1ull) moves_of_draw(i);
             const int c = __builtin_amdgcn_readlane(token, (int)i);
@@ -1973,7 +1977,6 @@ __device__ __forceinline__ void draw_regs(const DevModel &M, SlotDoc &S, const f
                 M, S, __builtin_amdgcn_readlane(t.v, c), recs[i].u0, SL,
                 [&](int32_t, int32_t k) { return count_of(S, k); }, Zd);
             lds_order();
-            a_draws &= ~(1ull << i);
             if (to < 0) {
                 to = (int32_t)(w >> 16);
                 a_draws |= 1ull << i;

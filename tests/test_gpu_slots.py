@@ -1,0 +1,192 @@
+"""Edges of the GPU kernels' splits, against the oracle: slots per lane and
+bytes per count in the z-step, dense layouts, the row formats of Phi's draws,
+the Phi-step's lists and scans, and the log joint's parts.  Integers and phi
+are compared exactly, draws by the teacher-forced replay (a difference must be
+a floating-point tie), sums of logs to 1e-10 relative (1e-12 for one document),
+as in the other parity tests."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1704_03581_amd import synth
+from tests.gpu_helpers import assert_phi_equal, oracle_phi, phi_from_gpu, say
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_1704_03581_amd import pulda
+else:  # collected on CPU-only hosts, never run there
+    pulda = None
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _corpus(lens, V, K, seed, probs=None):
+    rng = np.random.default_rng(seed)
+    lens = np.asarray(lens, np.int64)
+    off = np.zeros(len(lens) + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    if probs is None:
+        probs = 1.0 / (10.0 + np.arange(V))
+    words = rng.choice(V, size=int(off[-1]), p=probs / probs.sum()).astype(np.int32)
+    return synth.Corpus("slots", len(lens), V, K, 0.1, 0.01, off, words, None)
+
+
+def _plan(c, seed, alpha=None, beta=None):
+    p = pulda.Plan(c.K, c.V, c.D, c.N, alpha=c.alpha if alpha is None else alpha,
+                   beta=c.beta if beta is None else beta, seed=seed)
+    p.upload(c.doc_off, c.words)
+    return p
+
+
+def _z_steps(c, p, seed, sweeps=2):
+    for t in range(1, sweeps + 1):
+        z0 = p.get_z()
+        p.phi_step(t)
+        phi, wt = phi_from_gpu(p.get_phi(), c.K, c.V)
+        p.z_step(t)
+        z1 = p.get_z()
+        r = oracle.replay(c.doc_off, c.words, z0, z1, seed, t, phi, wt, c.K, c.V)
+        say(f"  sweep {t}: {r}")
+        assert r["bad"] == 0, r
+        assert r["agree"] >= 0.9999 * c.N
+        n_o, _, _ = oracle.counts(c.doc_off, c.words, z1, c.K, c.V, with_m=False)
+        assert np.array_equal(p.counts_dense()[0], n_o)
+        _, deg, sumJ, sumA = oracle.z_step(c.doc_off, c.words, z0, seed, t, phi, wt, c.K, c.V)
+        st = p.stats()
+        assert st["degenerate_tokens"] == deg
+        if r["ties"] == 0:
+            assert (st["sum_J"], st["sum_A"]) == (sumJ, sumA)
+
+
+# slots per lane 1 to 16 and the layouts past them (one block of tokens less,
+# equal and more), 255 and 256 tokens (counts of one and two bytes), and
+# topic lists past 16 slots a lane, which turn dense (K > 16 G)
+@pytest.mark.parametrize("group,K,lens", [
+    (64, 1000, [0, 1, 2, 63, 64, 65, 127, 128, 129, 192, 255, 256, 257, 400, 700, 1500, 4000]),
+    (32, 1000, [0, 1, 31, 32, 33, 63, 64, 65, 160, 255, 256, 257, 448, 480]),
+    (16, 1000, [0, 1, 15, 16, 17, 33, 80, 150, 239, 240]),
+    (8, 1000, [0, 1, 7, 8, 9, 17, 40, 90, 119, 120]),
+    (64, 3000, [0, 30, 900, 1100, 5000]),
+    (64, 1025, [3, 8000]),
+    (32, 5, [1, 31, 32, 33, 255, 256, 300]),
+])
+def test_slots_per_lane(group, K, lens):
+    c = _corpus(lens * 3, 900, K, seed=group + K)
+    say(f"slots: group={group} K={K} N={c.N}")
+    p = _plan(c, 7)
+    p.set_schedule([0], [group], [64 // group * 4], [1])
+    p.init()
+    _z_steps(c, p, 7)
+
+
+# short documents on 64 lanes: a draw that fp32 leaves open takes its round
+# back, and the draws behind it, now with one count more, may turn from a slot
+# to the a-part
+def test_draws_behind_an_open_one():
+    c = _corpus(np.random.default_rng(1).integers(4, 12, size=200000), 300, 24, seed=2)
+    z = {}
+    for group in (64, 32):
+        p = _plan(c, 11)
+        p.set_schedule([0], [group], [64], [1])
+        p.init()
+        p.sweep(1, 120, want_ll=False)
+        z[group] = p.get_z()
+        say(f"open draws: group={group} {p.stats()['fallback_draws']}")
+    assert np.array_equal(z[64], z[32])
+
+
+# few documents to a work item where a bucket is small, many where it is large
+@pytest.mark.parametrize("D", [3, 1100, 9000])
+def test_documents_per_item(D):
+    c = _corpus(np.random.default_rng(D).integers(0, 40, size=D), 300, 20, seed=D)
+    p = _plan(c, 3)
+    p.init()
+    _z_steps(c, p, 3, sweeps=1)
+
+
+# a word's draws in rows of 32 bits (one word holds most tokens), 16 and 8
+# bits, for the slots (64, 16), one document per lane (1)
+@pytest.mark.parametrize("group", [64, 16, 1])
+def test_row_formats(group):
+    V, K = 1500, 4
+    probs = np.full(V, 0.1 / V)
+    probs[3], probs[7] = 0.87, 0.03
+    c = _corpus([190] * 2400, V, K, seed=5, probs=probs)
+    say(f"rows: group={group} N={c.N}")
+    p = _plan(c, 9)
+    p.set_schedule([0], [group], [64], [1])
+    p.init()
+    z = p.get_z()
+    p.phi_step(1)
+    g = p.get_phi()
+    top = np.maximum.reduceat(g["gamma"], g["colptr"][:-1].astype(np.int64)[np.diff(g["colptr"]) > 0])
+    assert top.max() >= 0xFFFF and ((top > 255) & (top < 0xFFFF)).any() and (top <= 255).any()
+    gam, S, phi, wt = oracle_phi(c.doc_off, c.words, z, K, V, c.alpha, c.beta, 100, 9, 1)
+    assert_phi_equal(g, gam, S, phi, wt, K, V)
+    _z_steps(c, p, 9)
+
+
+# short and long columns (256 nonzeros and
+# more), the scan's blocks and turns, the most topics a block of draws holds
+@pytest.mark.parametrize("V,K,N", [(4, 1, 50), (4095, 3, 20000), (4097, 3, 20000), (270001, 2, 60000), (40, 256, 40000),
+                                   (40, 257, 40000), (300, 1030, 60000), (60, 4096, 30000)])
+def test_phi_step_shapes(V, K, N):
+    c = _corpus([N // 50] * 50, V, K, seed=V + K)
+    say(f"phi: V={V} K={K}")
+    p = _plan(c, 4)
+    p.init()
+    z = p.get_z()
+    p.phi_step(2)
+    gam, S, phi, wt = oracle_phi(c.doc_off, c.words, z, K, V, c.alpha, c.beta, 100, 4, 2)
+    assert_phi_equal(p.get_phi(), gam, S, phi, wt, K, V)
+    st = p.stats()
+    assert st["nnz_phi"] == len(wt.topic) and st["empty_rows"] == int((S == 0).sum())
+
+
+# counts past the tables of logs (a topic of more than 256 tokens), documents
+# past the chunks loaded ahead, per-word priors with small and large counts
+@pytest.mark.parametrize("K", [1, 3, 257, 1000])
+@pytest.mark.parametrize("priors", ["symmetric", "vector"])
+def test_log_joint_parts(K, priors):
+    lens = [0, 1, 63, 64, 65, 255, 256, 257, 700, 0, 3000] * 7
+    c = _corpus(lens, 500, K, seed=K)
+    rng = np.random.default_rng(K)
+    alpha = rng.uniform(0.01, 1.0, size=K) if priors == "vector" else None
+    beta = rng.uniform(0.005, 0.5, size=c.V) if priors == "vector" else None
+    p = _plan(c, 2, alpha, beta)
+    p.init()
+    bv = beta if priors == "vector" else None
+    for t in (0, 1):
+        want = oracle.loglik(c.doc_off, c.words, p.get_z(), c.alpha if alpha is None else alpha, c.beta, c.K, c.V, beta_v=bv)
+        got = [p.loglik() for _ in range(3)]
+        assert got[0] == got[1] == got[2]
+        assert abs(got[0] - want) <= 1e-10 * abs(want), (got, want)
+        ll = p.sweep(t + 1, 1)[0]
+        assert abs(ll - p.loglik()) <= 1e-10 * abs(ll)
+
+
+# topic lists past 16 slots a lane in fold-in and the held-out estimate
+@pytest.mark.parametrize("group", [64, 32, 16])
+def test_dense_documents_out_of_the_corpus(group):
+    c = _corpus([200] * 60, 700, 1100, seed=1)
+    p = _plan(c, 6)
+    p.init()
+    p.sweep(1, 2, want_ll=False)
+    p.phi_step(3)
+    phi, wt = phi_from_gpu(p.get_phi(), c.K, c.V)
+    rng = np.random.default_rng(group)
+    docs = [rng.integers(0, c.V, size=n).astype(np.int32) for n in (0, 1, 255, 256, 5000)]
+    alpha = np.full(c.K, c.alpha)
+    f = pulda.FoldIn(p, sweeps=3, burn_in=1, max_slots=8, arena_tokens=8000, max_len=5000, group=group, seed=5)
+    for i, w in enumerate(docs):
+        r = f.run_one(i, w)
+        theta, ll, kept, dropped, _ = oracle.foldin(phi, wt, alpha, 5, i, w, S=3, burn_in=1)
+        assert (r["kept"], r["dropped"]) == (kept, dropped)
+        assert np.array_equal(r["theta"], theta), (group, len(w))
+        assert abs(r["loglik"] - ll) <= 1e-12 * max(1.0, abs(ll))
