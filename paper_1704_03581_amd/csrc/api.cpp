@@ -710,12 +710,18 @@ pulda_status pulda_set_counts(pulda_plan *p, const int32_t *n_dev, void *stream)
     return PULDA_OK;
 }
 
+// Phi's tables come from a Phi-step, not from pulda_set_phi
+static void phi_is_drawn(pulda_plan *p)
+{
+    p->m.phi_method = p->phi_method;
+    p->m.values = p->phi_method == PULDA_PHI_DIRICHLET;
+}
+
 static pulda_status enqueue_phi(pulda_plan *p, hipStream_t s)
 {
     size_t a = 0, b = 0;
     if (p->timing) HIP_TRY(phase_event(p, s, &a));
-    p->m.phi_method = p->phi_method;
-    p->m.values = p->phi_method == PULDA_PHI_DIRICHLET;
+    phi_is_drawn(p);
     if (p->phi_method == PULDA_PHI_DIRICHLET) HIP_TRY(launch_phi_step_dirichlet(p->m, p->stats, p->n_cu, s));
     else HIP_TRY(launch_phi_step(p->m, p->stats, p->n_cu, s));
     if (p->timing) {
@@ -848,6 +854,7 @@ pulda_status pulda_sweep(pulda_plan *p, uint32_t t_first, int32_t n_sweeps, doub
                 if (ec != hipSuccess) return fail(PULDA_ERR_DEVICE, "graph instantiate: %s", hipGetErrorString(ec));
             }
             for (int32_t i = 0; i < chunk; ++i) HIP_TRY(hipGraphLaunch(p->gexec, s));
+            phi_is_drawn(p);   // (a replay passes enqueue_phi by)
         } else {
             for (int32_t i = 0; i < chunk; ++i) {
                 pulda_status st = enqueue_sweep_body(p, s);

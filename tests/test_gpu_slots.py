@@ -190,3 +190,23 @@ def test_dense_documents_out_of_the_corpus(group):
         assert (r["kept"], r["dropped"]) == (kept, dropped)
         assert np.array_equal(r["theta"], theta), (group, len(w))
         assert abs(r["loglik"] - ll) <= 1e-12 * max(1.0, abs(ll))
+
+
+# Phi's kind follows the tables, also where a sweep is replayed from a graph
+# after values had been loaded
+def test_replayed_sweep_after_loaded_phi():
+    c = _corpus([60] * 50, 300, 20, seed=8)
+    p, q = _plan(c, 5), _plan(c, 5)
+    for x in (p, q):
+        x.set_graph(x is p)
+        x.init()
+        x.sweep(1, 2, want_ll=False)
+    g = p.get_phi()
+    p.set_phi(g["colptr"], g["topic"], g["phi"], g["alias_thr"], g["alias_topic"], g["sigma_a"])
+    w = np.arange(100, dtype=np.int32)
+    for x in (p, q):
+        x.sweep(3, 2, want_ll=False)
+    assert np.array_equal(p.get_z(), q.get_z())
+    r = [pulda.FoldIn(x, sweeps=4, burn_in=2, max_slots=4, arena_tokens=400, max_len=200, group=16, seed=5).run_one(0, w)
+         for x in (p, q)]
+    assert np.array_equal(r[0]["theta"], r[1]["theta"]) and r[0]["loglik"] == r[1]["loglik"]
