@@ -145,12 +145,12 @@ struct pulda_plan {
     int64_t ws_need = 0;
     struct {
         int64_t z, n, gam, phid, g16, g8, Rd, gamd, Sd, dpart, phimax, wrec, hot, hot_word, beta_v, ztp, ztp_off, longcol, colcnt, colptr, ctopic, cphi, calias, sigma_a, S, nk, alpha, pois, pois_off,
-            doc_order, items, queue, stats, ll_part, ll_out, ll_hist, tptr, err, scratch, cnt_a, ptr_a, cnt_b,
+            doc_order, items, queue, stats, ll_nk, ll_part, ll_done, ll_out, ll_hist, tptr, err, scratch, cnt_a, ptr_a, cnt_b,
             ptr_b, zsave, lg_beta, lg_alpha, lg_A, ll_doc;
     } off;
     int64_t cap = 0, items_cap = 0, hist_cap = 4096;
     int32_t ks16 = 0;                 // row stride of the 16-bit draw table
-    int32_t n_part_words = 1024, n_part_docs = 1024;
+    LLSpace ll_space{};
     std::vector<int32_t> pois_off_h;
     std::vector<uint64_t> pois_h;
     std::vector<double> lg_beta_h, lg_alpha_h, lg_A_h;  // log-joint term tables
@@ -166,7 +166,7 @@ struct pulda_plan {
     WorkItem *items = nullptr;
     int32_t *queue = nullptr;
     unsigned long long *stats = nullptr;
-    double *ll_part = nullptr, *ll_out = nullptr, *ll_hist = nullptr, *ll_doc = nullptr;
+    double *ll_out = nullptr, *ll_hist = nullptr, *ll_doc = nullptr;
     uint32_t *tptr = nullptr, *hist_idx = nullptr;
     int32_t *err = nullptr;
     int64_t *cnt_a = nullptr, *ptr_a = nullptr, *cnt_b = nullptr, *ptr_b = nullptr;
@@ -353,7 +353,12 @@ pulda_status pulda_plan_create(const pulda_model_desc *desc, int64_t D, int64_t 
     p->off.items = L.take(p->items_cap * (int64_t)sizeof(WorkItem));
     p->off.queue = L.take(Z_QUEUES * 4);
     p->off.stats = L.take(ST_COUNT * 8);
-    p->off.ll_part = L.take((int64_t)(p->n_part_words + p->n_part_docs) * 8);
+    // (at most 8 MiB of partial sums for K up to 4096)
+    p->ll_space.max_words = std::max(256, std::min(1024, (1 << 20) / p->K));
+    p->ll_space.max_docs = 2048;
+    p->off.ll_nk = L.take((int64_t)p->ll_space.max_words * p->K * 8);
+    p->off.ll_part = L.take((int64_t)(p->ll_space.max_words + p->ll_space.max_docs + (p->K + 15) / 16) * 8);
+    p->off.ll_done = L.take(4);
     p->off.ll_out = L.take(8);
     p->off.ll_hist = L.take(p->hist_cap * 8);
     p->off.tptr = L.take(16);
@@ -446,7 +451,9 @@ pulda_status pulda_plan_bind(pulda_plan *p, void *workspace_dev, int64_t bytes)
     p->items = (WorkItem *)(w + p->off.items);
     p->queue = (int32_t *)(w + p->off.queue);
     p->stats = (unsigned long long *)(w + p->off.stats);
-    p->ll_part = (double *)(w + p->off.ll_part);
+    p->ll_space.part_nk = (unsigned long long *)(w + p->off.ll_nk);
+    p->ll_space.part = (double *)(w + p->off.ll_part);
+    p->ll_space.done = (uint32_t *)(w + p->off.ll_done);
     p->ll_out = (double *)(w + p->off.ll_out);
     p->ll_hist = (double *)(w + p->off.ll_hist);
     p->err = (int32_t *)(w + p->off.err);
@@ -771,13 +778,13 @@ static pulda_status enqueue_z(pulda_plan *p, hipStream_t s, double *ll_doc = nul
     return PULDA_OK;
 }
 
-static pulda_status enqueue_ll(pulda_plan *p, hipStream_t s, double *hist, const uint32_t *hist_idx,
-                               const double *ll_doc = nullptr)
+// (advance_t: the sweep number that moves on afterwards, with the history index)
+static pulda_status enqueue_ll(pulda_plan *p, hipStream_t s, double *hist, uint32_t *hist_idx,
+                               const double *ll_doc = nullptr, uint32_t *advance_t = nullptr)
 {
     size_t a = 0, b = 0;
     if (p->timing) HIP_TRY(phase_event(p, s, &a));
-    HIP_TRY(launch_loglik(p->c, p->m, p->ll_part, p->n_part_words, p->n_part_docs, ll_doc, p->ll_out, hist,
-                          hist_idx, s));
+    HIP_TRY(launch_loglik(p->c, p->m, p->ll_space, ll_doc, p->ll_out, hist, hist_idx, advance_t, s));
     if (p->timing) {
         HIP_TRY(phase_event(p, s, &b));
         p->ev_ll.push_back({a, b});
@@ -819,10 +826,7 @@ static pulda_status enqueue_sweep_body(pulda_plan *p, hipStream_t s)
     double *ll_doc = (p->symmetric_alpha && p->fused_ll) ? p->ll_doc : nullptr;
     st = enqueue_z(p, s, ll_doc);
     if (st != PULDA_OK) return st;
-    st = enqueue_ll(p, s, p->ll_hist, p->hist_idx, ll_doc);
-    if (st != PULDA_OK) return st;
-    HIP_TRY(launch_advance(p->tptr, p->hist_idx, s));
-    return PULDA_OK;
+    return enqueue_ll(p, s, p->ll_hist, p->hist_idx, ll_doc, p->tptr);
 }
 
 pulda_status pulda_sweep(pulda_plan *p, uint32_t t_first, int32_t n_sweeps, double *ll_host, void *stream)
@@ -834,8 +838,7 @@ pulda_status pulda_sweep(pulda_plan *p, uint32_t t_first, int32_t n_sweeps, doub
     int32_t done = 0;
     while (done < n_sweeps) {
         const int32_t chunk = (int32_t)std::min<int64_t>(n_sweeps - done, p->hist_cap);
-        HIP_TRY(launch_fill_u32(p->tptr, t_first + (uint32_t)done, 1, s));
-        HIP_TRY(launch_fill_u32(p->hist_idx, 0u, 1, s));
+        HIP_TRY(launch_set_sweep(p->tptr, t_first + (uint32_t)done, p->hist_idx, s));
         if (p->graph_on && !p->timing) {
             if (!p->gexec) {
                 // capture one sweep on a private stream (the caller's stream

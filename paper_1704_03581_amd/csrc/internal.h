@@ -210,12 +210,21 @@ hipError_t launch_z_prepare(const DevModel &m, int32_t *queues, unsigned long lo
 hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, int32_t longest,
                           const WorkItem *items, int32_t n_items, int32_t n_cu, int32_t *queue, unsigned long long *stats,
                           double *ll_doc, hipStream_t s);
+// working space of the log joint
+struct LLSpace {
+    int32_t max_words, max_docs;   // most blocks of the words' part, of the documents'
+    unsigned long long *part_nk;   // [max_words * K]
+    double *part;                  // [max_words + max_docs + ceil(K / 16)]
+    uint32_t *done;
+};
+// sweep number t, history index 0
+hipError_t launch_set_sweep(uint32_t *tptr, uint32_t t, uint32_t *hist_idx, hipStream_t s);
 // log joint of the current state; with ll_doc non-null the document terms
-// are taken from it (written by the z-step) instead of recounted from z
-hipError_t launch_loglik(const DevCorpus &c, const DevModel &m, double *partials, int32_t n_part_words,
-                         int32_t n_part_docs, const double *ll_doc, double *out, double *hist,
-                         const uint32_t *hist_idx, hipStream_t s);
-hipError_t launch_advance(uint32_t *tptr, uint32_t *hist_idx, hipStream_t s);
+// are taken from it (written by the z-step) instead of recounted from z.
+// With advance_t non-null the sweep number there and the history index move
+// on by one afterwards.
+hipError_t launch_loglik(const DevCorpus &c, const DevModel &m, const LLSpace &space, const double *ll_doc, double *out,
+                         double *hist, uint32_t *hist_idx, uint32_t *advance_t, hipStream_t s);
 hipError_t launch_n_colcount(const DevModel &m, int64_t *cnt, hipStream_t s);
 // rebuild the per-word records from colptr, sigma_a and phimax
 hipError_t launch_word_records(const DevModel &m, hipStream_t s);

@@ -320,11 +320,12 @@ hipError_t launch_row_sums(const int32_t *dense, int32_t V, int32_t K, unsigned 
 // ---------------------------------------------------------------------------
 // bytes of LDS per topic: the block's sums, and a wave's draws and list
 constexpr int32_t PHI_SUM_BYTES = 8, PHI_WAVE_BYTES = 6;
+constexpr int PHI_DRAW_WAVES = 4;   // per block
 
-template <int WAVES>
-__global__ void __launch_bounds__(64 * WAVES) phi_draw_kernel(DevModel m, unsigned long long *part,
-                                                              unsigned long long *stats)
+__global__ void __launch_bounds__(64 * PHI_DRAW_WAVES) phi_draw_kernel(DevModel m, unsigned long long *part,
+                                                                       unsigned long long *stats)
 {
+    constexpr int WAVES = PHI_DRAW_WAVES;
     extern __shared__ __align__(16) uint8_t phi_lds[];
     const uint32_t t = *m.tptr;
     const int lane = __lane_id();
@@ -994,24 +995,16 @@ hipError_t launch_phi_step(const DevModel &m, unsigned long long *stats, int32_t
 {
     // the partial sums use the alias records' space, written after them
     unsigned long long *part = (unsigned long long *)m.calias;
-    auto lds_of = [&](int waves) { return (size_t)m.ks16 * (PHI_SUM_BYTES + PHI_WAVE_BYTES * waves); };
-    int32_t rows = 0;
-    auto draw = [&](auto kernel, int waves) -> hipError_t {
-        // persistent blocks: one row of partial sums each
-        const size_t lds = lds_of(waves);
-        const int64_t fit = (int64_t)(LDS_BYTES / lds), most = 32 / waves;
-        int64_t blocks = (int64_t)(n_cu > 0 ? n_cu : 1) * (fit < most ? fit : most);
-        const int64_t need = ((int64_t)m.V + waves - 1) / waves;
-        if (blocks < 1) blocks = 1;   // (the launch then fails)
-        if (blocks > need) blocks = need;
-        rows = (int32_t)blocks;
-        kernel<<<(unsigned)blocks, 64 * waves, lds, s>>>(m, part, stats);
-        return hipGetLastError();
-    };
-    // four waves to a block, fewer where K topics of LDS leave no room
-    hipError_t e = lds_of(4) <= LDS_BYTES ? draw(phi_draw_kernel<4>, 4)
-                                          : (lds_of(2) <= LDS_BYTES ? draw(phi_draw_kernel<2>, 2)
-                                                                    : draw(phi_draw_kernel<1>, 1));
+    // persistent blocks: one row of partial sums each (K up to 4096: 128 KB)
+    constexpr int W = PHI_DRAW_WAVES;
+    const size_t lds = (size_t)m.ks16 * (PHI_SUM_BYTES + PHI_WAVE_BYTES * W);
+    const int64_t fit = (int64_t)(LDS_BYTES / lds), most = 32 / W;
+    int64_t blocks = (int64_t)(n_cu > 0 ? n_cu : 1) * (fit < most ? fit : most);
+    const int64_t need = ((int64_t)m.V + W - 1) / W;
+    if (blocks > need) blocks = need;
+    const int32_t rows = (int32_t)blocks;
+    phi_draw_kernel<<<rows, 64 * W, lds, s>>>(m, part, stats);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     e = launch_phi_sums(m, part, rows, stats, s);
     if (e != hipSuccess) return e;
@@ -2521,24 +2514,25 @@ static int topics_per_lane_log2(int K, int G)
     return c;
 }
 
-__global__ void bump_kernel(unsigned long long *x)
+// what a z-step starts from: no counts, empty queues, one more z-step counted
+__global__ void __launch_bounds__(256) z_prepare_kernel(int32_t *n, int64_t cells, int32_t *queues,
+                                                        unsigned long long *stats)
 {
-    if (threadIdx.x == 0) *x += 1ull;
+    const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t quads = cells >> 2;   // (the table is 256-byte aligned)
+    for (int64_t i = i0; i < quads; i += (int64_t)gridDim.x * blockDim.x) ((int4 *)n)[i] = make_int4(0, 0, 0, 0);
+    if (i0 < (cells & 3)) n[4 * quads + i0] = 0;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < Z_QUEUES) queues[threadIdx.x] = 0;
+        if (threadIdx.x == 0 && stats) stats[ST_TOKENS] += 1ull;
+    }
 }
 
 hipError_t launch_z_prepare(const DevModel &m, int32_t *queues, unsigned long long *stats, hipStream_t s)
 {
-    hipError_t e;
-    if (m.n) {
-        e = launch_fill_u32((uint32_t *)m.n, 0u, (int64_t)m.V * m.K, s);
-        if (e != hipSuccess) return e;
-    }
-    if (stats) {
-        bump_kernel<<<1, 64, 0, s>>>(&stats[ST_TOKENS]);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return launch_fill_u32((uint32_t *)queues, 0u, Z_QUEUES, s);
+    const int64_t cells = m.n ? (int64_t)m.V * m.K : 0;
+    z_prepare_kernel<<<grid_for(cells / 4, 256, 16384), 256, 0, s>>>(m.n, cells, queues, stats);
+    return hipGetLastError();
 }
 
 hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, int32_t longest,
@@ -2615,9 +2609,19 @@ hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, 
 //          + sum_{k,v: n_kv > 0} [lgamma(n_kv + beta) - lgamma(beta)]
 //   docs:  sum_d [lgamma(A) - lgamma(N_d + A)
 //          + sum_{k: m_dk > 0} (lgamma(m_dk + alpha_k) - lgamma(alpha_k))]
-// Partial sums per block in a fixed order, then one fixed-order reduction,
-// so the value is the same on every run.
+// Two launches.  The first reads the counts once: a block adds its words'
+// counts by topic in LDS beside the cells' terms, and writes one row of
+// partial sums; its other blocks take the documents.  The second adds the rows up by topic, and
+// its last block to finish adds everything else.  Partial sums are added in a
+// fixed order, so the value is the same on every run.
+// Measured at V = 28,000, K = 1000 and 200,000 documents of 90 tokens: 117 +
+// 17 us, from 330 us when the counts were read twice (50 + 53 us) and every
+// document cleared and read a table of K counts (215 us).  The words alone take
+// 55 us (112 MB of counts: the table lookups and LDS adds of 28M cells), the
+// documents alone 75 us (instruction issue, about 150 a document).
 // ---------------------------------------------------------------------------
+constexpr int32_t LL_DOCS = 256;   // documents' terms per block, at least
+
 __device__ __forceinline__ double block_sum_f64(double x, double *red)
 {
     for (int o = 32; o > 0; o >>= 1) x += __shfl_down(x, o, 64);
@@ -2630,159 +2634,333 @@ __device__ __forceinline__ double block_sum_f64(double x, double *red)
     return t;
 }
 
-// (beta_v: per-word priors, cells word-major with K per word; else the
-// symmetric beta through the table of lgamma(x + beta) - lgamma(beta))
-__global__ void __launch_bounds__(256) ll_words_kernel(const int32_t *n, int64_t cells, int32_t K, double beta,
-                                                       double lgb, const double *lg_beta, const double *beta_v,
-                                                       double *partials)
+struct LLArgs {
+    const int32_t *n;
+    int32_t V, K;
+    int32_t words;              // words per block of the words' part
+    int32_t nw, nd;             // blocks of the words' part, of the documents'
+    double beta, lgb;
+    const double *lg_beta, *beta_v;
+    unsigned long long *part_nk;   // [nw * K]
+    double *part;                  // [nw + nd], then [ceil(K / 16)] of the second launch
+    unsigned long long *nk;        // [K]
+    DevCorpus c;
+    const double *ll_doc;          // the documents' terms, or null: counted from z
+    const double *alpha, *lg_A;
+    int32_t symmetric;
+    uint32_t *done;                // blocks of the second launch that have finished
+    double Vbeta, *out, *hist;
+    const uint32_t *hist_idx;
+    uint32_t *advance_t, *advance_hist;   // sweep number and history index, moved on when set
+};
+
+// The words' part: a block's cells in one run, U a thread in flight.  A cell's term is lgamma(n + beta) - lgamma(beta), by table for the symmetric
+// beta (an entry of zero for n = 0, so that every lane reads without a
+// branch); with per-word priors log(beta (beta + 1) .. (beta + n - 1)) for
+// small counts.  Counts are added to their topic in LDS.
+__device__ __forceinline__ double ll_words(const LLArgs &a, unsigned long long *sum)
 {
-    __shared__ double red[4];
+    const int tid = threadIdx.x;
+    const int32_t K = a.K;
+    const int32_t v0 = blockIdx.x * a.words;
+    const int64_t c0 = (int64_t)v0 * K;
+    const int64_t c1 = (int64_t)(v0 + a.words < a.V ? v0 + a.words : a.V) * K;
+    for (int32_t k = tid; k < K; k += 256) sum[k] = 0;
+    __syncthreads();
     double acc = 0.0;
-    // lgamma(n + beta) - lgamma(beta) of one cell (zero for an empty cell)
-    auto term = [&](int32_t c, int64_t i) -> double {
-        if (c <= 0) return 0.0;
-        if (beta_v) {
-            const double b = beta_v[i / K];
-            return lgamma((double)c + b) - lgamma(b);
-        }
-        return c < LG_TABLE ? lg_beta[c] : lgamma((double)c + beta) - lgb;
-    };
-    // four cells per 16-byte load (the table is 256-byte aligned), four
-    // loads in flight per thread; the cells past a multiple of four after
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t n4 = cells >> 2;
-    const int4 *q = (const int4 *)n;
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    for (; i + 3 * stride < n4; i += 4 * stride) {
-        int4 a[4];
+    constexpr int U = 16;
+    const int32_t dv = 256 / K, dk = 256 - dv * K;   // a turn's step in words and topics
+    int32_t v = v0 + tid / K, k = tid % K;
+    const int32_t *n0 = a.n + c0 + tid;
+    const int32_t cells = (int32_t)(c1 - c0);
+    for (int32_t cb = 0; cb < cells; cb += 256 * U) {
+        int32_t x[U];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) a[j] = q[i + j * stride];
-        for (int j = 0; j < 4; ++j) {
-            const int64_t c0 = 4 * (i + j * stride);
-            acc += term(a[j].x, c0) + term(a[j].y, c0 + 1) + term(a[j].z, c0 + 2) + term(a[j].w, c0 + 3);
+        for (int u = 0; u < U; ++u) x[u] = cb + 256 * u + tid < cells ? n0[cb + 256 * u] : 0;
+        if (!a.beta_v) {
+            double t[U];
+            bool far = false;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool in = (uint32_t)x[u] < (uint32_t)LG_TABLE;
+                t[u] = a.lg_beta[in ? x[u] : 0];
+                far |= !in;
+            }
+#pragma unroll
+            for (int u = 0; u < U; u += 4) acc += (t[u] + t[u + 1]) + (t[u + 2] + t[u + 3]);
+            if (far) {
+#pragma unroll 1
+                for (int u = 0; u < U; ++u) {
+                    const int32_t c = cb + 256 * u + tid < cells ? n0[cb + 256 * u] : 0;
+                    if (c >= LG_TABLE) acc += lgamma((double)c + a.beta) - a.lgb;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            atomicAdd(&sum[k], (unsigned long long)(uint32_t)x[u]);
+            if (a.beta_v && x[u] > 0) {
+                const double b = a.beta_v[v];
+                if (x[u] <= 8) {
+                    double p = b;
+                    for (int q = 1; q < x[u]; ++q) p *= b + (double)q;
+                    acc += log(p);
+                } else {
+                    acc += lgamma((double)x[u] + b) - lgamma(b);
+                }
+            }
+            v += dv;
+            k += dk;
+            if (k >= K) {
+                k -= K;
+                ++v;
+            }
         }
     }
-    for (; i < n4; i += stride) {
-        const int4 a = q[i];
-        acc += term(a.x, 4 * i) + term(a.y, 4 * i + 1) + term(a.z, 4 * i + 2) + term(a.w, 4 * i + 3);
-    }
-    for (int64_t r = 4 * n4 + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < cells; r += stride)
-        acc += term(n[r], r);
-    const double t = block_sum_f64(acc, red);
-    if (threadIdx.x == 0) partials[blockIdx.x] = t;
+    __syncthreads();
+    unsigned long long *row = a.part_nk + (int64_t)blockIdx.x * K;
+    for (int32_t q = tid; q < K; q += 256) row[q] = sum[q];
+    return acc;
+}
+
+// Documents counted from z, a wave to a document: sum over topics of
+// lgamma(m + alpha_k) - lgamma(alpha_k) = sum over the tokens of
+// log(alpha_k + j), j the tokens of the topic counted before (LDS handles a
+// wave's adds to one address in lane order).  So no table of K counts is
+// cleared or read per document: the tokens clear what they counted.  The
+// offsets of 64 documents and the next document's first tokens are in flight
+// while one is counted.
+constexpr int32_t LL_LOGS = 256;   // log(alpha + j) in LDS (symmetric alpha), and a zero
+constexpr int32_t LL_IDLE = 64;    // a count for each lane without a token
+
+inline size_t ll_docs_lds(int32_t K)
+{
+    return (LL_LOGS + 1) * sizeof(double) + 4 * ((size_t)(K + 1) / 2 + LL_IDLE) * sizeof(uint32_t);
 }
 
 template <bool SYM>
-__global__ void __launch_bounds__(256) ll_docs_kernel(DevCorpus c, int32_t K, const double *alpha,
-                                                      const double *lg_alpha, const double *lg_A, int32_t log2c,
-                                                      double *partials)
+__device__ __forceinline__ double ll_docs(const LLArgs &a, uint8_t *lds)
 {
-    extern __shared__ uint16_t ll_lds[];
-    __shared__ double red[4];
-    const int lane = __lane_id();
-    const int wv = threadIdx.x >> 6;
-    const int32_t C = 1 << log2c;
-    uint16_t *mt = ll_lds + wv * (64 * C);
-    uint32_t *w32 = (uint32_t *)mt;
+    const int lane = __lane_id(), wv = threadIdx.x >> 6;
+    double *logs = (double *)lds;
+    const int32_t words = (a.K + 1) / 2 + LL_IDLE;
+    uint32_t *cnt = (uint32_t *)(lds + (LL_LOGS + 1) * sizeof(double)) + wv * words;
+    const int32_t idle = 2 * (words - LL_IDLE + lane);   // the "topic" of no token
+    for (int32_t i = lane; i < words; i += 64) cnt[i] = 0;
+    if (SYM) {
+        logs[threadIdx.x] = log(a.alpha[0] + (double)threadIdx.x);
+        if (threadIdx.x == 0) logs[LL_LOGS] = 0.0;
+    }
+    __syncthreads();
+    const int64_t waves = (int64_t)a.nd * 4;
+    const int64_t per = (a.c.D + waves - 1) / waves;
+    const int64_t d0 = ((int64_t)(blockIdx.x - a.nw) * 4 + wv) * per;
+    const int64_t d1 = d0 + per < a.c.D ? d0 + per : a.c.D;
+    constexpr int C = 4;   // 64-token chunks at a time
+    const uint16_t *zl = a.c.z + lane;
     double acc = 0.0;
-    const int64_t nw = (int64_t)gridDim.x * 4;
-    for (int64_t d = blockIdx.x * 4 + wv; d < c.D; d += nw) {
-        const int64_t s = c.doc_off[d], e = c.doc_off[d + 1];
-        for (int32_t i = lane; i < 32 * C; i += 64) w32[i] = 0;
-        __builtin_amdgcn_wave_barrier();
-        for (int64_t i = s + lane; i < e; i += 64) {
-            const int32_t k = c.z[i];
-            const int32_t slot = (k & (C - 1)) * 64 + (k >> log2c);
-            atomicAdd(w32 + (slot >> 1), (slot & 1) ? 65536u : 1u);
+    // C chunks of a document's tokens from token p
+    auto load = [&](int64_t s, int32_t p, int32_t n, int32_t (&k)[C]) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            k[c] = idle;
+            if (p + 64 * c < n && p + 64 * c + lane < n) k[c] = zl[s + p + 64 * c];
         }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        double part = 0.0;
-        for (int32_t b = 0; b < C; ++b) {
-            const int32_t cnt = mt[b * 64 + lane];
-            if (cnt) {
-                const int32_t k = lane * C + b;
-                if constexpr (SYM) part += lg_alpha[cnt];
-                else part += lgamma((double)cnt + alpha[k]) - lgamma(alpha[k]);
+    };
+    auto count = [&](int32_t p, int32_t n, const int32_t (&k)[C]) {
+        uint32_t was[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (p + 64 * c < n) was[c] = atomicAdd(&cnt[k[c] >> 1], 1u << (16 * (k[c] & 1)));
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (p + 64 * c >= n) continue;
+            const int32_t j = (int32_t)__builtin_amdgcn_ubfe(was[c], 16 * (k[c] & 1), 16);
+            const bool on = k[c] < idle - 2 * lane;
+            if (SYM) {
+                acc += logs[on && j < LL_LOGS ? j : LL_LOGS];
+                if (__builtin_amdgcn_ballot_w64(on && j >= LL_LOGS)) acc += on && j >= LL_LOGS ? log(a.alpha[0] + (double)j) : 0.0;
+            } else if (on) {
+                acc += log(a.alpha[k[c]] + (double)j);
             }
         }
-        if (lane == 0) part += lg_A[e - s];
-        acc += part;
+    };
+    auto clear = [&](int32_t p, int32_t n, const int32_t (&k)[C]) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (p + 64 * c < n) cnt[k[c] >> 1] = 0;
+    };
+    for (int64_t db = d0; db < d1; db += 64) {
+        const int nb = (int)(d1 - db < 64 ? d1 - db : 64);
+        int64_t off = 0;
+        int32_t len = 0;
+        if (lane < nb) {
+            off = a.c.doc_off[db + lane];
+            len = (int32_t)(a.c.doc_off[db + lane + 1] - off);
+            acc += a.lg_A[len];
+        }
+        int64_t s = 0;
+        int32_t n = 0, z[C];
+        auto next = [&](int i) {
+            s = (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)off, i) |
+                          (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(off >> 32), i) << 32);
+            n = __builtin_amdgcn_readlane(len, i);
+            load(s, 0, n, z);
+        };
+        next(0);
+        for (int i = 0; i < nb; ++i) {
+            const int64_t sd = s;
+            const int32_t nd = n;
+            int32_t k[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) k[c] = z[c];
+            if (i + 1 < nb) next(i + 1);
+            count(0, nd, k);
+            if (nd > 64 * C) {
+                int32_t more[C];
+                for (int32_t p = 64 * C; p < nd; p += 64 * C) {
+                    load(sd, p, nd, more);
+                    count(p, nd, more);
+                }
+                lds_order();
+                for (int32_t p = 64 * C; p < nd; p += 64 * C) {
+                    load(sd, p, nd, more);
+                    clear(p, nd, more);
+                }
+            }
+            lds_order();
+            clear(0, nd, k);
+            lds_order();
+        }
     }
-    const double t = block_sum_f64(acc, red);
-    if (threadIdx.x == 0) partials[blockIdx.x] = t;
+    return acc;
 }
 
-// fixed-order partial sums of the per-document terms written by the z-step
-__global__ void __launch_bounds__(256) ll_docsum_kernel(const double *ll_doc, int64_t D, double *partials)
+// COUNT: documents counted from z; else their terms as the z-step left them
+template <bool COUNT>
+__global__ void __launch_bounds__(256) ll_terms_kernel(LLArgs a)
 {
+    extern __shared__ __align__(16) uint8_t ll_lds[];
     __shared__ double red[4];
-    const int64_t per = (D + gridDim.x - 1) / gridDim.x;
-    const int64_t a = blockIdx.x * per, b = a + per < D ? a + per : D;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.done = 0;
     double acc = 0.0;
-    for (int64_t d = a + threadIdx.x; d < b; d += blockDim.x) acc += ll_doc[d];
+    if ((int)blockIdx.x < a.nw) {
+        unsigned long long *sum = (unsigned long long *)ll_lds;
+        acc = ll_words(a, sum);
+    } else if constexpr (COUNT) {
+        acc = a.symmetric ? ll_docs<true>(a, ll_lds) : ll_docs<false>(a, ll_lds);
+    } else {
+        const int64_t per = (a.c.D + a.nd - 1) / a.nd;
+        const int64_t d0 = (int64_t)(blockIdx.x - a.nw) * per, d1 = d0 + per < a.c.D ? d0 + per : a.c.D;
+        for (int64_t d = d0 + threadIdx.x; d < d1; d += 256) acc += a.ll_doc[d];
+    }
     const double t = block_sum_f64(acc, red);
-    if (threadIdx.x == 0) partials[blockIdx.x] = t;
+    if (threadIdx.x == 0) a.part[blockIdx.x] = t;
 }
 
-// one block of 256: the topics' terms and the partial sums strided over the
-// threads, then a fixed-order block sum (deterministic)
-__global__ void __launch_bounds__(256) ll_final_kernel(const double *partials, int32_t np,
-                                                       const unsigned long long *nk, int32_t K, double Vbeta,
-                                                       double *out, double *hist, const uint32_t *hist_idx)
+// 16 topics to a block, 64 threads to a topic
+__global__ void __launch_bounds__(1024) ll_final_kernel(LLArgs a)
 {
-    __shared__ double red[4];
+    __shared__ unsigned long long sums[256];
+    __shared__ double red[16];
+    __shared__ int last;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int32_t k = blockIdx.x * 16 + (tid & 15);
+    unsigned long long s = 0;
+    if (k < a.K)
+        for (int32_t r = tid >> 4; r < a.nw; r += 64) s += a.part_nk[(int64_t)r * a.K + k];
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    if (lane < 16) sums[w * 16 + lane] = s;
+    __syncthreads();
     double acc = 0.0;
-    for (int32_t k = threadIdx.x; k < K; k += blockDim.x) acc -= lgamma((double)nk[k] + Vbeta);
-    for (int32_t i = threadIdx.x; i < np; i += blockDim.x) acc += partials[i];
-    const double t = block_sum_f64(acc, red);
-    if (threadIdx.x == 0) {
-        const double ll = (double)K * lgamma(Vbeta) + t;
-        *out = ll;
-        if (hist) hist[*hist_idx] = ll;
+    if (tid < 16 && k < a.K) {
+        s = 0;
+        for (int j = 0; j < 16; ++j) s += sums[j * 16 + tid];
+        a.nk[k] = s;
+        acc = -lgamma((double)s + a.Vbeta);
+    }
+    const int32_t np = a.nw + a.nd;
+    double t = block_sum_f64(acc, red);
+    if (tid == 0) {
+        a.part[np + blockIdx.x] = t;
+        __threadfence();
+        last = atomicAdd(a.done, 1u) == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    acc = 0.0;
+    for (int32_t i = tid; i < np + (int32_t)gridDim.x; i += 1024)
+        acc += __hip_atomic_load(&a.part[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    t = block_sum_f64(acc, red);
+    if (tid == 0) {
+        const double ll = (double)a.K * lgamma(a.Vbeta) + t;
+        *a.out = ll;
+        if (a.hist) a.hist[*a.hist_idx] = ll;
+        if (a.advance_t) {
+            *a.advance_t += 1u;
+            *a.advance_hist += 1u;
+        }
     }
 }
 
-__global__ void advance_kernel(uint32_t *tptr, uint32_t *hist_idx)
+__global__ void set_sweep_kernel(uint32_t *tptr, uint32_t t, uint32_t *hist_idx)
 {
     if (threadIdx.x == 0) {
-        *tptr += 1u;
-        *hist_idx += 1u;
+        *tptr = t;
+        *hist_idx = 0u;
     }
 }
 
-hipError_t launch_advance(uint32_t *tptr, uint32_t *hist_idx, hipStream_t s)
+hipError_t launch_set_sweep(uint32_t *tptr, uint32_t t, uint32_t *hist_idx, hipStream_t s)
 {
-    advance_kernel<<<1, 64, 0, s>>>(tptr, hist_idx);
+    set_sweep_kernel<<<1, 64, 0, s>>>(tptr, t, hist_idx);
     return hipGetLastError();
 }
 
-hipError_t launch_loglik(const DevCorpus &c, const DevModel &m, double *partials, int32_t n_part_words,
-                         int32_t n_part_docs, const double *ll_doc, double *out, double *hist,
-                         const uint32_t *hist_idx, hipStream_t s)
+hipError_t launch_loglik(const DevCorpus &c, const DevModel &m, const LLSpace &space, const double *ll_doc, double *out,
+                         double *hist, uint32_t *hist_idx, uint32_t *advance_t, hipStream_t s)
 {
-    hipError_t e = launch_row_sums(m.n, m.V, m.K, m.nk, s);
-    if (e != hipSuccess) return e;
-    ll_words_kernel<<<n_part_words, 256, 0, s>>>(m.n, (int64_t)m.V * m.K, m.K, m.beta, lgamma(m.beta), m.lg_beta,
-                                                 m.beta_v, partials);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    LLArgs a;
+    a.n = m.n;
+    a.V = m.V;
+    a.K = m.K;
+    // at least a turn of the block's cells, and of K sums
+    const int32_t share = (m.V + space.max_words - 1) / space.max_words, least = 4096 / m.K + 4;
+    a.words = share > least ? share : least;
+    a.nw = (m.V + a.words - 1) / a.words;
+    const int64_t docs = ll_doc ? (c.D + LL_DOCS - 1) / LL_DOCS : (c.D + 15) / 16;
+    a.nd = (int32_t)(docs < 1 ? 1 : (docs < space.max_docs ? docs : space.max_docs));
+    a.beta = m.beta;
+    a.lgb = lgamma(m.beta);
+    a.lg_beta = m.lg_beta;
+    a.beta_v = m.beta_v;
+    a.part_nk = space.part_nk;
+    a.part = space.part;
+    a.nk = m.nk;
+    a.c = c;
+    a.ll_doc = ll_doc;
+    a.alpha = m.alpha;
+    a.lg_A = m.lg_A;
+    a.symmetric = m.lg_alpha != nullptr;
+    a.done = space.done;
+    a.Vbeta = m.beta_sum;
+    a.out = out;
+    a.hist = hist;
+    a.hist_idx = hist_idx;
+    a.advance_t = advance_t;
+    a.advance_hist = hist_idx;
+    const size_t sums = (size_t)m.K * 8;
     if (ll_doc) {
-        ll_docsum_kernel<<<n_part_docs, 256, 0, s>>>(ll_doc, c.D, partials + n_part_words);
+        ll_terms_kernel<false><<<a.nw + a.nd, 256, sums, s>>>(a);
     } else {
-        const int log2c = topics_per_lane_log2(m.K, 64);
-        const size_t lds = 4 * 64 * (1 << log2c) * sizeof(uint16_t);
-        if (m.lg_alpha)
-            ll_docs_kernel<true><<<n_part_docs, 256, lds, s>>>(c, m.K, m.alpha, m.lg_alpha, m.lg_A, log2c,
-                                                               partials + n_part_words);
-        else
-            ll_docs_kernel<false><<<n_part_docs, 256, lds, s>>>(c, m.K, m.alpha, m.lg_alpha, m.lg_A, log2c,
-                                                                partials + n_part_words);
+        const size_t tables = ll_docs_lds(m.K);
+        ll_terms_kernel<true><<<a.nw + a.nd, 256, sums > tables ? sums : tables, s>>>(a);
     }
-    e = hipGetLastError();
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    ll_final_kernel<<<1, 256, 0, s>>>(partials, n_part_words + n_part_docs, m.nk, m.K, m.beta_sum, out, hist,
-                                      hist_idx);
+    ll_final_kernel<<<(m.K + 15) / 16, 1024, 0, s>>>(a);
     return hipGetLastError();
 }
 
