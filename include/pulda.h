@@ -284,26 +284,24 @@ pulda_status pulda_set_timing(pulda_plan *plan, int32_t enable);
  * per work item (a multiple of 64 / group; fewer where the bucket would
  * otherwise leave part of the chip idle).  Group 1 runs one document per lane
  * (its b-sum is the sequential ascending sum) and takes documents shorter
- * than 128 tokens (256 when K <= 127); groups of 8 take documents shorter than 256
- * tokens; a
- * work item whose group would not fit runs on a larger group size.  A token's b-terms (Section 3.5) are summed
- * over the word's Phi column or over the document's topics; a group prefers
- * the column when K_v <= side_ratio[b] * K_d (side_ratio NULL: all 1, the
- * smaller side) and a wave takes the document side when any of its groups
- * prefers it.  Results do not depend on the schedule except through fp64
- * rounding order. */
+ * than 128 tokens (256 when K <= 127); groups of 8 take documents shorter than
+ * 256 tokens; a work item whose group would not fit runs on a larger group
+ * size.  A token's b-terms (Section 3.5) are summed over the document's
+ * topics; side_ratio[b] (1 to 1024, NULL: all 1), once the ratio of column to
+ * topics up to which the word's Phi column was walked instead, is kept and
+ * returned and has no effect.  Results do not depend on the schedule except
+ * through fp64 rounding order. */
 pulda_status pulda_set_schedule(pulda_plan *plan, int32_t n_buckets, const int32_t *min_len_host,
                                 const int32_t *group_host, const int32_t *docs_per_item_host,
                                 const int32_t *side_ratio_host);
 pulda_status pulda_get_schedule(const pulda_plan *plan, int32_t cap, int32_t *n_buckets, int32_t *min_len_host,
                                 int32_t *group_host, int32_t *docs_per_item_host, int32_t *side_ratio_host);
 
-/* Time each candidate group size (1, 8, 16, 32, 64) and side ratio (1, 4, 16) on
- * each bucket (z-step at sweep t, reps repetitions, current Phi) and keep the
- * fastest; then time the whole z-step, as a sweep launches it, with each
- * bucket moved into every other bucket's group and side ratio, and keep a
- * move that makes it faster (a bucket alone in its kernel may run after the
- * others).  Restores z and n.  Synchronises. */
+/* Time each candidate group size (1, 8, 16, 32, 64) on each bucket (z-step at
+ * sweep t, reps repetitions, current Phi) and keep the fastest; then time the
+ * whole z-step, as a sweep launches it, with each bucket moved into every
+ * other bucket's group, and keep a move that makes it faster (a bucket alone
+ * in its kernel may run after the others).  Restores z and n.  Synchronises. */
 pulda_status pulda_autotune(pulda_plan *plan, uint32_t t, int32_t reps, void *stream);
 
 /* In pulda_sweep, let the z-step write each document's term of the log

@@ -1096,7 +1096,7 @@ pulda_status pulda_autotune(pulda_plan *p, uint32_t t, int32_t reps, void *strea
     HIP_TRY(hipEventCreate(&e1));
     const std::vector<int32_t> keep_group = p->group, keep_dpi = p->dpi;
     const int32_t nb = (int32_t)p->min_len.size();
-    std::vector<int32_t> best_g(keep_group), best_d(keep_dpi), best_r(p->side);
+    std::vector<int32_t> best_g(keep_group), best_d(keep_dpi);
     std::vector<double> bucket_mean(nb, 0.0);   // mean document length (0: empty bucket)
     for (int32_t b = 0; b < nb; ++b) {
         // documents of bucket b
@@ -1117,46 +1117,41 @@ pulda_status pulda_autotune(pulda_plan *p, uint32_t t, int32_t reps, void *strea
         float best_ms = 1e30f;
         for (int gsz : {64, 32, 16, 8, 1}) {
             if (!z_group_fits(gsz, p->K, p->len_sorted[lo])) continue;
-            for (int ratio : {1, 4, 16}) {
-                const int ng = 64 / gsz;
-                int per = (int)std::max(1.0, std::round(4096.0 / std::max(1.0, mean_len) / ng)) * ng;
-                per = docs_per_item(hi - lo, per, gsz, p->n_cu);
-                std::vector<WorkItem> items;
-                for (int64_t q = lo; q < hi; q += per)
-                    items.push_back({(int32_t)q, (int32_t)std::min<int64_t>(per, hi - q), gsz, ratio});
-                HIP_TRY(hipMemcpyAsync(p->items, items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice,
-                                       s));
-                float total = 0;
-                for (int r = 0; r <= reps; ++r) {
-                    if (p->N) HIP_TRY(hipMemcpyAsync(p->c.z, p->zsave, p->N * 2, hipMemcpyDeviceToDevice, s));
-                    HIP_TRY(hipEventRecord(e0, s));
-                    HIP_TRY(launch_z_prepare(p->m, p->queue, nullptr, s));
-                    HIP_TRY(launch_z_class(p->c, p->m, gsz, p->len_sorted[lo], p->items,
-                                           (int32_t)items.size(), p->n_cu, p->queue, nullptr, nullptr, s));
-                    HIP_TRY(hipEventRecord(e1, s));
-                    HIP_TRY(hipEventSynchronize(e1));
-                    float ms;
-                    HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-                    if (r > 0) total += ms;  // first run warms up
-                }
-                if (total < best_ms) {
-                    best_ms = total;
-                    best_g[b] = gsz;
-                    best_d[b] = per;
-                    best_r[b] = ratio;
-                }
+            const int ng = 64 / gsz;
+            int per = (int)std::max(1.0, std::round(4096.0 / std::max(1.0, mean_len) / ng)) * ng;
+            per = docs_per_item(hi - lo, per, gsz, p->n_cu);
+            std::vector<WorkItem> items;
+            for (int64_t q = lo; q < hi; q += per)
+                items.push_back({(int32_t)q, (int32_t)std::min<int64_t>(per, hi - q), gsz, p->side[b]});
+            HIP_TRY(hipMemcpyAsync(p->items, items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice, s));
+            float total = 0;
+            for (int r = 0; r <= reps; ++r) {
+                if (p->N) HIP_TRY(hipMemcpyAsync(p->c.z, p->zsave, p->N * 2, hipMemcpyDeviceToDevice, s));
+                HIP_TRY(hipEventRecord(e0, s));
+                HIP_TRY(launch_z_prepare(p->m, p->queue, nullptr, s));
+                HIP_TRY(launch_z_class(p->c, p->m, gsz, p->len_sorted[lo], p->items, (int32_t)items.size(), p->n_cu,
+                                       p->queue, nullptr, nullptr, s));
+                HIP_TRY(hipEventRecord(e1, s));
+                HIP_TRY(hipEventSynchronize(e1));
+                float ms;
+                HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+                if (r > 0) total += ms;  // first run warms up
+            }
+            if (total < best_ms) {
+                best_ms = total;
+                best_g[b] = gsz;
+                best_d[b] = per;
             }
         }
     }
     p->group = best_g;
     p->dpi = best_d;
-    p->side = best_r;
     pulda_status st = build_items(p);
     if (st != PULDA_OK) return st;
     // Then the whole z-step.  Each work-item class is a kernel of its own on
     // a forked stream, and a small class whose stream shares a hardware
     // queue with the caller's runs only after the others.  So each bucket is
-    // also tried in every other bucket's group (and side ratio), and a change
+    // also tried in every other bucket's group, and a change
     // is kept when the whole z-step, timed as the sweep launches it, is
     // faster.
     auto whole = [&](float *out) -> pulda_status {
@@ -1186,12 +1181,11 @@ pulda_status pulda_autotune(pulda_plan *p, uint32_t t, int32_t reps, void *strea
         if (bucket_mean[b] == 0) continue;
         for (int32_t b2 = 0; b2 < nb; ++b2) {
             if (b2 == b || bucket_mean[b2] == 0 || p->group[b2] == p->group[b]) continue;
-            const int32_t g0 = p->group[b], d0 = p->dpi[b], r0 = p->side[b];
+            const int32_t g0 = p->group[b], d0 = p->dpi[b];
             const int32_t gsz = p->group[b2];
             const int ng = 64 / gsz;
             p->group[b] = gsz;
             p->dpi[b] = (int32_t)std::max(1.0, std::round(4096.0 / std::max(1.0, bucket_mean[b]) / ng)) * ng;
-            p->side[b] = p->side[b2];
             float ms = 0;
             st = build_items(p);
             if (st == PULDA_OK) st = whole(&ms);
@@ -1200,7 +1194,6 @@ pulda_status pulda_autotune(pulda_plan *p, uint32_t t, int32_t reps, void *strea
             } else {
                 p->group[b] = g0;
                 p->dpi[b] = d0;
-                p->side[b] = r0;
             }
         }
     }

@@ -93,9 +93,7 @@ struct DevCorpus {
 };
 
 // a unit of z-step work: `count` documents of doc_order starting at `first`,
-// processed by groups of `group` lanes; the b-terms of a token are taken
-// from the word's Phi column when K_v <= side_ratio * K_d, else from the
-// document's topics (which side is walked changes cost, not the result)
+// processed by groups of `group` lanes (side_ratio: of the schedule, unused)
 struct WorkItem {
     int32_t first, count, group, side_ratio;
 };
