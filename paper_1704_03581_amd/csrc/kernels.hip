@@ -2851,16 +2851,18 @@ __device__ __forceinline__ double ll_docs(const LLArgs &a, uint8_t *lds)
             if (i + 1 < nb) next(i + 1);
             count(0, nd, k);
             if (nd > 64 * C) {
-                int32_t more[C];
+                // a long document: the next chunks in flight while these are
+                // counted, and the table cleared whole
+                int32_t a1[C], a2[C];
+                load(sd, 64 * C, nd, a1);
                 for (int32_t p = 64 * C; p < nd; p += 64 * C) {
-                    load(sd, p, nd, more);
-                    count(p, nd, more);
+                    load(sd, p + 64 * C, nd, a2);
+                    count(p, nd, a1);
+#pragma unroll
+                    for (int c = 0; c < C; ++c) a1[c] = a2[c];
                 }
                 lds_order();
-                for (int32_t p = 64 * C; p < nd; p += 64 * C) {
-                    load(sd, p, nd, more);
-                    clear(p, nd, more);
-                }
+                for (int32_t w = lane; w < words; w += 64) cnt[w] = 0;
             }
             lds_order();
             clear(0, nd, k);
