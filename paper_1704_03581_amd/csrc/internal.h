@@ -52,8 +52,8 @@ struct DevModel {
     float *cphi;                  // [cap]
     uint64_t *calias;             // [cap] thr | topic << 32 | alias_topic << 48
     double *sigma_a;              // [V]
-    // row format << 30 | largest phi of the word's column (bits of a float
-    // below 2; set where the rows are values)
+    // where Phi has draws: row format << 30; where it is values (all ROW_32):
+    // bits of the largest phi of the word's column, any float
     uint32_t *phimax;             // [V]
     // per word, what a z-step token needs of its word in one 16-byte load:
     // {first CSC entry, column length | row format << 30, fp32(sigma_a),
@@ -107,7 +107,7 @@ constexpr size_t LDS_BYTES = 160 * 1024;   // per CU, and the most a block takes
 // draw: 8-bit draws (g8), 16-bit draws (g16) or the dense 32-bit table (the
 // urn's draws gam; phi itself where Phi has no draws: Algorithm 1's, or one
 // loaded as values).  log2 of the bytes per topic, held in the top two bits
-// of phimax[v] and of wrec[v].y.
+// of wrec[v].y (a column has at most 4096 entries).
 constexpr uint32_t ROW_8 = 0, ROW_16 = 1, ROW_32 = 2;
 constexpr uint32_t WREC_LOW = 0x3FFFFFFFu;
 

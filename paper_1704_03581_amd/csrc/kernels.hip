@@ -676,7 +676,7 @@ __global__ void __launch_bounds__(256) phi_dense_kernel(DevModel m)
         const float y = __shfl_xor(fmax, o, 64);
         fmax = y > fmax ? y : fmax;
     }
-    if (lane == 0) m.phimax[v] = __float_as_uint(fmax) | (ROW_32 << 30);
+    if (lane == 0) m.phimax[v] = __float_as_uint(fmax);
 }
 
 // ---------------------------------------------------------------------------
@@ -755,11 +755,12 @@ __device__ __forceinline__ void phi_column(const DevModel &m, double *alias_lds,
     const int32_t cb = m.colptr[v];
     const int32_t nv = m.colptr[v + 1] - cb;
     if (SMALL && nv > ALIAS_SMALL) return;
-    const uint32_t pm = m.phimax[v];   // row format in the top bits, and Algorithm 1's largest phi
+    const uint32_t pm = m.phimax[v];   // row format in the top bits; DIR: the largest phi
+    const uint32_t fmt = DIR ? ROW_32 : pm >> 30;
     if (nv == 0) {
         if (lane == 0) {
             m.sigma_a[v] = 0.0;
-            m.wrec[v] = make_uint4((uint32_t)cb, pm & ~WREC_LOW, 0u, 0u);
+            m.wrec[v] = make_uint4((uint32_t)cb, fmt << 30, 0u, 0u);
         }
         return;
     }
@@ -770,7 +771,6 @@ __device__ __forceinline__ void phi_column(const DevModel &m, double *alias_lds,
     uint16_t *lst = (uint16_t *)(pq + cap);   // small entries from the front, large ones from the back
     uint16_t *ctop = DIR ? m.ctopic + cb : lst + cap;                   // topic of entry e
     uint8_t *mark = (uint8_t *)(lst + cap + (DIR ? 0 : cap));           // 1 at the FIFO steps where the head turned small
-    const uint32_t fmt = pm >> 30;
     if constexpr (!DIR) {
         if (fmt == ROW_8) compact_row<ROW_8>(m, v, (uint64_t *)pq);
         else if (fmt == ROW_16) compact_row<ROW_16>(m, v, (uint64_t *)pq);
@@ -939,8 +939,8 @@ __device__ __forceinline__ void phi_column(const DevModel &m, double *alias_lds,
         }
     }
     if (lane == 0)
-        m.wrec[v] = make_uint4((uint32_t)cb, (uint32_t)nv | (pm & ~WREC_LOW), __float_as_uint((float)s),
-                               DIR ? pm & WREC_LOW : __float_as_uint(fmax));
+        m.wrec[v] = make_uint4((uint32_t)cb, (uint32_t)nv | fmt << 30, __float_as_uint((float)s),
+                               DIR ? pm : __float_as_uint(fmax));
     lds_order();
 }
 
@@ -959,14 +959,14 @@ __global__ void __launch_bounds__(SMALL ? 256 : 64) phi_alias_kernel(DevModel m)
     }
 }
 
+// (of a Phi loaded as values)
 __global__ void word_records_kernel(DevModel m)
 {
     const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= m.V) return;
     const int32_t cb = m.colptr[v];
-    const uint32_t pm = m.phimax[v];   // row format in the top bits
-    m.wrec[v] = make_uint4((uint32_t)cb, (uint32_t)(m.colptr[v + 1] - cb) | (pm & ~WREC_LOW),
-                           __float_as_uint((float)m.sigma_a[v]), pm & WREC_LOW);
+    m.wrec[v] = make_uint4((uint32_t)cb, (uint32_t)(m.colptr[v + 1] - cb) | ROW_32 << 30,
+                           __float_as_uint((float)m.sigma_a[v]), m.phimax[v]);
 }
 
 hipError_t launch_word_records(const DevModel &m, hipStream_t s)
@@ -1528,11 +1528,13 @@ __device__ __forceinline__ int32_t draw_f64(const DevModel &M, int32_t v, float 
     const int32_t q = COL ? (n + G - 1) / G : per;
     const int32_t e0 = g * q;
     const int32_t e1 = e0 + q < n ? e0 + q : n;
-    // term of entry e (exact in fp64: a 24-bit phi times a count below 2^16)
+    // term of entry e (exact in fp64: a 24-bit phi times a count below 2^16;
+    // none for a topic without a count, whatever its loaded phi)
     auto term = [&](int32_t e) -> double {
         const int32_t k = COL ? M.ctopic[rec.x + (uint32_t)e] : lst[e];
         const float f = COL ? M.cphi[rec.x + (uint32_t)e] : phi_at(M, v, k);
-        return (double)f * (double)count(e, k);
+        const uint32_t c = count(e, k);
+        return c ? (double)f * (double)c : 0.0;
     };
     double p = 0.0;
 #pragma unroll 1
@@ -1722,7 +1724,8 @@ __device__ __forceinline__ void draw_slots(const DevModel &M, const SlotDoc &S, 
             // a decided group has all its lanes in in_a or one in in_b
             if (__builtin_expect(
                     __builtin_popcountll(in_a) + G * __builtin_popcountll(in_b) != __builtin_popcountll(here), 0)) {
-                const bool open = !is_a && group_ballot<G>(mine) == 0;
+                // (a record without a draw can only be open where loaded values pass fp32's range)
+                const bool open = !is_a && group_ballot<G>(mine) == 0 && c < G;
                 double Zd;
                 const int32_t vc = __shfl(v, c & (G - 1), G);
                 const int32_t at = slots_draw_f64<G, false>(
@@ -1970,6 +1973,9 @@ __device__ __forceinline__ void draw_regs(const DevModel &M, SlotDoc &S, const f
             }
             if (__builtin_expect(open != 0, 0)) break;
         }
+        // (a record past the last draw can only be open where loaded values
+        // pass fp32's range)
+        if (open) open &= (uint32_t)((2ull << (n_draws - 1 - i0)) - 1ull);
         if (__builtin_expect(open == 0, 1)) break;
         // a draw of this round is too close to a boundary for fp32: the round
         // again up to it, in fp64 from the counts in LDS (the draws before it
@@ -2377,7 +2383,7 @@ __device__ __forceinline__ void lane_block_terms(const uint16_t *kl, const uint8
             if (xx[u] && (xx[u] >= 0xFFFFu || rr[u] <= 0x1p-27)) fk[u] = (float)((double)xx[u] / (double)M.S[kk[u]]);
     }
 #pragma unroll
-    for (int u = 0; u < LANE_BLK; ++u) bb[u] = (double)fk[u] * (double)mm[u];
+    for (int u = 0; u < LANE_BLK; ++u) bb[u] = (double)(mm[u] ? fk[u] : 0.0f) * (double)mm[u];
 }
 
 __global__ void __launch_bounds__(64) z_lane_kernel(ZArgs a)
@@ -3062,7 +3068,7 @@ __global__ void import_phi_kernel(DevModel m, const int64_t *colptr64, const uin
         const float y = __shfl_xor(fmax, o, 64);
         fmax = y > fmax ? y : fmax;
     }
-    if (lane == 0) m.phimax[v] = __float_as_uint(fmax) | (ROW_32 << 30);
+    if (lane == 0) m.phimax[v] = __float_as_uint(fmax);
 }
 
 hipError_t launch_import_phi(const DevModel &m, const int64_t *colptr64, const uint16_t *topic, const float *phi_e,
