@@ -144,12 +144,14 @@ struct pulda_plan {
     uint8_t *ws = nullptr;
     int64_t ws_need = 0;
     struct {
-        int64_t z, n, gam, phid, g16, g8, Rd, gamd, Sd, dpart, phimax, wrec, hot, hot_word, beta_v, ztp, ztp_off, longcol, colcnt, colptr, ctopic, cphi, calias, sigma_a, S, nk, alpha, pois, pois_off,
+        int64_t z, n, gam, phid, Rd, gamd, Sd, dpart, phimax, wrec, hot, hot_word, beta_v, ztp, ztp_off, longcol, colcnt, colptr, ctopic, cphi, calias, sigma_a, S, nk, alpha, pois, pois_off,
             doc_order, items, queue, stats, ll_nk, ll_part, ll_done, ll_out, ll_hist, tptr, err, scratch, cnt_a, ptr_a, cnt_b,
             ptr_b, zsave, lg_beta, lg_alpha, lg_A, ll_doc;
     } off;
     int64_t cap = 0, items_cap = 0, hist_cap = 4096;
-    int32_t ks16 = 0;                 // row stride of the 16-bit draw table
+    int32_t ks16 = 0;                 // K rounded up to 64
+    bool one_table = false;           // rows of draws of every format in one table
+    int64_t row_base[3] = {};
     LLSpace ll_space{};
     std::vector<int32_t> pois_off_h;
     std::vector<uint64_t> pois_h;
@@ -321,10 +323,19 @@ pulda_status pulda_plan_create(const pulda_model_desc *desc, int64_t D, int64_t 
     Layout L;
     p->off.z = L.take(N * 2);
     p->off.n = L.take(VK * 4);
-    p->off.gam = L.take(VK * 4);
+    // the rows of draws: tables of 32, 16 and 8 bits a topic one after the
+    // other (a row's last topics are read 4 bytes at a time), or one table
+    // where they end past the 4 GiB that a 32-bit offset reaches (from about
+    // 613M padded cells on)
     p->ks16 = (p->K + 63) / 64 * 64;
-    p->off.g16 = L.take((int64_t)p->V * p->ks16 * 2);
-    p->off.g8 = L.take((int64_t)p->V * p->ks16 + 4);   // (a row's last topics are read 4 bytes at a time)
+    const int64_t VP = (int64_t)p->V * p->ks16;
+    p->row_base[2] = 0;
+    p->row_base[1] = align_up(VK * 4);
+    p->row_base[0] = p->row_base[1] + align_up(VP * 2);
+    const int64_t tables = p->row_base[0] + VP + 4;
+    p->one_table = tables > (1ll << 32);
+    if (p->one_table) p->row_base[0] = p->row_base[1] = 0;
+    p->off.gam = L.take(p->one_table ? VP * 4 : tables);
     p->off.phid = L.take(VK * 4);
     p->off.Rd = L.take((int64_t)p->K * 8);
     p->off.gamd = L.take(VK * 8);
@@ -403,15 +414,14 @@ pulda_status pulda_plan_bind(pulda_plan *p, void *workspace_dev, int64_t bytes)
     m.alpha = (const double *)(w + p->off.alpha);
     m.n = (int32_t *)(w + p->off.n);
     m.nk = (unsigned long long *)(w + p->off.nk);
-    m.gam = (int32_t *)(w + p->off.gam);
+    m.gam = w + p->off.gam;
     m.S = (unsigned long long *)(w + p->off.S);
     m.phid = (float *)(w + p->off.phid);
-    m.g16 = (uint16_t *)(w + p->off.g16);
     m.ks16 = p->ks16;
-    m.g8 = w + p->off.g8;
-    const bool near = p->off.g8 + (int64_t)p->V * p->ks16 - p->off.gam < (1ll << 32);
-    m.row16 = near ? (uint32_t)(p->off.g16 - p->off.gam) : 0u;
-    m.row8 = near ? (uint32_t)(p->off.g8 - p->off.gam) : 0u;
+    for (int f = 0; f < 3; ++f) {
+        m.row_base[f] = (uint32_t)p->row_base[f];
+        m.row_step[f] = p->one_table ? 4u * (uint32_t)p->ks16 : (uint32_t)(f == 2 ? p->K : p->ks16) << f;
+    }
     m.values = 0;
     m.Rd = (double *)(w + p->off.Rd);
     m.gamd = (double *)(w + p->off.gamd);

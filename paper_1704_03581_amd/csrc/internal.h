@@ -19,21 +19,20 @@ struct DevModel {
     unsigned long long *nk;       // [K]
     // Phi-step
     unsigned long long *S;        // [K] row sums
-    // The urn's draws gamma_kv, word-major: each word's row is in one of
-    // three tables, the narrowest that holds its largest draw, and only there
-    // (format ROW_8, ROW_16 or ROW_32 in the word's record): row stride K in
-    // gam, ks16 (K rounded up to 64: aligned rows) in the others.  phi_kv is
+    // The urn's draws gamma_kv: each word's row has the narrowest of three
+    // formats that holds its largest draw (ROW_8, ROW_16 or ROW_32 in the
+    // word's record), topic k at k << format.  A row of format f starts at
+    // byte row_base[f] + v row_step[f] of gam: three tables while they end
+    // within 4 GiB of gam, the reach of a 32-bit offset, so that the narrow
+    // rows lie close together; past that one table, a word's row at the
+    // start of its 32-bit one's space whatever the format.  phi_kv is
     // fp32(RN64(gamma_kv / S_k)); fp32(gamma_kv * R_k) with
     // R_k = RN64(1 / S_k) equals it bit for bit for gamma < 2^16 and
     // S_k < 2^27, where no fp32 rounding midpoint lies within the product's
     // error of the quotient.
-    int32_t *gam;                 // [V*K]
-    uint16_t *g16;                // [V*ks16]
-    uint8_t *g8;                  // [V*ks16]
-    int32_t ks16;
-    // the byte offsets of g16 and g8 from gam (32-bit; 0: the tables span
-    // more than 4 GiB and every word is ROW_32)
-    uint32_t row16, row8;
+    uint8_t *gam;
+    uint32_t row_base[3], row_step[3];
+    int32_t ks16;                 // K rounded up to 64
     // Phi has no integer draws (Algorithm 1's, or one loaded as values): the
     // rows are phid's fp32 values, format ROW_32
     int32_t values;
@@ -104,9 +103,8 @@ constexpr int32_t SLOTS_MAX = 16;
 constexpr int32_t SLOTS_FEW = 6;           // the most of the kernels for short lists
 constexpr size_t LDS_BYTES = 160 * 1024;   // per CU, and the most a block takes
 // the row that a word's b-terms are gathered from, by the word's largest
-// draw: 8-bit draws (g8), 16-bit draws (g16) or the dense 32-bit table (the
-// urn's draws gam; phi itself where Phi has no draws: Algorithm 1's, or one
-// loaded as values).  log2 of the bytes per topic, held in the top two bits
+// draw: 8-bit, 16-bit or 32-bit draws (ROW_32 also for phi itself, where Phi
+// has no draws: Algorithm 1's, or one loaded as values).  log2 of the bytes per topic, held in the top two bits
 // of wrec[v].y (a column has at most 4096 entries).
 constexpr uint32_t ROW_8 = 0, ROW_16 = 1, ROW_32 = 2;
 constexpr uint32_t WREC_LOW = 0x3FFFFFFFu;

@@ -9,8 +9,8 @@
 //
 // Layouts in HBM (all word-major, so one word's column is contiguous):
 //   n[v*K + k]                                  dense counts
-//   gam, g16, g8                                 the draws, each word's row in
-//     the narrowest table that holds it; phid[v*K + k] fp32 values instead
+//   gam                                          the draws, each word's row in
+//     the narrowest format that holds it; phid[v*K + k] fp32 values instead
 //     where Phi has no draws
 //   colptr[v] .. colptr[v+1]                    CSC of Phi's nonzeros by word,
 //     ctopic (u16, ascending), cphi (f32), calias (u64: thr | topic << 32 |
@@ -68,12 +68,20 @@ __device__ __forceinline__ void lds_order()
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
+// byte offset of word v's row of draws from gam
+__device__ __forceinline__ uint32_t draws_offset(const DevModel &m, uint32_t fmt, int32_t v)
+{
+    return fmt == ROW_8 ? m.row_base[0] + (uint32_t)v * m.row_step[0]
+                        : (fmt == ROW_16 ? m.row_base[1] + (uint32_t)v * m.row_step[1] : (uint32_t)v * m.row_step[2]);
+}
+
 // draw of topic k in word v's row of format fmt (Phi of draws)
 __device__ __forceinline__ uint32_t row_draw(const DevModel &m, uint32_t fmt, int32_t v, int32_t k)
 {
-    if (fmt == ROW_8) return m.g8[(int64_t)v * m.ks16 + k];
-    if (fmt == ROW_16) return m.g16[(int64_t)v * m.ks16 + k];
-    return (uint32_t)m.gam[(int64_t)v * m.K + k];
+    const uint8_t *row = m.gam + draws_offset(m, fmt, v);
+    if (fmt == ROW_8) return row[k];
+    if (fmt == ROW_16) return ((const uint16_t *)row)[k];
+    return ((const uint32_t *)row)[k];
 }
 
 // phi_kv = fp32(gamma / S_k), the quotient in fp64; or the loaded value
@@ -466,7 +474,7 @@ __global__ void __launch_bounds__(64 * PHI_DRAW_WAVES) phi_draw_kernel(DevModel 
             const int32_t c = a > b ? a : b;
             xmax = c > xmax ? c : xmax;
         }
-        const uint32_t fmt = m.row8 == 0 || __builtin_amdgcn_ballot_w64(xmax >= 0xFFFF) != 0
+        const uint32_t fmt = __builtin_amdgcn_ballot_w64(xmax >= 0xFFFF) != 0
                                  ? ROW_32
                                  : (__builtin_amdgcn_ballot_w64(xmax > 0xFF) != 0 ? ROW_16 : ROW_8);
         auto row4 = [&](int32_t k) {
@@ -474,21 +482,19 @@ __global__ void __launch_bounds__(64 * PHI_DRAW_WAVES) phi_draw_kernel(DevModel 
             return make_uint4(x.x > 0 ? (uint32_t)x.x : 0u, x.y > 0 ? (uint32_t)x.y : 0u, x.z > 0 ? (uint32_t)x.z : 0u,
                               x.w > 0 ? (uint32_t)x.w : 0u);
         };
+        uint8_t *row = m.gam + draws_offset(m, fmt, v);
         if (fmt == ROW_8) {
-            uint8_t *col = m.g8 + (int64_t)v * kpad;
             for (int32_t k = 4 * lane; k < kpad; k += 256) {
                 const uint4 x = row4(k);
-                *(uint32_t *)&col[k] = x.x | x.y << 8 | x.z << 16 | x.w << 24;
+                *(uint32_t *)(row + k) = x.x | x.y << 8 | x.z << 16 | x.w << 24;
             }
         } else if (fmt == ROW_16) {
-            uint16_t *col = m.g16 + (int64_t)v * kpad;
             for (int32_t k = 4 * lane; k < kpad; k += 256) {
                 const uint4 x = row4(k);
-                *(uint2 *)&col[k] = make_uint2(x.x | x.y << 16, x.z | x.w << 16);
+                *(uint2 *)(row + 2 * k) = make_uint2(x.x | x.y << 16, x.z | x.w << 16);
             }
         } else {
-            int32_t *col = m.gam + (int64_t)v * K;
-            for (int32_t k = lane; k < K; k += 64) col[k] = g[k] > 0 ? g[k] : 0;
+            for (int32_t k = lane; k < K; k += 64) ((int32_t *)row)[k] = g[k] > 0 ? g[k] : 0;
         }
         cnt = group_scan_incl_i32<64>(cnt);
         if (lane == 63) {
@@ -709,6 +715,7 @@ __device__ __forceinline__ void compact_row(const DevModel &m, int32_t v, uint64
 {
     constexpr int JB = 4;
     const int lane = __lane_id();
+    const uint8_t *row = m.gam + draws_offset(m, FMT, v);
     int32_t run = 0;
     for (int32_t kb = 0; kb < m.ks16; kb += 256 * JB) {
         uint32_t x[JB][4];
@@ -717,18 +724,18 @@ __device__ __forceinline__ void compact_row(const DevModel &m, int32_t v, uint64
             const int32_t k = kb + 256 * j + 4 * lane;
             const bool in = k < m.ks16;
             if (FMT == ROW_8) {
-                const uint32_t y = in ? *(const uint32_t *)&m.g8[(int64_t)v * m.ks16 + k] : 0u;
+                const uint32_t y = in ? *(const uint32_t *)(row + k) : 0u;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) x[j][u] = (y >> (8 * u)) & 0xFFu;
             } else if (FMT == ROW_16) {
-                const uint2 y = in ? *(const uint2 *)&m.g16[(int64_t)v * m.ks16 + k] : make_uint2(0u, 0u);
+                const uint2 y = in ? *(const uint2 *)(row + 2 * k) : make_uint2(0u, 0u);
                 x[j][0] = y.x & 0xFFFFu;
                 x[j][1] = y.x >> 16;
                 x[j][2] = y.y & 0xFFFFu;
                 x[j][3] = y.y >> 16;
             } else {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) x[j][u] = k + u < m.K ? (uint32_t)m.gam[(int64_t)v * m.K + k + u] : 0u;
+                for (int u = 0; u < 4; ++u) x[j][u] = k + u < m.K ? ((const uint32_t *)row)[k + u] : 0u;
             }
         }
 #pragma unroll
@@ -1280,8 +1287,7 @@ __device__ __forceinline__ uint32_t load_u32_at(const void *base, uint32_t byte_
 // byte offset of word v's row from gam (phid for values)
 __device__ __forceinline__ uint32_t row_offset(const DevModel &M, uint32_t fmt, int32_t v)
 {
-    const uint32_t vs = (uint32_t)v * (uint32_t)M.ks16;
-    return fmt == ROW_8 ? M.row8 + vs : (fmt == ROW_16 ? M.row16 + 2u * vs : (uint32_t)v * (uint32_t)M.K * 4u);
+    return M.values ? (uint32_t)v * (uint32_t)M.K * 4u : draws_offset(M, fmt, v);
 }
 
 // the bits of a gathered word that are the draw
