@@ -343,8 +343,9 @@ pulda_status pulda_plan_create(const pulda_model_desc *desc, int64_t D, int64_t 
     p->off.dpart = L.take(((int64_t)p->V + ROWSUM_COLS - 1) / ROWSUM_COLS * p->K * 8);
     p->off.colcnt = L.take((int64_t)p->V * 4);
     p->off.colptr = L.take(((int64_t)p->V + 1) * 4);
-    p->off.ctopic = L.take(p->cap * 2);
-    p->off.cphi = L.take(p->cap * 4);
+    // (a column's entries are read COL_PAD at a time, also past the last)
+    p->off.ctopic = L.take((p->cap + COL_PAD) * 2);
+    p->off.cphi = L.take((p->cap + COL_PAD) * 4);
     p->off.longcol = L.take(((int64_t)p->V + 1) * 4);
     p->off.calias = L.take(p->cap * 8);
     p->off.sigma_a = L.take((int64_t)p->V * 8);
@@ -1354,7 +1355,6 @@ pulda_status pulda_foldin_bind(pulda_foldin *f, void *ws, int64_t bytes)
     F.sweeps = f->desc.sweeps;
     F.burn_in = f->desc.burn_in;
     F.group = f->desc.group;
-    F.max_len = f->desc.max_len;
     F.key0 = (uint32_t)f->desc.seed;
     F.key1 = (uint32_t)(f->desc.seed >> 32);
     F.A = f->model->A;
@@ -1454,13 +1454,14 @@ pulda_status pulda_foldin_step(pulda_foldin *f, int32_t draws, void *stream)
     const int32_t S = f->desc.max_slots;
     FoldSlot *slots_pin = (FoldSlot *)f->stage_ctl[b];
     int32_t *active = (int32_t *)(f->stage_ctl[b] + (size_t)S * sizeof(FoldSlot));
-    int32_t n_active = 0;
+    int32_t n_active = 0, longest = 0;
     const int64_t step_no = f->n_steps + 1;
     for (int32_t i = 0; i < S; ++i) {
         FoldSlot &sl = f->slots[i];
         if (f->resident[i] && !f->finished[i]) {
             sl.budget = draws;
             active[n_active++] = i;
+            longest = std::max(longest, sl.len);
             if (sl.fresh) f->first_step[i] = step_no;
         } else {
             sl.budget = 0;
@@ -1474,6 +1475,7 @@ pulda_status pulda_foldin_step(pulda_foldin *f, int32_t draws, void *stream)
     f->stage_used[b] = true;
     f->stage_cur = b ^ 1;
     f->f.step_no = step_no;
+    f->f.max_len = longest;
     HIP_TRY(launch_foldin_step(f->model->m, f->f, f->active_dev, n_active, s));
     f->n_steps = step_no;
     HIP_TRY(hipEventRecord(f->step_ev[step_no & 1], s));

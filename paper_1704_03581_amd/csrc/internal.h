@@ -47,8 +47,8 @@ struct DevModel {
     int32_t *colcnt;              // [V]
     int32_t *longcol;             // columns with long alias tables, in order; [V]: their number
     int32_t *colptr;              // [V+1]
-    uint16_t *ctopic;             // [cap] CSC by word, ascending topic
-    float *cphi;                  // [cap]
+    uint16_t *ctopic;             // [cap + COL_PAD] CSC by word, ascending topic
+    float *cphi;                  // [cap + COL_PAD]
     uint64_t *calias;             // [cap] thr | topic << 32 | alias_topic << 48
     double *sigma_a;              // [V]
     // where Phi has draws: row format << 30; where it is values (all ROW_32):
@@ -107,6 +107,7 @@ constexpr size_t LDS_BYTES = 160 * 1024;   // per CU, and the most a block takes
 // has no draws: Algorithm 1's, or one loaded as values).  log2 of the bytes per topic, held in the top two bits
 // of wrec[v].y (a column has at most 4096 entries).
 constexpr uint32_t ROW_8 = 0, ROW_16 = 1, ROW_32 = 2;
+constexpr int32_t COL_PAD = 8;             // entries of a column read at once
 constexpr uint32_t WREC_LOW = 0x3FFFFFFFu;
 
 // LDS of one group of lanes with a document of at most `longest` tokens:
@@ -152,6 +153,21 @@ inline SlotLds slot_lds(int32_t G, int32_t K, int32_t longest)
     return A;
 }
 
+// a document's topics and the block's a-parts fit the slots of G lanes
+inline bool slots_fit(int32_t G, int32_t K, int32_t longest)
+{
+    return (K < longest + G ? K : longest + G) <= SLOTS_MAX * G;
+}
+
+// lanes for fold-in and held-out documents of at most `longest` tokens: the
+// group asked for, or the next larger that their slots fit (64 lanes take
+// every document)
+inline int32_t slots_group(int32_t group, int32_t K, int32_t longest)
+{
+    while (group < 64 && !slots_fit(group, K, longest)) group *= 2;
+    return group;
+}
+
 // a z-step group size fits documents of at most `longest` tokens when their
 // slots do (groups of 8 take documents shorter than 256 tokens; 64 lanes
 // take every document); one document per lane (group 1) keeps a list of at
@@ -162,8 +178,7 @@ inline bool z_group_fits(int32_t group, int32_t K, int32_t longest)
     if (group == 1) return longest < 128 || (K <= 127 && longest < 256);
     if (group == 64) return true;
     if (group == 8 && longest >= 256) return false;
-    const int32_t most = K < longest + group ? K : longest + group;
-    return most <= SLOTS_MAX * group &&
+    return slots_fit(group, K, longest) &&
            (size_t)(K * 4 + 15) / 16 * 16 + 4 * (64 / group) * (size_t)slot_lds(group, K, longest).group_bytes <=
                LDS_BYTES;
 }
@@ -250,7 +265,7 @@ struct FoldSlot {
 
 struct DevFoldin {
     int32_t sweeps, burn_in, group;
-    int32_t max_len;        // longest request
+    int32_t max_len;        // longest request of the step
     uint32_t key0, key1;
     double A;
     const FoldSlot *slots;  // [max_slots] control, written by the host

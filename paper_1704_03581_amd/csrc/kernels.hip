@@ -1213,12 +1213,13 @@ hipError_t launch_phi_step_dirichlet(const DevModel &m, unsigned long long *stat
 // when y lies farther than tol = (64 + 8 SL) u Z from the boundary it is
 // compared with (more than twice that error); it is then the decision of
 // exact arithmetic, which is also the fp64 path's.  Otherwise (a few draws in
-// ten thousand) draw_f64 decides in fp64.  So the result is the fp64 one bit
+// ten thousand) slots_draw_f64 decides in fp64.  So the result is the fp64 one bit
 // for bit, whatever the split of the topics over lanes.
 //
-// When the list would exceed 16 G slots (possible only when K > 16 G) the
-// wave's groups turn dense: slot = topic, and every draw sums the word's Phi
-// column in fp64 with the counts read by topic.
+// A document whose topics could pass SLOTS_MAX slots a lane takes more lanes;
+// on 64 (where that needs K > 1024) its list turns dense once it is longer:
+// slot = topic, and every draw sums the word's Phi column with the counts read
+// by topic (draw_dense).
 //
 // What bounds it: the draws of a document are a serial chain (LDS add, LDS
 // read, the scan, the decision), so a long document is bound by the chain's
@@ -1414,7 +1415,7 @@ __device__ __forceinline__ void slots_layout(SlotDoc &S, const SlotLds &A, int32
         }
     const int32_t incl = group_scan_incl_i32<G>(n);
     const int32_t L = group_bcast<G>(incl, G - 1);
-    if (BIG && __builtin_amdgcn_ballot_w64(S.dense || L > SLOTS_MAX * G) != 0) {
+    if (BIG && G == 64 && (S.dense || L > SLOTS_MAX * 64)) {
         S.dense = true;
         S.L = K;
         return;
@@ -1520,25 +1521,34 @@ __device__ __forceinline__ LaneTok stage_token(const DevModel &M, int32_t v, int
     return x;
 }
 
-// The draw in fp64: every lane sums its terms in ascending order, the group
-// scan orders the lanes.  COL: the terms are the word's Phi column, the
-// counts read by topic (dense layout); else the slots.  Returns the slot of
-// the new topic, or -1 for the a-part; Z: sigma_a + sigma_b.
-template <int G, bool COL, typename Count>
-__device__ __forceinline__ int32_t draw_f64(const DevModel &M, int32_t v, float u0, Count count, const uint16_t *lst,
-                                            int32_t L, int32_t per, double &Zo)
+// the group's lane whose terms hold y: the first whose running sum (incl, of
+// the lanes' sums p) passes it; none (rounding): the last with a positive
+// term; -1: no positive term, the a-part is the whole law
+template <int G>
+__device__ __forceinline__ int crossing_lane(double incl, double p, double y)
+{
+    const uint64_t bal = group_ballot<G>(incl > y);
+    if (bal) return __builtin_ctzll(bal);
+    const uint64_t pos = group_ballot<G>(p > 0.0);
+    return pos ? 63 - __builtin_clzll(pos) : -1;
+}
+
+// The draw in fp64 over the slots, `per` a lane: every lane sums its terms in
+// ascending order, the group scan orders the lanes.  count(e, k): the count of
+// slot e, of topic k.  Returns the slot of the new topic, or -1 for the
+// a-part; Z: sigma_a + sigma_b.
+template <int G, typename Count>
+__device__ __forceinline__ int32_t slots_draw_f64(const DevModel &M, const SlotDoc &S, int32_t v, float u0, int32_t per,
+                                                  Count count, double &Z)
 {
     const int g = __lane_id() & (G - 1);
-    const uint4 rec = M.wrec[v];
-    const int32_t n = COL ? (int32_t)(rec.y & WREC_LOW) : L;
-    const int32_t q = COL ? (n + G - 1) / G : per;
-    const int32_t e0 = g * q;
-    const int32_t e1 = e0 + q < n ? e0 + q : n;
+    const int32_t e0 = g * per;
+    const int32_t e1 = e0 + per < S.L ? e0 + per : S.L;
     // term of entry e (exact in fp64: a 24-bit phi times a count below 2^16;
     // none for a topic without a count, whatever its loaded phi)
     auto term = [&](int32_t e) -> double {
-        const int32_t k = COL ? M.ctopic[rec.x + (uint32_t)e] : lst[e];
-        const float f = COL ? M.cphi[rec.x + (uint32_t)e] : phi_at(M, v, k);
+        const int32_t k = S.lst[e];
+        const float f = phi_at(M, v, k);
         const uint32_t c = count(e, k);
         return c ? (double)f * (double)c : 0.0;
     };
@@ -1546,23 +1556,12 @@ __device__ __forceinline__ int32_t draw_f64(const DevModel &M, int32_t v, float 
 #pragma unroll 1
     for (int32_t e = e0; e < e1; ++e) p += term(e);
     const double incl = group_scan_incl<G>(p);
-    const double T = group_bcast_f64<G>(incl, G - 1);
     const double sa = M.sigma_a[v];
-    const double Z = sa + T;
-    Zo = Z;
+    Z = sa + group_bcast_f64<G>(incl, G - 1);
     const double x = (double)u0 * Z;
     if (x < sa) return -1;
     const double y = x - sa;
-    // the first lane whose running sum passes y; none (rounding): the last
-    // positive term; no positive term: the a-part is the whole law
-    const uint64_t bal = group_ballot<G>(incl > y);
-    int f = -1;
-    if (bal) {
-        f = __builtin_ctzll(bal);
-    } else {
-        const uint64_t pos = group_ballot<G>(p > 0.0);
-        if (pos) f = 63 - __builtin_clzll(pos);
-    }
+    const int f = crossing_lane<G>(incl, p, y);
     if (f < 0) return -1;
     int32_t at = -1;
     if (g == f) {
@@ -1576,17 +1575,101 @@ __device__ __forceinline__ int32_t draw_f64(const DevModel &M, int32_t v, float 
                 if (c > y) break;
             }
         }
-        if (COL && at >= 0) at = M.ctopic[rec.x + (uint32_t)at];
     }
     return __shfl(at, f, G);
 }
 
-// (count(e, k): the count of slot e, of topic k)
-template <int G, bool COL, typename Count>
-__device__ __forceinline__ int32_t slots_draw_f64(const DevModel &M, const SlotDoc &S, int32_t v, float u0,
-                                                  int32_t per, Count count, double &Z)
+// a word's Phi column: its first CSC entry and their number
+struct Column {
+    uint32_t first;
+    int32_t n;
+};
+
+__device__ __forceinline__ Column column_of(const DevModel &M, int32_t v)
 {
-    return draw_f64<G, COL>(M, v, u0, count, S.lst, S.L, per, Z);
+    const uint4 rec = M.wrec[v];
+    return {rec.x, (int32_t)(rec.y & WREC_LOW)};
+}
+
+// A column on 64 lanes: chunks of 64 N entries, N neighbours a lane, so that a
+// chunk is a few contiguous loads; N = COL_N (one chunk) for columns of up to
+// 64 COL_N entries, COL_B for longer ones
+constexpr int COL_N = 4, COL_B = COL_PAD;
+static_assert(4096 <= 64 * 64 * COL_B, "a lane per chunk");
+
+__device__ __forceinline__ int32_t col_chunks(const Column &c) { return (c.n + 64 * COL_B - 1) / (64 * COL_B); }
+
+struct ColEntries {
+    float f[COL_B];
+    uint16_t k[COL_B];
+};
+
+// COL_B entries of a column from entry e on
+__device__ __forceinline__ ColEntries col_entries(const DevModel &M, const Column &c, int32_t e)
+{
+    const uint32_t i = c.first + (uint32_t)(e < c.n ? e : c.n);
+    ColEntries x;
+    __builtin_memcpy(x.f, M.cphi + i, sizeof(x.f));
+    __builtin_memcpy(x.k, M.ctopic + i, sizeof(x.k));
+    return x;
+}
+
+// the count of topic k in the dense layout (documents of 960 tokens and more:
+// two bytes)
+__device__ __forceinline__ uint32_t dense_count(const SlotDoc &S, int32_t k) { return ((const uint16_t *)S.mt)[k]; }
+
+// The draw in fp64 over the word's column on 64 lanes, the counts read by
+// topic; lane b keeps the running sum after chunk b.  Returns the new topic, or
+// -1 for the a-part.
+__device__ __forceinline__ int32_t column_draw_f64(const DevModel &M, const SlotDoc &S, int32_t v, float u0, double &Z)
+{
+    const int g = __lane_id();
+    const Column col = column_of(M, v);
+    const int32_t chunks = col_chunks(col);
+    ColEntries x = {};
+    double b[COL_B], p = 0.0;
+    auto terms = [&](int32_t ch) {
+        x = col_entries(M, col, (ch * 64 + g) * COL_B);
+        const int32_t own = col.n - (ch * 64 + g) * COL_B;
+        p = 0.0;
+#pragma unroll
+        for (int u = 0; u < COL_B; ++u) {
+            const uint32_t c = u < own ? dense_count(S, x.k[u]) : 0u;
+            b[u] = c ? (double)x.f[u] * (double)c : 0.0;
+            p += b[u];
+        }
+    };
+    double T = 0.0, ends = 0.0;
+    int32_t last = -1;   // the last chunk with a positive term
+#pragma unroll 1
+    for (int32_t ch = 0; ch < chunks; ++ch) {
+        terms(ch);
+        T = group_bcast_f64<64>(T + group_scan_incl<64>(p), 63);
+        ends = g == ch ? T : ends;
+        if (__builtin_amdgcn_ballot_w64(p > 0.0) != 0) last = ch;
+    }
+    const double sa = M.sigma_a[v];
+    Z = sa + T;
+    const double xz = (double)u0 * Z;
+    if (xz < sa || last < 0) return -1;
+    const double y = xz - sa;
+    const uint64_t over = __builtin_amdgcn_ballot_w64(g < chunks && ends > y);
+    const int32_t ch = over != 0 ? __builtin_ctzll(over) : last;
+    terms(ch);
+    const double incl = (ch ? group_bcast_f64<64>(ends, ch - 1) : 0.0) + group_scan_incl<64>(p);
+    const int f = crossing_lane<64>(incl, p, y);
+    double c = incl - p;
+    int32_t k = -1;
+    bool found = false;
+#pragma unroll
+    for (int u = 0; u < COL_B; ++u) {
+        if (b[u] > 0.0 && !found) {
+            c += b[u];
+            k = x.k[u];
+            found = c > y;
+        }
+    }
+    return f < 0 ? -1 : __builtin_amdgcn_readlane(k, f);
 }
 
 // a lane's token during a block: old slot, a-part slot, the counts its old
@@ -1734,7 +1817,7 @@ __device__ __forceinline__ void draw_slots(const DevModel &M, const SlotDoc &S, 
                 const bool open = !is_a && group_ballot<G>(mine) == 0 && c < G;
                 double Zd;
                 const int32_t vc = __shfl(v, c & (G - 1), G);
-                const int32_t at = slots_draw_f64<G, false>(
+                const int32_t at = slots_draw_f64<G>(
                     M, S, vc, u0, SL, [&](int32_t e, int32_t) { return (uint32_t)S.ms[e]; }, Zd);
                 if (open) {
                     if (at >= 0) {
@@ -2005,7 +2088,7 @@ __device__ __forceinline__ void draw_regs(const DevModel &M, SlotDoc &S, const f
             }
             store(false);
             double Zd;
-            int32_t to = slots_draw_f64<64, false>(
+            int32_t to = slots_draw_f64<64>(
                 M, S, __builtin_amdgcn_readlane(t.v, c), recs[i].u0, SL,
                 [&](int32_t, int32_t k) { return count_of(S, k); }, Zd);
             lds_order();
@@ -2028,50 +2111,153 @@ __device__ __forceinline__ void draw_regs(const DevModel &M, SlotDoc &S, const f
     }
 }
 
-// the block's draws in the dense layout (fp64 over the word's column)
-template <int G>
-__device__ __forceinline__ void draw_dense(const DevModel &M, const SlotDoc &S, const int32_t v, LaneDraw &d,
-                                           const uint32_t n_max, const int g)
+// The terms of a lane's N entries of a column and their sum; own: how many of
+// them are the column's (FULL: all)
+template <int N, bool FULL>
+__device__ __forceinline__ float col_terms(const SlotDoc &S, const ColEntries &x, int32_t own, int32_t K, float (&b)[N])
 {
-    // one token leaves or enters topic k (one lane of the group); the count before
-    auto change = [&](int32_t k, int by) {
-        const uint32_t was = count_of(S, k);
-        set_count(S, k, was + (uint32_t)by);
-        return (float)was;
+    uint32_t c[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) c[u] = dense_count(S, FULL || u < own ? x.k[u] : K);   // (topic K: no count)
+    float p = 0.0f;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        b[u] = FULL || u < own ? x.f[u] * (float)c[u] : 0.0f;
+        p += b[u];
+    }
+    return p;
+}
+
+// the topic of a lane's N entries that holds y, s the running sum before them;
+// -2: none, or too close to a boundary
+template <int N>
+__device__ __forceinline__ int32_t col_walk(const ColEntries &x, const float (&b)[N], float s, float y, float tol)
+{
+    int32_t at = -2;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const float hi = s + b[u];
+        if (b[u] > 0.0f && s <= y && hi > y) at = y - s > tol && hi - y > tol ? (int32_t)x.k[u] : -2;
+        s = hi;
+    }
+    return at;
+}
+
+// The block's draws in the dense layout (64 lanes; topic lists past SLOTS_MAX
+// slots a lane): each sums its word's column in fp32, the counts read by topic,
+// and decides as the draws over slots do; undecided ones are drawn in fp64.
+// Lane c keeps the running sum after chunk c, and the chunk that holds the
+// crossing is read once more.  What a draw reads from memory does not depend on
+// the draws before it, so the records of two words and the first entries of one
+// are loaded ahead.
+// tol: a chunk's running sum adds one rounding to the bound at the head of
+// this section, with SL = COL_B.
+template <bool STATS>
+__device__ __forceinline__ void draw_dense(const DevModel &M, const SlotDoc &S, const LaneTok &t, LaneDraw &d,
+                                           const uint32_t place, const uint32_t n_draws, const int g)
+{
+    // one token leaves or enters topic k (one lane); the count before
+    auto change = [&](uint32_t k, uint32_t by) {
+        const uint32_t shift = (k & 1u) << 4;
+        const uint32_t was = atomicAdd((uint32_t *)S.mt + (k >> 1), by << shift);
+        return STATS ? (float)__builtin_amdgcn_ubfe(was, shift, 16u) : 0.0f;
     };
     auto moves = [&](uint32_t i) {
-        for (uint32_t t = i << 7; __builtin_amdgcn_ballot_w64(d.key == t) != 0; ++t) {
-            if (d.key == t) {
-                d.ro = change(d.po, -1);
-                d.rn = change(d.pa, 1);
+        for (uint32_t key = i << 7; __builtin_amdgcn_ballot_w64(d.key == key) != 0; ++key) {
+            if (d.key == key) {
+                const float ro = change((uint32_t)d.po, 0xFFFFFFFFu), rn = change((uint32_t)d.pa, 1u);
+                if (STATS) {
+                    d.ro = ro;
+                    d.rn = rn;
+                }
             }
-            lds_order();
         }
     };
-    for (uint32_t i = 0; i < n_max; ++i) {
+    // (lane i: the token of draw i)
+    const int32_t token = __builtin_amdgcn_ds_permute((int)place << 2, g);
+    auto column = [&](uint32_t i) {
+        const int c = __builtin_amdgcn_readlane(token, (int)(i < n_draws ? i : 0u));
+        return column_of(M, __builtin_amdgcn_readlane(t.v, c));
+    };
+    auto head = [&](const Column &c) { return col_entries(M, c, g * (c.n <= 64 * COL_N ? COL_N : COL_B)); };
+    Column col = column(0), next = column(1);
+    ColEntries x = head(col);
+    for (uint32_t i = 0; i < n_draws; ++i) {
+        const Column after = column(i + 2);
+        const ColEntries xn = head(next);
         moves(i);
-        const DrawRec rec = S.tok[i];
-        const int c = rec.lane();
-        if (g == c) d.ro = change(d.po, -1);
-        lds_order();
-        double Z;
-        const int32_t vc = __shfl(v, c & (G - 1), G);
-        const int32_t at =
-            slots_draw_f64<G, true>(M, S, vc, rec.u0, 0, [&](int32_t, int32_t k) { return count_of(S, k); }, Z);
-        if (c < G) {
-            if (at >= 0) {
-                if (g == 0) {
-                    (void)change(at, 1);
-                    S.out[i] = (uint16_t)at;
+        const int c = __builtin_amdgcn_readlane(token, (int)i);
+        if (g == c) {
+            const float ro = change((uint32_t)d.po, 0xFFFFFFFFu);
+            if (STATS) d.ro = ro;
+        }
+        const float u0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t.u0), c));
+        const float sa = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t.saf), c));
+        float y, tol;
+        auto decide = [&](float T, int32_t chunks) {
+            const float Z = sa + T;
+            y = u0 * Z - sa;
+            tol = Z * ((float)(128 + 8 * chunks) * 0x1p-24f);
+            return __builtin_amdgcn_ballot_w64(y < -tol) != 0 ? -1 : -2;
+        };
+        int32_t k;   // the new topic; -1: the a-part, -2: undecided
+        if (col.n <= 64 * COL_N) {
+            float b[COL_N];
+            const float p = col_terms<COL_N, false>(S, x, col.n - g * COL_N, M.K, b);
+            const float incl = group_scan_incl_f32<64>(p);
+            k = decide(group_last_f32<64>(incl), 1);
+            const uint64_t lanes = __builtin_amdgcn_ballot_w64(incl > y && y > tol);
+            const int32_t at = col_walk<COL_N>(x, b, incl - p, y, tol);
+            if (lanes != 0) k = __builtin_amdgcn_readlane(at, __builtin_ctzll(lanes));
+        } else {
+            const int32_t chunks = col_chunks(col);
+            float b[COL_B], p = 0.0f, incl = 0.0f, T = 0.0f, ends = 0.0f;
+            int32_t ch = 0;
+            auto add = [&] {
+                incl = T + group_scan_incl_f32<64>(p);
+                T = group_last_f32<64>(incl);
+                ends = g == ch ? T : ends;
+            };
+            for (; ch + 1 < chunks; ++ch) {
+                const ColEntries ahead = col_entries(M, col, ((ch + 1) * 64 + g) * COL_B);
+                p = col_terms<COL_B, true>(S, x, 0, M.K, b);
+                add();
+                x = ahead;
+            }
+            p = col_terms<COL_B, false>(S, x, col.n - (ch * 64 + g) * COL_B, M.K, b);
+            add();
+            k = decide(T, chunks);
+            const uint64_t over = __builtin_amdgcn_ballot_w64(g < chunks && ends > y && y > tol);
+            if (over != 0) {
+                ch = __builtin_ctzll(over);
+                if (ch + 1 < chunks) {
+                    x = col_entries(M, col, (ch * 64 + g) * COL_B);
+                    p = col_terms<COL_B, true>(S, x, 0, M.K, b);
+                    incl = group_scan_incl_f32<64>(p);
+                    if (ch) incl += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ends), ch - 1));
                 }
-            } else if (g == c) {
-                d.rn = change(d.pa, 1);
-                d.a = 1;
+                const uint64_t lanes = __builtin_amdgcn_ballot_w64(incl > y);
+                const int32_t at = col_walk<COL_B>(x, b, incl - p, y, tol);
+                if (lanes != 0) k = __builtin_amdgcn_readlane(at, __builtin_ctzll(lanes));
             }
         }
+        if (__builtin_expect(k == -2, 0)) {
+            double Zd;
+            k = column_draw_f64(M, S, __builtin_amdgcn_readlane(t.v, c), u0, Zd);
+            if (g == c) d.fb = 1;
+        }
+        if (g == c) {
+            const float rn = change(k >= 0 ? (uint32_t)k : (uint32_t)d.pa, 1u);
+            if (STATS) d.rn = rn;
+            if (k >= 0) S.out[i] = (uint16_t)k;
+            else d.a = 1;
+        }
         lds_order();
+        col = next;
+        next = after;
+        x = xn;
     }
-    moves(n_max);
+    moves(n_draws);
 }
 
 // the block's records, in draw order, the lanes without a draw behind them
@@ -2170,14 +2356,11 @@ __device__ __forceinline__ int32_t draw_block(const DevModel &M, SlotDoc &S, con
     else if (!over(5)) PULDA_DRAW(5);
     else if (!BIG || !over(6)) PULDA_DRAW(6);
     else if constexpr (BIG) {
-        if (S.dense) {
-            stage_draws<G>(S, x, d, draws, place, g);
-            draw_dense<G>(M, S, x.v, d, n_max, g);
-        }
-        else if (!over(8)) PULDA_DRAW(8);
+        if (!over(8)) PULDA_DRAW(8);
         else if (!over(10)) PULDA_DRAW(10);
         else if (!over(12)) PULDA_DRAW(12);
-        else PULDA_DRAW(16);
+        else if (G < 64 || !S.dense) PULDA_DRAW(16);
+        else if constexpr (G == 64) draw_dense<STATS>(M, S, x, d, place, nd, g);
     }
 #undef PULDA_DRAW
 #undef PULDA_REGS
@@ -3352,16 +3535,17 @@ hipError_t launch_foldin_step(const DevModel &m, const DevFoldin &f, const int32
                               hipStream_t s)
 {
     if (n_active == 0) return hipSuccess;
-    const SlotLds A = slot_lds(f.group, m.K, f.max_len);
-    return launch_groups(m.K, f.group, n_active, A, [&](unsigned blocks, unsigned threads, size_t lds) {
+    const int32_t group = slots_group(f.group, m.K, f.max_len);
+    const SlotLds A = slot_lds(group, m.K, f.max_len);
+    return launch_groups(m.K, group, n_active, A, [&](unsigned blocks, unsigned threads, size_t lds) {
 #define PULDA_FOLDIN(G_, S_) foldin_step_kernel<G_, S_><<<blocks, threads, lds, s>>>(m, f, active, n_active, A)
         if (m.lg_alpha) {
-            if (f.group == 64) PULDA_FOLDIN(64, true);
-            else if (f.group == 32) PULDA_FOLDIN(32, true);
+            if (group == 64) PULDA_FOLDIN(64, true);
+            else if (group == 32) PULDA_FOLDIN(32, true);
             else PULDA_FOLDIN(16, true);
         } else {
-            if (f.group == 64) PULDA_FOLDIN(64, false);
-            else if (f.group == 32) PULDA_FOLDIN(32, false);
+            if (group == 64) PULDA_FOLDIN(64, false);
+            else if (group == 32) PULDA_FOLDIN(32, false);
             else PULDA_FOLDIN(16, false);
         }
 #undef PULDA_FOLDIN
@@ -3439,8 +3623,9 @@ __device__ __forceinline__ void ltr_particle(const DevModel &M, const DevHeldout
                 const int32_t ka = group_bcast<G>(x.ka, c);
                 double Z;
                 auto count = [&](int32_t, int32_t k) { return count_of(S, k); };
-                const int32_t at = S.dense ? slots_draw_f64<G, true>(M, S, v, u0, 0, count, Z)
-                                           : slots_draw_f64<G, false>(M, S, v, u0, (S.L + G - 1) / G, count, Z);
+                int32_t at;
+                if (G == 64 && S.dense) at = column_draw_f64(M, S, v, u0, Z);
+                else at = slots_draw_f64<G>(M, S, v, u0, (S.L + G - 1) / G, count, Z);
                 const int32_t k = at < 0 ? ka : topic_of(S, at);
                 if (g == 0) {
                     // (its bit may have been dropped with the block's counts)
@@ -3494,10 +3679,11 @@ __global__ void __launch_bounds__(256) ltr_finish_kernel(DevHeldout H)
 hipError_t launch_heldout(const DevModel &m, const DevHeldout &h, hipStream_t s)
 {
     if (h.D == 0) return hipSuccess;
-    const SlotLds A = slot_lds(h.group, m.K, h.longest);
-    hipError_t e = launch_groups(m.K, h.group, h.D * h.R, A, [&](unsigned blocks, unsigned threads, size_t lds) {
-        if (h.group == 64) ltr_kernel<64><<<blocks, threads, lds, s>>>(m, h, A);
-        else if (h.group == 32) ltr_kernel<32><<<blocks, threads, lds, s>>>(m, h, A);
+    const int32_t group = slots_group(h.group, m.K, h.longest);
+    const SlotLds A = slot_lds(group, m.K, h.longest);
+    hipError_t e = launch_groups(m.K, group, h.D * h.R, A, [&](unsigned blocks, unsigned threads, size_t lds) {
+        if (group == 64) ltr_kernel<64><<<blocks, threads, lds, s>>>(m, h, A);
+        else if (group == 32) ltr_kernel<32><<<blocks, threads, lds, s>>>(m, h, A);
         else ltr_kernel<16><<<blocks, threads, lds, s>>>(m, h, A);
     });
     if (e != hipSuccess) return e;
