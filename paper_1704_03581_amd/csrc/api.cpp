@@ -1476,7 +1476,7 @@ pulda_status pulda_foldin_step(pulda_foldin *f, int32_t draws, void *stream)
     f->stage_cur = b ^ 1;
     f->f.step_no = step_no;
     f->f.max_len = longest;
-    HIP_TRY(launch_foldin_step(f->model->m, f->f, f->active_dev, n_active, s));
+    HIP_TRY(launch_foldin_step(f->model->m, f->f, f->active_dev, n_active, f->model->n_cu, s));
     f->n_steps = step_no;
     HIP_TRY(hipEventRecord(f->step_ev[step_no & 1], s));
     for (int32_t j = 0; j < n_active; ++j) {

@@ -283,7 +283,7 @@ struct DevFoldin {
 };
 
 hipError_t launch_foldin_step(const DevModel &m, const DevFoldin &f, const int32_t *active, int32_t n_active,
-                              hipStream_t s);
+                              int32_t n_cu, hipStream_t s);
 
 // held-out log-likelihood of new documents (left-to-right estimate): the
 // region of document d's particle r in kw, z and Zs starts at

@@ -1456,9 +1456,18 @@ __device__ __forceinline__ void slots_counts(const SlotDoc &S, const uint32_t (&
 }
 
 template <int SL>
-__device__ __forceinline__ void slots_store(const SlotDoc &S, const uint32_t (&kk)[SL], int32_t e0, int32_t K,
+__device__ __forceinline__ void slots_store(const SlotDoc &S, const uint32_t (&topics)[SL], int32_t e0, int32_t K,
                                             const uint32_t (&c)[SL], bool drop)
 {
+    // (opaque to the compiler, which would otherwise keep the addresses of
+    // slots_counts, or spill them, throughout the block's draws)
+    uint32_t kk[SL];
+    asm volatile("" : "+v"(e0));
+#pragma unroll
+    for (int u = 0; u < SL; ++u) {
+        kk[u] = topics[u];
+        asm volatile("" : "+v"(kk[u]));
+    }
     if (S.wide) {
 #pragma unroll
         for (int u = 0; u < SL; ++u) ((uint16_t *)S.mt)[e0 + u < S.L ? kk[u] : (uint32_t)K] = (uint16_t)c[u];
@@ -1541,7 +1550,10 @@ template <int G, typename Count>
 __device__ __forceinline__ int32_t slots_draw_f64(const DevModel &M, const SlotDoc &S, int32_t v, float u0, int32_t per,
                                                   Count count, double &Z)
 {
-    const int g = __lane_id() & (G - 1);
+    // (opaque, or each number of slots' addresses of this seldom taken path
+    // are computed, and spilled, at the start of the kernel)
+    int g = __lane_id() & (G - 1);
+    asm volatile("" : "+v"(g));
     const int32_t e0 = g * per;
     const int32_t e1 = e0 + per < S.L ? e0 + per : S.L;
     // term of entry e (exact in fp64: a 24-bit phi times a count below 2^16;
@@ -2460,8 +2472,9 @@ __device__ __forceinline__ void z_step_item(const ZArgs &a, const WorkItem &w, c
 // GB at 6.3 TB/s, hence the 8-bit ones).  A document of 20,000 tokens on 64
 // lanes: 0.6 us a token (1.3 before), the latency of one draw's chain, about
 // 530 cycles, plus staging and layout, about 9,000 cycles a block of 64.
-template <int G, bool BIG, bool HOT>
-__global__ void __launch_bounds__(256, BIG ? 4 : 5) z_step_kernel(ZArgs a)
+// W: waves a SIMD that the registers leave room for (see fits_at_four_only).
+template <int G, bool BIG, bool HOT, int W>
+__global__ void __launch_bounds__(256, W) z_step_kernel(ZArgs a)
 {
     extern __shared__ __align__(16) uint8_t z_lds[];
     // fp32(R_k) for the fp32 b-terms (the fp64 path reads R_k from global
@@ -2764,6 +2777,15 @@ hipError_t launch_z_prepare(const DevModel &m, int32_t *queues, unsigned long lo
     return hipGetLastError();
 }
 
+// Registers of the token kernels.  At 4 waves a SIMD (128 registers) the
+// longest lists' kernels on 64 lanes spill 70 to 100 of them, at 3 (168) few or
+// none, and draw faster: z-step of 20,000 documents of 700 tokens at K = 1000
+// 2.67 and 2.37 ms.  But where the work is one wave each (a document, a
+// request) and fits the chip at once at 4 and not at 3, the second round costs
+// more: 4,000 documents of 3,000 tokens 3.86 and 4.31 ms, fold-in of 4,096
+// requests of 300 tokens at K = 100 2.97 and 3.39 ms.
+static bool fits_at_four_only(int64_t blocks, int32_t n_cu) { return blocks > 3 * (int64_t)n_cu && blocks <= 4 * (int64_t)n_cu; }
+
 hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, int32_t longest,
                           const WorkItem *items, int32_t n_items, int32_t n_cu, int32_t *queue, unsigned long long *stats,
                           double *ll_doc, hipStream_t s)
@@ -2822,10 +2844,17 @@ hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, 
         z_lane_kernel<<<(unsigned)blocks, 64, llds, s>>>(a);
         return hipGetLastError();
     }
-#define PULDA_Z(G_)                                                                                    \
-    (a.lds.slots > SLOTS_FEW ? launch(z_step_kernel<G_, true, false>, z_step_kernel<G_, true, true>) \
-                                 : launch(z_step_kernel<G_, false, false>, z_step_kernel<G_, false, true>))
-    if (group == 64) return PULDA_Z(64);
+    const bool big = a.lds.slots > SLOTS_FEW;
+    if (group == 64) {
+        if (!big) return launch(z_step_kernel<64, false, false, 3>, z_step_kernel<64, false, true, 3>);
+        // (more than 384 topics: no frequent words' counters)
+        if (fits_at_four_only(((int64_t)n_items + 3) / 4, n_cu))
+            return launch(z_step_kernel<64, true, false, 4>, z_step_kernel<64, true, false, 4>);
+        return launch(z_step_kernel<64, true, false, 3>, z_step_kernel<64, true, false, 3>);
+    }
+#define PULDA_Z(G_)                                                                                      \
+    (big ? launch(z_step_kernel<G_, true, false, 3>, z_step_kernel<G_, true, true, 3>)                   \
+         : launch(z_step_kernel<G_, false, false, 4>, z_step_kernel<G_, false, true, 4>))
     if (group == 32) return PULDA_Z(32);
     if (group == 16) return PULDA_Z(16);
     return PULDA_Z(8);
@@ -3478,8 +3507,9 @@ __device__ __forceinline__ void foldin_slot(const DevModel &M, const DevFoldin &
     if (done == F.sweeps) {
         const double denom = (double)kept + F.A;
         const double ns = (double)(F.sweeps - F.burn_in);
+        float *theta = F.theta + (acc - F.acc);
         for (int32_t k = g; k < K; k += G)
-            F.theta[(int64_t)sid * K + k] = (float)(((double)acc[k] / ns + M.alpha[k]) / denom);
+            theta[k] = (float)(((double)acc[k] / ns + M.alpha[k]) / denom);
         double part = 0.0;
         for (int32_t q = g; q < kept; q += G) part += log((double)phi_at(M, wds[q], zz[q]));
         // (topics in a fixed order, whatever the slots)
@@ -3499,8 +3529,8 @@ __device__ __forceinline__ void foldin_slot(const DevModel &M, const DevFoldin &
     }
 }
 
-template <int G, bool SYM>
-__global__ void __launch_bounds__(256, 4) foldin_step_kernel(DevModel M, DevFoldin F, const int32_t *active,
+template <int G, bool SYM, int W>
+__global__ void __launch_bounds__(256, W) foldin_step_kernel(DevModel M, DevFoldin F, const int32_t *active,
                                                           int32_t n_active, SlotLds A)
 {
     extern __shared__ __align__(16) uint8_t f_lds[];
@@ -3532,21 +3562,24 @@ static hipError_t launch_groups(int32_t K, int32_t G, int64_t groups, const Slot
 }
 
 hipError_t launch_foldin_step(const DevModel &m, const DevFoldin &f, const int32_t *active, int32_t n_active,
-                              hipStream_t s)
+                              int32_t n_cu, hipStream_t s)
 {
     if (n_active == 0) return hipSuccess;
     const int32_t group = slots_group(f.group, m.K, f.max_len);
     const SlotLds A = slot_lds(group, m.K, f.max_len);
     return launch_groups(m.K, group, n_active, A, [&](unsigned blocks, unsigned threads, size_t lds) {
-#define PULDA_FOLDIN(G_, S_) foldin_step_kernel<G_, S_><<<blocks, threads, lds, s>>>(m, f, active, n_active, A)
+#define PULDA_FOLDIN(G_, S_, W_) foldin_step_kernel<G_, S_, W_><<<blocks, threads, lds, s>>>(m, f, active, n_active, A)
+        const bool four = group == 64 && fits_at_four_only(blocks, n_cu);
         if (m.lg_alpha) {
-            if (group == 64) PULDA_FOLDIN(64, true);
-            else if (group == 32) PULDA_FOLDIN(32, true);
-            else PULDA_FOLDIN(16, true);
+            if (four) PULDA_FOLDIN(64, true, 4);
+            else if (group == 64) PULDA_FOLDIN(64, true, 3);
+            else if (group == 32) PULDA_FOLDIN(32, true, 3);
+            else PULDA_FOLDIN(16, true, 3);
         } else {
-            if (group == 64) PULDA_FOLDIN(64, false);
-            else if (group == 32) PULDA_FOLDIN(32, false);
-            else PULDA_FOLDIN(16, false);
+            if (four) PULDA_FOLDIN(64, false, 4);
+            else if (group == 64) PULDA_FOLDIN(64, false, 3);
+            else if (group == 32) PULDA_FOLDIN(32, false, 3);
+            else PULDA_FOLDIN(16, false, 3);
         }
 #undef PULDA_FOLDIN
     });
@@ -3642,7 +3675,7 @@ __device__ __forceinline__ void ltr_particle(const DevModel &M, const DevHeldout
 }
 
 template <int G>
-__global__ void __launch_bounds__(256, 4) ltr_kernel(DevModel M, DevHeldout H, SlotLds A)
+__global__ void __launch_bounds__(256, 3) ltr_kernel(DevModel M, DevHeldout H, SlotLds A)
 {
     extern __shared__ __align__(16) uint8_t h_lds[];
     float *R = (float *)h_lds;
