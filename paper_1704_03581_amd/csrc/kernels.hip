@@ -482,19 +482,21 @@ __global__ void __launch_bounds__(64 * PHI_DRAW_WAVES) phi_draw_kernel(DevModel 
             return make_uint4(x.x > 0 ? (uint32_t)x.x : 0u, x.y > 0 ? (uint32_t)x.y : 0u, x.z > 0 ? (uint32_t)x.z : 0u,
                               x.w > 0 ? (uint32_t)x.w : 0u);
         };
-        uint8_t *row = m.gam + draws_offset(m, fmt, v);
         if (fmt == ROW_8) {
+            uint8_t *row = m.gam + draws_offset(m, ROW_8, v);
             for (int32_t k = 4 * lane; k < kpad; k += 256) {
                 const uint4 x = row4(k);
                 *(uint32_t *)(row + k) = x.x | x.y << 8 | x.z << 16 | x.w << 24;
             }
         } else if (fmt == ROW_16) {
+            uint8_t *row = m.gam + draws_offset(m, ROW_16, v);
             for (int32_t k = 4 * lane; k < kpad; k += 256) {
                 const uint4 x = row4(k);
                 *(uint2 *)(row + 2 * k) = make_uint2(x.x | x.y << 16, x.z | x.w << 16);
             }
         } else {
-            for (int32_t k = lane; k < K; k += 64) ((int32_t *)row)[k] = g[k] > 0 ? g[k] : 0;
+            int32_t *row = (int32_t *)(m.gam + draws_offset(m, ROW_32, v));
+            for (int32_t k = lane; k < K; k += 64) row[k] = g[k] > 0 ? g[k] : 0;
         }
         cnt = group_scan_incl_i32<64>(cnt);
         if (lane == 63) {
@@ -962,7 +964,7 @@ __global__ void __launch_bounds__(SMALL ? 256 : 64) phi_alias_kernel(DevModel m)
     } else {
         const int32_t n = m.longcol[m.V];
         for (int32_t i = blockIdx.x; i < n; i += gridDim.x)
-            phi_column<false, DIR>(m, alias_lds, m.longcol[i], 0, m.ks16);
+            phi_column<false, DIR>(m, alias_lds, __builtin_amdgcn_readfirstlane(m.longcol[i]), 0, m.ks16);
     }
 }
 
