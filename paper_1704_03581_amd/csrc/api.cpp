@@ -670,6 +670,7 @@ pulda_status pulda_corpus_upload(pulda_plan *p, const int64_t *doc_off_dev, cons
         order[at] = (int32_t)d;
         p->len_sorted[at] = (int32_t)l;
     }
+    p->c.longest = p->D ? p->len_sorted[0] : 0;
     if (p->D) HIP_TRY(hipMemcpy((void *)p->c.doc_order, order.data(), p->D * 4, hipMemcpyHostToDevice));
     HIP_TRY(choose_hot_words(p));
     pulda_status st = build_items(p);

@@ -89,6 +89,7 @@ struct DevCorpus {
     const int32_t *words;
     uint16_t *z;
     const int32_t *doc_order;     // documents by decreasing length
+    int32_t longest;              // tokens of the longest
 };
 
 // a unit of z-step work: `count` documents of doc_order starting at `first`,

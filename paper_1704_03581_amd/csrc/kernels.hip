@@ -2906,8 +2906,9 @@ struct LLArgs {
     unsigned long long *nk;        // [K]
     DevCorpus c;
     const double *ll_doc;          // the documents' terms, or null: counted from z
-    const double *alpha, *lg_A;
+    const double *alpha, *lg_alpha, *lg_A;   // (lg_alpha: symmetric alpha only)
     int32_t symmetric;
+    int32_t longest;               // tokens past which a document is counted by a block
     uint32_t *done;                // blocks of the second launch that have finished
     double Vbeta, *out, *hist;
     const uint32_t *hist_idx;
@@ -2990,6 +2991,13 @@ __device__ __forceinline__ double ll_words(const LLArgs &a, unsigned long long *
 // cleared or read per document: the tokens clear what they counted.  The
 // offsets of 64 documents and the next document's first tokens are in flight
 // while one is counted.
+// A document much longer than a wave's share would be a chain behind all
+// others: the wave sets it aside, and the block then counts it together, with
+// the terms of its topics by table (a sum over tokens would depend on which of
+// the waves' tokens came first).  4,000 documents of 20 tokens and one of
+// 65,535: 360 us a log joint in a wave, 55 so.
+constexpr int32_t LL_LONG = 1024;  // fewest tokens of such a document
+constexpr int32_t LL_ASIDE = 32;   // of them per wave; the others stay in the wave
 constexpr int32_t LL_LOGS = 256;   // log(alpha + j) in LDS (symmetric alpha), and a zero
 constexpr int32_t LL_IDLE = 64;    // a count for each lane without a token
 
@@ -2998,8 +3006,14 @@ inline size_t ll_docs_lds(int32_t K)
     return (LL_LOGS + 1) * sizeof(double) + 4 * ((size_t)(K + 1) / 2 + LL_IDLE) * sizeof(uint32_t);
 }
 
-template <bool SYM>
-__device__ __forceinline__ double ll_docs(const LLArgs &a, uint8_t *lds)
+struct LLAside {
+    int32_t n[4], doc[4][LL_ASIDE];
+};
+
+// LONG: there are documents to set aside (a kernel of its own: the code for
+// them takes 3% more time where there are none)
+template <bool SYM, bool LONG>
+__device__ __forceinline__ double ll_docs(const LLArgs &a, uint8_t *lds, LLAside *aside)
 {
     const int lane = __lane_id(), wv = threadIdx.x >> 6;
     double *logs = (double *)lds;
@@ -3019,6 +3033,7 @@ __device__ __forceinline__ double ll_docs(const LLArgs &a, uint8_t *lds)
     constexpr int C = 4;   // 64-token chunks at a time
     const uint16_t *zl = a.c.z + lane;
     double acc = 0.0;
+    int32_t n_aside = 0;
     // C chunks of a document's tokens from token p
     auto load = [&](int64_t s, int32_t p, int32_t n, int32_t (&k)[C]) {
 #pragma unroll
@@ -3059,6 +3074,17 @@ __device__ __forceinline__ double ll_docs(const LLArgs &a, uint8_t *lds)
             len = (int32_t)(a.c.doc_off[db + lane + 1] - off);
             acc += a.lg_A[len];
         }
+        // (set aside: empty for the wave)
+        const uint64_t big = LONG ? __builtin_amdgcn_ballot_w64(len > a.longest) : 0;
+        if (big != 0) {
+            const int32_t at = n_aside + __builtin_popcountll(big & ((1ull << lane) - 1ull));
+            if (len > a.longest && at < LL_ASIDE) {
+                aside->doc[wv][at] = (int32_t)(db + lane);
+                len = 0;
+            }
+            n_aside += __builtin_popcountll(big);
+            n_aside = n_aside < LL_ASIDE ? n_aside : LL_ASIDE;
+        }
         int64_t s = 0;
         int32_t n = 0, z[C];
         auto next = [&](int i) {
@@ -3095,11 +3121,40 @@ __device__ __forceinline__ double ll_docs(const LLArgs &a, uint8_t *lds)
             lds_order();
         }
     }
+    if constexpr (!LONG) return acc;
+    // the documents set aside, the block's tables as one of K counts
+    if (lane == 0) aside->n[wv] = n_aside;
+    uint32_t *all = (uint32_t *)(lds + (LL_LOGS + 1) * sizeof(double));
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+        for (int32_t j = 0; j < aside->n[w]; ++j) {
+            const int32_t d = aside->doc[w][j];
+            const int64_t s = a.c.doc_off[d];
+            const int32_t n = (int32_t)(a.c.doc_off[d + 1] - s);
+            constexpr int U = 16;
+            for (int32_t p = threadIdx.x; p < n; p += 256 * U) {
+                int32_t k[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) k[u] = p + 256 * u < n ? a.c.z[s + p + 256 * u] : -1;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (k[u] >= 0) atomicAdd(&all[k[u]], 1u);
+            }
+            __syncthreads();
+            for (int32_t k = threadIdx.x; k < a.K; k += 256) {
+                const uint32_t c = all[k];
+                all[k] = 0;
+                if (SYM) acc += c ? a.lg_alpha[c] : 0.0;
+                else if (c) acc += lgamma((double)c + a.alpha[k]) - lgamma(a.alpha[k]);
+            }
+            __syncthreads();
+        }
+    }
     return acc;
 }
 
 // COUNT: documents counted from z; else their terms as the z-step left them
-template <bool COUNT>
+template <bool COUNT, bool LONG>
 __global__ void __launch_bounds__(256) ll_terms_kernel(LLArgs a)
 {
     extern __shared__ __align__(16) uint8_t ll_lds[];
@@ -3110,7 +3165,12 @@ __global__ void __launch_bounds__(256) ll_terms_kernel(LLArgs a)
         unsigned long long *sum = (unsigned long long *)ll_lds;
         acc = ll_words(a, sum);
     } else if constexpr (COUNT) {
-        acc = a.symmetric ? ll_docs<true>(a, ll_lds) : ll_docs<false>(a, ll_lds);
+        LLAside *aside = nullptr;
+        if constexpr (LONG) {
+            __shared__ LLAside lists;
+            aside = &lists;
+        }
+        acc = a.symmetric ? ll_docs<true, LONG>(a, ll_lds, aside) : ll_docs<false, LONG>(a, ll_lds, aside);
     } else {
         const int64_t per = (a.c.D + a.nd - 1) / a.nd;
         const int64_t d0 = (int64_t)(blockIdx.x - a.nw) * per, d1 = d0 + per < a.c.D ? d0 + per : a.c.D;
@@ -3192,8 +3252,16 @@ hipError_t launch_loglik(const DevCorpus &c, const DevModel &m, const LLSpace &s
     const int32_t share = (m.V + space.max_words - 1) / space.max_words, least = 4096 / m.K + 4;
     a.words = share > least ? share : least;
     a.nw = (m.V + a.words - 1) / a.words;
-    const int64_t docs = ll_doc ? (c.D + LL_DOCS - 1) / LL_DOCS : (c.D + 15) / 16;
+    // a block for 16 documents; for 4,096 tokens while that is more and there
+    // are few (long documents on an idle chip)
+    int64_t docs = (c.D + LL_DOCS - 1) / LL_DOCS;
+    if (!ll_doc) {
+        const int64_t few = c.N / 4096 < 512 ? c.N / 4096 : 512;
+        docs = (c.D + 15) / 16 > few ? (c.D + 15) / 16 : few;
+    }
     a.nd = (int32_t)(docs < 1 ? 1 : (docs < space.max_docs ? docs : space.max_docs));
+    const int64_t share_tokens = c.N / (4 * (int64_t)a.nd);   // of a wave
+    a.longest = (int32_t)(share_tokens < LL_LONG ? LL_LONG : (share_tokens < 65536 ? share_tokens : 65536));
     a.beta = m.beta;
     a.lgb = lgamma(m.beta);
     a.lg_beta = m.lg_beta;
@@ -3204,6 +3272,7 @@ hipError_t launch_loglik(const DevCorpus &c, const DevModel &m, const LLSpace &s
     a.c = c;
     a.ll_doc = ll_doc;
     a.alpha = m.alpha;
+    a.lg_alpha = m.lg_alpha;
     a.lg_A = m.lg_A;
     a.symmetric = m.lg_alpha != nullptr;
     a.done = space.done;
@@ -3215,10 +3284,11 @@ hipError_t launch_loglik(const DevCorpus &c, const DevModel &m, const LLSpace &s
     a.advance_hist = hist_idx;
     const size_t sums = (size_t)m.K * 8;
     if (ll_doc) {
-        ll_terms_kernel<false><<<a.nw + a.nd, 256, sums, s>>>(a);
+        ll_terms_kernel<false, false><<<a.nw + a.nd, 256, sums, s>>>(a);
     } else {
-        const size_t tables = ll_docs_lds(m.K);
-        ll_terms_kernel<true><<<a.nw + a.nd, 256, sums > tables ? sums : tables, s>>>(a);
+        const size_t tables = ll_docs_lds(m.K), lds = sums > tables ? sums : tables;
+        if (c.longest > a.longest) ll_terms_kernel<true, true><<<a.nw + a.nd, 256, lds, s>>>(a);
+        else ll_terms_kernel<true, false><<<a.nw + a.nd, 256, lds, s>>>(a);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
