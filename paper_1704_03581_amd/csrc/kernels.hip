@@ -2550,13 +2550,14 @@ __device__ __forceinline__ int32_t lane_lower_bound(const uint16_t *kl, int32_t 
     return lo;
 }
 
-// one block of the lane's list: b-terms of entries [j0, j0 + 8) (zero past L)
+// one block of the lane's list: b-terms of entries [j0, j0 + 8) (zero past L,
+// and for a topic without a count, whatever its loaded phi)
+template <bool VALUES>
 __device__ __forceinline__ void lane_block_terms(const uint16_t *kl, const uint8_t *ml, int32_t L, int32_t j0,
                                                  const DevModel &M, uint32_t row, uint32_t fmt,
                                                  int32_t (&kk)[LANE_BLK], double (&bb)[LANE_BLK])
 {
     uint32_t mm[LANE_BLK], xx[LANE_BLK];
-    double rr[LANE_BLK];
 #pragma unroll
     for (int u = 0; u < LANE_BLK; ++u) {
         const bool ok = j0 + u < L;
@@ -2566,10 +2567,17 @@ __device__ __forceinline__ void lane_block_terms(const uint16_t *kl, const uint8
         kk[u] = ok ? k : 0;
         mm[u] = ok ? m : 0u;
     }
+    if constexpr (VALUES) {
+#pragma unroll
+        for (int u = 0; u < LANE_BLK; ++u) xx[u] = load_u32_at(M.phid, row + ((uint32_t)kk[u] << 2));
+#pragma unroll
+        for (int u = 0; u < LANE_BLK; ++u) bb[u] = (double)(mm[u] ? __uint_as_float(xx[u]) : 0.0f) * (double)mm[u];
+        return;
+    }
+    double rr[LANE_BLK];
 #pragma unroll
     for (int u = 0; u < LANE_BLK; ++u) {
-        xx[u] = load_u32_at(M.values ? (const void *)M.phid : (const void *)M.gam, row + ((uint32_t)kk[u] << fmt)) &
-                row_mask(fmt);
+        xx[u] = load_u32_at(M.gam, row + ((uint32_t)kk[u] << fmt)) & row_mask(fmt);
         rr[u] = M.Rd[kk[u]];
     }
     // phi_kv = fp32(x * R_k) == fp32(RN64(x / S_k)) for x < 0xFFFF and
@@ -2578,18 +2586,19 @@ __device__ __forceinline__ void lane_block_terms(const uint16_t *kl, const uint8
     bool far = false;
 #pragma unroll
     for (int u = 0; u < LANE_BLK; ++u) {
-        fk[u] = M.values ? __uint_as_float(xx[u]) : (float)((double)xx[u] * rr[u]);
+        fk[u] = (float)((double)xx[u] * rr[u]);
         far |= xx[u] && (xx[u] >= 0xFFFFu || rr[u] <= 0x1p-27);
     }
-    if (!M.values && __builtin_amdgcn_ballot_w64(far)) {
+    if (__builtin_amdgcn_ballot_w64(far)) {
 #pragma unroll
         for (int u = 0; u < LANE_BLK; ++u)
             if (xx[u] && (xx[u] >= 0xFFFFu || rr[u] <= 0x1p-27)) fk[u] = (float)((double)xx[u] / (double)M.S[kk[u]]);
     }
 #pragma unroll
-    for (int u = 0; u < LANE_BLK; ++u) bb[u] = (double)(mm[u] ? fk[u] : 0.0f) * (double)mm[u];
+    for (int u = 0; u < LANE_BLK; ++u) bb[u] = (double)fk[u] * (double)mm[u];
 }
 
+template <bool VALUES>
 __global__ void __launch_bounds__(64) z_lane_kernel(ZArgs a)
 {
     struct ZCount {
@@ -2648,8 +2657,8 @@ __global__ void __launch_bounds__(64) z_lane_kernel(ZArgs a)
                     ml[po * 64] = (uint8_t)(mo - 1);
                     const int32_t Kd = L - (mo == 1 ? 1 : 0);
                     cnt.J += (unsigned long long)(Kd < Kv ? Kd : Kv);
-                    const uint32_t fmt = M.wrec[v].y >> 30;
-                    const uint32_t row = row_offset(M, fmt, v);
+                    const uint32_t fmt = VALUES ? ROW_32 : M.wrec[v].y >> 30;
+                    const uint32_t row = VALUES ? (uint32_t)v * (uint32_t)M.K * 4u : draws_offset(M, fmt, v);
                     // sigma_b over the list, ascending, with the running sum after each block
                     double bs[LANE_NBLK];
                     double sb = 0.0;
@@ -2660,7 +2669,7 @@ __global__ void __launch_bounds__(64) z_lane_kernel(ZArgs a)
                         if (!__builtin_amdgcn_ballot_w64(blk * LANE_BLK < L)) continue;
                         int32_t kk[LANE_BLK];
                         double bb[LANE_BLK];
-                        lane_block_terms(kl, ml, L, blk * LANE_BLK, M, row, fmt, kk, bb);
+                        lane_block_terms<VALUES>(kl, ml, L, blk * LANE_BLK, M, row, fmt, kk, bb);
     #pragma unroll
                         for (int u = 0; u < LANE_BLK; ++u) {
                             sb += bb[u];
@@ -2688,7 +2697,7 @@ __global__ void __launch_bounds__(64) z_lane_kernel(ZArgs a)
                         if (blk >= 0) {
                             int32_t kk[LANE_BLK];
                             double bb[LANE_BLK];
-                            lane_block_terms(kl, ml, L, blk * LANE_BLK, M, row, fmt, kk, bb);
+                            lane_block_terms<VALUES>(kl, ml, L, blk * LANE_BLK, M, row, fmt, kk, bb);
                             double c = c0;
     #pragma unroll
                             for (int u = 0; u < LANE_BLK; ++u) {
@@ -2837,13 +2846,14 @@ hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, 
     if (group == 1) {
         // one document per lane: 64-thread blocks, the lanes' topic lists
         const size_t llds = (size_t)LANE_CAP * 64 * 3;
+        auto kernel = m.values ? z_lane_kernel<true> : z_lane_kernel<false>;
         int per_cu = 0;
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, z_lane_kernel, 64, llds);
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64, llds);
         if (e != hipSuccess) return e;
         if (per_cu <= 0) return hipErrorInvalidConfiguration;
         int64_t blocks = (int64_t)per_cu * (n_cu > 0 ? n_cu : 1);
         if (blocks > n_items) blocks = n_items;
-        z_lane_kernel<<<(unsigned)blocks, 64, llds, s>>>(a);
+        kernel<<<(unsigned)blocks, 64, llds, s>>>(a);
         return hipGetLastError();
     }
     const bool big = a.lds.slots > SLOTS_FEW;
