@@ -514,20 +514,15 @@ __global__ void __launch_bounds__(64 * PHI_DRAW_WAVES) phi_draw_kernel(DevModel 
 // the rows of partial sums (16 topics each, 64 threads to a topic): S_k, 1 /
 // S_k and the empty topics.  The scan's blocks (the first) turn the columns'
 // nonzeros into offsets: each adds up all columns before its own by itself,
-// from L2 (V/2 counts on average, a few microseconds for 141,000 words),
-// which takes one launch instead of three.  It also lists the columns with
-// more than ALIAS_SMALL nonzeros, in order.
+// from L2 (V/2 counts on average), which takes one launch instead of three.
+// Past COLS_BLOCKS tiles, where that costs more than another launch, one before
+// sums each tile up: V = 200,000 11 us instead of 21, 2M 16 instead of 184, 16M
+// 69 instead of 1,813.  It also lists the columns with more than ALIAS_SMALL
+// nonzeros, in order.
 // ---------------------------------------------------------------------------
 constexpr int32_t ALIAS_SMALL = 256;
-constexpr int32_t COLS_TILE = 4096;    // columns per turn of a block, four a thread
-constexpr int32_t COLS_BLOCKS = 64;    // most blocks of the scan
-
-// columns per block of the scan
-static inline int32_t cols_per_block(int32_t V)
-{
-    const int32_t tiles = (V + COLS_TILE - 1) / COLS_TILE;
-    return (tiles + COLS_BLOCKS - 1) / COLS_BLOCKS * COLS_TILE;
-}
+constexpr int32_t COLS_TILE = 4096;    // columns of a block, four a thread
+constexpr int32_t COLS_BLOCKS = 16;    // most blocks that add up the columns before their own
 
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
 {
@@ -535,7 +530,32 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
     return x;
 }
 
-__global__ void __launch_bounds__(1024) phi_sums_kernel(DevModel m, int32_t per, int32_t scan_blocks,
+// a column's nonzeros in the low 32 bits (fewer than 2^31 in all), one for a
+// long column in the high
+__device__ __forceinline__ unsigned long long col_val(int32_t c)
+{
+    return (unsigned long long)(uint32_t)c | ((unsigned long long)(c > ALIAS_SMALL) << 32);
+}
+
+// sum of a tile's columns
+__global__ void __launch_bounds__(1024) cols_tiles_kernel(DevModel m, unsigned long long *tiles)
+{
+    __shared__ unsigned long long red[16];
+    const int32_t v = blockIdx.x * COLS_TILE + 4 * threadIdx.x;
+    unsigned long long t = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t += v + u < m.V ? col_val(m.colcnt[v + u]) : 0;
+    t = wave_sum_u64(t);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int j = 1; j < 16; ++j) t += red[j];
+        tiles[blockIdx.x] = t;
+    }
+}
+
+// (tiles: the sums of the tiles, or null)
+__global__ void __launch_bounds__(1024) phi_sums_kernel(DevModel m, int32_t scan_blocks, const unsigned long long *tiles,
                                                         const unsigned long long *part, int32_t rows,
                                                         unsigned long long *stats)
 {
@@ -567,51 +587,49 @@ __global__ void __launch_bounds__(1024) phi_sums_kernel(DevModel m, int32_t per,
         }
         return;
     }
-    // nonzeros in the low 32 bits (fewer than 2^31 in all), long columns in the high
-    auto val = [](int32_t c) {
-        return (unsigned long long)(uint32_t)c | ((unsigned long long)(c > ALIAS_SMALL) << 32);
-    };
-    const int32_t v0 = (int32_t)blockIdx.x * per;
-    const int32_t v1 = v0 + per < m.V ? v0 + per : m.V;
+    const int32_t v0 = (int32_t)blockIdx.x * COLS_TILE;
+    const int32_t v1 = v0 + COLS_TILE < m.V ? v0 + COLS_TILE : m.V;
     unsigned long long t = 0;
-    for (int32_t v = 4 * tid; v < v0; v += 4 * 1024) {
-        const int4 c = *(const int4 *)&m.colcnt[v];   // (v0 is a multiple of four)
-        t += (val(c.x) + val(c.y)) + (val(c.z) + val(c.w));
+    if (tiles) {
+        for (int32_t i = tid; i < (int32_t)blockIdx.x; i += 1024) t += tiles[i];
+    } else {
+        for (int32_t v = 4 * tid; v < v0; v += 4 * 1024) {
+            const int4 c = *(const int4 *)&m.colcnt[v];   // (v0 is a multiple of four)
+            t += (col_val(c.x) + col_val(c.y)) + (col_val(c.z) + col_val(c.w));
+        }
     }
     t = wave_sum_u64(t);
     if (lane == 0) red[w] = t;
     __syncthreads();
     unsigned long long base = 0;
     for (int j = 0; j < 16; ++j) base += red[j];
-    for (int32_t u0 = v0; u0 < v1; u0 += COLS_TILE) {
-        const int32_t v = u0 + 4 * tid;
-        unsigned long long c[4], own = 0;
+    const int32_t v = v0 + 4 * tid;
+    unsigned long long c[4], own = 0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            c[u] = v + u < v1 ? val(m.colcnt[v + u]) : 0;
-            own += c[u];
-        }
-        unsigned long long incl = own;
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned long long y = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += y;
-        }
-        __syncthreads();
-        if (lane == 63) red[w] = incl;
-        __syncthreads();
-        unsigned long long at = base + incl - own;
-        for (int j = 0; j < 16; ++j) {
-            at += j < w ? red[j] : 0;
-            base += red[j];
-        }
+    for (int u = 0; u < 4; ++u) {
+        c[u] = v + u < v1 ? col_val(m.colcnt[v + u]) : 0;
+        own += c[u];
+    }
+    unsigned long long incl = own;
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    __syncthreads();
+    if (lane == 63) red[w] = incl;
+    __syncthreads();
+    unsigned long long at = base + incl - own;
+    for (int j = 0; j < 16; ++j) {
+        at += j < w ? red[j] : 0;
+        base += red[j];
+    }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (v + u < v1) {
-                m.colptr[v + u] = (int32_t)(uint32_t)at;
-                if (c[u] >> 32) m.longcol[at >> 32] = v + u;
-            }
-            at += c[u];
+    for (int u = 0; u < 4; ++u) {
+        if (v + u < v1) {
+            m.colptr[v + u] = (int32_t)(uint32_t)at;
+            if (c[u] >> 32) m.longcol[at >> 32] = v + u;
         }
+        at += c[u];
     }
     if (v1 == m.V && tid == 0) {
         m.colptr[m.V] = (int32_t)(uint32_t)base;
@@ -624,9 +642,15 @@ __global__ void __launch_bounds__(1024) phi_sums_kernel(DevModel m, int32_t per,
 static hipError_t launch_phi_sums(const DevModel &m, const unsigned long long *part, int32_t rows,
                                   unsigned long long *stats, hipStream_t s)
 {
-    const int32_t per = cols_per_block(m.V);
-    const int32_t nb = (m.V + per - 1) / per;
-    phi_sums_kernel<<<nb + (rows ? (m.K + 15) / 16 : 0), 1024, 0, s>>>(m, per, nb, part, rows, stats);
+    const int32_t nb = (m.V + COLS_TILE - 1) / COLS_TILE;
+    unsigned long long *tiles = nullptr;
+    if (nb > COLS_BLOCKS) {
+        tiles = (unsigned long long *)m.scratch;
+        cols_tiles_kernel<<<nb, 1024, 0, s>>>(m, tiles);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    phi_sums_kernel<<<nb + (rows ? (m.K + 15) / 16 : 0), 1024, 0, s>>>(m, nb, tiles, part, rows, stats);
     return hipGetLastError();
 }
 
