@@ -570,7 +570,6 @@ static pulda_status build_items(pulda_plan *p)
         for (int64_t s = start; s < pos;) {
             WorkItem w;
             w.first = (int32_t)s;
-            w.side_ratio = p->side[b];
             // documents are in decreasing length: the first is the longest
             const bool narrow = p->len_sorted[s] < 256;
             // the bucket's group size, or the next larger one that fits
@@ -1134,7 +1133,7 @@ pulda_status pulda_autotune(pulda_plan *p, uint32_t t, int32_t reps, void *strea
             per = docs_per_item(hi - lo, per, gsz, p->n_cu);
             std::vector<WorkItem> items;
             for (int64_t q = lo; q < hi; q += per)
-                items.push_back({(int32_t)q, (int32_t)std::min<int64_t>(per, hi - q), gsz, p->side[b]});
+                items.push_back({(int32_t)q, (int32_t)std::min<int64_t>(per, hi - q), gsz});
             HIP_TRY(hipMemcpyAsync(p->items, items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice, s));
             float total = 0;
             for (int r = 0; r <= reps; ++r) {

@@ -93,9 +93,9 @@ struct DevCorpus {
 };
 
 // a unit of z-step work: `count` documents of doc_order starting at `first`,
-// processed by groups of `group` lanes (side_ratio: of the schedule, unused)
+// processed by groups of `group` lanes
 struct WorkItem {
-    int32_t first, count, group, side_ratio;
+    int32_t first, count, group;
 };
 
 // The z-step's slots per lane: a draw handles up to SLOTS_MAX a lane with
