@@ -335,8 +335,8 @@ typedef struct {
     int32_t max_slots;    /* requests resident at once */
     int32_t arena_tokens; /* device token capacity shared by resident requests */
     int32_t max_len;      /* longest accepted request, <= arena_tokens, <= 65535 */
-    int32_t group;        /* lanes per request: 16, 32 or 64; a step with a request that may hold more
-                             topics than 16 a lane runs on the next larger that holds them (64 takes all) */
+    int32_t group;        /* lanes per request: 16, 32 or 64; more for requests whose topics are not
+                             likely to fit 16 a lane */
     uint64_t seed;
 } pulda_foldin_desc;
 
@@ -421,7 +421,7 @@ pulda_status pulda_foldin_occupancy(const pulda_foldin *f, int32_t *resident, in
  *   req_dev[D]: request ids; particle r's draw of token q at step n uses
  *     Philox counter (q, n, req, 7 + 256 r) under seed.
  *   particles in [1, 2^24); group: lanes per particle (16, 32, 64;
- *   more where the longest document may hold more topics than 16 a lane).
+ *   more for documents whose topics are not likely to fit 16 a lane).
  *   workspace_dev: pulda_heldout_workspace_bytes(model, D, N, particles) bytes,
  *     256-byte aligned, caller-owned.
  *   ll_dev[D] (fp64) and kept_dev[D] (kept tokens) are written; Z_dev (R*N

@@ -1354,7 +1354,6 @@ pulda_status pulda_foldin_bind(pulda_foldin *f, void *ws, int64_t bytes)
     DevFoldin &F = f->f;
     F.sweeps = f->desc.sweeps;
     F.burn_in = f->desc.burn_in;
-    F.group = f->desc.group;
     F.key0 = (uint32_t)f->desc.seed;
     F.key1 = (uint32_t)(f->desc.seed >> 32);
     F.A = f->model->A;
@@ -1454,7 +1453,7 @@ pulda_status pulda_foldin_step(pulda_foldin *f, int32_t draws, void *stream)
     const int32_t S = f->desc.max_slots;
     FoldSlot *slots_pin = (FoldSlot *)f->stage_ctl[b];
     int32_t *active = (int32_t *)(f->stage_ctl[b] + (size_t)S * sizeof(FoldSlot));
-    int32_t n_active = 0, longest = 0;
+    int32_t n_active = 0, n_wide = 0, longest = 0, wide_len = 0;
     const int64_t step_no = f->n_steps + 1;
     for (int32_t i = 0; i < S; ++i) {
         FoldSlot &sl = f->slots[i];
@@ -1468,6 +1467,21 @@ pulda_status pulda_foldin_step(pulda_foldin *f, int32_t draws, void *stream)
         }
     }
     if (n_active == 0) return PULDA_OK;
+    // lanes by the longest request: all on 16, or on 32 and those that are not
+    // likely to fit these on 64, first
+    const int32_t K = f->model->K;
+    int32_t group = f->desc.group;
+    if (group == 16 && !slots_likely(16, K, longest)) group = 32;
+    if (group == 32 && !slots_likely(32, K, longest)) {
+        wide_len = longest;
+        longest = 0;
+        for (int32_t j = 0; j < n_active; ++j) {
+            const int32_t len = f->slots[active[j]].len;
+            if (slots_likely(32, K, len)) longest = std::max(longest, len);
+            else std::swap(active[n_wide++], active[j]);
+        }
+    }
+    f->f.group = group;
     std::memcpy(slots_pin, f->slots.data(), (size_t)S * sizeof(FoldSlot));
     HIP_TRY(hipMemcpyAsync(f->slots_dev, slots_pin, (size_t)S * sizeof(FoldSlot), hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(f->active_dev, active, (size_t)n_active * 4, hipMemcpyHostToDevice, s));
@@ -1475,6 +1489,8 @@ pulda_status pulda_foldin_step(pulda_foldin *f, int32_t draws, void *stream)
     f->stage_used[b] = true;
     f->stage_cur = b ^ 1;
     f->f.step_no = step_no;
+    f->f.n_wide = n_wide;
+    f->f.wide_len = wide_len;
     f->f.max_len = longest;
     HIP_TRY(launch_foldin_step(f->model->m, f->f, f->active_dev, n_active, f->model->n_cu, s));
     f->n_steps = step_no;
@@ -1664,7 +1680,11 @@ static pulda_status heldout_run(const pulda_plan *model, int64_t D, const int64_
     h.D = D;
     h.R = particles;
     h.group = group;
-    h.longest = (int32_t)(off[order[0] + 1] - off[order[0]]);
+    auto len = [&](int64_t i) { return (int32_t)(off[order[i] + 1] - off[order[i]]); };
+    if (group == 16 && !slots_likely(16, model->K, len(0))) h.group = 32;
+    while (h.group == 32 && h.n_wide < D && !slots_likely(32, model->K, len(h.n_wide))) ++h.n_wide;
+    h.wide_len = h.n_wide ? len(0) : 0;
+    h.longest = h.n_wide < D ? len(h.n_wide) : 0;
     h.key0 = (uint32_t)seed;
     h.key1 = (uint32_t)(seed >> 32);
     h.A = model->A;

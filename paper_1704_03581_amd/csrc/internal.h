@@ -1,6 +1,7 @@
 // Internal declarations shared by the kernels and the C ABI (not installed).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <utility>
@@ -160,13 +161,12 @@ inline bool slots_fit(int32_t G, int32_t K, int32_t longest)
     return (K < longest + G ? K : longest + G) <= SLOTS_MAX * G;
 }
 
-// lanes for fold-in and held-out documents of at most `longest` tokens: the
-// group asked for, or the next larger that their slots fit (64 lanes take
-// every document)
-inline int32_t slots_group(int32_t group, int32_t K, int32_t longest)
+// They do for as many topics as tokens of uniform topics are expected to hold:
+// lanes for fold-in and held-out documents (a list that passes its slots all
+// the same is drawn slowly)
+inline bool slots_likely(int32_t G, int32_t K, int32_t tokens)
 {
-    while (group < 64 && !slots_fit(group, K, longest)) group *= 2;
-    return group;
+    return K * (1.0 - exp(-(double)tokens / K)) + G <= (double)(SLOTS_MAX * G);
 }
 
 // a z-step group size fits documents of at most `longest` tokens when their
@@ -266,7 +266,10 @@ struct FoldSlot {
 
 struct DevFoldin {
     int32_t sweeps, burn_in, group;
-    int32_t max_len;        // longest request of the step
+    // the step's requests whose topics are not likely to fit the slots of
+    // `group` lanes (32): the first n_wide active ones, on 64 lanes; longest
+    // request of them, of the others
+    int32_t n_wide, wide_len, max_len;
     uint32_t key0, key1;
     double A;
     const FoldSlot *slots;  // [max_slots] control, written by the host
@@ -292,7 +295,11 @@ hipError_t launch_foldin_step(const DevModel &m, const DevFoldin &f, const int32
 struct DevHeldout {
     int64_t D;
     int32_t R, group;
-    int32_t longest;           // tokens of the longest document
+    // the documents whose topics are not likely to fit the slots of `group`
+    // lanes (32): the first n_wide of the order, on 64 lanes; tokens of the
+    // longest of them, of the others
+    int64_t n_wide;
+    int32_t wide_len, longest;
     uint32_t key0, key1;
     double A;                  // sum_k alpha_k
     const int64_t *doc_off;    // [D+1]

@@ -1242,10 +1242,11 @@ hipError_t launch_phi_step_dirichlet(const DevModel &m, unsigned long long *stat
 // ten thousand) slots_draw_f64 decides in fp64.  So the result is the fp64 one bit
 // for bit, whatever the split of the topics over lanes.
 //
-// A document whose topics could pass SLOTS_MAX slots a lane takes more lanes;
-// on 64 (where that needs K > 1024) its list turns dense once it is longer:
-// slot = topic, and every draw sums the word's Phi column with the counts read
-// by topic (draw_dense).
+// A document whose topics could pass SLOTS_MAX slots a lane takes more lanes (in
+// fold-in and held-out calls: one whose topics are likely to); on 64, where that
+// needs K > 1024, its list turns dense once it is longer: slot = topic, and every
+// draw sums the word's Phi column with the counts read by topic (draw_dense;
+// draw_overflow on fewer lanes).
 //
 // What bounds it: the draws of a document are a serial chain (LDS add, LDS
 // read, the scan, the decision), so a long document is bound by the chain's
@@ -1441,7 +1442,7 @@ __device__ __forceinline__ void slots_layout(SlotDoc &S, const SlotLds &A, int32
         }
     const int32_t incl = group_scan_incl_i32<G>(n);
     const int32_t L = group_bcast<G>(incl, G - 1);
-    if (BIG && G == 64 && (S.dense || L > SLOTS_MAX * 64)) {
+    if (BIG && __builtin_amdgcn_ballot_w64(S.dense || L > SLOTS_MAX * G) != 0) {
         S.dense = true;
         S.L = K;
         return;
@@ -1629,13 +1630,13 @@ __device__ __forceinline__ Column column_of(const DevModel &M, int32_t v)
     return {rec.x, (int32_t)(rec.y & WREC_LOW)};
 }
 
-// A column on 64 lanes: chunks of 64 N entries, N neighbours a lane, so that a
-// chunk is a few contiguous loads; N = COL_N (one chunk) for columns of up to
-// 64 COL_N entries, COL_B for longer ones
+// A column on G lanes: chunks of G N entries, N neighbours a lane, so that a chunk
+// is a few contiguous loads; on 64 lanes N = COL_N (one chunk) for columns of up
+// to 64 COL_N entries, COL_B for longer ones
 constexpr int COL_N = 4, COL_B = COL_PAD;
-static_assert(4096 <= 64 * 64 * COL_B, "a lane per chunk");
 
-__device__ __forceinline__ int32_t col_chunks(const Column &c) { return (c.n + 64 * COL_B - 1) / (64 * COL_B); }
+template <int G>
+__device__ __forceinline__ int32_t col_chunks(const Column &c) { return (c.n + G * COL_B - 1) / (G * COL_B); }
 
 struct ColEntries {
     float f[COL_B];
@@ -1652,62 +1653,67 @@ __device__ __forceinline__ ColEntries col_entries(const DevModel &M, const Colum
     return x;
 }
 
-// the count of topic k in the dense layout (documents of 960 tokens and more:
-// two bytes)
+// the count of topic k in the dense layout of 64 lanes (documents of 960 tokens
+// and more: two bytes)
 __device__ __forceinline__ uint32_t dense_count(const SlotDoc &S, int32_t k) { return ((const uint16_t *)S.mt)[k]; }
 
-// The draw in fp64 over the word's column on 64 lanes, the counts read by
-// topic; lane b keeps the running sum after chunk b.  Returns the new topic, or
-// -1 for the a-part.
+// The draw in fp64 over the word's column, the counts read by topic: the sum of
+// its chunks, then once more up to the chunk that holds the crossing.  Returns
+// the new topic, or -1 for the a-part.
+template <int G>
 __device__ __forceinline__ int32_t column_draw_f64(const DevModel &M, const SlotDoc &S, int32_t v, float u0, double &Z)
 {
-    const int g = __lane_id();
+    int g = __lane_id() & (G - 1);
+    asm volatile("" : "+v"(g));
     const Column col = column_of(M, v);
-    const int32_t chunks = col_chunks(col);
+    const int32_t chunks = col_chunks<G>(col);
     ColEntries x = {};
     double b[COL_B], p = 0.0;
     auto terms = [&](int32_t ch) {
-        x = col_entries(M, col, (ch * 64 + g) * COL_B);
-        const int32_t own = col.n - (ch * 64 + g) * COL_B;
+        x = col_entries(M, col, (ch * G + g) * COL_B);
+        const int32_t own = col.n - (ch * G + g) * COL_B;
         p = 0.0;
 #pragma unroll
         for (int u = 0; u < COL_B; ++u) {
-            const uint32_t c = u < own ? dense_count(S, x.k[u]) : 0u;
+            const uint32_t c = u < own ? (G == 64 ? dense_count(S, x.k[u]) : count_of(S, x.k[u])) : 0u;
             b[u] = c ? (double)x.f[u] * (double)c : 0.0;
             p += b[u];
         }
     };
-    double T = 0.0, ends = 0.0;
-    int32_t last = -1;   // the last chunk with a positive term
+    double T = 0.0;
 #pragma unroll 1
     for (int32_t ch = 0; ch < chunks; ++ch) {
         terms(ch);
-        T = group_bcast_f64<64>(T + group_scan_incl<64>(p), 63);
-        ends = g == ch ? T : ends;
-        if (__builtin_amdgcn_ballot_w64(p > 0.0) != 0) last = ch;
+        T = group_bcast_f64<G>(T + group_scan_incl<G>(p), G - 1);
     }
     const double sa = M.sigma_a[v];
     Z = sa + T;
     const double xz = (double)u0 * Z;
-    if (xz < sa || last < 0) return -1;
+    if (xz < sa) return -1;
     const double y = xz - sa;
-    const uint64_t over = __builtin_amdgcn_ballot_w64(g < chunks && ends > y);
-    const int32_t ch = over != 0 ? __builtin_ctzll(over) : last;
-    terms(ch);
-    const double incl = (ch ? group_bcast_f64<64>(ends, ch - 1) : 0.0) + group_scan_incl<64>(p);
-    const int f = crossing_lane<64>(incl, p, y);
-    double c = incl - p;
-    int32_t k = -1;
-    bool found = false;
+    double before = 0.0;
+    int32_t k = -1;      // (where rounding leaves no crossing: the last positive term)
+#pragma unroll 1
+    for (int32_t ch = 0; ch < chunks; ++ch) {
+        terms(ch);
+        const double incl = before + group_scan_incl<G>(p);
+        const int f = crossing_lane<G>(incl, p, y);
+        double c = incl - p;
+        int32_t at = -1;
+        bool found = false;
 #pragma unroll
-    for (int u = 0; u < COL_B; ++u) {
-        if (b[u] > 0.0 && !found) {
-            c += b[u];
-            k = x.k[u];
-            found = c > y;
+        for (int u = 0; u < COL_B; ++u) {
+            if (b[u] > 0.0 && !found) {
+                c += b[u];
+                at = x.k[u];
+                found = c > y;
+            }
         }
+        before = group_bcast_f64<G>(incl, G - 1);
+        if (f >= 0) k = __shfl(at, f, G);
+        if (before > y) break;
     }
-    return f < 0 ? -1 : __builtin_amdgcn_readlane(k, f);
+    return k;
 }
 
 // a lane's token during a block: old slot, a-part slot, the counts its old
@@ -2149,6 +2155,41 @@ __device__ __forceinline__ void draw_regs(const DevModel &M, SlotDoc &S, const f
     }
 }
 
+// The block's draws of lists that pass SLOTS_MAX slots a lane on fewer than 64
+// lanes, slot = topic for every group of the wave: one fp64 draw over the word's
+// column after the other.
+template <int G>
+__device__ __forceinline__ void draw_overflow(const DevModel &M, const SlotDoc &S, const int32_t v, const LaneDraw &d,
+                                              const uint32_t n_max, const int g)
+{
+    auto change = [&](int32_t k, int by) { set_count(S, k, count_of(S, k) + (uint32_t)by); };
+    auto moves = [&](uint32_t i) {
+        for (uint32_t t = i << 7; __builtin_amdgcn_ballot_w64(d.key == t) != 0; ++t) {
+            if (d.key == t) {
+                change(d.po, -1);
+                change(d.pa, 1);
+            }
+            lds_order();
+        }
+    };
+#pragma unroll 1
+    for (uint32_t i = 0; i < n_max; ++i) {
+        moves(i);
+        const DrawRec rec = S.tok[i];
+        const int c = rec.lane();   // (127: the group has no draw left)
+        if (g == c) change(d.po, -1);
+        lds_order();
+        double Z;
+        const int32_t k = column_draw_f64<G>(M, S, __shfl(v, c & (G - 1), G), rec.u0, Z);
+        if (g == c) {
+            change(k >= 0 ? k : d.pa, 1);
+            if (k >= 0) S.out[i] = (uint16_t)k;
+        }
+        lds_order();
+    }
+    moves(n_max);
+}
+
 // The terms of a lane's N entries of a column and their sum; own: how many of
 // them are the column's (FULL: all)
 template <int N, bool FULL>
@@ -2248,7 +2289,8 @@ __device__ __forceinline__ void draw_dense(const DevModel &M, const SlotDoc &S, 
             const int32_t at = col_walk<COL_N>(x, b, incl - p, y, tol);
             if (lanes != 0) k = __builtin_amdgcn_readlane(at, __builtin_ctzll(lanes));
         } else {
-            const int32_t chunks = col_chunks(col);
+            static_assert(4096 <= 64 * 64 * COL_B, "a lane per chunk");
+            const int32_t chunks = col_chunks<64>(col);
             float b[COL_B], p = 0.0f, incl = 0.0f, T = 0.0f, ends = 0.0f;
             int32_t ch = 0;
             auto add = [&] {
@@ -2281,7 +2323,7 @@ __device__ __forceinline__ void draw_dense(const DevModel &M, const SlotDoc &S, 
         }
         if (__builtin_expect(k == -2, 0)) {
             double Zd;
-            k = column_draw_f64(M, S, __builtin_amdgcn_readlane(t.v, c), u0, Zd);
+            k = column_draw_f64<64>(M, S, __builtin_amdgcn_readlane(t.v, c), u0, Zd);
             if (g == c) d.fb = 1;
         }
         if (g == c) {
@@ -2397,8 +2439,13 @@ __device__ __forceinline__ int32_t draw_block(const DevModel &M, SlotDoc &S, con
         if (!over(8)) PULDA_DRAW(8);
         else if (!over(10)) PULDA_DRAW(10);
         else if (!over(12)) PULDA_DRAW(12);
-        else if (G < 64 || !S.dense) PULDA_DRAW(16);
-        else if constexpr (G == 64) draw_dense<STATS>(M, S, x, d, place, nd, g);
+        else if (!S.dense) PULDA_DRAW(16);
+        else if constexpr (G == 64) {
+            draw_dense<STATS>(M, S, x, d, place, nd, g);
+        } else if constexpr (!STATS) {   // (the z-step's documents fit)
+            stage_draws<G>(S, x, d, draws, place, g);
+            draw_overflow<G>(M, S, x.v, d, n_max, g);
+        }
     }
 #undef PULDA_DRAW
 #undef PULDA_REGS
@@ -3635,33 +3682,46 @@ __device__ __forceinline__ void foldin_slot(const DevModel &M, const DevFoldin &
     }
 }
 
+// one group's layout of a launch, and of its groups of 64 lanes (beside groups of
+// 32, for what is not likely to fit those: the first blocks)
+struct GroupLds {
+    SlotLds own, wide;
+};
+
 template <int G, bool SYM, int W>
 __global__ void __launch_bounds__(256, W) foldin_step_kernel(DevModel M, DevFoldin F, const int32_t *active,
-                                                          int32_t n_active, SlotLds A)
+                                                          int32_t n_active, GroupLds A)
 {
     extern __shared__ __align__(16) uint8_t f_lds[];
     // the block's copy of fp32(R_k), then the groups' regions
     float *R = (float *)f_lds;
     for (int32_t k = threadIdx.x; k < M.K; k += blockDim.x) R[k] = (float)M.Rd[k];
     __syncthreads();
-    constexpr int NG = 64 / G;
-    const int slot = (int)(threadIdx.x >> 6) * NG + (int)(__lane_id() / G);   // group in the block
-    const int64_t gid = (int64_t)blockIdx.x * (blockDim.x / G) + slot;
-    if (gid >= n_active) return;
-    foldin_slot<G, SYM>(M, F, active[gid], R, f_lds + (M.K * 4 + 15) / 16 * 16 + slot * A.group_bytes, A);
+    uint8_t *base = f_lds + (M.K * 4 + 15) / 16 * 16;
+    const int waves = (int)(blockDim.x >> 6), wave = (int)(threadIdx.x >> 6);
+    const int32_t wide_blocks = G == 32 ? (F.n_wide + waves - 1) / waves : 0;
+    if (G == 32 && (int32_t)blockIdx.x < wide_blocks) {
+        const int32_t i = (int32_t)blockIdx.x * waves + wave;
+        if (i < F.n_wide) foldin_slot<64, SYM>(M, F, active[i], R, base + wave * A.wide.group_bytes, A.wide);
+        return;
+    }
+    const int slot = wave * (64 / G) + (int)(__lane_id() / G);   // group in the block
+    const int32_t i = (G == 32 ? F.n_wide : 0) + ((int32_t)blockIdx.x - wide_blocks) * (waves * (64 / G)) + slot;
+    if (i < n_active) foldin_slot<G, SYM>(M, F, active[i], R, base + slot * A.own.group_bytes, A.own);
 }
 
-// Launch of a kernel with one group of G lanes per unit of work, its slots
-// in LDS behind the block's copy of R_k: four waves a block, or as many as
-// LDS holds
+// Launch of a kernel with groups of G lanes (wide: some of 64 lanes), their slots
+// in LDS behind the block's copy of R_k: four waves a block, or as many as LDS
+// holds.  go(waves, LDS bytes)
 template <typename Launch>
-static hipError_t launch_groups(int32_t K, int32_t G, int64_t groups, const SlotLds &A, Launch go)
+static hipError_t launch_groups(int32_t K, int32_t G, bool wide, const GroupLds &A, Launch go)
 {
     for (int waves = 4; waves >= 1; waves >>= 1) {
-        const int per_block = waves * (64 / G);
-        const size_t lds = (size_t)(K * 4 + 15) / 16 * 16 + (size_t)per_block * A.group_bytes;
+        size_t groups = (size_t)waves * (64 / G) * A.own.group_bytes;
+        if (wide && groups < (size_t)waves * A.wide.group_bytes) groups = (size_t)waves * A.wide.group_bytes;
+        const size_t lds = (size_t)(K * 4 + 15) / 16 * 16 + groups;
         if (lds > LDS_BYTES) continue;
-        go((unsigned)((groups + per_block - 1) / per_block), (unsigned)(waves * 64), lds);
+        go(waves, lds);
         return hipGetLastError();
     }
     return hipErrorInvalidConfiguration;  // a wave's LDS exceeds the CU's
@@ -3671,10 +3731,12 @@ hipError_t launch_foldin_step(const DevModel &m, const DevFoldin &f, const int32
                               int32_t n_cu, hipStream_t s)
 {
     if (n_active == 0) return hipSuccess;
-    const int32_t group = slots_group(f.group, m.K, f.max_len);
-    const SlotLds A = slot_lds(group, m.K, f.max_len);
-    return launch_groups(m.K, group, n_active, A, [&](unsigned blocks, unsigned threads, size_t lds) {
-#define PULDA_FOLDIN(G_, S_, W_) foldin_step_kernel<G_, S_, W_><<<blocks, threads, lds, s>>>(m, f, active, n_active, A)
+    const int32_t group = f.group;
+    const GroupLds A = {slot_lds(group, m.K, f.max_len), slot_lds(64, m.K, f.wide_len)};
+    return launch_groups(m.K, group, f.n_wide > 0, A, [&](int waves, size_t lds) {
+        const int32_t per = waves * (64 / group);
+        const int32_t blocks = (f.n_wide + waves - 1) / waves + (n_active - f.n_wide + per - 1) / per;
+#define PULDA_FOLDIN(G_, S_, W_) foldin_step_kernel<G_, S_, W_><<<blocks, 64 * waves, lds, s>>>(m, f, active, n_active, A)
         const bool four = group == 64 && fits_at_four_only(blocks, n_cu);
         if (m.lg_alpha) {
             if (four) PULDA_FOLDIN(64, true, 4);
@@ -3763,7 +3825,7 @@ __device__ __forceinline__ void ltr_particle(const DevModel &M, const DevHeldout
                 double Z;
                 auto count = [&](int32_t, int32_t k) { return count_of(S, k); };
                 int32_t at;
-                if (G == 64 && S.dense) at = column_draw_f64(M, S, v, u0, Z);
+                if (S.dense) at = column_draw_f64<G>(M, S, v, u0, Z);
                 else at = slots_draw_f64<G>(M, S, v, u0, (S.L + G - 1) / G, count, Z);
                 const int32_t k = at < 0 ? ka : topic_of(S, at);
                 if (g == 0) {
@@ -3780,19 +3842,51 @@ __device__ __forceinline__ void ltr_particle(const DevModel &M, const DevHeldout
     }
 }
 
-template <int G>
-__global__ void __launch_bounds__(256, 3) ltr_kernel(DevModel M, DevHeldout H, SlotLds A)
+// The particles of a document read the same words' rows again and again, so its
+// blocks are put on one XCD (block b runs on XCD b mod 8), beside few other
+// documents: document j of a launch's part on XCD j mod 8, in order.  With parts
+// of fewer than LTR_SPREAD documents blocks follow each other (one document's
+// would fill one XCD only).  2,000 documents of up to 500 tokens, 10 particles,
+// Algorithm 1's Phi (4 KB a row): 438 ms on 64 lanes, 398 so; the urn's 132 and 124.
+constexpr int64_t LTR_SPREAD = 64;
+constexpr int32_t XCDS = 8;
+
+// blocks of `per` particles for n documents
+__host__ __device__ inline int64_t ltr_blocks(int64_t n, int64_t R, int64_t per)
+{
+    return n < LTR_SPREAD ? (n * R + per - 1) / per : XCDS * (((n + XCDS - 1) / XCDS * R + per - 1) / per);
+}
+
+// document and particle of group `slot` of block b; false: none
+__device__ __forceinline__ bool ltr_work(int64_t n, int32_t R, int32_t per, int64_t b, int slot, int64_t &j, int32_t &r)
+{
+    const int64_t spread = n < LTR_SPREAD ? 1 : XCDS;
+    const int64_t i = b / spread * per + slot;
+    j = b % spread + spread * (i / R);
+    r = (int32_t)(i % R);
+    return j < n;
+}
+
+template <int G, int W>
+__global__ void __launch_bounds__(256, W) ltr_kernel(DevModel M, DevHeldout H, GroupLds A)
 {
     extern __shared__ __align__(16) uint8_t h_lds[];
     float *R = (float *)h_lds;
     for (int32_t k = threadIdx.x; k < M.K; k += blockDim.x) R[k] = (float)M.Rd[k];
     __syncthreads();
-    constexpr int NG = 64 / G;
-    const int slot = (int)(threadIdx.x >> 6) * NG + (int)(__lane_id() / G);   // group in the block
-    const int64_t gid = (int64_t)blockIdx.x * (blockDim.x / G) + slot;
-    if (gid >= H.D * H.R) return;
-    ltr_particle<G>(M, H, H.order[gid / H.R], (int32_t)(gid % H.R), R,
-                    h_lds + (M.K * 4 + 15) / 16 * 16 + slot * A.group_bytes, A);
+    uint8_t *base = h_lds + (M.K * 4 + 15) / 16 * 16;
+    const int waves = (int)(blockDim.x >> 6), wave = (int)(threadIdx.x >> 6);
+    const int64_t wide_blocks = G == 32 ? ltr_blocks(H.n_wide, H.R, waves) : 0;
+    int64_t j;
+    int32_t r;
+    if (G == 32 && (int64_t)blockIdx.x < wide_blocks) {
+        if (ltr_work(H.n_wide, H.R, waves, blockIdx.x, wave, j, r))
+            ltr_particle<64>(M, H, H.order[j], r, R, base + wave * A.wide.group_bytes, A.wide);
+        return;
+    }
+    const int slot = wave * (64 / G) + (int)(__lane_id() / G);   // group in the block
+    if (ltr_work(H.D - H.n_wide, H.R, waves * (64 / G), (int64_t)blockIdx.x - wide_blocks, slot, j, r))
+        ltr_particle<G>(M, H, H.order[H.n_wide + j], r, R, base + slot * A.own.group_bytes, A.own);
 }
 
 // one wave per document: sum over steps of log((1/R) sum_r Z_n^(r) / (n + A)),
@@ -3818,12 +3912,16 @@ __global__ void __launch_bounds__(256) ltr_finish_kernel(DevHeldout H)
 hipError_t launch_heldout(const DevModel &m, const DevHeldout &h, hipStream_t s)
 {
     if (h.D == 0) return hipSuccess;
-    const int32_t group = slots_group(h.group, m.K, h.longest);
-    const SlotLds A = slot_lds(group, m.K, h.longest);
-    hipError_t e = launch_groups(m.K, group, h.D * h.R, A, [&](unsigned blocks, unsigned threads, size_t lds) {
-        if (group == 64) ltr_kernel<64><<<blocks, threads, lds, s>>>(m, h, A);
-        else if (group == 32) ltr_kernel<32><<<blocks, threads, lds, s>>>(m, h, A);
-        else ltr_kernel<16><<<blocks, threads, lds, s>>>(m, h, A);
+    const int32_t group = h.group;
+    const GroupLds A = {slot_lds(group, m.K, h.longest), slot_lds(64, m.K, h.wide_len)};
+    hipError_t e = launch_groups(m.K, group, h.n_wide > 0, A, [&](int waves, size_t lds) {
+        const unsigned blocks = (unsigned)(ltr_blocks(h.n_wide, h.R, waves) + ltr_blocks(h.D - h.n_wide, h.R, waves * (64 / group)));
+        // (phi's own rows, Algorithm 1's: 227 ms with 128 registers, 264 with
+        // 168, at the sizes of ltr_blocks; the urn's 140 and 134)
+        if (group == 64) ltr_kernel<64, 3><<<blocks, 64 * waves, lds, s>>>(m, h, A);
+        else if (group == 32 && m.values) ltr_kernel<32, 4><<<blocks, 64 * waves, lds, s>>>(m, h, A);
+        else if (group == 32) ltr_kernel<32, 3><<<blocks, 64 * waves, lds, s>>>(m, h, A);
+        else ltr_kernel<16, 3><<<blocks, 64 * waves, lds, s>>>(m, h, A);
     });
     if (e != hipSuccess) return e;
     ltr_finish_kernel<<<(unsigned)((h.D + 3) / 4), 256, 0, s>>>(h);

@@ -98,6 +98,58 @@ def test_lanes_for_new_documents(group, K, lens, method):
             assert abs(r["loglik"] - ll) <= 1e-12 * max(1.0, abs(ll))
 
 
+# topics that were not likely to pass the slots of 16 lanes (240 of 4,096 at up to
+# 247 tokens) and do, beside a block's 16 a-parts
+@pytest.mark.parametrize("method", ["polya_urn", "dirichlet"])
+def test_lists_that_overflow_few_lanes(method):
+    K, n, R = 4096, 247, 24
+    c, p = _plan([200] * 40, 500, K, method, seed=7)
+    say(f"overflow: {method}")
+    p.sweep(1, 1, want_ll=False)
+    p.phi_step(2)
+    phi, wt = phi_from_gpu(p.get_phi(), K, c.V)
+    rng = np.random.default_rng(1)
+    docs = [rng.integers(0, c.V, size=n).astype(np.int32) for _ in range(R)]
+    first = [len({(int(oracle.philox([q, i, 0, 4], [5, 0])[0]) * K) >> 32 for q in range(n)}) for i in range(R)]
+    assert max(first) >= 243
+    f = pulda.FoldIn(p, sweeps=3, burn_in=1, max_slots=R, arena_tokens=R * n, max_len=n, group=16, seed=5)
+    for i, w in enumerate(docs):
+        assert f.submit(i, w)
+    f.step(2 ** 31 - 1)
+    got = {r["request_id"]: r for r in f.poll(R)}
+    for i, w in enumerate(docs):
+        theta, ll, kept, dropped, _ = oracle.foldin(phi, wt, 0.1, 5, i, w, S=3, burn_in=1)
+        r = got[i]
+        assert (r["kept"], r["dropped"]) == (kept, dropped)
+        assert np.array_equal(r["theta"], theta), (i, first[i])
+        assert abs(r["loglik"] - ll) <= 1e-12 * max(1.0, abs(ll))
+
+
+# many documents (a document's blocks on one XCD) and few; some past 32 lanes
+@pytest.mark.parametrize("group", [16, 32, 64])
+@pytest.mark.parametrize("D", [3, 63, 64, 70])
+def test_held_out_blocks(D, group):
+    K = 600
+    c, p = _plan([200] * 40, 500, K, "polya_urn", seed=3)
+    say(f"held-out blocks: D={D} group={group}")
+    p.sweep(1, 1, want_ll=False)
+    p.phi_step(2)
+    phi, wt = phi_from_gpu(p.get_phi(), K, c.V)
+    rng = np.random.default_rng(D)
+    lens = rng.integers(0, 40, size=D)
+    lens[D // 2] = 1100 if D == 70 else 45
+    docs = [rng.integers(0, c.V, size=n).astype(np.int32) for n in lens]
+    R = 3
+    ll, kept, Z = p.heldout_loglik(docs, particles=R, group=group, seed=9, want_Z=True)
+    for i, w in enumerate(docs):
+        if len(w) > 1000:
+            continue   # (long for the oracle; the documents beside it are checked)
+        e, k, Zo = oracle.heldout_ltr(phi, wt, 0.1, 9, i, w, R, want_Z=True)
+        assert kept[i] == k
+        assert np.all(np.abs(Z[i] - Zo) <= 1e-10 * np.abs(Zo))
+        assert abs(ll[i] - e) <= 1e-12 * max(1.0, abs(e))
+
+
 @pytest.mark.parametrize("group,K,lens", [(16, 300, [30, 250]), (32, 520, [500]), (64, 1100, [20, 1200])])
 def test_lanes_for_held_out_documents(group, K, lens):
     c, p = _plan([200] * 40, 500, K, "polya_urn", seed=group + K)
