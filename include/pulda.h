@@ -421,7 +421,8 @@ pulda_status pulda_foldin_occupancy(const pulda_foldin *f, int32_t *resident, in
  *   req_dev[D]: request ids; particle r's draw of token q at step n uses
  *     Philox counter (q, n, req, 7 + 256 r) under seed.
  *   particles in [1, 2^24); group: lanes per particle (16, 32, 64;
- *   more for documents whose topics are not likely to fit 16 a lane).
+ *   more for documents whose topics are not likely to fit 16 a lane, or could not
+ *   under a Phi of draws).
  *   workspace_dev: pulda_heldout_workspace_bytes(model, D, N, particles) bytes,
  *     256-byte aligned, caller-owned.
  *   ll_dev[D] (fp64) and kept_dev[D] (kept tokens) are written; Z_dev (R*N

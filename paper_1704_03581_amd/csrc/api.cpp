@@ -1682,6 +1682,12 @@ static pulda_status heldout_run(const pulda_plan *model, int64_t D, const int64_
     h.group = group;
     auto len = [&](int64_t i) { return (int32_t)(off[order[i] + 1] - off[order[i]]); };
     if (group == 16 && !slots_likely(16, model->K, len(0))) h.group = 32;
+    // rows of draws: 64 lanes for all where a document could fill 32 lanes' slots
+    // (10 particles each: 1,000 documents of 150 tokens and one of 500 40 ms, 61
+    // on 32 lanes; 2,000 of 500 383 and 422).  Phi's own rows, four bytes a
+    // topic, are faster on 32: 226 and 396 ms at the sizes of ltr_blocks, so only
+    // the documents not likely to fit take 64
+    if (h.group == 32 && !model->m.values && !slots_fit(32, model->K, len(0))) h.group = 64;
     while (h.group == 32 && h.n_wide < D && !slots_likely(32, model->K, len(h.n_wide))) ++h.n_wide;
     h.wide_len = h.n_wide ? len(0) : 0;
     h.longest = h.n_wide < D ? len(h.n_wide) : 0;

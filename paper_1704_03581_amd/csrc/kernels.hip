@@ -2538,13 +2538,13 @@ __device__ __forceinline__ void z_step_item(const ZArgs &a, const WorkItem &w, c
 
 // one persistent kernel per group size and layout: waves take work items
 // from this class's queue until it is empty.
-// Measured at K = 1000.  738M tokens in documents of 90: 103.7 ms, from 118.5
-// with sorted topic lists kept token by token; of its eighth (92M tokens) 13.1
-// ms on 32 lanes, 13.3 on 16, 16.5 on 8 and 18.4 on 64, at 43 VALU
-// instructions a token (82 before), bound by what leaves L2 (16-bit rows: 98
-// GB at 6.3 TB/s, hence the 8-bit ones).  A document of 20,000 tokens on 64
-// lanes: 0.6 us a token (1.3 before), the latency of one draw's chain, about
-// 530 cycles, plus staging and layout, about 9,000 cycles a block of 64.
+// Measured at K = 1000.  738M tokens in documents of 90: 85.5 ms on 32 lanes
+// (103.7 with the spills that the opaque addresses took out, 118.5 with sorted
+// topic lists kept token by token); of its eighth (92M tokens) 10.8 ms on 32
+// lanes, 11.8 on 64, 12.5 on 16 and 12.9 on 8.  On 64 lanes a long document alone
+// on its SIMD takes, by slots a lane, 0.23 us a token at 1, 0.34 at 3, 0.45 at 5,
+// 0.60 at 8, 0.71 at 10, 0.81 at 12 and 1.11 at 16: the latency of one draw's
+// chain, and about 0.05 us of instructions a slot.
 // W: waves a SIMD that the registers leave room for (see fits_at_four_only).
 template <int G, bool BIG, bool HOT, int W>
 __global__ void __launch_bounds__(256, W) z_step_kernel(ZArgs a)
@@ -2959,7 +2959,9 @@ hipError_t launch_z_class(const DevCorpus &c, const DevModel &m, int32_t group, 
 // 17 us, from 330 us when the counts were read twice (50 + 53 us) and every
 // document cleared and read a table of K counts (215 us).  The words alone take
 // 55 us (112 MB of counts: the table lookups and LDS adds of 28M cells), the
-// documents alone 75 us (instruction issue, about 150 a document).
+// documents alone 75 us.  Bound by latency at two waves a SIMD (199 registers, the
+// rare cells' lgamma and log inlined): the VALU is busy 39% of the cycles, a wave
+// waits in 53% of its own.
 // ---------------------------------------------------------------------------
 constexpr int32_t LL_DOCS = 256;   // documents' terms per block, at least
 

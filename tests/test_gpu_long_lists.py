@@ -165,3 +165,24 @@ def test_lanes_for_held_out_documents(group, K, lens):
         assert kept[i] == k
         assert np.all(np.abs(Z[i] - Zo) <= 1e-10 * np.abs(Zo))
         assert abs(ll[i] - e) <= 1e-12 * abs(e)
+
+
+# phi's own rows: documents not likely to fit 32 lanes' slots on 64, beside the others;
+# rows of draws: all on 64 where one could fill them
+@pytest.mark.parametrize("method", ["polya_urn", "dirichlet"])
+@pytest.mark.parametrize("group", [16, 32])
+def test_held_out_lanes_by_the_document(group, method):
+    K = 4096
+    c, p = _plan([200] * 40, 500, K, method, seed=group)
+    say(f"held-out lanes by the document: group={group} {method}")
+    p.sweep(1, 1, want_ll=False)
+    p.phi_step(2)
+    phi, wt = phi_from_gpu(p.get_phi(), K, c.V)
+    rng = np.random.default_rng(group)
+    docs = [rng.integers(0, c.V, size=n).astype(np.int32) for n in (30, 520, 0, 300, 525, 40)]
+    ll, kept, Z = p.heldout_loglik(docs, particles=2, group=group, seed=9, want_Z=True)
+    for i, w in enumerate(docs):
+        e, k, Zo = oracle.heldout_ltr(phi, wt, 0.1, 9, i, w, 2, want_Z=True)
+        assert kept[i] == k
+        assert np.all(np.abs(Z[i] - Zo) <= 1e-10 * np.abs(Zo))
+        assert abs(ll[i] - e) <= 1e-12 * max(1.0, abs(e))
